@@ -70,8 +70,6 @@ struct mg_ctx {
   // 0 = no limit
   size_t hbm_budget = 0;
   size_t lds_per_block = 65536;
-  int tail64_top = 3;          // highest FP64 level held by the LDS coarse tail
-  bool tail_fas = false;       // the tail also runs FAS cycles (LDS for phibar beside u and f)
   char* ws = nullptr;
   size_t ws_cap = 0;
   double* part = nullptr;      // reduction partials
@@ -445,23 +443,24 @@ struct Solver {
     c->kev_id.push_back(id);
   }
 
+  // The levels 0..top (<= T_top) in one launch; norm (device, may be null) receives the sum of
+  // squared defects of level top's result.
   template <typename T>
-  void tail(Hier<T>& H, int mode, const LevelBC& bc_top) {
+  void tail(Hier<T>& H, int top, int mode, const LevelBC& bc_top, double* norm = nullptr) {
     TailArgs a;
     std::memset(&a, 0, sizeof(a));
-    a.top = H.T_top;
+    a.top = top;
     a.mode = mode;
     a.npre = H.npre;
     a.npost = H.npost;
     a.omega = H.omega;
-    for (int l = 0; l <= H.T_top; ++l) {
-      a.h[l] = H.h[l];
-      a.phys[l] = H.phys[l];
-      a.fg[l] = H.f[l];
-    }
+    a.h = H.h[top];
+    for (int l = 0; l <= top; ++l) a.phys[l] = H.phys[l];
     a.bc_top = bc_top;
     a.hom = H.hom;
-    a.ug = H.u[H.T_top];
+    a.f = H.f[top];
+    a.ug = H.u[top];
+    a.norm = norm;
     launch_tail<T>(a, s);
   }
 
@@ -565,8 +564,9 @@ struct Solver {
       }
     }
     if (l == H.T_top) {
-      tail(H, top_call ? TAIL_LOAD_U : 0, bc);
-      return false;
+      const bool norm = want_norm && sizeof(T) == 8;
+      tail(H, l, top_call ? TAIL_LOAD_U : 0, bc, norm ? scal + 2 : nullptr);
+      return norm;
     }
     const int n = 1 << l;
     const double h = H.h[l];
@@ -757,57 +757,17 @@ struct Solver {
     return cur;
   }
 
-  static bool fixes_zero(const LevelBC& bc) {
-    for (int f = 0; f < 6; ++f)
-      if (bc.kind[f] != BC_PERIODIC && bc.kind[f] != BC_ZERO_GRADIENT) return true;
-    return false;
-  }
-
   // done: pre-sweeps of the top level already run by the head pass (result in u2).  want_norm
-  // (top level): the two-sweep up pass may leave the sum of squared defects of the result in
-  // scal[2]; returns whether it did.
-  // Can the LDS tail run the FAS cycle from level l: its FAS form allowed, and no level's
-  // description (nor the corrections') carrying face values?
-  bool fas_tail_ok(const Hier<double>& H, int l) const {
-    if (!c->tail_fas) return false;
-    auto valueless = [](const LevelBC& q) {
-      for (int f = 0; f < 6; ++f)
-        if (q.kind[f] != BC_PERIODIC && q.kind[f] != BC_ZERO_GRADIENT && q.b[f]) return false;
-      return true;
-    };
-    if (!valueless(H.hom)) return false;
-    for (int q = 0; q <= l; ++q)
-      if (!valueless(H.phys[q])) return false;
-    return true;
-  }
-
+  // (top level): the sum of squared defects of the result may be left in scal[2] (by the
+  // two-sweep up pass, the tile leg or the tail); returns whether it was.
   bool fas_cycle(Hier<double>& H, double* const* pbar, int l, int done = 0, bool want_norm = false) {
-    if (l == 0) {
-      // the single cell with its physical conditions, from the iterate phibar; when no face
-      // fixes the zero point any value solves it and phibar is kept (zero correction)
-      if (fixes_zero(H.phys[0])) launch_coarsest<double>(H.u[0], H.f[0], H.h[0], H.phys[0], s);
-      return false;
-    }
-    if (done == 0 && l <= H.T_top && fas_tail_ok(H, l)) {
-      // the whole FAS cycle from level l in one LDS-resident workgroup (levels <= 16^3 whose
-      // descriptions carry no face values)
-      TailArgs a;
-      std::memset(&a, 0, sizeof(a));
-      a.top = l;
-      a.mode = TAIL_FAS | TAIL_LOAD_U;
-      a.npre = H.npre;
-      a.npost = H.npost;
-      a.omega = H.omega;
-      for (int q = 0; q <= l; ++q) {
-        a.h[q] = H.h[q];
-        a.phys[q] = H.phys[q];
-        a.fg[q] = H.f[q];
-      }
-      a.bc_top = H.phys[l];
-      a.hom = H.hom;
-      a.ug = H.u[l];
-      launch_tail<double>(a, s);
-      return false;
+    if (done == 0 && l <= H.T_top) {
+      // The levels <= 16^3 in one workgroup, in correction form: below level l, FAS solves for
+      // u = phibar + e with the source R(defect) + L phibar, and every step of Alg. 3 on a linear
+      // operator (smoothing, restriction, the single cell) keeps phibar and moves e exactly as
+      // Alg. 1 moves the correction, which is all the levels above see (psi - phibar).
+      tail(H, l, TAIL_LOAD_U, H.phys[l], want_norm ? scal + 2 : nullptr);
+      return want_norm;
     }
     const int n = 1 << l;
     const LevelBC& bc = H.phys[l];
@@ -896,9 +856,9 @@ struct Solver {
   // Alg. 2 with FAS in place of the V-cycle.
   // Returns whether the finest level's cycle left the norm of its result in scal[2].
   bool fas_fmg(Hier<double>& H, double* const* pbar) {
-    launch_coarsest<double>(H.u[0], H.f[0], H.h[0], H.phys[0], s);
-    bool normed = false;
-    for (int l = 1; l <= H.L; ++l) {
+    bool normed = H.L == H.T_top;
+    tail(H, H.T_top, TAIL_FMG, H.phys[H.T_top], normed ? scal + 2 : nullptr);
+    for (int l = H.T_top + 1; l <= H.L; ++l) {
       launch_prolong<double>(H.u[l - 1], H.u[l], 1 << (l - 1), H.phys[l - 1], 1, s);
       normed = fas_cycle(H, pbar, l, 0, l == H.L);
     }
@@ -910,8 +870,8 @@ struct Solver {
   // (returns whether it did).
   template <typename T>
   bool fmg(Hier<T>& H, bool norm_top = false) {
-    tail(H, TAIL_FMG, H.phys[H.T_top]);
-    bool normed = false;
+    bool normed = norm_top && H.L == H.T_top && sizeof(T) == 8;
+    tail(H, H.T_top, TAIL_FMG, H.phys[H.T_top], normed ? scal + 2 : nullptr);
     for (int l = H.T_top + 1; l <= H.L; ++l) {
       if (Lb >= 0 && l > Lb) {
         blk_prolong<T>(H.u[l - 1], H.u[l], l - Lb, Lb, H.phys[l - 1], 1, s);
@@ -1033,10 +993,11 @@ struct Solver {
     return false;
   }
 
-  // Source hierarchy f_{l-1} = restriction of f_l (Alg. 2 step 1) in either layout.
+  // Source hierarchy f_{l-1} = restriction of f_l (Alg. 2 step 1) in either layout, down to the
+  // tail's top level (the tail restricts its own).
   template <typename T>
   void restrict_sources(Hier<T>& H) {
-    for (int l = H.L; l >= 1; --l) {
+    for (int l = H.L; l > H.T_top; --l) {
       if (Lb >= 0 && l > Lb) blk_restrict<T, T>(H.f[l], H.f[l - 1], l - Lb, Lb, s);
       else launch_restrict<T, T>(H.f[l], H.f[l - 1], 1 << (l - 1), s);
     }
@@ -1113,9 +1074,6 @@ int mg_ctx_create(mg_ctx** out, int device, size_t hbm_budget) {
     mg_ctx_destroy(c);
     return MG_ERR_DEVICE;
   }
-  // the FP64 coarse tail keeps levels <= 16^3 in LDS when the device allows it per block
-  c->tail64_top = tail_prepare(c->lds_per_block);
-  c->tail_fas = c->tail64_top == 4 && tail_fas_prepare(c->lds_per_block);
   blk_prepare<double>(c->lds_per_block);
   blk_prepare<float>(c->lds_per_block);
   // the static scratch's device address, once per device with the device current (a failure
@@ -1352,7 +1310,7 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
   for (int f = 0; f < 6; ++f)
     if (bc->kind[f] == MG_BC_FIXED || bc->kind[f] == MG_BC_MULTIPOLE) gauge_free = false;
   const bool mixed = y.mixed;
-  int tail_max = mixed ? 4 : c->tail64_top;
+  int tail_max = 4;
   if (c->tail_top[mixed ? 1 : 0] > 0) tail_max = std::min(tail_max, c->tail_top[mixed ? 1 : 0]);
   tail_max = std::min(tail_max, Lb >= 0 ? Lb : 99);
 
@@ -1422,7 +1380,7 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
       fmg_normed = S.fas_fmg(H64, pbar);
     } else if (!mixed) {
       // the finest level's FMG V-cycle takes the norm of its result when its up pass can
-      fmg_normed = S.fmg(H64, S.march_on<double>(H64, L, phys[L]) ||
+      fmg_normed = S.fmg(H64, L == H64.T_top || S.march_on<double>(H64, L, phys[L]) ||
                                   (p->n < S.fused_min_n64 && S.tile_on<double>(H64, L)));
     } else {
       S.fmg(H32);
@@ -1514,7 +1472,7 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
       } else {
         // defect correction: e32 solves L e = r32 from zero with homogeneous conditions
         if (L == H32.T_top) {
-          S.tail(H32, 0, hom);
+          S.tail(H32, L, 0, hom);
         } else {
           // the correction starts from zero: the first sweep does not read it (or the
           // V-cycle clears it when its first pass cannot skip the read)

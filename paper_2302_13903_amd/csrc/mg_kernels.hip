@@ -369,455 +369,6 @@ void launch_coarsest(T* u, const T* f, double h, const LevelBC& bc, hipStream_t 
   hipLaunchKernelGGL(k_coarsest<T>, dim3(1), dim3(64), 0, s, u, f, (T)(h * h), bc);
 }
 
-// ------------------------------------------------------------------ coarse tail (levels <= 2^TL)
-
-// All levels 0..T (T <= 4, at most 16^3 cells) of one hierarchy in LDS, one workgroup.
-// mode bits: TAIL_FMG runs Alg. 2 on levels 0..T with the physical description of each level
-// and writes u_T; otherwise one V-cycle (Alg. 1) at level T with bc_top (u_T loaded from
-// global when TAIL_LOAD_U, else started from zero) and homogeneous descriptions below.
-constexpr int kTailThreads = 1024;
-
-// Start of level l within the LDS arrays (levels 0..top stored back to back): the cells of
-// levels 0..l-1, sum of 8^q for q < l = (8^l - 1) / 7.
-__host__ __device__ __forceinline__ constexpr int level_offset(int l) { return ((1 << (3 * l)) - 1) / 7; }
-
-// KIND 1: every face of every description the launch uses is periodic.  Ghosts are then the
-// opposite cells, read by wrapping the index; this leaves the boundary code of the other kinds
-// out of the kernel image, which the tail's many short phases fetch cold otherwise (measured
-// 36 against 98 us for the tail from 16^3).  KIND 2: no description carries face values (the
-// homogeneous conditions of a V-cycle's coarse levels): a wall's ghost is kappa times the
-// cell's own value, taken by a select after a wrapped (always in range) read, with no
-// boundary branches either.  KIND 0: the general ghost rules.  Same values, same order of
-// operations.
-// The walls of a description without face values: per face, the ghost's factor on the cell's
-// own value (0 for a periodic face: never used).
-template <typename T>
-struct WallRule {
-  T k[6];
-  __device__ __forceinline__ explicit WallRule(const LevelBC& bc) {
-#pragma unroll
-    for (int f = 0; f < 6; ++f)
-      k[f] = bc.kind[f] == BC_PERIODIC ? (T)0 : (bc.kind[f] == BC_ZERO_GRADIENT ? (T)1 : (T)-1);
-  }
-};
-
-// LDS index of cell (i, j, k) of a level of 2^L cells per side (32-bit: LDS arrays are small)
-__device__ __forceinline__ int lds_idx(int L, int i, int j, int k) { return (k << (2 * L)) | (j << L) | i; }
-
-template <typename T, int KIND>
-__device__ __forceinline__ T lds_nb(const T* u, int n, int L, int i, int j, int k, T uc, const LevelBC& bc,
-                                    const WallRule<T>& wr) {
-  if (KIND != 0) {
-    const int m = n - 1;
-    T xm = u[lds_idx(L, (i - 1) & m, j, k)], xp = u[lds_idx(L, (i + 1) & m, j, k)];
-    T ym = u[lds_idx(L, i, (j - 1) & m, k)], yp = u[lds_idx(L, i, (j + 1) & m, k)];
-    T zm = u[lds_idx(L, i, j, (k - 1) & m)], zp = u[lds_idx(L, i, j, (k + 1) & m)];
-    if (KIND == 2) {
-      if (i == 0 && wr.k[0] != (T)0) xm = wr.k[0] * uc;
-      if (i == m && wr.k[1] != (T)0) xp = wr.k[1] * uc;
-      if (j == 0 && wr.k[2] != (T)0) ym = wr.k[2] * uc;
-      if (j == m && wr.k[3] != (T)0) yp = wr.k[3] * uc;
-      if (k == 0 && wr.k[4] != (T)0) zm = wr.k[4] * uc;
-      if (k == m && wr.k[5] != (T)0) zp = wr.k[5] * uc;
-    }
-    return ((((xm + xp) + ym) + yp) + zm) + zp;
-  }
-  const size_t c = cidx(L, i, j, k);
-  return neighbour_sum(u, n, L, i, j, k, c, uc, bc);
-}
-
-// KIND 2: a coarse index beyond a wall without values: wrapped (periodic) or clamped to the
-// boundary cell with the sign of the wall's rule.
-template <typename T>
-__device__ __forceinline__ int wall_tap(int c, int nc, int klo, int khi, T& s) {
-  if (c < 0) {
-    if (klo == BC_PERIODIC) return nc - 1;
-    if (klo != BC_ZERO_GRADIENT) s = -s;
-    return 0;
-  }
-  if (c >= nc) {
-    if (khi == BC_PERIODIC) return 0;
-    if (khi != BC_ZERO_GRADIENT) s = -s;
-    return nc - 1;
-  }
-  return c;
-}
-
-// One smoothing sweep on an LDS-resident level: work items enumerate only the cells of the
-// current colour (the x-pair index p picks the pair's cell of that colour), so no lane idles.
-template <typename T, int KIND>
-__device__ __forceinline__ void tail_smooth(T* u, const T* f, int L, T h2, T omega, const LevelBC& bc) {
-  const int n = 1 << L;
-  const T inv6 = (T)(1.0 / 6.0);
-  const int half = 1 << (3 * L - 1);
-  const WallRule<T> wr(bc);
-#pragma unroll 1
-  for (int colour = 0; colour < 2; ++colour) {
-#pragma unroll 1
-    for (int t = threadIdx.x; t < half; t += blockDim.x) {
-      const int p = t & ((n >> 1) - 1), j = (t >> (L - 1)) & (n - 1), k = t >> (2 * L - 1);
-      const int i = 2 * p + ((j + k + colour) & 1);
-      const int c = lds_idx(L, i, j, k);
-      const T uc = u[c];
-      const T nb = lds_nb<T, KIND>(u, n, L, i, j, k, uc, bc, wr);
-      u[c] = uc + omega * ((nb - h2 * f[c]) * inv6 - uc);
-    }
-    __syncthreads();
-  }
-}
-
-template <typename T, int KIND>
-__device__ __forceinline__ void tail_defect_restrict(const T* u, const T* f, T* fc, T* uc0, int L, T ih2, const LevelBC& bc) {
-  const int n = 1 << L, Lc = L - 1, nc = n >> 1, nc3 = 1 << (3 * Lc);
-  const WallRule<T> wr(bc);
-#pragma unroll 1
-  for (int C = threadIdx.x; C < nc3; C += blockDim.x) {
-    const int I = C & (nc - 1), J = (C >> Lc) & (nc - 1), K = C >> (2 * Lc);
-    T s = (T)0;
-    for (int c3 = 0; c3 < 2; ++c3)
-      for (int b = 0; b < 2; ++b)
-        for (int a = 0; a < 2; ++a) {
-          const int i = 2 * I + a, j = 2 * J + b, k = 2 * K + c3;
-          const int c = lds_idx(L, i, j, k);
-          const T ucv = u[c];
-          s += f[c] - (lds_nb<T, KIND>(u, n, L, i, j, k, ucv, bc, wr) - (T)6 * ucv) * ih2;
-        }
-    fc[C] = s * (T)0.125;
-    uc0[C] = (T)0;
-  }
-  __syncthreads();
-}
-
-template <typename T, int CUBIC, int KIND>
-__device__ __forceinline__ void tail_prolong(const T* uc, T* uf, int L, const LevelBC& bcc) {
-  const int n = 1 << L, n3 = 1 << (3 * L), Lc = L - 1, nc = n >> 1;
-#pragma unroll 1
-  for (int c = threadIdx.x; c < n3; c += blockDim.x) {
-    const int i = c & (n - 1), j = (c >> L) & (n - 1), k = c >> (2 * L);
-    const int I = i >> 1, J = j >> 1, K = k >> 1;
-    const bool inner = I > 0 && I < nc - 1 && J > 0 && J < nc - 1 && K > 0 && K < nc - 1;
-    T wx[3], wy[3], wz[3];
-    if (CUBIC) { cub_w(i & 1, wx); cub_w(j & 1, wy); cub_w(k & 1, wz); }
-    else { lin_w(i & 1, wx); lin_w(j & 1, wy); lin_w(k & 1, wz); }
-    T s = (T)0;
-    if (!CUBIC && KIND != 0) {
-      // trilinear: on each axis the tap of weight zero is the third (even fine index) or the
-      // first (odd), so the two others are slots o, o+1 with o = the index's parity; each
-      // axis's two coarse indices (wrapped, or clamped with the wall's sign) are taken once,
-      // and the eight terms are summed in the order of the 27-tap loop below
-      const int ox = i & 1, oy = j & 1, oz = k & 1;
-      int xo[2], yo[2], zo[2];
-      T xs[2], ys[2], zs[2];
-#pragma unroll
-      for (int d = 0; d < 2; ++d) {
-        xs[d] = ys[d] = zs[d] = (T)1;
-        if (KIND == 1) {
-          xo[d] = (I - 1 + ox + d) & (nc - 1);
-          yo[d] = ((J - 1 + oy + d) & (nc - 1)) << Lc;
-          zo[d] = ((K - 1 + oz + d) & (nc - 1)) << (2 * Lc);
-        } else {
-          xo[d] = wall_tap<T>(I - 1 + ox + d, nc, bcc.kind[0], bcc.kind[1], xs[d]);
-          yo[d] = wall_tap<T>(J - 1 + oy + d, nc, bcc.kind[2], bcc.kind[3], ys[d]) << Lc;
-          zo[d] = wall_tap<T>(K - 1 + oz + d, nc, bcc.kind[4], bcc.kind[5], zs[d]) << (2 * Lc);
-        }
-      }
-#pragma unroll
-      for (int cz = 0; cz < 2; ++cz)
-#pragma unroll
-        for (int by = 0; by < 2; ++by)
-#pragma unroll
-          for (int ax = 0; ax < 2; ++ax) {
-            const T w = wx[ox + ax] * wy[oy + by] * wz[oz + cz];
-            const T v = uc[zo[cz] | yo[by] | xo[ax]];
-            if (KIND == 1) s += w * v;
-            else s += w * (((xs[ax] * ys[by]) * zs[cz]) * v);
-          }
-      uf[c] += s;
-      continue;
-    }
-#pragma unroll
-    for (int cz = -1; cz <= 1; ++cz)
-#pragma unroll
-      for (int by = -1; by <= 1; ++by)
-#pragma unroll
-        for (int ax = -1; ax <= 1; ++ax) {
-          const T w = wx[ax + 1] * wy[by + 1] * wz[cz + 1];
-          if (w == (T)0) continue;
-          if (KIND == 1) {
-            s += w * uc[lds_idx(Lc, (I + ax) & (nc - 1), (J + by) & (nc - 1), (K + cz) & (nc - 1))];
-          } else if (KIND == 2) {
-            T sg = (T)1;
-            const int Ic = wall_tap<T>(I + ax, nc, bcc.kind[0], bcc.kind[1], sg);
-            const int Jc = wall_tap<T>(J + by, nc, bcc.kind[2], bcc.kind[3], sg);
-            const int Kc = wall_tap<T>(K + cz, nc, bcc.kind[4], bcc.kind[5], sg);
-            s += w * (sg * uc[lds_idx(Lc, Ic, Jc, Kc)]);
-          } else {
-            s += w * (inner ? uc[cidx(Lc, I + ax, J + by, K + cz)] : ghost_any(uc, nc, Lc, I + ax, J + by, K + cz, bcc));
-          }
-        }
-    if (CUBIC) uf[c] = s;
-    else uf[c] += s;
-  }
-  __syncthreads();
-}
-
-// Per-launch metadata copied to LDS once, so per-level lookups with a runtime level index
-// read LDS instead of spilling the argument block to private memory.
-struct TailMeta {
-  LevelBC phys[5];
-  LevelBC top;   // description of the top level in V-cycle mode
-  LevelBC hom;
-  double h2[5];
-};
-
-// V-cycle from level `topl` down to 0 and back, with bc_top on level topl and the
-// homogeneous description below.
-template <typename T, int KIND>
-__device__ __forceinline__ void tail_vcycle(T* base, int total, int topl, const TailMeta& m, const LevelBC& bc_top, int npre,
-                            int npost, T omega) {
-#pragma unroll 1
-  for (int l = topl; l >= 1; --l) {
-    const LevelBC bc = l == topl ? bc_top : m.hom;   // by value: kinds in registers
-    T* u = base + level_offset(l);
-    T* f = base + total + level_offset(l);
-    const T h2 = (T)m.h2[l];
-#pragma unroll 1
-    for (int it = 0; it < npre; ++it) tail_smooth<T, KIND>(u, f, l, h2, omega, bc);
-    tail_defect_restrict<T, KIND>(u, f, base + total + level_offset(l - 1), base + level_offset(l - 1), l, (T)(1.0 / m.h2[l]),
-                         bc);
-  }
-  const LevelBC hom = m.hom;
-  if (threadIdx.x == 0) base[0] = coarsest_value(base[total], (T)m.h2[0], topl == 0 ? bc_top : hom);
-  __syncthreads();
-#pragma unroll 1
-  for (int l = 1; l <= topl; ++l) {
-    const LevelBC bc = l == topl ? bc_top : hom;
-    T* u = base + level_offset(l);
-    tail_prolong<T, 0, KIND>(base + level_offset(l - 1), u, l, hom);
-#pragma unroll 1
-    for (int it = 0; it < npost; ++it) tail_smooth<T, KIND>(u, base + total + level_offset(l), l, (T)m.h2[l], omega, bc);
-  }
-}
-
-// FAS (Alg. 3 steps 2-7) on an LDS-resident level: the restricted defect into the coarse
-// source, the restricted u (phibar) into the coarse level's phibar and starting iterate --
-// the same terms in the same order as the per-operator FAS restriction
-template <typename T, int KIND>
-__device__ __forceinline__ void tail_fas_restrict(const T* u, const T* f, T* fc, T* pbar, T* uc, int L, T ih2,
-                                                  const LevelBC& bc) {
-  const int n = 1 << L, Lc = L - 1, nc = n >> 1, nc3 = 1 << (3 * Lc);
-  const WallRule<T> wr(bc);
-#pragma unroll 1
-  for (int C = threadIdx.x; C < nc3; C += blockDim.x) {
-    const int I = C & (nc - 1), J = (C >> Lc) & (nc - 1), K = C >> (2 * Lc);
-    T sd = (T)0, su = (T)0;
-    for (int c3 = 0; c3 < 2; ++c3)
-      for (int b = 0; b < 2; ++b)
-        for (int a = 0; a < 2; ++a) {
-          const int i = 2 * I + a, j = 2 * J + b, k = 2 * K + c3;
-          const int c = lds_idx(L, i, j, k);
-          const T ucv = u[c];
-          sd += f[c] - (lds_nb<T, KIND>(u, n, L, i, j, k, ucv, bc, wr) - (T)6 * ucv) * ih2;
-          su += ucv;
-        }
-    fc[C] = sd * (T)0.125;
-    const T pb = su * (T)0.125;
-    pbar[C] = pb;
-    uc[C] = pb;
-  }
-  __syncthreads();
-}
-
-// f += L phibar on an LDS-resident level, phibar's ghosts from the level's physical description
-template <typename T, int KIND>
-__device__ __forceinline__ void tail_fas_source(const T* pbar, T* f, int L, T ih2, const LevelBC& bc) {
-  const int n = 1 << L, n3 = 1 << (3 * L);
-  const WallRule<T> wr(bc);
-#pragma unroll 1
-  for (int c = threadIdx.x; c < n3; c += blockDim.x) {
-    const int i = c & (n - 1), j = (c >> L) & (n - 1), k = c >> (2 * L);
-    const T pc = pbar[c];
-    f[c] = f[c] + (lds_nb<T, KIND>(pbar, n, L, i, j, k, pc, bc, wr) - (T)6 * pc) * ih2;
-  }
-  __syncthreads();
-}
-
-// One FAS cycle (Alg. 3) from level topl down to 0 and back, each level with its physical
-// description; phibar of each level at base + 2 total.  Only the forms without face values
-// (KIND 1, 2).  The single cell is solved when a face fixes the zero point (a zero-valued
-// fixed face) and otherwise keeps phibar (a zero correction), as in the per-operator cycle.
-template <typename T, int KIND>
-__device__ __forceinline__ void tail_fas_vcycle(T* base, int total, int topl, const TailMeta& m, int npre, int npost,
-                                                T omega) {
-  T* pbase = base + 2 * total;
-#pragma unroll 1
-  for (int l = topl; l >= 1; --l) {
-    const LevelBC bc = m.phys[l];
-    T* u = base + level_offset(l);
-    T* f = base + total + level_offset(l);
-#pragma unroll 1
-    for (int it = 0; it < npre; ++it) tail_smooth<T, KIND>(u, f, l, (T)m.h2[l], omega, bc);
-    tail_fas_restrict<T, KIND>(u, f, base + total + level_offset(l - 1), pbase + level_offset(l - 1),
-                               base + level_offset(l - 1), l, (T)(1.0 / m.h2[l]), bc);
-    const LevelBC bcc = m.phys[l - 1];
-    tail_fas_source<T, KIND>(pbase + level_offset(l - 1), base + total + level_offset(l - 1), l - 1,
-                             (T)(1.0 / m.h2[l - 1]), bcc);
-  }
-  if (threadIdx.x == 0) {
-    const LevelBC b0 = m.phys[0];
-    bool fixes = false;
-    for (int f = 0; f < 6; ++f) fixes = fixes || bc_has_value(b0.kind[f]);
-    if (fixes) base[0] = coarsest_value(base[total], (T)m.h2[0], b0);
-  }
-  __syncthreads();
-  const LevelBC hom = m.hom;
-#pragma unroll 1
-  for (int l = 1; l <= topl; ++l) {
-    // the coarse-grid correction psi - phibar, prolonged with the homogeneous conditions
-    T* uc = base + level_offset(l - 1);
-    const T* pc = pbase + level_offset(l - 1);
-    const int nc3 = 1 << (3 * (l - 1));
-    for (int c = threadIdx.x; c < nc3; c += blockDim.x) uc[c] = uc[c] - pc[c];
-    __syncthreads();
-    T* u = base + level_offset(l);
-    tail_prolong<T, 0, KIND>(uc, u, l, hom);
-    const LevelBC bc = m.phys[l];
-#pragma unroll 1
-    for (int it = 0; it < npost; ++it) tail_smooth<T, KIND>(u, base + total + level_offset(l), l, (T)m.h2[l], omega, bc);
-  }
-}
-
-template <typename T, int KIND>
-__global__ void __launch_bounds__(kTailThreads) k_tail(TailArgs a) {
-  const T* const* fg = reinterpret_cast<const T* const*>(a.fg);
-  T* ug = reinterpret_cast<T*>(a.ug);
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ TailMeta m;
-  T* base = reinterpret_cast<T*>(smem_raw);
-  const int total = a.total, top = a.top;
-  if (threadIdx.x == 0) {
-    for (int l = 0; l < 5; ++l) {
-      m.phys[l] = a.phys[l];
-      m.h2[l] = a.h[l] * a.h[l];
-    }
-    m.top = a.bc_top;
-    m.hom = a.hom;
-  }
-  __syncthreads();
-  const int ntop = 1 << (3 * top);
-  const T omega = (T)a.omega;
-  const bool fmg = (a.mode & TAIL_FMG) != 0;
-  if (fmg) {
-    for (int l = 0; l <= top; ++l) {
-      const int n3 = 1 << (3 * l);
-      const T* src = fg[l];
-      T* dst = base + total + level_offset(l);
-      for (int c = threadIdx.x; c < n3; c += blockDim.x) dst[c] = src[c];
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) base[0] = coarsest_value(base[total], (T)m.h2[0], m.phys[0]);
-  } else {
-    T* u = base + level_offset(top);
-    T* f = base + total + level_offset(top);
-    const T* src = fg[top];
-    for (int c = threadIdx.x; c < ntop; c += blockDim.x) {
-      f[c] = src[c];
-      u[c] = (a.mode & TAIL_LOAD_U) ? ug[c] : (T)0;
-    }
-  }
-  __syncthreads();
-  // Alg. 2 (FMG): on each level l = 1..top, the tricubic prolongation, then one V-cycle with
-  // the level's own physical description (the V-cycle on level l overwrites the sources below
-  // with restricted defects, which FMG no longer needs: it proceeds upwards).  V-cycle mode:
-  // the one V-cycle on level top.  One copy of the V-cycle code serves both (a small kernel
-  // image keeps the instruction cache warm across the many short phases).
-  if ((a.mode & TAIL_FAS) != 0) {
-    if constexpr (KIND != 0) tail_fas_vcycle<T, KIND>(base, total, top, m, a.npre, a.npost, omega);
-  } else {
-#pragma unroll 1
-    for (int l = fmg ? 1 : top; l <= top; ++l) {
-      if (fmg) {
-        const LevelBC below = m.phys[l - 1];
-        tail_prolong<T, 1, KIND>(base + level_offset(l - 1), base + level_offset(l), l, below);
-      }
-      const LevelBC here = fmg ? m.phys[l] : m.top;
-      tail_vcycle<T, KIND>(base, total, l, m, here, a.npre, a.npost, omega);
-    }
-  }
-  const T* u = base + level_offset(top);
-  for (int c = threadIdx.x; c < ntop; c += blockDim.x) ug[c] = u[c];
-}
-
-template <typename T>
-void launch_tail(const TailArgs& a, hipStream_t s) {
-  TailArgs b = a;
-  b.total = level_offset(a.top + 1);
-  // FAS: phibar of every level beside u and f
-  const size_t lds = ((b.mode & TAIL_FAS) ? 3 : 2) * (size_t)b.total * sizeof(T);
-  // the periodic form when every description this launch reads is periodic
-  auto periodic = [](const LevelBC& q) {
-    for (int f = 0; f < 6; ++f)
-      if (q.kind[f] != BC_PERIODIC) return false;
-    return true;
-  };
-  // the wall form when no description carries face values
-  auto valueless = [](const LevelBC& q) {
-    for (int f = 0; f < 6; ++f)
-      if (q.kind[f] != BC_PERIODIC && q.kind[f] != BC_ZERO_GRADIENT && q.b[f]) return false;
-    return true;
-  };
-  // FMG and FAS read every level's physical description
-  const bool fmg = (b.mode & (TAIL_FMG | TAIL_FAS)) != 0;
-  bool per = periodic(b.hom) && (fmg || periodic(b.bc_top));
-  bool walls = valueless(b.hom) && (fmg || valueless(b.bc_top));
-  if (fmg)
-    for (int l = 0; l <= b.top; ++l) {
-      per = per && periodic(b.phys[l]);
-      walls = walls && valueless(b.phys[l]);
-    }
-  if (per)
-    hipLaunchKernelGGL((k_tail<T, 1>), dim3(1), dim3(kTailThreads), lds, s, b);
-  else if (walls)
-    hipLaunchKernelGGL((k_tail<T, 2>), dim3(1), dim3(kTailThreads), lds, s, b);
-  else
-    hipLaunchKernelGGL((k_tail<T, 0>), dim3(1), dim3(kTailThreads), lds, s, b);
-}
-
-// the FAS form (forms 1 and 2 only) holds phibar beside u and f
-static size_t tail_fas_lds(int top) { return tail_lds_bytes(top, sizeof(double)) / 2 * 3; }
-
-bool tail_fas_prepare(size_t lds_per_block) { return lds_per_block >= tail_fas_lds(4); }
-
-int tail_prepare(size_t lds_per_block) {
-  const size_t need64 = tail_lds_bytes(4, sizeof(double));
-  const size_t need32 = tail_lds_bytes(4, sizeof(float));
-  for (const void* k : {reinterpret_cast<const void*>(&k_tail<float, 0>), reinterpret_cast<const void*>(&k_tail<float, 1>),
-                        reinterpret_cast<const void*>(&k_tail<float, 2>)})
-    (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)need32);
-  if (lds_per_block < need64) return 3;
-  // forms 1 and 2 also run the FAS cycle, with phibar beside u and f, where that fits
-  const size_t need_fas = tail_fas_lds(4);
-  const size_t need12 = lds_per_block >= need_fas ? need_fas : need64;
-  const void* k64[3] = {reinterpret_cast<const void*>(&k_tail<double, 0>),
-                        reinterpret_cast<const void*>(&k_tail<double, 1>),
-                        reinterpret_cast<const void*>(&k_tail<double, 2>)};
-  for (int q = 0; q < 3; ++q)
-    if (hipFuncSetAttribute(k64[q], hipFuncAttributeMaxDynamicSharedMemorySize, (int)(q == 0 ? need64 : need12)) !=
-        hipSuccess) {
-      (void)hipGetLastError();
-      return 3;
-    }
-  return 4;
-}
-
-
-
-size_t tail_lds_bytes(int top, size_t elem) {
-  size_t total = 0;
-  for (int l = 0; l <= top; ++l) total += (size_t)1 << (3 * l);
-  return 2 * total * elem;
-}
-
 // ------------------------------------------------------------------ elementwise / set-up
 
 // u += shift (gauge fix, Sec. 2.3.6)
@@ -1076,8 +627,7 @@ void launch_face_restrict(const double* ef, double* ec, int nc, hipStream_t s) {
   template void launch_defect_restrict<T>(const T*, const T*, T*, T*, int, double, const LevelBC&,         \
                                           hipStream_t);                                                    \
   template void launch_prolong<T>(const T*, T*, int, const LevelBC&, int, hipStream_t);                    \
-  template void launch_coarsest<T>(T*, const T*, double, const LevelBC&, hipStream_t);                     \
-  template void launch_tail<T>(const TailArgs&, hipStream_t);
+  template void launch_coarsest<T>(T*, const T*, double, const LevelBC&, hipStream_t);
 
 MG_INST(double)
 MG_INST(float)

@@ -41,21 +41,23 @@ inline int ilog2(long long n) {
   return l;
 }
 
-enum : int { TAIL_FMG = 1, TAIL_LOAD_U = 2, TAIL_FAS = 4 };
+enum : int { TAIL_FMG = 1, TAIL_LOAD_U = 2 };
 
-// Arguments of the coarse-tail kernel (all levels <= 16^3 of one hierarchy in LDS).
+// Arguments of the coarse-tail kernel (mg_tail.hip): levels 0..top (top <= 4) of one hierarchy.
+// V-cycle mode: one V-cycle on u at level top, from u in ug (TAIL_LOAD_U) or from zero.
+// TAIL_FMG: full multigrid from the source of level top, whose restrictions the kernel makes.
 struct TailArgs {
-  int top;            // highest level held (level 0 is one cell)
-  int total;          // cells over levels 0..top (set by the launcher)
+  int top;
   int mode;           // TAIL_FMG / TAIL_LOAD_U bits
   int npre, npost;
   double omega;
-  double h[5];        // cell width per level
-  LevelBC bc_top;     // description of level `top` in V-cycle mode
-  LevelBC hom;        // homogeneous description (coarse corrections)
+  double h;           // cell width of level top
+  LevelBC bc_top;     // description of level top in V-cycle mode (face kinds as hom's)
+  LevelBC hom;        // homogeneous description (coarse corrections; its kinds are every level's)
   LevelBC phys[5];    // physical description per level (FMG mode)
-  const void* fg[5];  // device source per level (FMG mode: all levels; V-cycle mode: top only)
-  void* ug;           // device solution / correction of level `top` (in and out)
+  const void* f;      // device source of level top
+  void* ug;           // device solution / correction of level top (in and out)
+  double* norm;       // device: the sum of squared defects of the result, or null
 };
 
 template <typename T>
@@ -74,13 +76,6 @@ template <typename T>
 void launch_coarsest(T* u, const T* f, double h, const LevelBC& bc, hipStream_t s);
 template <typename T>
 void launch_tail(const TailArgs& a, hipStream_t s);
-size_t tail_lds_bytes(int top, size_t elem);
-// Allows the FP64 tail the LDS of its FAS form (u, f and phibar of levels 0..4); returns
-// whether it fits.
-bool tail_fas_prepare(size_t lds_per_block);
-// Allows the FP64 tail its dynamic LDS; returns the highest level it can hold (3 or 4).
-int tail_prepare(size_t lds_per_block);
-
 // FAS (Alg. 3): fc = restricted defect, pbar = uc = restricted u; f += L pbar on the coarse
 // level; u -= pbar (the coarse-grid correction)
 void launch_fas_restrict(const double* u, const double* f, double* fc, double* pbar, double* uc, int n, double h,
