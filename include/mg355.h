@@ -154,11 +154,11 @@ int mg_autotune(mg_ctx *ctx, const mg_params *p, int reps);
  * "tail fp64|fp32 l" (highest level, 1..4, solved by the single-workgroup LDS tail) and
  * "tb fp64|fp32 0|1" (1: large-level sweeps two per pass over HBM) and "blkz fp64|fp32 0|1"
  * (MeshBlock layout, 1: streaming passes across blocks on the large block levels) and
- * "march fp64|fp32 0|1|2" (V(2,2) legs of the levels >= 128^3, or >= the fusedmin size when
- * that was set larger, as two streaming passes -- down: two sweeps + restricted defect; up:
+ * "march fp64|fp32 0|1|2" (V(2,2) legs of the levels >= 256^3 -- all-periodic FP64 ones from 128^3 --, or >= the
+ * fusedmin size when that was set larger, as two streaming passes -- down: two sweeps + restricted defect; up:
  * prolongation + two sweeps + norm -- 0 off, 1 when every face is periodic, 2 always (default))
- * and "tile fp64|fp32 0|1" (1, the default: with V(2,2), each leg of the levels 32^3 .. 128^3
- * that the streaming passes do not take runs as one region-tile launch) and "split fp64 0|1"
+ * and "tile fp64|fp32 0|1" (1, the default: with one or two sweeps per leg, each leg of the
+ * levels 32^3 .. 128^3 that the streaming passes do not take runs as one region-tile launch) and "split fp64 0|1"
  * (1, the default: an FP64 streaming pass of a level with x or y walls runs its interior tiles
  * and its wall tiles as two launches on the context's second stream and the caller's, joined
  * before the pass returns; 0: one launch; the serving runtime sets 0) and "inner fp32 k"

@@ -305,12 +305,17 @@ struct Hier {
   double omega = 1.15;
 };
 
-// Smallest level side on which the two-sweep passes run: kMarchMinN, or the one-sweep passes'
-// threshold ("fusedmin") when that was set larger.
+// Smallest level side on which the two-sweep passes run, or the one-sweep passes' threshold
+// ("fusedmin") when that was set larger.  At 128^3 the passes are taken in FP64 on an all-periodic
+// level only (40 + 34 us for the two legs against 38 + 46 us as region tiles); with walls the
+// tiles win (43 + 56 us against 84 + 96 us), and in FP32 (24 + 25 us against 40 + 39 us with walls;
+// 25 us a leg either way without).
 template <typename T>
-int march_min_n(const mg_ctx* c) {
+int march_min_n(const mg_ctx* c, const LevelBC& bc) {
   const int v = c->fused_min_n[sizeof(T) == 8 ? 0 : 1];
-  return v > 0 ? std::max(kMarchMinN, v) : kMarchMinN;
+  bool per = sizeof(T) == 8;
+  for (int f = 0; f < 6; ++f) per = per && bc.kind[f] == BC_PERIODIC;
+  return std::max(per ? kMarchMinN : 2 * kMarchMinN, v);
 }
 
 // Does a MeshBlock level of 2^l cells per side fit the two-sweep passes' 32-bit block index?
@@ -351,8 +356,8 @@ struct Solver {
       // algorithmic bytes: u and f read, u written, coarse source and correction written
       if (timed) kernel_end(march_name<T>(false, false, bc), 3 * cellsT + cellsT / 4);
     } else {
-      tile_down<T>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], H.u[l - 1], n, 0, 0, H.h[l], H.omega, bc, s);
-      if (timed) kernel_end(tile_name<T>(false, false), 3 * cellsT + cellsT / 4);
+      tile_down<T>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], nullptr, H.u[l - 1], n, 0, H.npre, H.h[l], H.omega, bc, s);
+      if (timed) kernel_end(tile_name<T>(H.npre, false, bc, n), 3 * cellsT + cellsT / 4);
     }
   }
   // The same for MeshBlock level l (big: the two-sweep pass across blocks).
@@ -362,8 +367,8 @@ struct Solver {
     const double cellsT = (double)cells(l) * sizeof(T);
     if (timed) kernel_begin(true);
     if (big) march_down<T>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], H.u[l - 1], nl, H.h[l], H.omega, bc, s, Lm, aux_of());
-    else tile_down<T>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], H.u[l - 1], nl, Lm, Lb, H.h[l], H.omega, bc, s);
-    if (timed) kernel_end(big ? march_name<T>(false, false, bc, true) : tile_name<T>(false, false, true),
+    else tile_down<T>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], nullptr, H.u[l - 1], nl, Lm, H.npre, H.h[l], H.omega, bc, s);
+    if (timed) kernel_end(big ? march_name<T>(false, false, bc, true) : tile_name<T>(H.npre, false, bc, nl),
                           3 * cellsT + cellsT / 4);
   }
 
@@ -375,14 +380,14 @@ struct Solver {
   bool down_ahead(Hier<double>& H, const LevelBC& bc) {
     const int L = H.L;
     const bool timed = timed_top && ktiming;
-    if (H.npre != 2 || H.npost != 2 || L == H.T_top) return false;
+    if (L == H.T_top) return false;
     if (Lb < 0) {
       if (march_on<double>(H, L, bc)) down_leg<double>(H, L, bc, true, false, timed);
       else if ((1 << L) < fused_min_n64 && tile_on<double>(H, L)) down_leg<double>(H, L, bc, false, false, timed);
       else return false;
     } else {
       if (L <= Lb) return false;
-      const bool big = c->blk_zmarch[0] != 0 && (1 << L) >= march_min<double>() && march_blk_on<double>(H, L, bc);
+      const bool big = c->blk_zmarch[0] != 0 && (1 << L) >= march_min_n<double>(c, bc) && march_blk_on<double>(H, L, bc);
       if (!big && !tile_on<double>(H, L)) return false;
       blk_down_leg<double>(H, L, bc, big, timed);
     }
@@ -481,16 +486,11 @@ struct Solver {
   bool march_on(const Hier<T>& H, int l, const LevelBC& bc) const {
     const int mode = c->march[sizeof(T) == 8 ? 0 : 1] < 0 ? 2 : c->march[sizeof(T) == 8 ? 0 : 1];
     if (mode == 0 || !use_fused || !H.u2[l] || l == H.T_top || Lb >= 0 || H.npre != 2 || H.npost != 2) return false;
-    if ((1 << l) < march_min<T>() || tblock_on<T>()) return false;
+    if ((1 << l) < march_min_n<T>(c, bc) || tblock_on<T>()) return false;
     if (mode == 1)
       for (int f = 0; f < 6; ++f)
         if (bc.kind[f] != BC_PERIODIC) return false;
     return true;
-  }
-
-  template <typename T>
-  int march_min() const {
-    return march_min_n<T>(c);
   }
 
   // the second stream of the split passes (null: one launch per pass)
@@ -514,8 +514,8 @@ struct Solver {
   bool tile_on(const Hier<T>& H, int l) const {
     const int v = c->tile[sizeof(T) == 8 ? 0 : 1];
     const int n = 1 << l;
-    return (v < 0 || v == 1) && H.u2[l] && l != H.T_top && H.npre == 2 && H.npost == 2 && n >= kTileMinN &&
-           n <= kTileMaxN;
+    return (v < 0 || v == 1) && H.u2[l] && l != H.T_top && tile_sweeps_ok(H.npre) && tile_sweeps_ok(H.npost) &&
+           n >= kTileMinN && n <= kTileMaxN;
   }
 
   // FP64, dense: can the first pre-sweep of the finest level's V-cycle run as a head pass (a
@@ -599,8 +599,8 @@ struct Solver {
       vcycle(H, l - 1, H.hom, false, false);
       double* npart = want_norm && sizeof(T) == 8 ? part : nullptr;
       if (timed) kernel_begin(true);
-      const int np = tile_up<T>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, npart, n, 0, 0, h, H.omega, bc, s);
-      if (timed) kernel_end(tile_name<T>(true, npart != nullptr), 3 * cellsT + cellsT / 8);
+      const int np = tile_up<T>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, npart, n, 0, H.npost, h, H.omega, bc, s);
+      if (timed) kernel_end(tile_name<T>(H.npost, true, bc, n), 3 * cellsT + cellsT / 8);
       if (npart) launch_sum_partials(part, np, scal + 2, s);
       return npart != nullptr;
     }
@@ -797,15 +797,15 @@ struct Solver {
       // restricted defect, phibar, the coarse level started from it), steps 5-7 on the coarse
       // level, up (the prolonged correction psi - phibar, two sweeps, the norm when asked)
       if (timed) kernel_begin(true);
-      tile_down_fas<double>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], pbar[l - 1], H.u[l - 1], n, H.h[l], H.omega, bc, s);
-      if (timed) kernel_end("k_tile_leg<double, false, false, false, true>", 3 * cellsT + 3 * cellsT / 8);
+      tile_down<double>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], pbar[l - 1], H.u[l - 1], n, 0, H.npre, H.h[l], H.omega, bc, s);
+      if (timed) kernel_end(tile_name<double>(H.npre, false, bc, n), 3 * cellsT + 3 * cellsT / 8);
       launch_fas_source(pbar[l - 1], H.f[l - 1], n / 2, H.h[l - 1], H.phys[l - 1], s);       // 5
       fas_cycle(H, pbar, l - 1);                                                             // 6
       launch_fas_correction(H.u[l - 1], pbar[l - 1], cells(l - 1), s);                       // 7
       double* npart = want_norm ? part : nullptr;
       if (timed) kernel_begin(true);
-      const int np = tile_up<double>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, npart, n, 0, 0, H.h[l], H.omega, bc, s);
-      if (timed) kernel_end(tile_name<double>(true, npart != nullptr), 3 * cellsT + cellsT / 8);
+      const int np = tile_up<double>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, npart, n, 0, H.npost, H.h[l], H.omega, bc, s);
+      if (timed) kernel_end(tile_name<double>(H.npost, true, bc, n), 3 * cellsT + cellsT / 8);
       if (npart) launch_sum_partials(part, np, scal + 2, s);
       return npart != nullptr;
     }
@@ -941,8 +941,8 @@ struct Solver {
     const int Lm = l - Lb;
     const int nl = 1 << l;
     const int vz = c->blk_zmarch[sizeof(T) == 8 ? 0 : 1];
-    const bool big = vz != 0 && nl >= march_min<T>() && march_blk_on<T>(H, l, bc);
-    if ((big || tile_on<T>(H, l)) && H.npre == 2 && H.npost == 2) {
+    const bool big = vz != 0 && nl >= march_min_n<T>(c, bc) && march_blk_on<T>(H, l, bc);
+    if (big || tile_on<T>(H, l)) {
       // each leg of the block level in one launch over all blocks: the two-sweep streaming
       // passes on the large levels, region tiles below
       const bool timed = timed_top && l == H.L && ktiming;
@@ -954,9 +954,9 @@ struct Solver {
       if (timed) kernel_begin(true);
       const int np = big ? march_up<T>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, npart, nl, H.h[l], H.omega, bc, s, Lm,
                                        aux_of())
-                         : tile_up<T>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, npart, nl, Lm, Lb, H.h[l], H.omega, bc, s);
+                         : tile_up<T>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, npart, nl, Lm, H.npost, H.h[l], H.omega, bc, s);
       if (timed)
-        kernel_end(big ? march_name<T>(true, npart != nullptr, bc, true) : tile_name<T>(true, npart != nullptr, true),
+        kernel_end(big ? march_name<T>(true, npart != nullptr, bc, true) : tile_name<T>(H.npost, true, bc, nl),
                    3 * cellsT + cellsT / 8);
       if (npart) launch_sum_partials(part, np, scal + 2, s);
       return npart != nullptr;
@@ -1668,7 +1668,7 @@ int autotune_blocks(mg_ctx* c, const mg_params* p, int Lb, int reps) {
           if (ms < best_ms) { best_ms = ms; best = t; }
         }
     c->blk_tune[(sizeof(T) == 8 ? 0 : 1000) + 100 * Lm + Lb] = best;
-    if (l == L && p->npre == 2 && p->npost == 2 && (1 << l) >= march_min_n<T>(c) && blk_march_fits(l)) {
+    if (l == L && p->npre == 2 && p->npost == 2 && (1 << l) >= march_min_n<T>(c, bc) && blk_march_fits(l)) {
       // V(2,2) on the finest block level: both legs as the two-sweep streaming passes across
       // blocks against the four halo-tile sweeps alone (a lower bound on that schedule)
       T* fc = buf[3];
@@ -1978,7 +1978,7 @@ template <typename T>
 bool op_march(const mg_ctx* c, int n, int sweeps, const LevelBC& b) {
   const int v = c->march[sizeof(T) == 8 ? 0 : 1];
   const int mode = v < 0 ? 2 : v;
-  if (mode == 0 || sweeps != 2 || n < kMarchMinN) return false;
+  if (mode == 0 || sweeps != 2 || n < march_min_n<T>(c, b)) return false;
   if (mode == 1)
     for (int f = 0; f < 6; ++f)
       if (b.kind[f] != BC_PERIODIC) return false;
@@ -1999,7 +1999,7 @@ bool hom_arrays_null(const LevelBC& b) {
 template <typename T>
 bool op_tile(const mg_ctx* c, int n, int sweeps) {
   const int v = c->tile[sizeof(T) == 8 ? 0 : 1];
-  return (v < 0 || v == 1) && sweeps == 2 && n >= kTileMinN && n <= kTileMaxN && n < kFusedDefaultMinN;
+  return (v < 0 || v == 1) && tile_sweeps_ok(sweeps) && n >= kTileMinN && n <= kTileMaxN && n < kFusedDefaultMinN;
 }
 
 // Down step (Alg. 1 steps 1-3) with the context's fusion schedule for this precision.
@@ -2023,7 +2023,7 @@ int op_down(mg_ctx* c, int n, double h, double omega, int npre, const mg_level_b
     double* tmp = nullptr;
     st = op_scratch(c, cells(ilog2(n)) * sizeof(T), &tmp);
     if (st) return st;
-    tile_down<T>(u, reinterpret_cast<T*>(tmp), f, fc, uc, n, 0, 0, h, omega, b, s);
+    tile_down<T>(u, reinterpret_cast<T*>(tmp), f, fc, nullptr, uc, n, 0, npre, h, omega, b, s);
     HIP_CHECK(c, hipMemcpyAsync(u, tmp, cells(ilog2(n)) * sizeof(T), hipMemcpyDeviceToDevice, s));
     return op_epilogue(c);
   }
@@ -2073,7 +2073,7 @@ int op_up(mg_ctx* c, int n, double h, double omega, int npost, const mg_level_bc
     double* tmp = nullptr;
     st = op_scratch(c, cells(ilog2(n)) * sizeof(T), &tmp);
     if (st) return st;
-    (void)tile_up<T>(u, reinterpret_cast<T*>(tmp), f, uc, bcc, nullptr, n, 0, 0, h, omega, b, s);
+    (void)tile_up<T>(u, reinterpret_cast<T*>(tmp), f, uc, bcc, nullptr, n, 0, npost, h, omega, b, s);
     HIP_CHECK(c, hipMemcpyAsync(u, tmp, cells(ilog2(n)) * sizeof(T), hipMemcpyDeviceToDevice, s));
     return op_epilogue(c);
   }

@@ -1,0 +1,118 @@
+"""The one-launch kernels of the small levels at the sizes where they can go wrong: the region-tile
+legs (32^3: regions shorter than the halo, so a wall lies in the halo of the region after next;
+64^3 and 128^3) with one and two sweeps per leg, and the coarse tail (every grid <= 16^3, sweep
+counts 0..4), against the oracle.
+
+Bounds: a leg's u is 1e-13 (FP64) or 40 FP32 epsilons of the largest magnitude in its sums (the
+values, the face values and h^2 f); its coarse source the same of max|f| + 12 max|u| / h^2.  Whole
+solves at equal cycle counts: phi to 1e-10, as every solve check."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+from oracle import FIXED, PERIODIC, ZERO_GRADIENT
+from parity import rel
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+KINDS = {
+    "periodic": [PERIODIC] * 6,
+    "fixed": [FIXED] * 6,
+    "layer": [PERIODIC] * 4 + [FIXED, ZERO_GRADIENT],
+    "mixed": [FIXED, ZERO_GRADIENT, ZERO_GRADIENT, FIXED, PERIODIC, PERIODIC],
+}
+OMEGA = 1.15
+
+
+@pytest.fixture(scope="module")
+def mg():
+    import paper_2302_13903_amd as m
+    return m
+
+
+def dev(a, dt=torch.float64):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0", dt)
+
+
+def host(t):
+    torch.cuda.synchronize()
+    return t.cpu().numpy().astype(np.float64)
+
+
+def sweeps(u, f, h, kinds, bext, count):
+    for _ in range(count):
+        u = oracle.smooth(u, f, h, OMEGA, kinds, bext)
+    return u
+
+
+@pytest.mark.parametrize("f32", [False, True], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("ns", [1, 2])
+@pytest.mark.parametrize("n,kind", [(32, "periodic"), (32, "fixed"), (32, "layer"), (64, "layer"), (64, "mixed"),
+                                    (128, "fixed")])
+def test_tile_legs(mg, n, kind, ns, f32):
+    kinds = KINDS[kind]
+    hom = [k if k in (PERIODIC, ZERO_GRADIENT) else FIXED for k in kinds]
+    print(f"tile legs n={n} {kind} ns={ns} f32={f32}", flush=True)
+    rng = np.random.default_rng(n + ns)
+    u, e = rng.standard_normal((n,) * 3), rng.standard_normal((n // 2,) * 3)
+    f = rng.standard_normal((n,) * 3) * n * n
+    bext = [rng.standard_normal((n + 2,) * 2) if k == FIXED else None for k in kinds]
+    dt, h = (torch.float32 if f32 else torch.float64), 1.0 / n
+    if f32:
+        u, e, f = (a.astype(np.float32).astype(np.float64) for a in (u, e, f))
+    dbext = [None if b is None else dev(b) for b in bext]
+    ctx = mg.Context(0)
+    ctx.set_tuning("march fp64 0\nmarch fp32 0\n")
+    su = max(np.abs(u).max(), np.abs(e).max(), h * h * np.abs(f).max()) + 2 * max([0.0] + [np.abs(b).max() for b in bext if b is not None])
+    eps = 40 * float(np.finfo(np.float32).eps) if f32 else 1e-13
+    down, up = (mg.mg_op_down_f32, mg.mg_op_up_f32) if f32 else (mg.mg_op_down, mg.mg_op_up)
+
+    ref = sweeps(u, f, h, kinds, bext, ns)
+    ref_fc = oracle.restrict(oracle.defect(ref, f, h, kinds, bext))
+    du, fc, uc = dev(u, dt), dev(e, dt), dev(e, dt)
+    down(du, dev(f, dt), fc, uc, h, OMEGA, ns, kinds, dbext, ctx=ctx)
+    assert np.abs(host(du) - ref).max() <= eps * 6 * su
+    assert np.abs(host(fc) - ref_fc).max() <= eps * (np.abs(f).max() + 12 * su / h ** 2)
+    assert float(uc.abs().max()) == 0.0
+
+    ref = sweeps(oracle.prolong_add(e, u, hom), f, h, kinds, bext, ns)
+    du = dev(u, dt)
+    up(du, dev(f, dt), dev(e, dt), h, OMEGA, ns, kinds, dbext, hom, ctx=ctx)
+    assert np.abs(host(du) - ref).max() <= eps * 12 * su
+
+
+@pytest.mark.parametrize("kind", list(KINDS))
+@pytest.mark.parametrize("n,npre,npost", [(2, 2, 2), (4, 1, 3), (8, 0, 2), (8, 4, 0), (16, 2, 2), (16, 1, 1), (16, 3, 4),
+                                          (32, 1, 1), (64, 1, 2), (64, 1, 1)])
+@pytest.mark.parametrize("mode", ["fmg", "mgi"])
+def test_small_solves(mg, n, npre, npost, kind, mode):
+    kinds = KINDS[kind]
+    print(f"solve n={n} V({npre},{npost}) {kind} {mode}", flush=True)
+    rng = np.random.default_rng(7 * n + npre)
+    rho = rng.standard_normal((n,) * 3)
+    fb = [rng.standard_normal((n, n)) if k == FIXED else None for k in kinds]
+    phi0 = rng.standard_normal((n,) * 3)
+    ref, hist, _ = oracle.solve(rho, 1.0 / n, kinds, fixed_b=fb, fixed_cycles=4, npre=npre, npost=npost, mode=mode,
+                                phi0=phi0 if mode == "mgi" else None)
+    phi = dev(phi0)
+    got, ghist, _ = mg.solve(dev(rho), 1.0 / n, kinds, fixed_b=[None if b is None else dev(b) for b in fb],
+                             fixed_cycles=4, npre=npre, npost=npost, mode=mode, phi=phi)
+    assert rel(host(got), ref) < 1e-10
+    # a defect is a difference of terms 12 max|phi| / h^2: its floor beside the history's own 1e-6
+    rms_f = 4 * np.pi * np.sqrt(np.mean(rho ** 2))
+    floor = 12 * np.finfo(np.float64).eps * np.abs(ref).max() * n * n / rms_f
+    assert len(ghist) == len(hist)
+    for a, b in zip(ghist, hist):
+        assert abs(a - b) <= 1e-6 * b + 10 * floor
+
+
+@pytest.mark.parametrize("npre,npost", [(1, 1), (2, 1)])
+def test_blocks_one_sweep(mg, npre, npost):
+    """Block levels with one sweep per leg give the dense potential."""
+    n = 64
+    rho = wl.gaussian_clumps(n, 3, n_clumps=6)
+    a, _, _ = mg.solve(dev(rho), 1.0 / n, "fixed", fixed_cycles=4, npre=npre, npost=npost)
+    b, _, _ = mg.solve(mg.to_blocks(dev(rho), 16), 1.0 / n, "fixed", fixed_cycles=4, npre=npre, npost=npost, layout="blocks")
+    assert rel(host(mg.from_blocks(b, n, 16)), host(a)) < 1e-12
