@@ -212,7 +212,7 @@ int mg_solve_noalloc(mg_ctx *ctx, const mg_params *p, const mg_bc *bc, const dou
 int mg_solve_simple(mg_ctx *ctx, int n, const double *rho, int bc_kind, double dx, double tol, double *phi,
                     double *hist, int *n_hist, void *stream);
 
-/* Timing of the last mg_solve on this context, from HIP events on its stream:
+/* Timing of the last mg_solve on this context, from the device clock read on its stream:
  * *fmg_ms = set-up + FMG sweep; cycle_ms[c] = wall time of V-cycle c (including its
  * residual norm); *n = number of cycles (up to cap). */
 int mg_last_timing(const mg_ctx *ctx, double *setup_ms, double *fmg_ms, double *cycle_ms,

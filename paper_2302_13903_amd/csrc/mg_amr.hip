@@ -1492,12 +1492,16 @@ int amr_solve_impl(int device, const mg_params* p, const mg_amr_mesh* m, const m
       return fail_amr(err, MG_ERR_INVALID_ARG, "too many refinement levels for the multipole moments");
     }
     const double G = p->four_pi_g / (4.0 * M_PI);
-    for (size_t q = 0; q < pl.bface.size(); ++q) {
-      const int n = pl.bface_n[q];
-      double* out[6];
-      for (int f = 0; f < 6; ++f)
-        out[f] = bc->kind[f] == MG_BC_MULTIPOLE ? pl.bface[q] + (size_t)f * n * n : nullptr;
-      launch_multipole_faces(mps, bc->lmax, G, n, 1.0 / n, 1.0, out, s, 0);
+    for (size_t q = 0; q < pl.bface.size();) {
+      MpFaceLevels mp{};
+      for (; q < pl.bface.size() && mp.count < 16; ++q, ++mp.count) {
+        const int n = pl.bface_n[q];
+        mp.nl[mp.count] = n;
+        mp.hl[mp.count] = 1.0 / n;
+        for (int f = 0; f < 6; ++f)
+          mp.out[mp.count][f] = bc->kind[f] == MG_BC_MULTIPOLE ? pl.bface[q] + (size_t)f * n * n : nullptr;
+      }
+      launch_multipole_faces(mps, bc->lmax, G, 1.0, mp, s, 0);
     }
   }
 

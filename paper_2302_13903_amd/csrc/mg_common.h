@@ -157,4 +157,72 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
+// Where the sum over all workgroups of a launch (or of the launches of a split pass) goes.  The
+// workgroup that arrives last adds the partials in their fixed order, so no second launch is
+// needed and the result does not depend on the order of arrival.  (A launch for the final sum
+// and one to publish it cost 3.5 + 4 us per cycle; the last workgroup's part of it about 1.5.)
+constexpr int kPubScalars = 64;
+struct SumSink {
+  double* part = nullptr;            // one partial per workgroup; null: no sum wanted
+  int first = 0, total = 0;          // this launch's first partial, partials in all
+  unsigned* ticket = nullptr;        // arrivals, zero before the launch; left zero
+  double* out = nullptr;             // device: the sum
+  // coherent pinned host memory, or null: [0] the sum's bits, [2] the device clock (ticks of
+  // wall_clock64), [8 ..] kPubScalars doubles from `copy` when that is given, and last, when
+  // those have arrived, [1] = seq
+  unsigned long long* pub = nullptr;
+  unsigned long long seq = 0;
+  const double* copy = nullptr;
+};
+
+// By the first wave of a workgroup.
+__device__ __forceinline__ void publish_scalars(unsigned long long* pub, unsigned long long seq, double value,
+                                                const double* copy) {
+  const int lane = threadIdx.x & 63;
+  auto put = [&](int at, unsigned long long v) {
+    __hip_atomic_store(pub + at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  };
+  if (copy) put(8 + lane, __builtin_bit_cast(unsigned long long, copy[lane]));
+  if (lane == 0) {
+    put(0, __builtin_bit_cast(unsigned long long, value));
+    put(2, (unsigned long long)wall_clock64());
+  }
+  // every store of this wave has been acknowledged before the number is written
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if (lane == 0) put(1, seq);
+}
+
+// By every thread of a workgroup of THREADS; `mine`: this workgroup's sum (thread 0's counts);
+// red: THREADS / 64 doubles of shared memory, free on entry.
+template <int THREADS>
+__device__ __forceinline__ void finish_sum(const SumSink& S, double mine, double* red) {
+  __shared__ int last;
+  const int tid = threadIdx.x;
+  double sum = mine;
+  if (S.total > 1) {
+    if (tid == 0) {
+      // agent-scope (cache-bypassing) accesses: the partial is in memory before the arrival is counted
+      __hip_atomic_store(S.part + S.first + blockIdx.x, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      const unsigned t = __hip_atomic_fetch_add(S.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      last = t == (unsigned)S.total - 1u;
+    }
+    __syncthreads();
+    if (!last) return;
+    sum = 0.0;
+    for (int b = tid; b < S.total; b += THREADS)
+      sum += __hip_atomic_load(S.part + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    sum = wave_sum(sum);
+    if ((tid & 63) == 0) red[tid >> 6] = sum;
+    __syncthreads();
+    if (tid == 0) {
+      sum = 0.0;
+      for (int q = 0; q < THREADS / 64; ++q) sum += red[q];
+      __hip_atomic_store(S.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+  if (tid == 0 && S.out) *S.out = sum;
+  if (S.pub && tid < 64) publish_scalars(S.pub, S.seq, sum, S.copy);
+}
+
 }  // namespace mg

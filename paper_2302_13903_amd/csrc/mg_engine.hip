@@ -77,14 +77,15 @@ struct mg_ctx {
                                // [8..13] sum b^2 per face, [16..47] multipole scratch
   double* hscal = nullptr;     // pinned host mirror of scal
   // the stopping test's squared norm as the device publishes it after each cycle (coherent
-  // pinned memory: [0] the value's bits, [1] the publishing launch's sequence number); pub_ok
-  // turns false if a publication ever fails to arrive (blocking copies from then on)
+  // pinned memory, laid out as SumSink says); pub_ok turns false if a publication ever fails to
+  // arrive (blocking copies from then on)
   unsigned long long* hpub = nullptr;
   unsigned long long pub_seq = 0;
   bool pub_ok = true;
-  // timing of the last solve
-  hipEvent_t ev0 = nullptr, ev_setup = nullptr, ev_fmg = nullptr;
-  std::vector<hipEvent_t> ev_cycle;
+  // timing of the last solve, from the device clock (clock_khz) that the first kernel, the FMG
+  // start and every publication read: no event is recorded between kernels, which would idle the
+  // device for microseconds each
+  int clock_khz = 100000;
   double setup_ms = 0, fmg_ms = 0;
   std::vector<double> cycle_ms;
   // kernel timing of the finest-level smoothing kernels: an event pair per launch (from the
@@ -149,7 +150,18 @@ int amr_solve_impl(int device, const mg_params* p, const mg_amr_mesh* m, const m
 namespace {
 
 constexpr int kScal = 64;
+static_assert(kScal == kPubScalars, "publications copy every scalar");
 constexpr int kMpoleOff = 16;
+// device clock at the start of a solve and of its FMG sweep; arrivals of the sums (SumSink)
+constexpr int kClockStart = 48, kClockFmg = 49, kTicket = 50;
+
+SumSink sum_sink(double* part, double* scal, int out) {
+  SumSink k;
+  k.part = part;
+  k.ticket = reinterpret_cast<unsigned*>(scal + kTicket);
+  k.out = scal + out;
+  return k;
+}
 
 int fail(mg_ctx* c, int code, const std::string& msg) {
   if (c) c->err = msg;
@@ -329,6 +341,17 @@ struct Solver {
   double* part = nullptr;
   double* scal = nullptr;
   int ktiming = 0;
+  // publication asked of the next norm: taken by the kernel that makes the final sum
+  unsigned long long* pub = nullptr;
+  unsigned long long pub_seq = 0;
+  // The sink of a finest-level norm (scal[2]).
+  SumSink norm_sink() {
+    SumSink k = sum_sink(part, scal, 2);
+    k.pub = pub;
+    k.seq = pub_seq;
+    pub = nullptr;
+    return k;
+  }
   int fused_min_n64 = kFusedDefaultMinN, fused_min_n32 = kFusedDefaultMinN;
   // the next top-level V-cycle starts from u = 0 without u having been cleared: its first
   // sweep must not read u (set by the caller, consumed by vcycle)
@@ -448,12 +471,11 @@ struct Solver {
     c->kev_id.push_back(id);
   }
 
-  // The levels 0..top (<= T_top) in one launch; norm (device, may be null) receives the sum of
-  // squared defects of level top's result.
+  // The levels 0..top (<= T_top) in one launch; norm: the sum of squared defects of level top's
+  // result goes to the norm sink.
   template <typename T>
-  void tail(Hier<T>& H, int top, int mode, const LevelBC& bc_top, double* norm = nullptr) {
-    TailArgs a;
-    std::memset(&a, 0, sizeof(a));
+  void tail(Hier<T>& H, int top, int mode, const LevelBC& bc_top, bool norm = false) {
+    TailArgs a{};
     a.top = top;
     a.mode = mode;
     a.npre = H.npre;
@@ -465,7 +487,11 @@ struct Solver {
     a.hom = H.hom;
     a.f = H.f[top];
     a.ug = H.u[top];
-    a.norm = norm;
+    if (norm) {
+      a.sink = norm_sink();
+      a.sink.total = 1;
+    }
+    if ((mode & TAIL_FMG) != 0) a.clock = reinterpret_cast<unsigned long long*>(scal + kClockFmg);
     launch_tail<T>(a, s);
   }
 
@@ -535,7 +561,7 @@ struct Solver {
     if (timed) kernel_begin();
     const int np = fused_sweep_input_norm<double>(H.u[L], H.u2[L], H.f[L], part, n, H.h[L], H.omega, bc, s);
     if (timed) kernel_end(fused_pass_name<double>(false, 3), 3.0 * (double)cells(L) * sizeof(double));
-    launch_sum_partials(part, np, scal + 2, s);
+    launch_sum_partials(np, norm_sink(), s);
     head_done = true;
   }
 
@@ -565,7 +591,7 @@ struct Solver {
     }
     if (l == H.T_top) {
       const bool norm = want_norm && sizeof(T) == 8;
-      tail(H, l, top_call ? TAIL_LOAD_U : 0, bc, norm ? scal + 2 : nullptr);
+      tail(H, l, top_call ? TAIL_LOAD_U : 0, bc, norm);
       return norm;
     }
     const int n = 1 << l;
@@ -580,13 +606,13 @@ struct Solver {
       if (top_call && down_done) down_done = false;   // queued ahead of the stopping test
       else down_leg<T>(H, l, bc, true, zin, timed);
       vcycle(H, l - 1, H.hom, false, false);
-      double* npart = want_norm && sizeof(T) == 8 ? part : nullptr;
+      const bool norm = want_norm && sizeof(T) == 8;
+      const SumSink sink = norm ? norm_sink() : SumSink{};
       if (timed) kernel_begin(true);
-      const int np = march_up<T>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, npart, n, h, H.omega, bc, s, 0, aux_of());
+      march_up<T>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, norm ? &sink : nullptr, n, h, H.omega, bc, s, 0, aux_of());
       // algorithmic bytes: u, f and the coarse correction read, u written
-      if (timed) kernel_end(march_name<T>(true, npart != nullptr, bc), 3 * cellsT + cellsT / 8);
-      if (npart) launch_sum_partials(part, np, scal + 2, s);
-      return npart != nullptr;
+      if (timed) kernel_end(march_name<T>(true, norm, bc), 3 * cellsT + cellsT / 8);
+      return norm;
     }
     if (n < (sizeof(T) == 8 ? fused_min_n64 : fused_min_n32) && tile_on<T>(H, l)) {
       // a small level: each leg in one region-tile launch
@@ -597,12 +623,12 @@ struct Solver {
       if (top_call && down_done) down_done = false;   // queued ahead of the stopping test
       else down_leg<T>(H, l, bc, false, false, timed);
       vcycle(H, l - 1, H.hom, false, false);
-      double* npart = want_norm && sizeof(T) == 8 ? part : nullptr;
+      const bool norm = want_norm && sizeof(T) == 8;
+      const SumSink sink = norm ? norm_sink() : SumSink{};
       if (timed) kernel_begin(true);
-      const int np = tile_up<T>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, npart, n, 0, H.npost, h, H.omega, bc, s);
+      tile_up<T>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, norm ? &sink : nullptr, n, 0, H.npost, h, H.omega, bc, s);
       if (timed) kernel_end(tile_name<T>(H.npost, true, bc, n), 3 * cellsT + cellsT / 8);
-      if (npart) launch_sum_partials(part, np, scal + 2, s);
-      return npart != nullptr;
+      return norm;
     }
     if (use_fused && H.u2[l] && n >= (sizeof(T) == 8 ? fused_min_n64 : fused_min_n32) && tblock_on<T>()) {
       // temporally blocked: sweeps two at a time per pass; the restricted defect and the norm
@@ -646,7 +672,7 @@ struct Solver {
         if (timed) kernel_begin();
         const int np = fused_defect_norm<T>(cur, H.f[l], part, n, h, bc, s);
         if (timed) kernel_end(fused_pass_name<T>(false, 2, false), 2 * cellsT);
-        launch_sum_partials(part, np, scal + 2, s);
+        launch_sum_partials(np, norm_sink(), s);
         normed = true;
       }
       if (cur != H.u[l]) (void)hipMemcpyAsync(H.u[l], cur, cells(l) * sizeof(T), hipMemcpyDeviceToDevice, s);
@@ -692,7 +718,7 @@ struct Solver {
         } else if (last && want_norm && !snorm) {
           const int np = fused_sweep_norm<T>(cur, oth, H.f[l], part, n, h, H.omega, bc, s);
           if (timed) kernel_end(fused_pass_name<T>(false, 2), 3 * cellsT);
-          launch_sum_partials(part, np, scal + 2, s);
+          launch_sum_partials(np, norm_sink(), s);
           normed = true;
         } else {
           fused_sweep<T>(cur, oth, H.f[l], n, h, H.omega, bc, s);
@@ -704,7 +730,7 @@ struct Solver {
         if (timed) kernel_begin();
         const int np = fused_defect_norm<T>(cur, H.f[l], part, n, h, bc, s);
         if (timed) kernel_end(fused_pass_name<T>(false, 2, false), 2 * cellsT);
-        launch_sum_partials(part, np, scal + 2, s);
+        launch_sum_partials(np, norm_sink(), s);
         normed = true;
       }
       if (cur != H.u[l]) (void)hipMemcpyAsync(H.u[l], cur, cells(l) * sizeof(T), hipMemcpyDeviceToDevice, s);
@@ -766,7 +792,7 @@ struct Solver {
       // u = phibar + e with the source R(defect) + L phibar, and every step of Alg. 3 on a linear
       // operator (smoothing, restriction, the single cell) keeps phibar and moves e exactly as
       // Alg. 1 moves the correction, which is all the levels above see (psi - phibar).
-      tail(H, l, TAIL_LOAD_U, H.phys[l], want_norm ? scal + 2 : nullptr);
+      tail(H, l, TAIL_LOAD_U, H.phys[l], want_norm);
       return want_norm;
     }
     const int n = 1 << l;
@@ -784,13 +810,13 @@ struct Solver {
       launch_fas_source(pbar[l - 1], H.f[l - 1], n / 2, H.h[l - 1], H.phys[l - 1], s);       // 5
       fas_cycle(H, pbar, l - 1);                                                             // 6
       launch_fas_correction(H.u[l - 1], pbar[l - 1], cells(l - 1), s);                       // 7
-      double* npart = want_norm ? part : nullptr;
+      const SumSink sink = want_norm ? norm_sink() : SumSink{};
+      const bool norm = want_norm;
       if (timed) kernel_begin(true);
-      const int np = march_up<double>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, npart, n, H.h[l], H.omega, bc, s, 0,
-                                      aux_of());
-      if (timed) kernel_end(march_name<double>(true, npart != nullptr, bc), 3 * cellsT + cellsT / 8);
-      if (npart) launch_sum_partials(part, np, scal + 2, s);
-      return npart != nullptr;
+      march_up<double>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, norm ? &sink : nullptr, n, H.h[l], H.omega, bc, s, 0,
+                       aux_of());
+      if (timed) kernel_end(march_name<double>(true, norm, bc), 3 * cellsT + cellsT / 8);
+      return norm;
     }
     if (done == 0 && n < fused_min_n64 && tile_on<double>(H, l)) {
       // a small level: each V(2,2) leg in one region-tile launch -- down (two sweeps,
@@ -802,12 +828,12 @@ struct Solver {
       launch_fas_source(pbar[l - 1], H.f[l - 1], n / 2, H.h[l - 1], H.phys[l - 1], s);       // 5
       fas_cycle(H, pbar, l - 1);                                                             // 6
       launch_fas_correction(H.u[l - 1], pbar[l - 1], cells(l - 1), s);                       // 7
-      double* npart = want_norm ? part : nullptr;
+      const SumSink sink = want_norm ? norm_sink() : SumSink{};
+      const bool norm = want_norm;
       if (timed) kernel_begin(true);
-      const int np = tile_up<double>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, npart, n, 0, H.npost, H.h[l], H.omega, bc, s);
+      tile_up<double>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, norm ? &sink : nullptr, n, 0, H.npost, H.h[l], H.omega, bc, s);
       if (timed) kernel_end(tile_name<double>(H.npost, true, bc, n), 3 * cellsT + cellsT / 8);
-      if (npart) launch_sum_partials(part, np, scal + 2, s);
-      return npart != nullptr;
+      return norm;
     }
     const bool streamed = use_fused && H.u2[l] && n >= fused_min_n64;
     // 1: the pre-sweeps; on streamed levels the last one carries steps 2-4 (fused below)
@@ -857,7 +883,7 @@ struct Solver {
   // Returns whether the finest level's cycle left the norm of its result in scal[2].
   bool fas_fmg(Hier<double>& H, double* const* pbar) {
     bool normed = H.L == H.T_top;
-    tail(H, H.T_top, TAIL_FMG, H.phys[H.T_top], normed ? scal + 2 : nullptr);
+    tail(H, H.T_top, TAIL_FMG, H.phys[H.T_top], normed);
     for (int l = H.T_top + 1; l <= H.L; ++l) {
       launch_prolong<double>(H.u[l - 1], H.u[l], 1 << (l - 1), H.phys[l - 1], 1, s);
       normed = fas_cycle(H, pbar, l, 0, l == H.L);
@@ -871,7 +897,7 @@ struct Solver {
   template <typename T>
   bool fmg(Hier<T>& H, bool norm_top = false) {
     bool normed = norm_top && H.L == H.T_top && sizeof(T) == 8;
-    tail(H, H.T_top, TAIL_FMG, H.phys[H.T_top], normed ? scal + 2 : nullptr);
+    tail(H, H.T_top, TAIL_FMG, H.phys[H.T_top], normed);
     for (int l = H.T_top + 1; l <= H.L; ++l) {
       if (Lb >= 0 && l > Lb) {
         blk_prolong<T>(H.u[l - 1], H.u[l], l - Lb, Lb, H.phys[l - 1], 1, s);
@@ -950,16 +976,16 @@ struct Solver {
       if (l == H.L && down_done) down_done = false;   // queued ahead of the stopping test
       else blk_down_leg<T>(H, l, bc, big, timed);
       vcycle_blk(H, l - 1, H.hom);
-      double* npart = want_norm && sizeof(T) == 8 ? part : nullptr;
+      const bool norm = want_norm && sizeof(T) == 8;
+      const SumSink sink = norm ? norm_sink() : SumSink{};
       if (timed) kernel_begin(true);
-      const int np = big ? march_up<T>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, npart, nl, H.h[l], H.omega, bc, s, Lm,
-                                       aux_of())
-                         : tile_up<T>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, npart, nl, Lm, H.npost, H.h[l], H.omega, bc, s);
+      if (big) march_up<T>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, norm ? &sink : nullptr, nl, H.h[l], H.omega, bc, s, Lm,
+                           aux_of());
+      else tile_up<T>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, norm ? &sink : nullptr, nl, Lm, H.npost, H.h[l], H.omega, bc, s);
       if (timed)
-        kernel_end(big ? march_name<T>(true, npart != nullptr, bc, true) : tile_name<T>(H.npost, true, bc, nl),
+        kernel_end(big ? march_name<T>(true, norm, bc, true) : tile_name<T>(H.npost, true, bc, nl),
                    3 * cellsT + cellsT / 8);
-      if (npart) launch_sum_partials(part, np, scal + 2, s);
-      return npart != nullptr;
+      return norm;
     }
     if (blk_zmarch_on<T>(l) && H.npre > 0 && H.npost > 0) {
       // streaming passes across block boundaries: one sweep per pass, the restricted defect
@@ -1003,19 +1029,19 @@ struct Solver {
     }
   }
 
-  // Sum of squared finest-level defects into out (device); optionally the FP32 defect.
-  void defect_norm(const double* u, const double* f, float* r32, int n, double h, const LevelBC& bc, double* out) {
+  // Sum of squared finest-level defects to the norm sink; optionally the FP32 defect.
+  void defect_norm(const double* u, const double* f, float* r32, int n, double h, const LevelBC& bc) {
     if (Lb >= 0 && n >= kFusedMinN) {
       const int np = fused_blk_defect_norm<double>(u, f, part, ilog2(n) - Lb, Lb, h, bc, s, r32);
-      launch_sum_partials(part, np, out, s);
+      launch_sum_partials(np, norm_sink(), s);
     } else if (Lb >= 0) {
       const int np = blk_defect_norm(u, f, r32, ilog2(n) - Lb, Lb, h, bc, part, s);
-      launch_sum_partials(part, np, out, s);
+      launch_sum_partials(np, norm_sink(), s);
     } else if (n >= kFusedMinN) {
       const int np = fused_defect_norm<double>(u, f, part, n, h, bc, s, r32);
-      launch_sum_partials(part, np, out, s);
+      launch_sum_partials(np, norm_sink(), s);
     } else {
-      launch_defect_norm(u, f, r32, n, h, bc, part, out, s);
+      launch_defect_norm(u, f, r32, n, h, bc, norm_sink(), s);
     }
   }
 };
@@ -1068,12 +1094,14 @@ int mg_ctx_create(mg_ctx** out, int device, size_t hbm_budget) {
   if (hipMalloc((void**)&c->part, sizeof(double) * kMaxPartials * 32) != hipSuccess ||
       hipMalloc((void**)&c->scal, sizeof(double) * kScal) != hipSuccess ||
       hipHostMalloc((void**)&c->hscal, sizeof(double) * kScal, hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc((void**)&c->hpub, 2 * sizeof(unsigned long long), hipHostMallocCoherent) != hipSuccess ||
-      hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev_setup) != hipSuccess ||
-      hipEventCreate(&c->ev_fmg) != hipSuccess) {
+      hipHostMalloc((void**)&c->hpub, (8 + kPubScalars) * sizeof(unsigned long long), hipHostMallocCoherent) != hipSuccess ||
+      hipMemset(c->scal, 0, sizeof(double) * kScal) != hipSuccess) {
     mg_ctx_destroy(c);
     return MG_ERR_DEVICE;
   }
+  std::memset(c->hpub, 0, (8 + kPubScalars) * sizeof(unsigned long long));
+  int khz = 0;
+  if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) == hipSuccess && khz > 0) c->clock_khz = khz;
   blk_prepare<double>(c->lds_per_block);
   blk_prepare<float>(c->lds_per_block);
   // the static scratch's device address, once per device with the device current (a failure
@@ -1104,13 +1132,9 @@ void mg_ctx_destroy(mg_ctx* c) {
   if (c->scal) (void)hipFree(c->scal);
   if (c->hscal) (void)hipHostFree(c->hscal);
   if (c->hpub) (void)hipHostFree(c->hpub);
-  if (c->ev0) (void)hipEventDestroy(c->ev0);
   if (c->aux.s2) (void)hipStreamDestroy(c->aux.s2);
   if (c->aux.fork) (void)hipEventDestroy(c->aux.fork);
   if (c->aux.join) (void)hipEventDestroy(c->aux.join);
-  if (c->ev_setup) (void)hipEventDestroy(c->ev_setup);
-  if (c->ev_fmg) (void)hipEventDestroy(c->ev_fmg);
-  for (auto e : c->ev_cycle) (void)hipEventDestroy(e);
   for (auto e : c->kev) (void)hipEventDestroy(e);
   delete c;
 }
@@ -1184,38 +1208,36 @@ int setup_faces(char* ws, double* part, double* scal, const Layout& y, const mg_
     launch_multipole_moments(rho, p->n, Lb >= 0 ? L - Lb : 0, p->dx, bc->lmax, bc->use_origin, bc->origin, part,
                              mps, s);
   const double G = p->four_pi_g / (4.0 * M_PI);
+  const double* src[6];
+  double* ext[16];
+  MpFaceLevels mp{};
+  bool any_values = false;
+  for (int f = 0; f < 6; ++f) {
+    src[f] = bc->kind[f] == MG_BC_FIXED ? bc->fixed_b[f] : nullptr;
+    any_values |= src[f] != nullptr;
+  }
+  mp.count = L + 1;
   for (int l = L; l >= 0; --l) {
-    double* fb = reinterpret_cast<double*>(ws + y.faces[l]);
-    double* mp_out[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+    ext[l] = reinterpret_cast<double*>(ws + y.faces[l]);
+    mp.nl[l] = 1 << l;
+    mp.hl[l] = p->dx * (double)(1 << (L - l));
     for (int f = 0; f < 6; ++f) {
       const int k = bc->kind[f];
-      double* e = fb + (size_t)f * face_sz(l);
+      double* e = ext[l] + (size_t)f * face_sz(l);
       phys[l].kind[f] = k == MG_BC_MULTIPOLE ? MG_BC_FIXED : k;
-      phys[l].b[f] = nullptr;
-      if (k == MG_BC_FIXED && bc->fixed_b[f]) {
-        if (l == L) launch_face_extend(bc->fixed_b[f], e, 1 << l, s);
-        else launch_face_restrict(reinterpret_cast<double*>(ws + y.faces[l + 1]) + (size_t)f * face_sz(l + 1), e,
-                                  1 << l, s);
-        phys[l].b[f] = e;
-      } else if (k == MG_BC_FIXED) {
-        // no values: a zero-fixed face, described without an array (ghost = -u, as in the
-        // homogeneous descriptions), so the kernels' forms without face values apply
-      } else if (k == MG_BC_MULTIPOLE) {
-        mp_out[f] = e;
-        phys[l].b[f] = e;
-      }
+      // a FIXED face without values is described without an array (ghost = -u, as in the
+      // homogeneous descriptions), so the kernels' forms without face values apply
+      phys[l].b[f] = (src[f] || k == MG_BC_MULTIPOLE) ? e : nullptr;
+      mp.out[l][f] = k == MG_BC_MULTIPOLE ? e : nullptr;
     }
-    if (any_mp) launch_multipole_faces(mps, bc->lmax, G, 1 << l, p->dx * (double)(1 << (L - l)), p->n * p->dx, mp_out, s);
   }
+  // non-finite fixed values are reported with the rho check (scal[8 + face])
+  if (any_values) launch_faces(src, ext, L, 0, scal + 8, s);
+  if (any_mp) launch_multipole_faces(mps, bc->lmax, G, p->n * p->dx, mp, s);
   for (int f = 0; f < 6; ++f) {
     const int k = bc->kind[f];
     hom->kind[f] = (k == MG_BC_PERIODIC || k == MG_BC_ZERO_GRADIENT) ? k : MG_BC_FIXED;
     hom->b[f] = nullptr;
-  }
-  // non-finite fixed values are reported with the rho check
-  for (int f = 0; f < 6; ++f) {
-    if (bc->kind[f] == MG_BC_FIXED && bc->fixed_b[f])
-      launch_sum(bc->fixed_b[f], (size_t)p->n * p->n, 2, part, scal + 8 + f, s);
   }
   return MG_OK;
 }
@@ -1234,58 +1256,46 @@ struct SolveMem {
   bool noalloc = false;
 };
 
-// The squared defect norm *dnorm (device) of the cycle just queued on s, for the host's
-// stopping test (Sec. 2.3.7), in two steps so that more work can be queued between them.
-// post_norm: a one-lane kernel publishes the value with a sequence number (returned) into
-// coherent pinned memory; done != nullptr: that event, which ends the cycle's timing, is taken
-// from the publishing kernel's own dispatch (an event recorded between kernels would idle the
-// device for microseconds; at the publication it costs nothing the host's reply does not
-// already).  await_norm: the host spins on the number (waking from a stream synchronisation
-// costs tens of microseconds per cycle), polling the stream after 20 ms and every 20 ms from
-// then on, so that a failed launch ends the wait with an error; if the stream has finished and the number has not
-// arrived, the value is read by a blocking copy and publishing is given up for good (then
-// post_norm queues a copy and returns 0).
-unsigned long long post_norm(mg_ctx* c, const double* dnorm, hipStream_t s, hipEvent_t done) {
-  if (c->pub_ok) {
-    const unsigned long long want = ++c->pub_seq;
-    launch_publish(dnorm, c->hpub, want, s, done);
-    return want;
-  }
-  if (done) (void)hipEventRecord(done, s);
-  (void)hipMemcpyAsync(c->hscal + 2, dnorm, sizeof(double), hipMemcpyDeviceToHost, s);
-  return 0;
-}
-
-int await_norm(mg_ctx* c, const double* dnorm, hipStream_t s, unsigned long long want, double* out) {
+// The squared defect norm (scal[2]) of the cycle just queued on s, for the host's stopping test
+// (Sec. 2.3.7).  The kernel that makes the norm's final sum publishes it with a sequence number
+// and the device clock into coherent pinned memory (SumSink); await_norm: the host spins on the
+// number (waking from a stream synchronisation costs tens of microseconds per cycle), polling the
+// stream after 20 ms and every 20 ms from then on, so that a failed launch ends the wait with an
+// error; if the stream has finished and the number has not arrived (want = 0: nothing was
+// published), the scalars are read by a blocking copy and publishing is given up for good.
+// *clock: the device clock at the publication (0 when it was a copy).
+int await_norm(mg_ctx* c, const double* scal, hipStream_t s, unsigned long long want, double* out,
+               unsigned long long* clock) {
   HIP_CHECK(c, hipGetLastError());
+  auto arrived = [&]() {
+    if (__atomic_load_n(c->hpub + 1, __ATOMIC_ACQUIRE) != want) return false;
+    *out = __builtin_bit_cast(double, __atomic_load_n(c->hpub, __ATOMIC_RELAXED));
+    *clock = __atomic_load_n(c->hpub + 2, __ATOMIC_RELAXED);
+    return true;
+  };
   if (want != 0) {
     // the stream is polled only once the wait has lasted kPollMs, then every kPollMs: a query
     // queues a marker behind the last command, which idles the device for microseconds
     constexpr double kPollMs = 20.0;
     auto t_next = std::chrono::steady_clock::now() + std::chrono::duration<double, std::milli>(kPollMs);
     for (unsigned spin = 1;; ++spin) {
-      if (__atomic_load_n(c->hpub + 1, __ATOMIC_ACQUIRE) == want) {
-        *out = __builtin_bit_cast(double, __atomic_load_n(c->hpub, __ATOMIC_RELAXED));
-        return MG_OK;
-      }
+      if (arrived()) return MG_OK;
       if ((spin & 1023u) == 0 && std::chrono::steady_clock::now() >= t_next) {
         t_next = std::chrono::steady_clock::now() + std::chrono::duration<double, std::milli>(kPollMs);
         const hipError_t q = hipStreamQuery(s);
         if (q == hipErrorNotReady) continue;
         HIP_CHECK(c, q);
-        if (__atomic_load_n(c->hpub + 1, __ATOMIC_ACQUIRE) == want) {
-          *out = __builtin_bit_cast(double, __atomic_load_n(c->hpub, __ATOMIC_RELAXED));
-          return MG_OK;
-        }
+        if (arrived()) return MG_OK;
         c->pub_ok = false;
-        HIP_CHECK(c, hipMemcpyAsync(c->hscal + 2, dnorm, sizeof(double), hipMemcpyDeviceToHost, s));
         break;
       }
       __builtin_ia32_pause();
     }
   }
+  HIP_CHECK(c, hipMemcpyAsync(c->hscal, scal, sizeof(double) * kScal, hipMemcpyDeviceToHost, s));
   HIP_CHECK(c, hipStreamSynchronize(s));
   *out = c->hscal[2];
+  *clock = 0;
   return MG_OK;
 }
 
@@ -1314,15 +1324,14 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
   if (c->tail_top[mixed ? 1 : 0] > 0) tail_max = std::min(tail_max, c->tail_top[mixed ? 1 : 0]);
   tail_max = std::min(tail_max, Lb >= 0 ? Lb : 99);
 
-  HIP_CHECK(c, hipEventRecord(c->ev0, s));
-  launch_zero(scal, sizeof(double) * kScal, s);
+  launch_begin(scal, kScal, kClockStart, s);
 
   // ---- source (eq. poisson, f = 4 pi G rho; mean removed when gauge-free, Sec. 2.3.6)
   double* f64L = reinterpret_cast<double*>(ws + y.f64L);
   float* f32L = mixed ? reinterpret_cast<float*>(ws + y.f32[L]) : nullptr;
   // (gauge-free: the source kernel reads the sum of rho from scal[0] and shifts by the mean)
-  launch_sum(rho, n3, 0, part, scal + 0, s);
-  launch_source(rho, f64L, f32L, n3, p->four_pi_g, gauge_free ? scal + 0 : nullptr, part, scal + 1, s);
+  if (gauge_free) launch_sum(rho, n3, sum_sink(part, scal, 0), s);
+  launch_source(rho, f64L, f32L, n3, p->four_pi_g, gauge_free ? scal + 0 : nullptr, sum_sink(part, scal, 1), s);
 
   LevelBC phys[16], hom;
   setup_faces(ws, part, scal, y, p, bc, rho, s, phys, &hom);
@@ -1368,7 +1377,6 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
     }
     S.restrict_sources(H32);
   }
-  HIP_CHECK(c, hipEventRecord(c->ev_setup, s));
 
   // ---- FMG sweep (Alg. 2) or the caller's initial guess
   double* pbar[16] = {nullptr};
@@ -1392,33 +1400,40 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
   // (of the FAS cycle 1 with the Full Approximation Scheme)
   const bool head_mode = !mixed && Lb < 0 && S.head_possible(H64);
   if (head_mode) S.head(H64, phys[L]);
-  else if (!fmg_normed) S.defect_norm(phi, f64L, mixed ? H32.f[L] : nullptr, p->n, p->dx, phys[L], scal + 2);
-  HIP_CHECK(c, hipEventRecord(c->ev_fmg, s));
-  HIP_CHECK(c, hipMemcpyAsync(c->hscal, scal, sizeof(double) * 16, hipMemcpyDeviceToHost, s));
-  HIP_CHECK(c, hipStreamSynchronize(s));
-  bool finite = std::isfinite(c->hscal[0]) && std::isfinite(c->hscal[1]);
-  for (int f = 0; f < 6; ++f) finite = finite && c->hscal[8 + f] == 0.0;
+  else if (!fmg_normed) S.defect_norm(phi, f64L, mixed ? H32.f[L] : nullptr, p->n, p->dx, phys[L]);
+  // the residual with every scalar (finiteness of rho and the face values), published as each
+  // cycle's norm is
+  unsigned long long want = 0, clock_fmg = 0;
+  if (c->pub_ok) {
+    SumSink all = sum_sink(part, scal, 2);
+    all.pub = c->hpub;
+    all.seq = want = ++c->pub_seq;
+    all.copy = scal;
+    launch_publish(scal + 2, all, s);
+  }
+  double d2 = 0.0;
+  if (const int st = await_norm(c, scal, s, want, &d2, &clock_fmg); st != MG_OK) return st;
+  double hs[kScal];
+  for (int q = 0; q < kScal; ++q)
+    hs[q] = clock_fmg ? __builtin_bit_cast(double, __atomic_load_n(c->hpub + 8 + q, __ATOMIC_RELAXED)) : c->hscal[q];
+  auto clock_of = [&](int q) { return __builtin_bit_cast(unsigned long long, hs[q]); };
+  bool finite = std::isfinite(hs[0]) && std::isfinite(hs[1]);
+  for (int f = 0; f < 6; ++f) finite = finite && hs[8 + f] == 0.0;
   if (!finite) return fail(c, MG_ERR_NONFINITE, "non-finite values in rho or fixed boundary values");
-  const double rms_f = std::sqrt(c->hscal[1] / (double)n3);
+  const double rms_f = std::sqrt(hs[1] / (double)n3);
   auto rel = [&](double sumsq) {
     const double rd = std::sqrt(sumsq / (double)n3);
     return rms_f > 0 ? rd / rms_f : rd;
   };
-  double r = rel(c->hscal[2]);
+  double r = rel(d2);
   int nh = 0;
   hist[nh++] = r;
 
   // ---- V-cycles until the stopping test (Sec. 2.3.7)
   const int ncyc = p->fixed_cycles > 0 ? p->fixed_cycles : p->max_cycles;
-  // per-cycle timing events (created once, reused; none in the allocation-free form)
-  while (!mem.noalloc && (int)c->ev_cycle.size() < ncyc) {
-    hipEvent_t e;
-    HIP_CHECK(c, hipEventCreate(&e));
-    c->ev_cycle.push_back(e);
-  }
-  const bool cyc_timed = !mem.noalloc;
+  std::vector<unsigned long long> clocks;
   int status = p->fixed_cycles > 0 ? MG_OK : MG_NOT_CONVERGED;
-  int slow = 0, done_cycles = 0;
+  int slow = 0;
   double* phi_cur = phi;     // mixed mode alternates phi with its ping-pong partner
   double* phi_oth = y.phi2 == (size_t)-1 ? nullptr : reinterpret_cast<double*>(ws + y.phi2);
   // mixed: FP32 V-cycles per outer step -- the "inner" setting, else (to a tolerance) as many
@@ -1435,6 +1450,10 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
   if (p->fixed_cycles > 0 || r > p->tol) {
     for (int cyc = 0; cyc < ncyc; ++cyc) {
       S.timed_top = true;
+      // this cycle's norm is published by the kernel that makes its final sum
+      want = c->pub_ok ? ++c->pub_seq : 0;
+      S.pub = want ? c->hpub : nullptr;
+      S.pub_seq = want;
       int inner = 1;
       if (mixed && !(Lb < 0 && L == H32.T_top)) {
         if (c->inner > 0) {
@@ -1450,7 +1469,7 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
         const bool normed = S.fas_cycle(H64, pbar, L, head_mode ? 1 : 0, !head_mode);
         S.head_done = false;
         if (head_mode && cyc + 1 < ncyc) S.head(H64, phys[L]);
-        else if (!normed) S.defect_norm(phi, f64L, nullptr, p->n, p->dx, phys[L], scal + 2);
+        else if (!normed) S.defect_norm(phi, f64L, nullptr, p->n, p->dx, phys[L]);
       } else if (head_mode) {
         // the rest of this V-cycle (its first sweep ran in the head pass), then the head of the
         // next one, which measures this cycle's result; after the last allowed cycle the
@@ -1458,17 +1477,17 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
         S.head_done = true;
         S.vcycle(H64, L, phys[L], true, false);
         if (cyc + 1 < ncyc) S.head(H64, phys[L]);
-        else S.defect_norm(phi, f64L, nullptr, p->n, p->dx, phys[L], scal + 2);
+        else S.defect_norm(phi, f64L, nullptr, p->n, p->dx, phys[L]);
       } else if (!mixed && Lb >= 0) {
-        if (!S.vcycle_blk(H64, L, phys[L], true)) S.defect_norm(phi, f64L, nullptr, p->n, p->dx, phys[L], scal + 2);
+        if (!S.vcycle_blk(H64, L, phys[L], true)) S.defect_norm(phi, f64L, nullptr, p->n, p->dx, phys[L]);
       } else if (mixed && Lb >= 0) {
         launch_zero(H32.u[L], n3 * sizeof(float), s);
         for (int k = 0; k < inner; ++k) S.vcycle_blk(H32, L, hom);
         launch_add_f32(phi, H32.u[L], n3, s);
-        S.defect_norm(phi, f64L, H32.f[L], p->n, p->dx, phys[L], scal + 2);
+        S.defect_norm(phi, f64L, H32.f[L], p->n, p->dx, phys[L]);
       } else if (!mixed) {
         const bool normed = S.vcycle(H64, L, phys[L], true, true);
-        if (!normed) S.defect_norm(phi, f64L, nullptr, p->n, p->dx, phys[L], scal + 2);
+        if (!normed) S.defect_norm(phi, f64L, nullptr, p->n, p->dx, phys[L]);
       } else {
         // defect correction: e32 solves L e = r32 from zero with homogeneous conditions
         if (L == H32.T_top) {
@@ -1486,26 +1505,25 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
           // phi += e and the FP64 defect (with its FP32 copy and norm) in one streaming pass
           const int np = fused_mixed_update_defect(phi_cur, phi_oth, H32.u[L], f64L, H32.f[L], part, p->n, p->dx,
                                                    phys[L], s);
-          launch_sum_partials(part, np, scal + 2, s);
+          launch_sum_partials(np, S.norm_sink(), s);
           std::swap(phi_cur, phi_oth);
         } else {
           launch_add_f32(phi, H32.u[L], n3, s);
-          S.defect_norm(phi, f64L, H32.f[L], p->n, p->dx, phys[L], scal + 2);
+          S.defect_norm(phi, f64L, H32.f[L], p->n, p->dx, phys[L]);
         }
       }
-      const unsigned long long want = post_norm(c, scal + 2, s, cyc_timed ? c->ev_cycle[cyc] : nullptr);
       // the next cycle's first leg is queued before this cycle's norm is read when that leg
       // reads u only and another cycle will run: always with a fixed cycle count, and when the
       // tolerance is still at least 4x past what this cycle reaches at the contraction seen so
       // far (had the solve stopped after all, that leg's results go unused)
       if (ahead_ok && cyc + 1 < ncyc && (p->fixed_cycles > 0 || 0.25 * rho_seen * r > p->tol))
         (void)S.down_ahead(H64, phys[L]);
-      double d2 = 0.0;
-      if (const int st = await_norm(c, scal + 2, s, want, &d2); st != MG_OK) return st;
+      unsigned long long clock = 0;
+      if (const int st = await_norm(c, scal, s, want, &d2, &clock); st != MG_OK) return st;
+      clocks.push_back(clock);
       const double rn = rel(d2);
       if (r > 0 && rn > 0) rho_seen = std::min(1.0, rn / r);
       hist[nh++] = rn;
-      ++done_cycles;
       if (mixed) {
         c->last_inner += inner;
         if (r > 0 && rn > 0 && rn < r) rho_est = std::min(0.5, std::max(0.01, std::pow(rn / r, 1.0 / inner)));
@@ -1528,20 +1546,25 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
 
   // ---- gauge (Sec. 2.3.6): zero mean potential when no face fixes the zero point
   if (gauge_free) {
-    launch_sum(phi, n3, 0, part, scal + 3, s);
+    launch_sum(phi, n3, sum_sink(part, scal, 3), s);
     launch_sub_mean(phi, n3, scal + 3, s);
   }
   HIP_CHECK(c, hipStreamSynchronize(s));
   HIP_CHECK(c, hipGetLastError());
 
   // ---- timing
-  c->setup_ms = elapsed(c->ev0, c->ev_setup);
-  c->fmg_ms = elapsed(c->ev_setup, c->ev_fmg);
+  auto ms = [&](unsigned long long a, unsigned long long b) {
+    return a && b > a ? (double)(b - a) / (double)c->clock_khz : 0.0;
+  };
+  const unsigned long long t0 = clock_of(kClockStart);
+  const unsigned long long t1 = clock_of(kClockFmg) ? clock_of(kClockFmg) : clock_fmg;   // no FMG sweep: at the residual
+  c->setup_ms = ms(t0, t1);
+  c->fmg_ms = ms(t1, clock_fmg);
   c->cycle_ms.clear();
-  hipEvent_t prev = c->ev_fmg;
-  for (int cyc = 0; cyc < done_cycles && cyc_timed; ++cyc) {
-    c->cycle_ms.push_back(elapsed(prev, c->ev_cycle[cyc]));
-    prev = c->ev_cycle[cyc];
+  unsigned long long prev = clock_fmg;
+  for (size_t cyc = 0; cyc < clocks.size() && !mem.noalloc; ++cyc) {
+    c->cycle_ms.push_back(ms(prev, clocks[cyc]));
+    prev = clocks[cyc];
   }
   if (ktiming) {
     for (size_t q = 0; q + 1 < c->kev.size(); q += 2) {
@@ -2196,10 +2219,10 @@ int mg_op_sweep_input_norm(mg_ctx* c, int n, double h, double omega, const mg_le
     st = op_scratch(c, n3 * sizeof(double), &tmp);
     if (st) return st;
     const int np = fused_sweep_input_norm<double>(u, tmp, f, c->part, n, h, omega, b, s);
-    launch_sum_partials(c->part, np, c->scal + 2, s);
+    launch_sum_partials(np, sum_sink(c->part, c->scal, 2), s);
     HIP_CHECK(c, hipMemcpyAsync(u, tmp, n3 * sizeof(double), hipMemcpyDeviceToDevice, s));
   } else {
-    launch_defect_norm(u, f, nullptr, n, h, b, c->part, c->scal + 2, s);
+    launch_defect_norm(u, f, nullptr, n, h, b, sum_sink(c->part, c->scal, 2), s);
     for (int colour = 0; colour < 2; ++colour) launch_half_sweep<double>(u, f, n, h, omega, colour, b, s);
   }
   HIP_CHECK(c, hipMemcpyAsync(c->hscal + 2, c->scal + 2, sizeof(double), hipMemcpyDeviceToHost, s));
@@ -2222,11 +2245,11 @@ int mg_op_mixed_update(mg_ctx* c, int n, double h, const mg_level_bc* bc, double
     st = op_scratch(c, n3 * sizeof(double), &tmp);
     if (st) return st;
     const int np = fused_mixed_update_defect(phi, tmp, e, f, r32, c->part, n, h, b, s);
-    launch_sum_partials(c->part, np, c->scal + 2, s);
+    launch_sum_partials(np, sum_sink(c->part, c->scal, 2), s);
     HIP_CHECK(c, hipMemcpyAsync(phi, tmp, n3 * sizeof(double), hipMemcpyDeviceToDevice, s));
   } else {
     launch_add_f32(phi, e, n3, s);
-    launch_defect_norm(phi, f, r32, n, h, b, c->part, c->scal + 2, s);
+    launch_defect_norm(phi, f, r32, n, h, b, sum_sink(c->part, c->scal, 2), s);
   }
   HIP_CHECK(c, hipMemcpyAsync(c->hscal + 2, c->scal + 2, sizeof(double), hipMemcpyDeviceToHost, s));
   HIP_CHECK(c, hipStreamSynchronize(s));
@@ -2294,24 +2317,28 @@ int mg_gravity(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* phi
     st = op_scratch(c, 6 * face_sz(L) * sizeof(double), &fb);
     if (st) return st;
   }
-  double* mp_out[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+  MpFaceLevels mp{};
+  const double* src[6];
+  double* ext[16] = {nullptr};
+  bool any_values = false;
+  ext[L] = fb;
+  mp.count = 1;
+  mp.nl[0] = n;
+  mp.hl[0] = p->dx;
   for (int f = 0; f < 6; ++f) {
     const int k = bc->kind[f];
     lb.kind[f] = k == MG_BC_MULTIPOLE ? MG_BC_FIXED : k;
-    lb.b[f] = nullptr;
+    src[f] = k == MG_BC_FIXED ? bc->fixed_b[f] : nullptr;
+    any_values |= src[f] != nullptr;
     double* e = fb ? fb + (size_t)f * face_sz(L) : nullptr;
-    if (k == MG_BC_FIXED && bc->fixed_b[f]) {
-      launch_face_extend(bc->fixed_b[f], e, n, s);
-      lb.b[f] = e;
-    } else if (k == MG_BC_MULTIPOLE) {
-      mp_out[f] = e;
-      lb.b[f] = e;
-    }
+    lb.b[f] = (src[f] || k == MG_BC_MULTIPOLE) ? e : nullptr;
+    mp.out[0][f] = k == MG_BC_MULTIPOLE ? e : nullptr;
   }
+  if (any_values) launch_faces(src, ext, L, L, nullptr, s);
   if (any_mp) {
     double* mps = c->scal + kMpoleOff;
     launch_multipole_moments(rho, n, Lm, p->dx, bc->lmax, bc->use_origin, bc->origin, c->part, mps, s);
-    launch_multipole_faces(mps, bc->lmax, p->four_pi_g / (4.0 * M_PI), n, p->dx, n * p->dx, mp_out, s);
+    launch_multipole_faces(mps, bc->lmax, p->four_pi_g / (4.0 * M_PI), n * p->dx, mp, s);
   }
   launch_gravity(phi, rho, g, rhog, gface, n, Lm, p->dx, lb, s);
   return op_epilogue(c);

@@ -405,8 +405,8 @@ void launch_add_f32(double* phi, const float* e, size_t n3, hipStream_t s) {
 
 // ------------------------------------------------------------------ reductions
 
-// Deterministic two-stage sums: stage 1 writes one partial per block (grid-stride loop, fixed
-// grid, fixed tree); stage 2 sums the partials in index order in one block.
+// Deterministic sums: one partial per block (grid-stride loop, fixed grid, fixed tree), added in
+// index order by the block that arrives last (finish_sum).
 __device__ __forceinline__ double block_sum(double v, double* red) {
   v = wave_sum(v);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -420,29 +420,19 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
   return r;
 }
 
-// what: 0 = sum x, 1 = sum x^2, 2 = sum of squared non-finite flags (count of NaN/Inf)
-__global__ void __launch_bounds__(kBlock) k_sum_partials(const double* __restrict__ x, size_t n3, int what,
-                                                          double* __restrict__ part) {
+__global__ void __launch_bounds__(kBlock) k_sum(const double* __restrict__ x, size_t n3, SumSink sink) {
   __shared__ double red[kBlock / 64];
   double acc = 0.0;
-  for (size_t t = (size_t)blockIdx.x * kBlock + threadIdx.x; t < n3; t += (size_t)gridDim.x * kBlock) {
-    const double v = x[t];
-    acc += what == 0 ? v : (what == 1 ? v * v : (isfinite(v) ? 0.0 : 1.0));
-  }
-  const double r = block_sum(acc, red);
-  if (threadIdx.x == 0) part[blockIdx.x] = r;
+  for (size_t t = (size_t)blockIdx.x * kBlock + threadIdx.x; t < n3; t += (size_t)gridDim.x * kBlock) acc += x[t];
+  finish_sum<kBlock>(sink, block_sum(acc, red), red);
 }
 
-__global__ void __launch_bounds__(kBlock) k_sum_final(const double* __restrict__ part, int np, int stride,
-                                                       double* __restrict__ out, int nvals) {
-  // out[v] = sum_{b < np} part[b*stride + v] in index order, v < nvals
+__global__ void __launch_bounds__(kBlock) k_sum_final(const double* __restrict__ part, int np, SumSink sink) {
+  // the sum of part[b], b < np, in index order
   __shared__ double red[kBlock / 64];
-  for (int v = 0; v < nvals; ++v) {
-    double acc = 0.0;
-    for (int b = threadIdx.x; b < np; b += kBlock) acc += part[(size_t)b * stride + v];
-    const double r = block_sum(acc, red);
-    if (threadIdx.x == 0) out[v] = r;
-  }
+  double acc = 0.0;
+  for (int b = threadIdx.x; b < np; b += kBlock) acc += part[b];
+  finish_sum<kBlock>(sink, block_sum(acc, red), red);
 }
 
 int reduce_blocks(size_t n3) {
@@ -451,37 +441,40 @@ int reduce_blocks(size_t n3) {
   return (int)(b < 1 ? 1 : b);
 }
 
-// One device scalar copied into coherent pinned host memory (dst[0]), then the sequence number
-// `seq` stored beside it (dst[1]) with system-scope release, so that a host that sees the number
-// also sees the value.  Vector stores from one lane.
-__global__ void k_publish(const double* __restrict__ src, unsigned long long* dst, unsigned long long seq) {
-  if (threadIdx.x != 0) return;
-  __hip_atomic_store(dst, __builtin_bit_cast(unsigned long long, src[0]), __ATOMIC_RELAXED,
-                     __HIP_MEMORY_SCOPE_SYSTEM);
-  __hip_atomic_store(dst + 1, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+// The device scalars cleared at the start of a solve, the device clock in scal[at].
+__global__ void k_begin(double* scal, int count, int at) {
+  const int t = threadIdx.x;
+  if (t < count) scal[t] = t == at ? __builtin_bit_cast(double, (unsigned long long)wall_clock64()) : 0.0;
 }
 
-void launch_publish(const double* src, unsigned long long* dst_host, unsigned long long seq, hipStream_t s,
-                    hipEvent_t done) {
-  if (done) hipExtLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, nullptr, done, 0u, src, dst_host, seq);
-  else hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, src, dst_host, seq);
+void launch_begin(double* scal, int count, int at, hipStream_t s) {
+  hipLaunchKernelGGL(k_begin, dim3(1), dim3(64), 0, s, scal, count, at);
 }
 
-void launch_sum_partials(const double* part, int np, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(kBlock), 0, s, part, np, 1, out, 1);
+// Publication of a sum that a launch without a sink left in device memory.
+__global__ void k_publish(const double* __restrict__ src, SumSink sink) {
+  publish_scalars(sink.pub, sink.seq, src[0], sink.copy);
 }
 
-void launch_sum(const double* x, size_t n3, int what, double* part, double* out, hipStream_t s) {
-  const int nb = reduce_blocks(n3);
-  hipLaunchKernelGGL(k_sum_partials, dim3(nb), dim3(kBlock), 0, s, x, n3, what, part);
-  hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(kBlock), 0, s, part, nb, 1, out, 1);
+void launch_publish(const double* src, const SumSink& sink, hipStream_t s) {
+  hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, src, sink);
+}
+
+void launch_sum_partials(int np, SumSink sink, hipStream_t s) {
+  sink.total = 1;
+  hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(kBlock), 0, s, sink.part, np, sink);
+}
+
+void launch_sum(const double* x, size_t n3, SumSink sink, hipStream_t s) {
+  sink.total = reduce_blocks(n3);
+  hipLaunchKernelGGL(k_sum, dim3(sink.total), dim3(kBlock), 0, s, x, n3, sink);
 }
 
 // Defect of the finest level and its sum of squares (Sec. 2.3.7, eq. threshold); optionally
 // the defect itself in FP32 (mixed precision: right-hand side of the inner correction cycle).
 __global__ void __launch_bounds__(kBlock) k_defect_norm(const double* __restrict__ u, const double* __restrict__ f,
                                                          float* __restrict__ r32, int n, int L, double ih2, LevelBC bc,
-                                                         double* __restrict__ part) {
+                                                         SumSink sink) {
   __shared__ double red[kBlock / 64];
   const size_t n3 = (size_t)1 << (3 * L);
   double acc = 0.0;
@@ -495,72 +488,129 @@ __global__ void __launch_bounds__(kBlock) k_defect_norm(const double* __restrict
     acc += d * d;
     if (r32) r32[c] = (float)d;
   }
-  const double r = block_sum(acc, red);
-  if (threadIdx.x == 0) part[blockIdx.x] = r;
+  finish_sum<kBlock>(sink, block_sum(acc, red), red);
 }
 
 void launch_defect_norm(const double* u, const double* f, float* r32, int n, double h, const LevelBC& bc,
-                        double* part, double* out, hipStream_t s) {
+                        SumSink sink, hipStream_t s) {
   const int L = ilog2(n);
-  const size_t n3 = (size_t)1 << (3 * L);
-  const int nb = reduce_blocks(n3);
-  hipLaunchKernelGGL(k_defect_norm, dim3(nb), dim3(kBlock), 0, s, u, f, r32, n, L, 1.0 / (h * h), bc, part);
-  hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(kBlock), 0, s, part, nb, 1, out, 1);
+  sink.total = reduce_blocks((size_t)1 << (3 * L));
+  hipLaunchKernelGGL(k_defect_norm, dim3(sink.total), dim3(kBlock), 0, s, u, f, r32, n, L, 1.0 / (h * h), bc, sink);
 }
 
 // f = a * rho + c (the source 4 pi G rho, mean-shifted when gauge-free: c = -a * mean(rho),
 // read from the device so that the host need not wait for the sum), in FP64, plus the
-// FP32 copy when f32 != nullptr, and one partial sum of f^2 per block (fixed grid and tree,
-// so the sum is reproducible).
+// FP32 copy when f32 != nullptr, and the sum of f^2 (fixed grid and tree, so reproducible).
+// Without the sum of rho the block sums of rho are taken here for their finiteness alone: one
+// that is not finite makes the sum of f^2 not finite either.
 __global__ void __launch_bounds__(kBlock) k_source(const double* __restrict__ rho, double* __restrict__ f,
                                                     float* __restrict__ f32, size_t n3, double a,
-                                                    const double* __restrict__ rho_sum, double* __restrict__ part) {
+                                                    const double* __restrict__ rho_sum, SumSink sink) {
   __shared__ double red[kBlock / 64];
   // gauge-free: c = -a * mean(rho), from the sum the previous launch left in device memory
   const double c = rho_sum ? -a * (rho_sum[0] / (double)n3) : 0.0;
-  double acc = 0.0;
+  double acc = 0.0, total = 0.0;
   for (size_t t = (size_t)blockIdx.x * kBlock + threadIdx.x; t < n3; t += (size_t)gridDim.x * kBlock) {
-    const double v = a * rho[t] + c;
+    const double r = rho[t], v = a * r + c;
     f[t] = v;
     if (f32) f32[t] = (float)v;
     acc += v * v;
+    total += r;
   }
-  const double r = block_sum(acc, red);
-  if (threadIdx.x == 0) part[blockIdx.x] = r;
+  double sumsq = block_sum(acc, red);
+  total = block_sum(total, red);
+  if (!isfinite(total)) sumsq = __builtin_nan("");
+  finish_sum<kBlock>(sink, sumsq, red);
 }
 
-void launch_source(const double* rho, double* f, float* f32, size_t n3, double a, const double* rho_sum,
-                   double* part, double* sumsq, hipStream_t s) {
-  const int nb = reduce_blocks(n3);
-  hipLaunchKernelGGL(k_source, dim3(nb), dim3(kBlock), 0, s, rho, f, f32, n3, a, rho_sum, part);
-  hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(kBlock), 0, s, part, nb, 1, sumsq, 1);
+void launch_source(const double* rho, double* f, float* f32, size_t n3, double a, const double* rho_sum, SumSink sink,
+                   hipStream_t s) {
+  sink.total = reduce_blocks(n3);
+  hipLaunchKernelGGL(k_source, dim3(sink.total), dim3(kBlock), 0, s, rho, f, f32, n3, a, rho_sum, sink);
 }
 
 // ------------------------------------------------------------------ boundary face arrays
 
-// Finest-level FIXED face: extend the caller's n^2 face-centre array to (n+2)^2, the ring
-// taking the nearest face value.
-__global__ void __launch_bounds__(kBlock) k_face_extend(const double* __restrict__ b, double* __restrict__ e, int n) {
-  const int m = n + 2;
-  const int t = blockIdx.x * kBlock + threadIdx.x;
-  if (t >= m * m) return;
-  const int t1 = t % m - 1, t2 = t / m - 1;
-  const int c1 = t1 < 0 ? 0 : (t1 >= n ? n - 1 : t1);
-  const int c2 = t2 < 0 ? 0 : (t2 >= n ? n - 1 : t2);
-  e[t] = b ? b[(size_t)c2 * n + c1] : 0.0;
+// FIXED faces of every level, from the caller's n^2 face-centre values on the finest one: a
+// coarser face takes 2 x 2 area means, and each array is extended to (n+2)^2, the ring taking the
+// nearest face value.  One workgroup makes a tile of 32 x 32 finest values and all its coarser
+// levels in LDS; a second launch, one workgroup per face, makes the levels above the tiles.  (One
+// launch per face and level, and two more per face for the check of its values, took 126 us of a
+// 64^3 solve; these two take 6.)
+struct FaceArgs {
+  const double* src[6];   // null: not a face with values.  First launch: n^2 values
+  double* ext[16];        // per level: the six extended arrays one after another
+  double* nonfinite;      // per face: the count of non-finite values (first launch), or null
+  int top, bottom;        // the levels this launch makes
+};
+constexpr int kFaceTile = 32, kFaceTop = 64;
+
+template <int M, bool FIRST>
+__global__ void __launch_bounds__(kBlock) k_faces(FaceArgs A) {
+  __shared__ double v[M * M];
+  const int face = blockIdx.z;
+  if (!A.src[face]) return;
+  const int n = 1 << A.top, m0 = n < M ? n : M;
+  const int o1 = blockIdx.x * m0, o2 = blockIdx.y * m0;   // the tile's place on level top
+  auto store = [&](int l, int t1, int t2, double x) {
+    const int nl = 1 << l, w = nl + 2;
+    double* e = A.ext[l] + (size_t)face * w * w;
+    // the cell's own entry and the ring entries nearest to it
+    for (int b = t2 == 0 ? -1 : t2; b <= (t2 == nl - 1 ? nl : t2); ++b)
+      for (int a = t1 == 0 ? -1 : t1; a <= (t1 == nl - 1 ? nl : t1); ++a) e[(size_t)(b + 1) * w + a + 1] = x;
+  };
+  int bad = 0;
+  for (int q = threadIdx.x; q < m0 * m0; q += kBlock) {
+    const int t1 = o1 + q % m0, t2 = o2 + q / m0;
+    double x;
+    if (FIRST) {
+      x = A.src[face][(size_t)t2 * n + t1];
+      bad += isfinite(x) ? 0 : 1;
+      store(A.top, t1, t2, x);
+    } else {
+      x = A.ext[A.top][(size_t)face * (n + 2) * (n + 2) + (size_t)(t2 + 1) * (n + 2) + t1 + 1];
+    }
+    v[q] = x;
+  }
+  if (FIRST && bad && A.nonfinite) unsafeAtomicAdd(A.nonfinite + face, (double)bad);   // a whole number: any order
+  for (int m = m0 / 2, l = A.top - 1; m >= 1 && l >= A.bottom; m >>= 1, --l) {
+    __syncthreads();
+    double x[M * M / 4 / kBlock < 1 ? 1 : M * M / 4 / kBlock];
+    int c = 0;
+#pragma unroll
+    for (int s = 0; s < (int)(sizeof(x) / sizeof(double)); ++s) {
+      const int q = threadIdx.x + s * kBlock;
+      if (q < m * m) {
+        const double* r = v + (2 * (q / m)) * (2 * m) + 2 * (q % m);
+        x[s] = (r[0] + r[1] + r[2 * m] + r[2 * m + 1]) / 4.0;
+        ++c;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < (int)(sizeof(x) / sizeof(double)); ++s) {
+      const int q = threadIdx.x + s * kBlock;
+      if (s < c) {
+        v[q] = x[s];
+        store(l, (o1 * m) / m0 + q % m, (o2 * m) / m0 + q / m, x[s]);
+      }
+    }
+  }
 }
 
-// Coarser FIXED face: 2x2 area mean of the finer face values, then the extension ring.
-__global__ void __launch_bounds__(kBlock) k_face_restrict(const double* __restrict__ ef, double* __restrict__ ec, int nc) {
-  const int m = nc + 2, nf = 2 * nc, mf = nf + 2;
-  const int t = blockIdx.x * kBlock + threadIdx.x;
-  if (t >= m * m) return;
-  int t1 = t % m - 1, t2 = t / m - 1;
-  t1 = t1 < 0 ? 0 : (t1 >= nc ? nc - 1 : t1);
-  t2 = t2 < 0 ? 0 : (t2 >= nc ? nc - 1 : t2);
-  const double* r0 = ef + (size_t)(2 * t2 + 1) * mf + 1;
-  const double* r1 = ef + (size_t)(2 * t2 + 2) * mf + 1;
-  ec[t] = (r0[2 * t1] + r0[2 * t1 + 1] + r1[2 * t1] + r1[2 * t1 + 1]) / 4.0;
+void launch_faces(const double* const src[6], double* const* ext, int L, int bottom, double* nonfinite, hipStream_t s) {
+  FaceArgs A{};
+  for (int f = 0; f < 6; ++f) A.src[f] = src[f];
+  for (int l = bottom; l <= L; ++l) A.ext[l] = ext[l];
+  A.nonfinite = nonfinite;
+  A.top = L;
+  A.bottom = bottom;
+  const int tiles = std::max(1, (1 << L) / kFaceTile);
+  hipLaunchKernelGGL((k_faces<kFaceTile, true>), dim3(tiles, tiles, 6), dim3(kBlock), 0, s, A);
+  if (tiles > 1 && bottom < ilog2(tiles)) {
+    A.top = ilog2(tiles);
+    hipLaunchKernelGGL((k_faces<kFaceTop, false>), dim3(1, 1, 6), dim3(kBlock), 0, s, A);
+  }
 }
 
 // ------------------------------------------------------------------ clearing device memory
@@ -607,16 +657,6 @@ __global__ void __launch_bounds__(kBlock) k_fill(const double* __restrict__ u, d
 void launch_fill(const double* u, double* out, int n, const LevelBC& bc, hipStream_t s) {
   const size_t m = (size_t)n + 2;
   hipLaunchKernelGGL(k_fill, dim3(grid_for(m * m * m)), dim3(kBlock), 0, s, u, out, n, ilog2(n), bc);
-}
-
-void launch_face_extend(const double* b, double* e, int n, hipStream_t s) {
-  const int m = n + 2;
-  hipLaunchKernelGGL(k_face_extend, dim3((m * m + kBlock - 1) / kBlock), dim3(kBlock), 0, s, b, e, n);
-}
-
-void launch_face_restrict(const double* ef, double* ec, int nc, hipStream_t s) {
-  const int m = nc + 2;
-  hipLaunchKernelGGL(k_face_restrict, dim3((m * m + kBlock - 1) / kBlock), dim3(kBlock), 0, s, ef, ec, nc);
 }
 
 // ------------------------------------------------------------------ explicit instantiations

@@ -57,7 +57,8 @@ struct TailArgs {
   LevelBC phys[5];    // physical description per level (FMG mode)
   const void* f;      // device source of level top
   void* ug;           // device solution / correction of level top (in and out)
-  double* norm;       // device: the sum of squared defects of the result, or null
+  SumSink sink;       // where the sum of squared defects of the result goes (out null: not wanted)
+  unsigned long long* clock;   // device, or null: receives the device clock at the start
 };
 
 template <typename T>
@@ -83,25 +84,26 @@ void launch_fas_restrict(const double* u, const double* f, double* fc, double* p
 void launch_fas_source(const double* pbar, double* f, int n, double h, const LevelBC& bc, hipStream_t s);
 void launch_fas_correction(double* u, const double* pbar, size_t n3, hipStream_t s);
 
-// f = a rho + c (and its FP32 copy when f32 != nullptr); sumsq[0] = sum of f^2 (device).
-// c = -a * rho_sum[0] / n3 when rho_sum (device) is given (the gauge-free source), else 0.
-void launch_source(const double* rho, double* f, float* f32, size_t n3, double a, const double* rho_sum,
-                   double* part, double* sumsq, hipStream_t s);
+// f = a rho + c (and its FP32 copy when f32 != nullptr); the sum of f^2 to the sink (not finite
+// when rho is not).  c = -a * rho_sum[0] / n3 when rho_sum (device) is given (the gauge-free
+// source), else 0.
+void launch_source(const double* rho, double* f, float* f32, size_t n3, double a, const double* rho_sum, SumSink sink,
+                   hipStream_t s);
 void launch_sub_mean(double* u, size_t n3, const double* sum_dev, hipStream_t s);
 void launch_f32_to_f64(const float* a, double* b, size_t n3, hipStream_t s);
 void launch_add_f32(double* phi, const float* e, size_t n3, hipStream_t s);
 
 int reduce_blocks(size_t n3);
-// what: 0 = sum x, 1 = sum x^2, 2 = count of non-finite values; result in out[0] (device)
-void launch_sum(const double* x, size_t n3, int what, double* part, double* out, hipStream_t s);
-// out[0] = sum of part[0..np) in index order (second stage of a deterministic reduction)
-// Publish *src (device) to dst_host[0] and then seq to dst_host[1] (coherent pinned memory);
-// done != nullptr: that event takes the end of the publishing kernel (from its own dispatch).
-void launch_publish(const double* src, unsigned long long* dst_host, unsigned long long seq, hipStream_t s,
-                    hipEvent_t done);
-void launch_sum_partials(const double* part, int np, double* out, hipStream_t s);
+// Sums to a sink (its total is the launcher's to set): of x; of sink.part[0..np) in index order
+// (the second stage of a launch that left partials there).
+void launch_sum(const double* x, size_t n3, SumSink sink, hipStream_t s);
+void launch_sum_partials(int np, SumSink sink, hipStream_t s);
+// Clears scal[0..count) (count <= 64) and stores the device clock's bits in scal[at].
+void launch_begin(double* scal, int count, int at, hipStream_t s);
+// Publishes *src (device) as a sink's launch would.
+void launch_publish(const double* src, const SumSink& sink, hipStream_t s);
 void launch_defect_norm(const double* u, const double* f, float* r32, int n, double h, const LevelBC& bc,
-                        double* part, double* out, hipStream_t s);
+                        SumSink sink, hipStream_t s);
 
 // zero `bytes` of device memory at p (8-byte aligned) with a kernel
 void launch_zero(void* p, size_t bytes, hipStream_t s);
@@ -109,17 +111,26 @@ void launch_zero(void* p, size_t bytes, hipStream_t s);
 // out ((n+2)^3) = u with its ghost layer, edges and corners included, filled from bc
 void launch_fill(const double* u, double* out, int n, const LevelBC& bc, hipStream_t s);
 
-void launch_face_extend(const double* b, double* e, int n, hipStream_t s);
-void launch_face_restrict(const double* ef, double* ec, int nc, hipStream_t s);
+// The extended arrays of the levels bottom..L (ext[l]: six of (2^l + 2)^2 one after another) of
+// the faces with values (src[f]: n^2 finest values, or null); adds the count of each face's
+// non-finite values to nonfinite[face] (null: not wanted).
+void launch_faces(const double* const src[6], double* const* ext, int L, int bottom, double* nonfinite, hipStream_t s);
 
 // multipole (mg_multipole.hip)
 // moments[0..3] = (M, Mx, My, Mz) sums; origin[3]; q[25]
 // rho of n^3 cells, dense (Lm = 0) or in the MeshBlock layout with 2^Lm-cell blocks
 void launch_multipole_moments(const double* rho, int n, int Lm, double dx, int lmax, int use_origin,
                               const double* origin_host, double* part, double* scratch, hipStream_t s);
-// faces[f]: (nl + 2 ext)^2 values over transverse positions (t + 1/2) hl, t = -ext .. nl - 1 + ext
-void launch_multipole_faces(const double* scratch, int lmax, double G, int nl, double hl, double length,
-                            double* faces[6], hipStream_t s, int ext = 1);
+// out[q][f]: (nl + 2 ext)^2 values over transverse positions (t + 1/2) hl, t = -ext .. nl - 1 + ext
+// of level q of `count` (null: not wanted), all in one launch
+struct MpFaceLevels {
+  int count;
+  int nl[16];
+  double hl[16];
+  double* out[16][6];
+};
+void launch_multipole_faces(const double* scratch, int lmax, double G, double length, const MpFaceLevels& F,
+                            hipStream_t s, int ext = 1);
 // Moments over the cells of up to kMpMaxBoxes boxes (dense, x fastest), skipping each box's
 // covered sub-box [hlo, hhi); cell (i, j, k) of a box sits at ((o + i + 1/2) h, ..).  part holds
 // multipole_box_blocks() * nbox * 25 doubles; scratch as above.

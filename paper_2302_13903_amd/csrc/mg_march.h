@@ -32,12 +32,11 @@ void march_down(const T* uin, T* uout, const T* f, T* fc, T* uc0, int n, double 
                 hipStream_t s, int Lm = 0, const MarchAux* aux = nullptr);
 
 // Up step (Alg. 1 steps 5-7) in one pass: u += trilinear(ec) (ec's ghosts from bcc) as u is
-// loaded, then two smoothing sweeps.  part != nullptr: one partial sum of squared defects of
-// the result per workgroup into part (the convergence norm, Sec. 2.3.7); returns the number of
-// partials (0 without part).
+// loaded, then two smoothing sweeps.  sink != nullptr: the sum of squared defects of the result
+// (the convergence norm, Sec. 2.3.7) goes there.
 template <typename T>
-int march_up(const T* uin, T* uout, const T* f, const T* ec, const LevelBC& bcc, double* part, int n, double h,
-             double omega, const LevelBC& bc, hipStream_t s, int Lm = 0, const MarchAux* aux = nullptr);
+void march_up(const T* uin, T* uout, const T* f, const T* ec, const LevelBC& bcc, const SumSink* sink, int n, double h,
+              double omega, const LevelBC& bc, hipStream_t s, int Lm = 0, const MarchAux* aux = nullptr);
 
 // Down step of a Full Approximation Scheme cycle (Alg. 3 steps 1-4) in one pass: two sweeps,
 // the defect of the result restricted into fc, the result itself restricted into pbar (phibar)

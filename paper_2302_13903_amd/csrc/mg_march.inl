@@ -75,7 +75,7 @@ struct MarchArgs {
   void* fc;          // down: restricted defect (n/2)^3
   void* uc0;         // down: coarse correction to clear (FAS: to start from phibar)
   void* pbar;        // FAS down: the restricted potential phibar
-  double* part;      // norm: one partial sum per workgroup
+  SumSink sink;      // norm: where the sum of squared defects goes
   LevelBC bc;        // this level
   LevelBC bcc;       // up: coarse level (homogeneous)
   int n, L, xo, yo, zc, tiles_x, tiles_y, ntiles;
@@ -819,11 +819,11 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
     __syncthreads();
-    if (threadIdx.x == 0) {
-      double s = 0.0;
+    double s = 0.0;
+    if (threadIdx.x == 0)
       for (int q = 0; q < W; ++q) s += red[q];
-      A.part[blockIdx.x] = s;
-    }
+    __syncthreads();
+    finish_sum<kLanes * W>(A.sink, s, red);
   }
 }
 
@@ -881,7 +881,7 @@ bool march_split_plan(int n, int nint, int nring, int hz, int& zi, int& zr) {
 }
 
 template <typename T, bool UP, bool NORM, bool BLK>
-int launch_march(MarchArgs A, hipStream_t s, const MarchAux* aux) {
+void launch_march(MarchArgs A, hipStream_t s, const MarchAux* aux) {
   bool per = true;
   for (int f = 0; f < 6; ++f) per = per && A.bc.kind[f] == BC_PERIODIC;
   bool xyper = true;
@@ -913,7 +913,8 @@ int launch_march(MarchArgs A, hipStream_t s, const MarchAux* aux) {
     Ar.zc = zr;
     Ar.ntiles = (2 * A.tiles_x + 2 * (A.tiles_y - 2)) * ((A.n + zr - 1) / zr);
     const int gr = (Ar.ntiles + 7) / 8 * 8;
-    if (A.part) Ar.part = A.part + gi;
+    Ai.sink.total = Ar.sink.total = gi + gr;
+    Ar.sink.first = gi;
     LaunchTiming& lt = launch_timing();
     const bool timed = lt.armed;
     lt.armed = false;
@@ -925,16 +926,16 @@ int launch_march(MarchArgs A, hipStream_t s, const MarchAux* aux) {
     (void)hipEventRecord(aux->join, aux->s2);
     (void)hipStreamWaitEvent(s, aux->join, 0);
     if (timed) (void)hipEventRecord(lt.e1, s);
-    return gi + gr;
+    return;
   }
   A.zc = march_zchunk(A.n, A.tiles_x * A.tiles_y, HZ);
   const int chunks = (A.n + A.zc - 1) / A.zc;
   A.ntiles = A.tiles_x * A.tiles_y * chunks;
   const int grid = (A.ntiles + 7) / 8 * 8;
+  A.sink.total = grid;
   if (per) launch_maybe_timed(k_march<T, W, UP, NORM, 0, BLK>, dim3(grid), dim3(kLanes * W), 0, s, A);
   else if (xyper) launch_maybe_timed(k_march<T, W, UP, NORM, 1, BLK>, dim3(grid), dim3(kLanes * W), 0, s, A);
   else launch_maybe_timed(k_march<T, W, UP, NORM, 2, BLK>, dim3(grid), dim3(kLanes * W), 0, s, A);
-  return grid;
 }
 
 // The FAS down pass: one launch over every tile, the wall form chosen by the level's faces.
@@ -960,8 +961,7 @@ void launch_march_fas(MarchArgs A, hipStream_t s) {
 
 template <typename T>
 MarchArgs base_args(const T* uin, T* uout, const T* f, int n, double h, double omega, const LevelBC& bc) {
-  MarchArgs A;
-  std::memset(&A, 0, sizeof(A));
+  MarchArgs A{};
   A.uin = uin;
   A.uout = uout;
   A.f = f;
@@ -998,21 +998,20 @@ void march_down_fas(const T* uin, T* uout, const T* f, T* fc, T* pbar, T* uc0, i
 }
 
 template <typename T>
-int march_up(const T* uin, T* uout, const T* f, const T* ec, const LevelBC& bcc, double* part, int n, double h,
-             double omega, const LevelBC& bc, hipStream_t s, int Lm, const MarchAux* aux) {
+void march_up(const T* uin, T* uout, const T* f, const T* ec, const LevelBC& bcc, const SumSink* sink, int n, double h,
+              double omega, const LevelBC& bc, hipStream_t s, int Lm, const MarchAux* aux) {
   MarchArgs A = base_args(uin, uout, f, n, h, omega, bc);
   A.ec = ec;
   A.bcc = bcc;
-  A.part = part;
+  if (sink) A.sink = *sink;
   A.Lm = Lm;
   if (Lm > 0) {
-    if (part) return launch_march<T, true, true, true>(A, s, aux);
-    launch_march<T, true, false, true>(A, s, aux);
-    return 0;
+    if (sink) launch_march<T, true, true, true>(A, s, aux);
+    else launch_march<T, true, false, true>(A, s, aux);
+  } else {
+    if (sink) launch_march<T, true, true, false>(A, s, aux);
+    else launch_march<T, true, false, false>(A, s, aux);
   }
-  if (part) return launch_march<T, true, true, false>(A, s, aux);
-  launch_march<T, true, false, false>(A, s, aux);
-  return 0;
 }
 
 template <typename T>
@@ -1040,8 +1039,8 @@ std::string march_name(bool up, bool norm, const LevelBC& bc, bool blk) {
 #endif
 template void march_down<MG_MARCH_T>(const MG_MARCH_T*, MG_MARCH_T*, const MG_MARCH_T*, MG_MARCH_T*, MG_MARCH_T*, int,
                                      double, double, const LevelBC&, hipStream_t, int, const MarchAux*);
-template int march_up<MG_MARCH_T>(const MG_MARCH_T*, MG_MARCH_T*, const MG_MARCH_T*, const MG_MARCH_T*, const LevelBC&,
-                                  double*, int, double, double, const LevelBC&, hipStream_t, int, const MarchAux*);
+template void march_up<MG_MARCH_T>(const MG_MARCH_T*, MG_MARCH_T*, const MG_MARCH_T*, const MG_MARCH_T*, const LevelBC&,
+                                   const SumSink*, int, double, double, const LevelBC&, hipStream_t, int, const MarchAux*);
 template std::string march_name<MG_MARCH_T>(bool, bool, const LevelBC&, bool);
 template std::string march_fas_name<MG_MARCH_T>(const LevelBC&);
 template void march_down_fas<MG_MARCH_T>(const MG_MARCH_T*, MG_MARCH_T*, const MG_MARCH_T*, MG_MARCH_T*, MG_MARCH_T*,

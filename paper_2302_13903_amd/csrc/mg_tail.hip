@@ -93,6 +93,7 @@ __global__ void __launch_bounds__(kThreads) k_tail(TailArgs a) {
   __shared__ TailMem<T> m;
   const int t = threadIdx.x, wave = t >> 6;
   const int top = a.top, npre = a.npre, npost = a.npost;
+  if (a.clock && t == 0) *a.clock = (unsigned long long)wall_clock64();
   const T w6 = (T)(a.omega / 6.0);
   const bool fmg = (a.mode & TAIL_FMG) != 0;
   // the ghost's factor on the boundary cell's own value per face (0: periodic)
@@ -473,7 +474,7 @@ __global__ void __launch_bounds__(kThreads) k_tail(TailArgs a) {
       ug[g + 256 * (2 * q)] = p ? B[q] : R[q];
       ug[g + 256 * (2 * q + 1)] = p ? R[q] : B[q];
     }
-    if (a.norm) {
+    if (a.sink.out) {
       T r[2], q[2];
       resid16(R, B, fR, bR, m.x[1], zR, p != 0, r);
       resid16(B, R, fB, bB, m.x[0], zB, p == 0, q);
@@ -482,22 +483,21 @@ __global__ void __launch_bounds__(kThreads) k_tail(TailArgs a) {
   } else if (t < (1 << (3 * top))) {
     const T u = m.us[level_offset(top) + t];
     ug[t] = u;
-    if (a.norm) {
+    if (a.sink.out) {
       place(top);
       const T r = resid_small(u, m.fs[level_offset(top) + t]);
       acc = (double)r * (double)r;
     }
   }
-  if (a.norm) {
+  if (a.sink.out) {
     acc = wave_sum(acc);
     if ((t & 63) == 0) m.red[wave] = acc;
     __syncthreads();
-    if (t == 0) {
-      double s = 0.0;
+    double s = 0.0;
+    if (t == 0)
       for (int q = 0; q < kThreads / 64; ++q) s += m.red[q];
-      const double ih2 = 1.0 / (a.h * a.h);
-      a.norm[0] = s * (ih2 * ih2);
-    }
+    const double ih2 = 1.0 / (a.h * a.h);
+    finish_sum<kThreads>(a.sink, s * (ih2 * ih2), m.red);
   }
 }
 

@@ -19,8 +19,8 @@ template <typename T, int NS>
 void tile_down_ns(const T* uin, T* uout, const T* f, T* fc, T* pbar, T* uc0, int n, int Lm, double h, double omega,
                   const LevelBC& bc, hipStream_t s);
 template <typename T, int NS>
-int tile_up_ns(const T* uin, T* uout, const T* f, const T* ec, const LevelBC& bcc, double* part, int n, int Lm, double h,
-               double omega, const LevelBC& bc, hipStream_t s);
+void tile_up_ns(const T* uin, T* uout, const T* f, const T* ec, const LevelBC& bcc, const SumSink* sink, int n, int Lm,
+                double h, double omega, const LevelBC& bc, hipStream_t s);
 
 // May a leg of ns sweeps run as a region tile?
 inline bool tile_sweeps_ok(int ns) { return ns == 1 || ns == 2; }
@@ -40,13 +40,13 @@ void tile_down(const T* uin, T* uout, const T* f, T* fc, T* pbar, T* uc0, int n,
 }
 
 // Up step (Alg. 1 steps 5-7) in one launch: u += trilinear(ec) (ec's ghosts from the
-// homogeneous description bcc), then ns sweeps (uin -> uout).  part != nullptr: one partial
-// sum of squared defects of the result per workgroup (returns their number, else 0).
+// homogeneous description bcc), then ns sweeps (uin -> uout).  sink != nullptr: the sum of
+// squared defects of the result goes there.
 template <typename T>
-int tile_up(const T* uin, T* uout, const T* f, const T* ec, const LevelBC& bcc, double* part, int n, int Lm, int ns,
-            double h, double omega, const LevelBC& bc, hipStream_t s) {
-  if (ns == 1) return tile_up_ns<T, 1>(uin, uout, f, ec, bcc, part, n, Lm, h, omega, bc, s);
-  return tile_up_ns<T, 2>(uin, uout, f, ec, bcc, part, n, Lm, h, omega, bc, s);
+void tile_up(const T* uin, T* uout, const T* f, const T* ec, const LevelBC& bcc, const SumSink* sink, int n, int Lm,
+             int ns, double h, double omega, const LevelBC& bc, hipStream_t s) {
+  if (ns == 1) tile_up_ns<T, 1>(uin, uout, f, ec, bcc, sink, n, Lm, h, omega, bc, s);
+  else tile_up_ns<T, 2>(uin, uout, f, ec, bcc, sink, n, Lm, h, omega, bc, s);
 }
 
 // Name of the kernel of such a leg, as profilers list it.

@@ -32,8 +32,6 @@
 // block level is the dense root grid).
 #include "mg_tile.h"
 
-#include <cstring>
-
 #include "mg_launch.h"
 
 namespace mg {
@@ -60,7 +58,7 @@ struct TileArgs {
   void* uc0;         // down: coarse correction to clear (FAS: to start from phibar)
   void* pbar;        // FAS down (Alg. 3 steps 2-4), else null: receives phibar, the mean of the
                      // 8 children of the swept u, from which the coarse level then starts
-  double* part;      // up with norm, else null: one partial sum per workgroup
+  SumSink sink;      // up: where the sum of squared defects goes (part null: not wanted)
   LevelBC bc;        // this level
   LevelBC bcc;       // up: coarse level (homogeneous)
   int n, L, Lm, per, nrx, nry;
@@ -385,7 +383,7 @@ __global__ void __launch_bounds__(tile_threads(NS, SH), SH == 0 ? 4 : 1) k_tile_
 
   // ---- residuals of the region's slots QL..QH: for the restriction (per coarse plane the two
   // cells of the column added) or the norm
-  const bool fas = !UP && A.pbar, norm = UP && A.part;
+  const bool fas = !UP && A.pbar, norm = UP && A.sink.part;
   if (!UP || norm) {
     T zs[UP ? 1 : MZ];
     double acc = 0.0;
@@ -441,19 +439,18 @@ __global__ void __launch_bounds__(tile_threads(NS, SH), SH == 0 ? 4 : 1) k_tile_
       acc = wave_sum(own_col ? acc : 0.0);
       if ((tid & 63) == 0) red[tid >> 6] = acc;
       __syncthreads();
-      if (tid == 0) {
-        double t = 0.0;
+      double t = 0.0;
+      if (tid == 0)
         for (int q = 0; q < kThreads / 64; ++q) t += red[q];
-        A.part[blockIdx.x] = t * (A.ih2 * A.ih2);
-      }
+      __syncthreads();
+      finish_sum<kThreads>(A.sink, t * (A.ih2 * A.ih2), red);
     }
   }
 }
 
 template <typename T>
 TileArgs base_args(const T* uin, T* uout, const T* f, int n, int Lm, double h, double omega, const LevelBC& bc) {
-  TileArgs A;
-  std::memset(&A, 0, sizeof(A));
+  TileArgs A{};
   A.uin = uin;
   A.uout = uout;
   A.f = f;
@@ -504,20 +501,20 @@ void tile_down_ns(const T* uin, T* uout, const T* f, T* fc, T* pbar, T* uc0, int
 }
 
 template <typename T, int NS>
-int tile_up_ns(const T* uin, T* uout, const T* f, const T* ec, const LevelBC& bcc, double* part, int n, int Lm, double h,
-               double omega, const LevelBC& bc, hipStream_t s) {
+void tile_up_ns(const T* uin, T* uout, const T* f, const T* ec, const LevelBC& bcc, const SumSink* sink, int n, int Lm,
+                double h, double omega, const LevelBC& bc, hipStream_t s) {
   TileArgs A = base_args(uin, uout, f, n, Lm, h, omega, bc);
   A.ec = ec;
   A.bcc = bcc;
-  A.part = part;
+  if (sink) A.sink = *sink;
+  A.sink.total = regions(n);
   launch_leg<T, NS, true>(A, s);
-  return part ? regions(n) : 0;
 }
 
 #define MG_TILE_INST(T, NS)                                                                                       \
   template void tile_down_ns<T, NS>(const T*, T*, const T*, T*, T*, T*, int, int, double, double, const LevelBC&, \
                                     hipStream_t);                                                                 \
-  template int tile_up_ns<T, NS>(const T*, T*, const T*, const T*, const LevelBC&, double*, int, int, double,     \
-                                 double, const LevelBC&, hipStream_t);
+  template void tile_up_ns<T, NS>(const T*, T*, const T*, const T*, const LevelBC&, const SumSink*, int, int,     \
+                                  double, double, const LevelBC&, hipStream_t);
 
 }  // namespace mg
