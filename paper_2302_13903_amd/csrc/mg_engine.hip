@@ -900,7 +900,9 @@ struct Solver {
     tail(H, H.T_top, TAIL_FMG, H.phys[H.T_top], normed);
     for (int l = H.T_top + 1; l <= H.L; ++l) {
       if (Lb >= 0 && l > Lb) {
-        blk_prolong<T>(H.u[l - 1], H.u[l], l - Lb, Lb, H.phys[l - 1], 1, s);
+        const int Lm = l - Lb;
+        if (l - 1 >= 4) launch_prolong_fmg<T>(H.u[l - 1], H.u[l], 1 << (l - 1), Lm - 1, Lm, H.phys[l - 1], s);
+        else blk_prolong<T>(H.u[l - 1], H.u[l], Lm, Lb, H.phys[l - 1], 1, s);
         vcycle_blk(H, l, H.phys[l]);
       } else {
         launch_prolong<T>(H.u[l - 1], H.u[l], 1 << (l - 1), H.phys[l - 1], 1, s);
@@ -1019,11 +1021,12 @@ struct Solver {
     return false;
   }
 
-  // Source hierarchy f_{l-1} = restriction of f_l (Alg. 2 step 1) in either layout, down to the
-  // tail's top level (the tail restricts its own).
+  // Source hierarchy f_{l-1} = restriction of f_l (Alg. 2 step 1) in either layout, from the level
+  // below the finest (whose restriction the source kernel makes) to the tail's top level (the tail
+  // restricts its own).
   template <typename T>
   void restrict_sources(Hier<T>& H) {
-    for (int l = H.L; l > H.T_top; --l) {
+    for (int l = H.L - 1; l > H.T_top; --l) {
       if (Lb >= 0 && l > Lb) blk_restrict<T, T>(H.f[l], H.f[l - 1], l - Lb, Lb, s);
       else launch_restrict<T, T>(H.f[l], H.f[l - 1], 1 << (l - 1), s);
     }
@@ -1328,11 +1331,8 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
 
   // ---- source (eq. poisson, f = 4 pi G rho; mean removed when gauge-free, Sec. 2.3.6)
   double* f64L = reinterpret_cast<double*>(ws + y.f64L);
-  float* f32L = mixed ? reinterpret_cast<float*>(ws + y.f32[L]) : nullptr;
   // (gauge-free: the source kernel reads the sum of rho from scal[0] and shifts by the mean)
   if (gauge_free) launch_sum(rho, n3, sum_sink(part, scal, 0), s);
-  launch_source(rho, f64L, f32L, n3, p->four_pi_g, gauge_free ? scal + 0 : nullptr, sum_sink(part, scal, 1), s);
-
   LevelBC phys[16], hom;
   setup_faces(ws, part, scal, y, p, bc, rho, s, phys, &hom);
 
@@ -1367,6 +1367,8 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
     H64.f[L] = f64L;
     for (int l = 0; l <= L; ++l)
       H64.u2[l] = y.u2[l] == (size_t)-1 ? nullptr : reinterpret_cast<double*>(ws + y.u2[l]);
+    launch_source<double>(rho, f64L, nullptr, L > H64.T_top ? H64.f[L - 1] : nullptr, L, Lb >= 0 ? L - Lb : 0,
+                          p->four_pi_g, gauge_free ? scal + 0 : nullptr, sum_sink(part, scal, 1), s);
     S.restrict_sources(H64);
   } else {
     fill_common(H32, tail_max);
@@ -1375,6 +1377,8 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
       H32.f[l] = reinterpret_cast<float*>(ws + y.f32[l]);
       H32.u2[l] = y.u2[l] == (size_t)-1 ? nullptr : reinterpret_cast<float*>(ws + y.u2[l]);
     }
+    launch_source<float>(rho, f64L, H32.f[L], L > H32.T_top ? H32.f[L - 1] : nullptr, L, Lb >= 0 ? L - Lb : 0,
+                         p->four_pi_g, gauge_free ? scal + 0 : nullptr, sum_sink(part, scal, 1), s);
     S.restrict_sources(H32);
   }
 

@@ -336,8 +336,69 @@ __global__ void __launch_bounds__(kBlock) k_prolong(const T* __restrict__ uc, T*
     }
 }
 
+// The FMG prolongation of the levels from 16^3: a workgroup stages its 256 coarse cells and their
+// neighbours, ghosts included, in LDS (one cell or two per thread, the ghost rules evaluated side
+// by side), then each thread interpolates separably in x, y, z and writes the 8 children of one
+// cell.  Bound by the writes; small levels by one global and one LDS latency, where 27 taps through
+// the ghost rules one after another took 17-22 us a level.  Lmc, Lmf: MeshBlock layout of the
+// coarse and the fine level (0: dense).
+constexpr int kProlongMinNc = 16;
+template <typename T, int TX>
+__global__ void __launch_bounds__(kBlock) k_prolong_tile(const T* __restrict__ uc, T* __restrict__ uf, int Lc, int Lmc,
+                                                          int Lmf, LevelBC bcc) {
+  constexpr int TY = 4, TZ = kBlock / (TX * TY), SX = TX + 2, SY = TY + 2, SZ = TZ + 2;
+  __shared__ T v[SZ * SY * SX];
+  const int nc = 1 << Lc, tx = nc / TX, ty = nc / TY;
+  const int I0 = (int)(blockIdx.x % tx) * TX, J0 = (int)((blockIdx.x / tx) % ty) * TY, K0 = (int)(blockIdx.x / (tx * ty)) * TZ;
+  for (int q = threadIdx.x; q < SZ * SY * SX; q += kBlock) {
+    const int i = I0 + q % SX - 1, j = J0 + (q / SX) % SY - 1, k = K0 + q / (SX * SY) - 1;
+    const bool inside = i >= 0 && i < nc && j >= 0 && j < nc && k >= 0 && k < nc;
+    v[q] = inside ? uc[lidx(Lc, Lmc, i, j, k)] : ghost_any(uc, nc, Lc, i, j, k, bcc, Lmc);
+  }
+  __syncthreads();
+  const int a = threadIdx.x % TX, b = (threadIdx.x / TX) % TY, c = threadIdx.x / (TX * TY);
+  const T* p = v + (c * SY + b) * SX + a;
+  T ey[3][2][2];   // [plane][y child][x child]
+#pragma unroll
+  for (int z = 0; z < 3; ++z) {
+    T ex[3][2];
+#pragma unroll
+    for (int y = 0; y < 3; ++y) {
+      const T* r = p + (z * SY + y) * SX;
+      ex[y][0] = interp3<T, 1>(0, r[0], r[1], r[2]);
+      ex[y][1] = interp3<T, 1>(1, r[0], r[1], r[2]);
+    }
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      ey[z][0][x] = interp3<T, 1>(0, ex[0][x], ex[1][x], ex[2][x]);
+      ey[z][1][x] = interp3<T, 1>(1, ex[0][x], ex[1][x], ex[2][x]);
+    }
+  }
+  // the two x-children are adjacent (even index first); written past the caches, which leaves them
+  // to the coarse rows that neighbouring workgroups read
+  typedef T tv2 __attribute__((ext_vector_type(2)));
+  const int L = Lc + 1, I = I0 + a, J = J0 + b, K = K0 + c;
+#pragma unroll
+  for (int z = 0; z < 2; ++z)
+#pragma unroll
+    for (int y = 0; y < 2; ++y) {
+      const T lo = interp3<T, 1>(z, ey[0][y][0], ey[1][y][0], ey[2][y][0]);
+      const T hi = interp3<T, 1>(z, ey[0][y][1], ey[1][y][1], ey[2][y][1]);
+      __builtin_nontemporal_store(tv2{lo, hi}, reinterpret_cast<tv2*>(uf + lidx(L, Lmf, 2 * I, 2 * J + y, 2 * K + z)));
+    }
+}
+
+template <typename T>
+void launch_prolong_fmg(const T* uc, T* uf, int nc, int Lmc, int Lmf, const LevelBC& bcc, hipStream_t s) {
+  const int Lc = ilog2(nc);
+  const dim3 g((unsigned)(((size_t)1 << (3 * Lc)) / kBlock));
+  if (nc >= 32) hipLaunchKernelGGL((k_prolong_tile<T, 32>), g, dim3(kBlock), 0, s, uc, uf, Lc, Lmc, Lmf, bcc);
+  else hipLaunchKernelGGL((k_prolong_tile<T, 16>), g, dim3(kBlock), 0, s, uc, uf, Lc, Lmc, Lmf, bcc);
+}
+
 template <typename T>
 void launch_prolong(const T* uc, T* uf, int nc, const LevelBC& bcc, int cubic, hipStream_t s) {
+  if (cubic && nc >= kProlongMinNc) return launch_prolong_fmg<T>(uc, uf, nc, 0, 0, bcc, s);
   const int Lc = ilog2(nc);
   const dim3 g(grid_for((size_t)1 << (3 * Lc)));
   if (cubic) hipLaunchKernelGGL((k_prolong<T, 1>), g, dim3(kBlock), 0, s, uc, uf, Lc, bcc);
@@ -406,7 +467,12 @@ void launch_add_f32(double* phi, const float* e, size_t n3, hipStream_t s) {
 // ------------------------------------------------------------------ reductions
 
 // Deterministic sums: one partial per block (grid-stride loop, fixed grid, fixed tree), added in
-// index order by the block that arrives last (finish_sum).
+// index order by the block that arrives last (finish_sum).  The blocks are large and at most
+// kSumBlocks: each arrival is an atomic on one counter, 11 ns apart (2048 blocks of 256 threads
+// took 23 us longer than the reading at 256^3).
+constexpr int kSumBlock = 1024, kSumBlocks = 512;
+
+template <int THREADS>
 __device__ __forceinline__ double block_sum(double v, double* red) {
   v = wave_sum(v);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -414,17 +480,34 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
   __syncthreads();
   double r = 0.0;
   if (threadIdx.x == 0) {
-    for (int q = 0; q < kBlock / 64; ++q) r += red[q];
+    for (int q = 0; q < THREADS / 64; ++q) r += red[q];
   }
   __syncthreads();
   return r;
 }
 
-__global__ void __launch_bounds__(kBlock) k_sum(const double* __restrict__ x, size_t n3, SumSink sink) {
-  __shared__ double red[kBlock / 64];
-  double acc = 0.0;
-  for (size_t t = (size_t)blockIdx.x * kBlock + threadIdx.x; t < n3; t += (size_t)gridDim.x * kBlock) acc += x[t];
-  finish_sum<kBlock>(sink, block_sum(acc, red), red);
+// blocks of kSumBlock threads for `items` grid-strided work items
+static int sum_blocks(size_t items) {
+  const size_t b = (items + kSumBlock - 1) / kSumBlock;
+  return (int)std::min<size_t>(std::max<size_t>(b, 1), kSumBlocks);
+}
+
+__global__ void __launch_bounds__(kSumBlock) k_sum(const double* __restrict__ x, size_t n3, SumSink sink) {
+  typedef double dv2 __attribute__((ext_vector_type(2)));
+  __shared__ double red[kSumBlock / 64];
+  double acc = 0.0, acc2 = 0.0;
+  if (((size_t)x & 15) == 0 && (n3 & 1) == 0) {
+    const dv2* p = reinterpret_cast<const dv2*>(x);
+#pragma unroll 4
+    for (size_t t = (size_t)blockIdx.x * kSumBlock + threadIdx.x; t < n3 / 2; t += (size_t)gridDim.x * kSumBlock) {
+      const dv2 v = p[t];
+      acc += v.x;
+      acc2 += v.y;
+    }
+  } else {
+    for (size_t t = (size_t)blockIdx.x * kSumBlock + threadIdx.x; t < n3; t += (size_t)gridDim.x * kSumBlock) acc += x[t];
+  }
+  finish_sum<kSumBlock>(sink, block_sum<kSumBlock>(acc + acc2, red), red);
 }
 
 __global__ void __launch_bounds__(kBlock) k_sum_final(const double* __restrict__ part, int np, SumSink sink) {
@@ -432,7 +515,7 @@ __global__ void __launch_bounds__(kBlock) k_sum_final(const double* __restrict__
   __shared__ double red[kBlock / 64];
   double acc = 0.0;
   for (int b = threadIdx.x; b < np; b += kBlock) acc += part[b];
-  finish_sum<kBlock>(sink, block_sum(acc, red), red);
+  finish_sum<kBlock>(sink, block_sum<kBlock>(acc, red), red);
 }
 
 int reduce_blocks(size_t n3) {
@@ -466,19 +549,19 @@ void launch_sum_partials(int np, SumSink sink, hipStream_t s) {
 }
 
 void launch_sum(const double* x, size_t n3, SumSink sink, hipStream_t s) {
-  sink.total = reduce_blocks(n3);
-  hipLaunchKernelGGL(k_sum, dim3(sink.total), dim3(kBlock), 0, s, x, n3, sink);
+  sink.total = sum_blocks((n3 + 7) / 8);
+  hipLaunchKernelGGL(k_sum, dim3(sink.total), dim3(kSumBlock), 0, s, x, n3, sink);
 }
 
 // Defect of the finest level and its sum of squares (Sec. 2.3.7, eq. threshold); optionally
 // the defect itself in FP32 (mixed precision: right-hand side of the inner correction cycle).
-__global__ void __launch_bounds__(kBlock) k_defect_norm(const double* __restrict__ u, const double* __restrict__ f,
+__global__ void __launch_bounds__(kSumBlock) k_defect_norm(const double* __restrict__ u, const double* __restrict__ f,
                                                          float* __restrict__ r32, int n, int L, double ih2, LevelBC bc,
                                                          SumSink sink) {
-  __shared__ double red[kBlock / 64];
+  __shared__ double red[kSumBlock / 64];
   const size_t n3 = (size_t)1 << (3 * L);
   double acc = 0.0;
-  for (size_t c = (size_t)blockIdx.x * kBlock + threadIdx.x; c < n3; c += (size_t)gridDim.x * kBlock) {
+  for (size_t c = (size_t)blockIdx.x * kSumBlock + threadIdx.x; c < n3; c += (size_t)gridDim.x * kSumBlock) {
     const int i = (int)(c & (size_t)(n - 1));
     const int j = (int)((c >> L) & (size_t)(n - 1));
     const int k = (int)(c >> (2 * L));
@@ -488,46 +571,75 @@ __global__ void __launch_bounds__(kBlock) k_defect_norm(const double* __restrict
     acc += d * d;
     if (r32) r32[c] = (float)d;
   }
-  finish_sum<kBlock>(sink, block_sum(acc, red), red);
+  finish_sum<kSumBlock>(sink, block_sum<kSumBlock>(acc, red), red);
 }
 
 void launch_defect_norm(const double* u, const double* f, float* r32, int n, double h, const LevelBC& bc,
                         SumSink sink, hipStream_t s) {
   const int L = ilog2(n);
-  sink.total = reduce_blocks((size_t)1 << (3 * L));
-  hipLaunchKernelGGL(k_defect_norm, dim3(sink.total), dim3(kBlock), 0, s, u, f, r32, n, L, 1.0 / (h * h), bc, sink);
+  sink.total = sum_blocks((size_t)1 << (3 * L));
+  hipLaunchKernelGGL(k_defect_norm, dim3(sink.total), dim3(kSumBlock), 0, s, u, f, r32, n, L, 1.0 / (h * h), bc, sink);
 }
 
 // f = a * rho + c (the source 4 pi G rho, mean-shifted when gauge-free: c = -a * mean(rho),
 // read from the device so that the host need not wait for the sum), in FP64, plus the
-// FP32 copy when f32 != nullptr, and the sum of f^2 (fixed grid and tree, so reproducible).
-// Without the sum of rho the block sums of rho are taken here for their finiteness alone: one
-// that is not finite makes the sum of f^2 not finite either.
-__global__ void __launch_bounds__(kBlock) k_source(const double* __restrict__ rho, double* __restrict__ f,
-                                                    float* __restrict__ f32, size_t n3, double a,
-                                                    const double* __restrict__ rho_sum, SumSink sink) {
-  __shared__ double red[kBlock / 64];
+// FP32 copy when f32 != nullptr, and the sum of f^2 (fixed grid and tree, so reproducible); with
+// fc also its restriction to the level below (Alg. 2 step 1), while the eight children are in
+// registers (at 512^3 a pass of its own over f took 238 us).  Without the sum of rho the block
+// sums of rho are taken here for their finiteness alone: one that is not finite makes the sum of
+// f^2 not finite either.  One work item per coarse cell, in the coarse level's storage order:
+// four row pairs of 16 bytes.  Lm: MeshBlock layout with 2^Lm-cell blocks (0: dense).
+template <typename T>
+__global__ void __launch_bounds__(kSumBlock) k_source(const double* __restrict__ rho, double* __restrict__ f,
+                                                       float* __restrict__ f32, T* __restrict__ fc, int L, int Lm,
+                                                       double a, const double* __restrict__ rho_sum, SumSink sink) {
+  typedef double dv2 __attribute__((ext_vector_type(2), aligned(8)));   // rho is the caller's: 8-byte aligned
+  typedef float fv2 __attribute__((ext_vector_type(2)));
+  __shared__ double red[kSumBlock / 64];
+  const size_t n3 = (size_t)1 << (3 * L), items = n3 >> 3;
   // gauge-free: c = -a * mean(rho), from the sum the previous launch left in device memory
   const double c = rho_sum ? -a * (rho_sum[0] / (double)n3) : 0.0;
+  const int Lf = Lm > 0 ? Lm : L, Lc = Lf - 1;   // the cube of 2^Lf cells that is stored x fastest
   double acc = 0.0, total = 0.0;
-  for (size_t t = (size_t)blockIdx.x * kBlock + threadIdx.x; t < n3; t += (size_t)gridDim.x * kBlock) {
-    const double r = rho[t], v = a * r + c;
-    f[t] = v;
-    if (f32) f32[t] = (float)v;
-    acc += v * v;
-    total += r;
+  for (size_t C = (size_t)blockIdx.x * kSumBlock + threadIdx.x; C < items; C += (size_t)gridDim.x * kSumBlock) {
+    const size_t r = C & (((size_t)1 << (3 * Lc)) - 1);
+    size_t cube = C >> (3 * Lc);
+    if (Lm == 1) {   // blocks of one coarse cell each: the level below is the dense root grid
+      const int m = (1 << (L - 1)) - 1;
+      cube = morton3((int)C & m, (int)(C >> (L - 1)) & m, (int)(C >> (2 * L - 2)));
+    }
+    const size_t i = r & (((size_t)1 << Lc) - 1), j = (r >> Lc) & (((size_t)1 << Lc) - 1), k = r >> (2 * Lc);
+    const size_t o = (cube << (3 * Lf)) | (k << (2 * Lf + 1)) | (j << (Lf + 1)) | (i << 1);
+    double sum = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const size_t at = o + ((q & 1) ? (size_t)1 << Lf : 0) + ((q & 2) ? (size_t)1 << (2 * Lf) : 0);
+      const dv2 x = *reinterpret_cast<const dv2*>(rho + at);
+      const dv2 v = dv2{a * x.x + c, a * x.y + c};
+      *reinterpret_cast<dv2*>(f + at) = v;
+      if (f32) *reinterpret_cast<fv2*>(f32 + at) = fv2{(float)v.x, (float)v.y};
+      acc += v.x * v.x + v.y * v.y;
+      total += x.x + x.y;
+      sum += v.x + v.y;
+    }
+    if (fc) fc[C] = (T)(0.125 * sum);
   }
-  double sumsq = block_sum(acc, red);
-  total = block_sum(total, red);
+  double sumsq = block_sum<kSumBlock>(acc, red);
+  total = block_sum<kSumBlock>(total, red);
   if (!isfinite(total)) sumsq = __builtin_nan("");
-  finish_sum<kBlock>(sink, sumsq, red);
+  finish_sum<kSumBlock>(sink, sumsq, red);
 }
 
-void launch_source(const double* rho, double* f, float* f32, size_t n3, double a, const double* rho_sum, SumSink sink,
-                   hipStream_t s) {
-  sink.total = reduce_blocks(n3);
-  hipLaunchKernelGGL(k_source, dim3(sink.total), dim3(kBlock), 0, s, rho, f, f32, n3, a, rho_sum, sink);
+template <typename T>
+void launch_source(const double* rho, double* f, float* f32, T* fc, int L, int Lm, double a, const double* rho_sum,
+                   SumSink sink, hipStream_t s) {
+  sink.total = sum_blocks((size_t)1 << (3 * L - 3));
+  hipLaunchKernelGGL(k_source<T>, dim3(sink.total), dim3(kSumBlock), 0, s, rho, f, f32, fc, L, Lm, a, rho_sum, sink);
 }
+template void launch_source<double>(const double*, double*, float*, double*, int, int, double, const double*, SumSink,
+                                    hipStream_t);
+template void launch_source<float>(const double*, double*, float*, float*, int, int, double, const double*, SumSink,
+                                   hipStream_t);
 
 // ------------------------------------------------------------------ boundary face arrays
 
@@ -667,6 +779,7 @@ void launch_fill(const double* u, double* out, int n, const LevelBC& bc, hipStre
   template void launch_defect_restrict<T>(const T*, const T*, T*, T*, int, double, const LevelBC&,         \
                                           hipStream_t);                                                    \
   template void launch_prolong<T>(const T*, T*, int, const LevelBC&, int, hipStream_t);                    \
+  template void launch_prolong_fmg<T>(const T*, T*, int, int, int, const LevelBC&, hipStream_t);           \
   template void launch_coarsest<T>(T*, const T*, double, const LevelBC&, hipStream_t);
 
 MG_INST(double)

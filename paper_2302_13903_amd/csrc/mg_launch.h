@@ -73,6 +73,10 @@ template <typename Tin, typename Tout>
 void launch_restrict(const Tin* uf, Tout* uc, int nc, hipStream_t s);
 template <typename T>
 void launch_prolong(const T* uc, T* uf, int nc, const LevelBC& bcc, int cubic, hipStream_t s);
+// The FMG prolongation alone, for coarse levels of at least 16^3 (nc >= 16), either level in the
+// MeshBlock layout with 2^Lmc- (2^Lmf-) cell blocks (0: dense).
+template <typename T>
+void launch_prolong_fmg(const T* uc, T* uf, int nc, int Lmc, int Lmf, const LevelBC& bcc, hipStream_t s);
 template <typename T>
 void launch_coarsest(T* u, const T* f, double h, const LevelBC& bc, hipStream_t s);
 template <typename T>
@@ -84,11 +88,13 @@ void launch_fas_restrict(const double* u, const double* f, double* fc, double* p
 void launch_fas_source(const double* pbar, double* f, int n, double h, const LevelBC& bc, hipStream_t s);
 void launch_fas_correction(double* u, const double* pbar, size_t n3, hipStream_t s);
 
-// f = a rho + c (and its FP32 copy when f32 != nullptr); the sum of f^2 to the sink (not finite
-// when rho is not).  c = -a * rho_sum[0] / n3 when rho_sum (device) is given (the gauge-free
-// source), else 0.
-void launch_source(const double* rho, double* f, float* f32, size_t n3, double a, const double* rho_sum, SumSink sink,
-                   hipStream_t s);
+// f = a rho + c (and its FP32 copy when f32 != nullptr; and its restriction to the level below when
+// fc != nullptr) on a level of 2^L cells per side (Lm > 0: MeshBlock layout); the sum of f^2 to the
+// sink (not finite when rho is not).  c = -a * rho_sum[0] / n3 when rho_sum (device) is given (the
+// gauge-free source), else 0.
+template <typename T>
+void launch_source(const double* rho, double* f, float* f32, T* fc, int L, int Lm, double a, const double* rho_sum,
+                   SumSink sink, hipStream_t s);
 void launch_sub_mean(double* u, size_t n3, const double* sum_dev, hipStream_t s);
 void launch_f32_to_f64(const float* a, double* b, size_t n3, hipStream_t s);
 void launch_add_f32(double* phi, const float* e, size_t n3, hipStream_t s);
