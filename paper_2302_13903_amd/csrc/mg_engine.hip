@@ -15,6 +15,7 @@
 #include <mutex>
 #include <sstream>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "mg355.h"
@@ -311,8 +312,8 @@ struct Hier {
   T* u2[16];          // ping-pong partner of u[l] for fused levels, else nullptr
   T* f[16];
   double h[16];
-  LevelBC phys[16];
-  LevelBC hom;
+  LevelBC phys[16];   // with face values: for the tail, and for prolonging a full iterate
+  LevelBC hom;        // without: for corrections, and for every level whose f carries the face values
   int npre = 2, npost = 2;
   double omega = 1.15;
 };
@@ -792,11 +793,11 @@ struct Solver {
       // u = phibar + e with the source R(defect) + L phibar, and every step of Alg. 3 on a linear
       // operator (smoothing, restriction, the single cell) keeps phibar and moves e exactly as
       // Alg. 1 moves the correction, which is all the levels above see (psi - phibar).
-      tail(H, l, TAIL_LOAD_U, H.phys[l], want_norm);
+      tail(H, l, TAIL_LOAD_U, H.L > H.T_top ? H.hom : H.phys[l], want_norm);
       return want_norm;
     }
     const int n = 1 << l;
-    const LevelBC& bc = H.phys[l];
+    const LevelBC& bc = H.hom;
     const bool timed = timed_top && l == H.L && ktiming;
     const double cellsT = (double)cells(l) * sizeof(double);
     if (done == 0 && march_on<double>(H, l, bc)) {
@@ -807,7 +808,7 @@ struct Solver {
       march_down_fas<double>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], pbar[l - 1], H.u[l - 1], n, H.h[l], H.omega, bc, s);
       // algorithmic bytes: u and f read, u written, three coarse arrays written
       if (timed) kernel_end(march_fas_name<double>(bc), 3 * cellsT + 3 * cellsT / 8);
-      launch_fas_source(pbar[l - 1], H.f[l - 1], n / 2, H.h[l - 1], H.phys[l - 1], s);       // 5
+      launch_fas_source(pbar[l - 1], H.f[l - 1], n / 2, H.h[l - 1], H.hom, s);               // 5
       fas_cycle(H, pbar, l - 1);                                                             // 6
       launch_fas_correction(H.u[l - 1], pbar[l - 1], cells(l - 1), s);                       // 7
       const SumSink sink = want_norm ? norm_sink() : SumSink{};
@@ -825,7 +826,7 @@ struct Solver {
       if (timed) kernel_begin(true);
       tile_down<double>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], pbar[l - 1], H.u[l - 1], n, 0, H.npre, H.h[l], H.omega, bc, s);
       if (timed) kernel_end(tile_name<double>(H.npre, false, bc, n), 3 * cellsT + 3 * cellsT / 8);
-      launch_fas_source(pbar[l - 1], H.f[l - 1], n / 2, H.h[l - 1], H.phys[l - 1], s);       // 5
+      launch_fas_source(pbar[l - 1], H.f[l - 1], n / 2, H.h[l - 1], H.hom, s);               // 5
       fas_cycle(H, pbar, l - 1);                                                             // 6
       launch_fas_correction(H.u[l - 1], pbar[l - 1], cells(l - 1), s);                       // 7
       const SumSink sink = want_norm ? norm_sink() : SumSink{};
@@ -855,7 +856,7 @@ struct Solver {
     if (timed)
       kernel_end(streamed ? fused_fas_restrict_name(fuse) : "k_fas_restrict",
                  (fuse ? 3 * cellsT : 2 * cellsT) + 3 * cellsT / 8);
-    launch_fas_source(pbar[l - 1], H.f[l - 1], n / 2, H.h[l - 1], H.phys[l - 1], s);         // 5
+    launch_fas_source(pbar[l - 1], H.f[l - 1], n / 2, H.h[l - 1], H.hom, s);                 // 5
     fas_cycle(H, pbar, l - 1);                                                               // 6
     launch_fas_correction(H.u[l - 1], pbar[l - 1], cells(l - 1), s);                         // 7
     // 8-10: the correction obeys the homogeneous conditions (the physical values cancel in
@@ -903,10 +904,10 @@ struct Solver {
         const int Lm = l - Lb;
         if (l - 1 >= 4) launch_prolong_fmg<T>(H.u[l - 1], H.u[l], 1 << (l - 1), Lm - 1, Lm, H.phys[l - 1], s);
         else blk_prolong<T>(H.u[l - 1], H.u[l], Lm, Lb, H.phys[l - 1], 1, s);
-        vcycle_blk(H, l, H.phys[l]);
+        vcycle_blk(H, l, H.hom);
       } else {
         launch_prolong<T>(H.u[l - 1], H.u[l], 1 << (l - 1), H.phys[l - 1], 1, s);
-        normed = vcycle(H, l, H.phys[l], false, norm_top && l == H.L);
+        normed = vcycle(H, l, H.hom, false, norm_top && l == H.L);
       }
     }
     return normed;
@@ -1382,6 +1383,29 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
     S.restrict_sources(H32);
   }
 
+  // ---- face values into the sources of the levels above the tail's (the tail, which makes
+  // the sources of its levels itself, reads the face arrays): every level with the FMG sweep, the
+  // finest alone without (the others then hold corrections)
+  const bool fold = L > (mixed ? H32.T_top : H64.T_top);
+  if (fold) {
+    auto fold_levels = [&](auto& H, int from) {
+      using T = std::remove_reference_t<decltype(*H.f[0])>;
+      FoldLevel lv[16];
+      int count = 0;
+      for (int l = L; l >= from; --l)
+        lv[count++] = FoldLevel{H.f[l], 1.0 / (H.h[l] * H.h[l]), l, Lb >= 0 && l > Lb ? l - Lb : 0, phys[l]};
+      launch_fold_faces<T>(lv, count, s);
+    };
+    if (!mixed) {
+      fold_levels(H64, p->mode == MG_MODE_FMG ? H64.T_top + 1 : L);
+    } else {
+      const FoldLevel top{f64L, 1.0 / (p->dx * p->dx), L, Lb >= 0 ? L - Lb : 0, phys[L]};
+      launch_fold_faces<double>(&top, 1, s);
+      if (p->mode == MG_MODE_FMG) fold_levels(H32, H32.T_top + 1);
+    }
+  }
+  const LevelBC bcL = fold ? hom : phys[L];   // the finest level's operator on the iterate
+
   // ---- FMG sweep (Alg. 2) or the caller's initial guess
   double* pbar[16] = {nullptr};
   if (fas)
@@ -1392,7 +1416,7 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
       fmg_normed = S.fas_fmg(H64, pbar);
     } else if (!mixed) {
       // the finest level's FMG V-cycle takes the norm of its result when its up pass can
-      fmg_normed = S.fmg(H64, L == H64.T_top || S.march_on<double>(H64, L, phys[L]) ||
+      fmg_normed = S.fmg(H64, L == H64.T_top || S.march_on<double>(H64, L, bcL) ||
                                   (p->n < S.fused_min_n64 && S.tile_on<double>(H64, L)));
     } else {
       S.fmg(H32);
@@ -1403,8 +1427,8 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
   // on the fused path: taken by the head pass, which is also the first sweep of V-cycle 1
   // (of the FAS cycle 1 with the Full Approximation Scheme)
   const bool head_mode = !mixed && Lb < 0 && S.head_possible(H64);
-  if (head_mode) S.head(H64, phys[L]);
-  else if (!fmg_normed) S.defect_norm(phi, f64L, mixed ? H32.f[L] : nullptr, p->n, p->dx, phys[L]);
+  if (head_mode) S.head(H64, bcL);
+  else if (!fmg_normed) S.defect_norm(phi, f64L, mixed ? H32.f[L] : nullptr, p->n, p->dx, bcL);
   // the residual with every scalar (finiteness of rho and the face values), published as each
   // cycle's norm is
   unsigned long long want = 0, clock_fmg = 0;
@@ -1472,26 +1496,26 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
         // two-sweep up pass does)
         const bool normed = S.fas_cycle(H64, pbar, L, head_mode ? 1 : 0, !head_mode);
         S.head_done = false;
-        if (head_mode && cyc + 1 < ncyc) S.head(H64, phys[L]);
-        else if (!normed) S.defect_norm(phi, f64L, nullptr, p->n, p->dx, phys[L]);
+        if (head_mode && cyc + 1 < ncyc) S.head(H64, bcL);
+        else if (!normed) S.defect_norm(phi, f64L, nullptr, p->n, p->dx, bcL);
       } else if (head_mode) {
         // the rest of this V-cycle (its first sweep ran in the head pass), then the head of the
         // next one, which measures this cycle's result; after the last allowed cycle the
         // residual alone (a head's sweep would be discarded)
         S.head_done = true;
-        S.vcycle(H64, L, phys[L], true, false);
-        if (cyc + 1 < ncyc) S.head(H64, phys[L]);
-        else S.defect_norm(phi, f64L, nullptr, p->n, p->dx, phys[L]);
+        S.vcycle(H64, L, bcL, true, false);
+        if (cyc + 1 < ncyc) S.head(H64, bcL);
+        else S.defect_norm(phi, f64L, nullptr, p->n, p->dx, bcL);
       } else if (!mixed && Lb >= 0) {
-        if (!S.vcycle_blk(H64, L, phys[L], true)) S.defect_norm(phi, f64L, nullptr, p->n, p->dx, phys[L]);
+        if (!S.vcycle_blk(H64, L, bcL, true)) S.defect_norm(phi, f64L, nullptr, p->n, p->dx, bcL);
       } else if (mixed && Lb >= 0) {
         launch_zero(H32.u[L], n3 * sizeof(float), s);
         for (int k = 0; k < inner; ++k) S.vcycle_blk(H32, L, hom);
         launch_add_f32(phi, H32.u[L], n3, s);
-        S.defect_norm(phi, f64L, H32.f[L], p->n, p->dx, phys[L]);
+        S.defect_norm(phi, f64L, H32.f[L], p->n, p->dx, bcL);
       } else if (!mixed) {
-        const bool normed = S.vcycle(H64, L, phys[L], true, true);
-        if (!normed) S.defect_norm(phi, f64L, nullptr, p->n, p->dx, phys[L]);
+        const bool normed = S.vcycle(H64, L, bcL, true, true);
+        if (!normed) S.defect_norm(phi, f64L, nullptr, p->n, p->dx, bcL);
       } else {
         // defect correction: e32 solves L e = r32 from zero with homogeneous conditions
         if (L == H32.T_top) {
@@ -1508,12 +1532,12 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
         if (phi_oth) {
           // phi += e and the FP64 defect (with its FP32 copy and norm) in one streaming pass
           const int np = fused_mixed_update_defect(phi_cur, phi_oth, H32.u[L], f64L, H32.f[L], part, p->n, p->dx,
-                                                   phys[L], s);
+                                                   bcL, s);
           launch_sum_partials(np, S.norm_sink(), s);
           std::swap(phi_cur, phi_oth);
         } else {
           launch_add_f32(phi, H32.u[L], n3, s);
-          S.defect_norm(phi, f64L, H32.f[L], p->n, p->dx, phys[L]);
+          S.defect_norm(phi, f64L, H32.f[L], p->n, p->dx, bcL);
         }
       }
       // the next cycle's first leg is queued before this cycle's norm is read when that leg
@@ -1521,7 +1545,7 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
       // tolerance is still at least 4x past what this cycle reaches at the contraction seen so
       // far (had the solve stopped after all, that leg's results go unused)
       if (ahead_ok && cyc + 1 < ncyc && (p->fixed_cycles > 0 || 0.25 * rho_seen * r > p->tol))
-        (void)S.down_ahead(H64, phys[L]);
+        (void)S.down_ahead(H64, bcL);
       unsigned long long clock = 0;
       if (const int st = await_norm(c, scal, s, want, &d2, &clock); st != MG_OK) return st;
       clocks.push_back(clock);
@@ -2012,11 +2036,40 @@ bool op_march(const mg_ctx* c, int n, int sweeps, const LevelBC& b) {
   return true;
 }
 
-// The region-tile and streaming up passes take the coarse correction's ghosts from the face
-// kinds alone (homogeneous conditions, no face values).
+// Are there no face values (the conditions homogeneous)?
 bool hom_arrays_null(const LevelBC& b) {
   for (int f = 0; f < 6; ++f)
     if (b.b[f]) return false;
+  return true;
+}
+
+// The region-tile and streaming passes know homogeneous faces only, face values standing in f
+// (launch_fold_faces).  Operator scratch for such a pass on level n: its output *tmp and, when b has
+// values, a copy *f of the caller's source that holds them; *b is then homogeneous.  False without
+// an error: values and a context with a memory budget, whose scratch is not doubled for the copy,
+// or no memory for it -- the passes that read face arrays run instead.
+template <typename T>
+bool op_leg_scratch(mg_ctx* c, int n, double h, LevelBC* b, T** tmp, const T** f, hipStream_t s, int* st) {
+  const int L = ilog2(n);
+  const bool values = !hom_arrays_null(*b);
+  if (values && c->hbm_budget != 0) return false;
+  double* mem = nullptr;
+  *st = op_scratch(c, cells(L) * sizeof(T) * (values ? 2 : 1), &mem);
+  if (values && *st == MG_ERR_OOM) *st = MG_OK, mem = nullptr;
+  if (!mem) return false;
+  *tmp = reinterpret_cast<T*>(mem);
+  if (values) {
+    T* copy = *tmp + cells(L);
+    const hipError_t e = hipMemcpyAsync(copy, *f, cells(L) * sizeof(T), hipMemcpyDeviceToDevice, s);
+    if (e != hipSuccess) {
+      *st = fail(c, MG_ERR_DEVICE, hipGetErrorString(e));
+      return false;
+    }
+    const FoldLevel lv{copy, 1.0 / (h * h), L, 0, *b};
+    launch_fold_faces<T>(&lv, 1, s);
+    *f = copy;
+    for (int q = 0; q < 6; ++q) b->b[q] = nullptr;
+  }
   return true;
 }
 
@@ -2038,21 +2091,18 @@ int op_down(mg_ctx* c, int n, double h, double omega, int npre, const mg_level_b
   if (n < 2 || npre < 0 || npre > 4) return fail(c, MG_ERR_INVALID_ARG, "n >= 2, npre 0..4");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const LevelBC b = to_level_bc(bc);
-  if (op_march<T>(c, n, npre, b)) {
-    double* tmp = nullptr;
-    st = op_scratch(c, cells(ilog2(n)) * sizeof(T), &tmp);
+  const bool march = op_march<T>(c, n, npre, b);
+  if (march || op_tile<T>(c, n, npre)) {
+    LevelBC hb = b;
+    T* tmp = nullptr;
+    const T* fv = f;
+    if (op_leg_scratch<T>(c, n, h, &hb, &tmp, &fv, s, &st)) {
+      if (march) march_down<T>(u, tmp, fv, fc, uc, n, h, omega, hb, s);
+      else tile_down<T>(u, tmp, fv, fc, nullptr, uc, n, 0, npre, h, omega, hb, s);
+      HIP_CHECK(c, hipMemcpyAsync(u, tmp, cells(ilog2(n)) * sizeof(T), hipMemcpyDeviceToDevice, s));
+      return op_epilogue(c);
+    }
     if (st) return st;
-    march_down<T>(u, reinterpret_cast<T*>(tmp), f, fc, uc, n, h, omega, b, s);
-    HIP_CHECK(c, hipMemcpyAsync(u, tmp, cells(ilog2(n)) * sizeof(T), hipMemcpyDeviceToDevice, s));
-    return op_epilogue(c);
-  }
-  if (op_tile<T>(c, n, npre)) {
-    double* tmp = nullptr;
-    st = op_scratch(c, cells(ilog2(n)) * sizeof(T), &tmp);
-    if (st) return st;
-    tile_down<T>(u, reinterpret_cast<T*>(tmp), f, fc, nullptr, uc, n, 0, npre, h, omega, b, s);
-    HIP_CHECK(c, hipMemcpyAsync(u, tmp, cells(ilog2(n)) * sizeof(T), hipMemcpyDeviceToDevice, s));
-    return op_epilogue(c);
   }
   if (fused_supported<T>(n) && npre > 0) {
     double* tmp = nullptr;
@@ -2088,21 +2138,19 @@ int op_up(mg_ctx* c, int n, double h, double omega, int npost, const mg_level_bc
   if (n < 2 || npost < 0 || npost > 4) return fail(c, MG_ERR_INVALID_ARG, "n >= 2, npost 0..4");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const LevelBC b = to_level_bc(bc), bcc = to_level_bc(bc_coarse);
-  if (op_march<T>(c, n, npost, b) && hom_arrays_null(bcc)) {
-    double* tmp = nullptr;
-    st = op_scratch(c, cells(ilog2(n)) * sizeof(T), &tmp);
+  // (their ghosts of the coarse correction are homogeneous too)
+  const bool march = op_march<T>(c, n, npost, b);
+  if ((march || op_tile<T>(c, n, npost)) && hom_arrays_null(bcc)) {
+    LevelBC hb = b;
+    T* tmp = nullptr;
+    const T* fv = f;
+    if (op_leg_scratch<T>(c, n, h, &hb, &tmp, &fv, s, &st)) {
+      if (march) march_up<T>(u, tmp, fv, uc, bcc, nullptr, n, h, omega, hb, s);
+      else tile_up<T>(u, tmp, fv, uc, bcc, nullptr, n, 0, npost, h, omega, hb, s);
+      HIP_CHECK(c, hipMemcpyAsync(u, tmp, cells(ilog2(n)) * sizeof(T), hipMemcpyDeviceToDevice, s));
+      return op_epilogue(c);
+    }
     if (st) return st;
-    (void)march_up<T>(u, reinterpret_cast<T*>(tmp), f, uc, bcc, nullptr, n, h, omega, b, s);
-    HIP_CHECK(c, hipMemcpyAsync(u, tmp, cells(ilog2(n)) * sizeof(T), hipMemcpyDeviceToDevice, s));
-    return op_epilogue(c);
-  }
-  if (op_tile<T>(c, n, npost) && hom_arrays_null(bcc)) {
-    double* tmp = nullptr;
-    st = op_scratch(c, cells(ilog2(n)) * sizeof(T), &tmp);
-    if (st) return st;
-    (void)tile_up<T>(u, reinterpret_cast<T*>(tmp), f, uc, bcc, nullptr, n, 0, npost, h, omega, b, s);
-    HIP_CHECK(c, hipMemcpyAsync(u, tmp, cells(ilog2(n)) * sizeof(T), hipMemcpyDeviceToDevice, s));
-    return op_epilogue(c);
   }
   if (fused_supported<T>(n) && npost > 0) {
     double* tmp = nullptr;

@@ -725,6 +725,62 @@ void launch_faces(const double* const src[6], double* const* ext, int L, int bot
   }
 }
 
+// A ghost beyond a face with value b is 2 b - u: the u part is a factor of the cell's own value,
+// the 2 b part a constant of that cell's equation, so it can stand in f once and for all.  Doing
+// so here, once per solve, takes the face arrays out of every leg of every cycle: read there,
+// they cost the 64^3 legs 6 and 8 us of 16 and 20, the 128^3 legs 35 us a cycle, and the streaming
+// passes 2 KiB of LDS and their registers' slack.  Bound by the launch below 128^3 and by
+// the strided cells of the x faces above.
+struct FoldArgs {
+  FoldLevel l[16];
+  unsigned first[17];   // the first block of each level
+};
+
+template <typename T>
+__global__ void __launch_bounds__(kBlock) k_fold_faces(FoldArgs A) {
+  int lv = 0;
+  while (blockIdx.x >= A.first[lv + 1]) ++lv;
+  const FoldLevel& V = A.l[lv];
+  const int L = V.L, n = 1 << L;
+  const unsigned t = (blockIdx.x - A.first[lv]) * kBlock + threadIdx.x;
+  const int face = (int)(t >> (2 * L));
+  auto valued = [&](int f) { return bc_has_value(V.bc.kind[f]) && V.bc.b[f]; };
+  if (face >= 6 || !valued(face)) return;
+  const int t1 = (int)(t & (unsigned)(n - 1)), t2 = (int)((t >> L) & (unsigned)(n - 1)), axis = face >> 1;
+  int c[3];
+  c[axis] = face & 1 ? n - 1 : 0;
+  c[axis == 0 ? 1 : 0] = t1;
+  c[axis == 2 ? 1 : 2] = t2;
+  // a cell on several faces belongs to the first of them
+  double sum = face_b(V.bc, face, n, t1, t2);
+  for (int f = 0; f < 6; ++f) {
+    const int a = f >> 1;
+    if (f == face || !valued(f) || c[a] != (f & 1 ? n - 1 : 0)) continue;
+    if (f < face) return;
+    sum += face_b(V.bc, f, n, c[a == 0 ? 1 : 0], c[a == 2 ? 1 : 2]);
+  }
+  T* at = reinterpret_cast<T*>(V.f) + lidx(L, V.Lm, c[0], c[1], c[2]);
+  *at = (T)((double)*at - 2.0 * V.ih2 * sum);
+}
+
+template <typename T>
+void launch_fold_faces(const FoldLevel* levels, int count, hipStream_t s) {
+  FoldArgs A{};
+  bool any = false;
+  for (int q = 0; q < 16; ++q) {
+    unsigned blocks = 0;
+    if (q < count) {
+      A.l[q] = levels[q];
+      for (int f = 0; f < 6; ++f) any = any || (bc_has_value(levels[q].bc.kind[f]) && levels[q].bc.b[f]);
+      blocks = (unsigned)((((size_t)6 << (2 * levels[q].L)) + kBlock - 1) / kBlock);
+    }
+    A.first[q + 1] = A.first[q] + blocks;
+  }
+  if (any) hipLaunchKernelGGL(k_fold_faces<T>, dim3(A.first[count]), dim3(kBlock), 0, s, A);
+}
+template void launch_fold_faces<double>(const FoldLevel*, int, hipStream_t);
+template void launch_fold_faces<float>(const FoldLevel*, int, hipStream_t);
+
 // ------------------------------------------------------------------ clearing device memory
 
 // Zero `words` 8-byte words (a kernel rather than a memset node, so the clear is an ordinary

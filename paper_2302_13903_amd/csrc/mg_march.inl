@@ -31,11 +31,8 @@
 // stays at six planes.  Tiles overlap by a halo of 6 cells (5 stages of radius 1, rounded up to
 // even) and are recomputed, so tiles are independent and the result goes to another array.
 //
-// Non-periodic faces (Sec. 2.3.6): a ghost value is kappa * (the adjacent active cell's current
-// value) + beta, with kappa = +1, beta = 0 for a zero-gradient face and kappa = -1, beta = 2 b
-// for a fixed face.  beta enters only the stencil of that active cell, and there with the
-// weight of a neighbour, so it is folded into the cell's source as f - beta / h^2 when f is
-// loaded; what remains of the ghost is kappa times the cell's own current value:
+// Non-periodic faces (Sec. 2.3.6): face values stand in f (launch_fold_faces), so a ghost is kappa
+// times the adjacent active cell's current value, +1 at a zero-gradient face and -1 at a fixed one:
 //   x: the lane holding x = 0 (x = n-1) takes kappa * c in place of its left (right) neighbour;
 //   y: with 52-row output tiles and a halo of 6 the rows beyond y = 0 and y = n-1 are always
 //      rows 1 and 2 of the same lane as their active neighbour; before each stage the ghost
@@ -128,15 +125,10 @@ __device__ __forceinline__ T from_right(T v) {  // value of lane + 1
   return dpp_move<kDppWaveShl1, UNTIED>(v);
 }
 
-// Ghost rule of a face as ghost = kappa * adjacent + beta: zero gradient kappa = 1, beta = 0;
-// fixed (and multipole) kappa = -1, beta = 2 b at the face point (t1, t2).
+// Ghost rule of a face as ghost = kappa * adjacent: zero gradient 1, fixed (and multipole) -1.
 template <typename T>
 __device__ __forceinline__ T kappa_of(const LevelBC& bc, int face) {
   return bc.kind[face] == BC_ZERO_GRADIENT ? (T)1 : (T)-1;
-}
-template <typename T>
-__device__ __forceinline__ T beta_of(const LevelBC& bc, int face, int n, int t1, int t2) {
-  return bc.kind[face] == BC_ZERO_GRADIENT ? (T)0 : (T)(2.0 * face_b(bc, face, n, t1, t2));
 }
 
 template <typename T>
@@ -184,11 +176,6 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
   constexpr int HZ = DSTAGE ? 5 : 4;              // planes marched before (and after) the chunk
   __shared__ Pair<T> xch[2][NB][2][SL];
   __shared__ Pair<T> fl[kFSlots][R][NT];
-  // walls with face values: -beta / h^2 of the wall cells of the plane being loaded, added to
-  // their f when that plane's f is taken up at the end of the step (x walls: per band, side
-  // and row; y walls: per side, column and cell)
-  __shared__ T fdx[XYW ? NB : 1][2][R];
-  __shared__ T fdy[2][XYW ? SL : 1][2];
   // non-periodic: the red cells' partial defects carried to the next step (registers are short)
   __shared__ T dredl[PER ? 1 : R][PER ? 1 : NT];
 
@@ -308,9 +295,6 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
     const int wy0 = ys - kHalo + w * 2 * R, wy1 = wy0 + 2 * R - 1;
     const bool wave_x = XYW && !px && (xs - kHalo < 0 || xs - kHalo + kTX - 1 >= n);
     const bool wave_y = XYW && !py && (wy0 < 0 || wy1 >= n);
-    // fold beta of the walls with face values into f (fixed and multipole faces)
-    const bool fold_x = wave_x && (A.bc.b[0] || A.bc.b[1]);
-    const bool fold_y = wave_y && (A.bc.b[2] || A.bc.b[3]);
     const T kx0 = kappa_of<T>(A.bc, 0), kx1 = kappa_of<T>(A.bc, 1), ky0 = kappa_of<T>(A.bc, 2);
     const T ky1 = kappa_of<T>(A.bc, 3), kz0 = kappa_of<T>(A.bc, 4), kz1 = kappa_of<T>(A.bc, 5);
     // up: the coarse correction's rules (homogeneous conditions)
@@ -349,56 +333,12 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
     }
 
     // ---- loads of u on plane P (unless zero on input) and f on plane P-1 (the plane the red
-    // stage of the next step works on), beta of the walls folded into f; up: the coarse taps
+    // stage of the next step works on); up: the coarse taps
     // of plane P
     // cTAPS (up): 0 load both coarse planes of P, 1 (P odd) keep the upper plane of P-1 as the
     // lower one and load the upper, 2 (P even) keep the pair of P-1
     auto load_plane = [&](int P, auto cTAPS) __attribute__((always_inline)) {
       const int Pg = P & nm, Pfg = (P - 1) & nm;
-      if constexpr (XYW) {
-        // beta of the x and y walls (fixed and multipole faces) for this plane's f: loaded
-        // before u and f, so waiting for them does not wait for the plane, and parked in LDS
-        // until the f it belongs to is taken up; every lane loads (from a valid address) and
-        // keeps its value or zero
-        if (fold_x || fold_y) {
-          const T bw = -(T)2 * ih2;   // f - beta / h^2 with beta = 2 b
-          const size_t row = (size_t)(Pfg + 1) * (size_t)(n + 2);
-          const double* bxa = A.bc.b[0] ? A.bc.b[0] : A.bc.b[1];
-          const double* bxb = A.bc.b[1] ? A.bc.b[1] : A.bc.b[0];
-          const double* bya = A.bc.b[2] ? A.bc.b[2] : A.bc.b[3];
-          const double* byb = A.bc.b[3] ? A.bc.b[3] : A.bc.b[2];
-          const bool hx = (wx0 && A.bc.b[0]) || (wx1 && A.bc.b[1]);
-          const bool hy = (gy0 && A.bc.b[2]) || (gy1 && A.bc.b[3]);
-          const double* bxp = wx1 ? bxb : bxa;
-          const double* byp = gy1 ? byb : bya;
-          T dx[R], dy[2];
-#pragma unroll
-          for (int r = 0; r < R; ++r) dx[r] = (T)0;
-          dy[0] = dy[1] = (T)0;
-          if (fold_x) {
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-              const double v = bxp[row + (size_t)(ygv[r] + 1)];
-              dx[r] = hx ? bw * (T)v : (T)0;
-            }
-          }
-          if (fold_y) {
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-              const double v = byp[row + (size_t)(((xag + e) & nm) + 1)];
-              dy[e] = hy ? bw * (T)v : (T)0;
-            }
-          }
-          if (wx0 || wx1) {
-#pragma unroll
-            for (int r = 0; r < R; ++r) fdx[band][wx1 ? 1 : 0][r] = dx[r];
-          }
-          if (gy0 || gy1) {
-            fdy[gy1 ? 1 : 0][xl][0] = dy[0];
-            fdy[gy1 ? 1 : 0][xl][1] = dy[1];
-          }
-        }
-      }
       if constexpr (PER) {
         // (the range tests are trivially true here; written out, they keep the compiler's
         // register allocation of the periodic passes at its best)
@@ -430,21 +370,6 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
           }
           const Pair<T> vf = *reinterpret_cast<const Pair<T>*>(fin + fidr(r, Pfg));
           pf[r][0] = vf.a; pf[r][1] = vf.b;
-        }
-      }
-      if constexpr (!PER) {
-        // the z walls: beta on the first and last plane of the level (two planes per pass;
-        // loaded and applied at once)
-        if (!pz && (Pfg == 0 || Pfg == nm)) {
-          const double* bz = Pfg == 0 ? A.bc.b[4] : A.bc.b[5];
-          if (bz) {
-            const T bw = -(T)2 * ih2;
-#pragma unroll
-            for (int r = 0; r < R; ++r)
-#pragma unroll
-              for (int e = 0; e < 2; ++e)
-                pf[r][e] += bw * (T)bz[(size_t)(ygv[r] + 1) * (size_t)(n + 2) + (size_t)(((xag + e) & nm) + 1)];
-          }
         }
       }
       if constexpr (UP) {
@@ -500,28 +425,6 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
           for (int i = 0; i < NTAP; ++i) {
             pc[i][0] = pc[i][1];
             pc[i][1] = tap(i, zlo + 1);
-          }
-        }
-      }
-    };
-
-    // ---- the parked wall terms of the f just taken up into fr
-    auto fold_take = [&]() __attribute__((always_inline)) {
-      if constexpr (XYW) {
-        if (fold_x) {
-#pragma unroll
-          for (int r = 0; r < R; ++r) {
-            const T d0 = fdx[band][0][r], d1 = fdx[band][1][r];
-            fr[r][0] += wx0 ? d0 : (T)0;
-            fr[r][1] += wx1 ? d1 : (T)0;
-          }
-        }
-        if (fold_y) {
-#pragma unroll
-          for (int e = 0; e < 2; ++e) {
-            const T d0 = fdy[0][xl][e], d1 = fdy[1][xl][e];
-            fr[2][e] += gy0 ? d0 : (T)0;
-            fr[1][e] += gy1 ? d1 : (T)0;
           }
         }
       }
@@ -740,11 +643,6 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
       u[0][r][0] = pu[r][0]; u[0][r][1] = pu[r][1];
       fr[r][0] = pf[r][0]; fr[r][1] = pf[r][1];
     }
-    if constexpr (XYW) {
-      if (fold_x || fold_y) {
-        fold_take();
-      }
-    }
     // one pipeline step: the plane in ring slot K is P = zstart + t, t = g + K with g a
     // multiple of 6, so P - j sits in slot (K - j) mod 6, has parity (HZ + K + j) mod 2, and
     // its f is in LDS slot (K - HZ - j) mod 3 (z0 is a multiple of 6)
@@ -795,11 +693,6 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
           u[s5][r][0] = pu[r][0]; u[s5][r][1] = pu[r][1];
           fl[Fs4::value][r][tid] = Pair<T>{fr[r][0], fr[r][1]};
           fr[r][0] = pf[r][0]; fr[r][1] = pf[r][1];
-        }
-        if constexpr (XYW) {
-          if (fold_x || fold_y) {
-            fold_take();
-          }
         }
       }
     };

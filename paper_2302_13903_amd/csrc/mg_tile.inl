@@ -24,9 +24,8 @@
 // of f in every pass; u and f here cross once.)  Levels and times: see launch_leg.
 //
 // u += (omega/6) r with r = (neighbours - h^2 f) - (6 - kappa) u = -h^2 times the defect, kappa
-// the ghosts' factors on the cell's own value; a face value b enters the source of the cell at
-// the face (f - 2b/h^2); cells outside the domain hold zero and are not updated (weight zero).  The up leg first stages
-// the coarse correction under the tile (homogeneous ghosts: periodic wrap, or the boundary cell
+// the ghosts' factors on the cell's own value (face values stand in f: launch_fold_faces); cells
+// outside the domain hold zero and are not updated (weight zero).  The up leg first stages the coarse correction under the tile (homogeneous ghosts: periodic wrap, or the boundary cell
 // with the face's sign).  The level may be dense or in the MeshBlock layout (the same code with
 // the block-major index, whose x, y and z parts are disjoint bits; the coarse side of the lowest
 // block level is the dense root grid).
@@ -250,46 +249,6 @@ __global__ void __launch_bounds__(tile_threads(NS, SH), SH == 0 ? 4 : 1) k_tile_
     fR[q] = p ? f0 : f1;
     fB[q] = p ? f1 : f0;
   }
-  if (WALLS) {
-    // face values enter the sources of the cells they touch
-    bool valued = false;
-#pragma unroll
-    for (int f = 0; f < 6; ++f) valued = valued || (bc_has_value(A.bc.kind[f]) && A.bc.b[f]);
-    if (valued && in) {
-      auto add = [&](int q, bool up, double v) __attribute__((always_inline)) {
-        const T t = (T)(-2.0 * A.ih2 * v);
-        fR[q] += p != up ? t : (T)0;   // the upper cell of a slot is red where p is false
-        fB[q] += p == up ? t : (T)0;
-      };
-      const int gi = ox - H + tx, gj = oy - H + ty;
-      int fx = -1, fy = -1;
-      if (!(per & 1)) fx = gi == 0 ? 0 : gi == nm ? 1 : -1;
-      if (!(per & 2)) fy = gj == 0 ? 2 : gj == nm ? 3 : -1;
-      const bool vx = fx >= 0 && bc_has_value(fx == 0 ? A.bc.kind[0] : A.bc.kind[1]);
-      const bool vy = fy >= 0 && bc_has_value(fy == 2 ? A.bc.kind[2] : A.bc.kind[3]);
-      const double* bx = vx ? (fx == 0 ? A.bc.b[0] : A.bc.b[1]) : nullptr;
-      const double* by = vy ? (fy == 2 ? A.bc.b[2] : A.bc.b[3]) : nullptr;
-      auto along_z = [&](const double* e) __attribute__((always_inline)) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q)
-#pragma unroll
-          for (int s = 0; s < 2; ++s) {
-            const int k = oz - H + 2 * q + s;
-            const double v = e[(size_t)((k & nm) + 1) * (size_t)(n + 2)];
-            add(q, s != 0, (per & 4) || (unsigned)k < (unsigned)n ? v : 0.0);
-          }
-      };
-      if (bx) along_z(bx + (j + 1));
-      if (by) along_z(by + (i + 1));
-      const size_t fz = (size_t)(j + 1) * (size_t)(n + 2) + (size_t)(i + 1);
-      const bool v4 = bc_has_value(A.bc.kind[4]) && A.bc.b[4], v5 = bc_has_value(A.bc.kind[5]) && A.bc.b[5];
-      if (zlo && v4) add(QL, true, A.bc.b[4][fz]);
-      if (zhi && v5) add(QH, false, A.bc.b[5][fz]);
-      if (NARROW && zlo2 && v4) add(0, true, A.bc.b[4][fz]);
-      if (NARROW && zhi2 && v5) add(NQ - 1, false, A.bc.b[5][fz]);
-    }
-  }
-
   if constexpr (UP) {
     // ---- u += trilinear prolongation (weights 3/4, 1/4 per axis).  The tile starts at an odd
     // fine cell, so tile coordinates 2a and 2a + 1 lie between coarse cells a and a + 1

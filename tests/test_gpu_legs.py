@@ -116,3 +116,26 @@ def test_blocks_one_sweep(mg, npre, npost):
     a, _, _ = mg.solve(dev(rho), 1.0 / n, "fixed", fixed_cycles=4, npre=npre, npost=npost)
     b, _, _ = mg.solve(mg.to_blocks(dev(rho), 16), 1.0 / n, "fixed", fixed_cycles=4, npre=npre, npost=npost, layout="blocks")
     assert rel(host(mg.from_blocks(b, n, 16)), host(a)) < 1e-12
+
+
+@pytest.mark.parametrize("f32", [False, True], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("n", [32, 256])
+def test_legs_with_face_values_under_a_budget(mg, n, f32):
+    """Face values reach a leg through a copy of the source, which a context with a memory budget
+    does not take: both ways give the same leg (bounds as above, each side's error counted)."""
+    kinds = KINDS["mixed"]
+    rng = np.random.default_rng(n)
+    dt, h = (torch.float32 if f32 else torch.float64), 1.0 / n
+    u, f = dev(rng.standard_normal((n,) * 3), dt), dev(rng.standard_normal((n,) * 3) * n * n, dt)
+    bext = [dev(rng.standard_normal((n + 2,) * 2)) if k == FIXED else None for k in kinds]
+    size = (4 if f32 else 8) * n ** 3
+    out = []
+    for ctx in (mg.Context(0), mg.Context(0, hbm_budget=(64 << 20) + size + size // 2)):
+        print(f"valued legs n={n} f32={f32}", flush=True)
+        a, fc, uc = u.clone(), torch.empty((n // 2,) * 3, dtype=dt, device="cuda:0"), torch.empty((n // 2,) * 3, dtype=dt, device="cuda:0")
+        (mg.mg_op_down_f32 if f32 else mg.mg_op_down)(a, f, fc, uc, h, OMEGA, 2, kinds, bext, ctx=ctx)
+        out.append((host(a), host(fc)))
+    eps = 40 * float(np.finfo(np.float32).eps) if f32 else 1e-13
+    su = max(float(u.abs().max()), h * h * float(f.abs().max())) + 2 * max(float(b.abs().max()) for b in bext if b is not None)
+    assert np.abs(out[0][0] - out[1][0]).max() <= 2 * eps * 6 * su
+    assert np.abs(out[0][1] - out[1][1]).max() <= 2 * eps * (float(f.abs().max()) + 12 * su / h ** 2)
