@@ -378,7 +378,8 @@ struct Solver {
       march_down<T>(zin ? nullptr : H.u[l], H.u2[l], H.f[l], H.f[l - 1], H.u[l - 1], n, H.h[l], H.omega, bc, s, 0,
                     aux_of());
       // algorithmic bytes: u and f read, u written, coarse source and correction written
-      if (timed) kernel_end(march_name<T>(false, false, bc), 3 * cellsT + cellsT / 4);
+      if (timed)
+        kernel_end(zin ? march_down1_name<T>(true, bc) : march_name<T>(false, false, bc), 3 * cellsT + cellsT / 4);
     } else {
       tile_down<T>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], nullptr, H.u[l - 1], n, 0, H.npre, H.h[l], H.omega, bc, s);
       if (timed) kernel_end(tile_name<T>(H.npre, false, bc, n), 3 * cellsT + cellsT / 4);
@@ -807,7 +808,7 @@ struct Solver {
       if (timed) kernel_begin(true);
       march_down_fas<double>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], pbar[l - 1], H.u[l - 1], n, H.h[l], H.omega, bc, s);
       // algorithmic bytes: u and f read, u written, three coarse arrays written
-      if (timed) kernel_end(march_fas_name<double>(bc), 3 * cellsT + 3 * cellsT / 8);
+      if (timed) kernel_end(march_down1_name<double>(false, bc), 3 * cellsT + 3 * cellsT / 8);
       launch_fas_source(pbar[l - 1], H.f[l - 1], n / 2, H.h[l - 1], H.hom, s);               // 5
       fas_cycle(H, pbar, l - 1);                                                             // 6
       launch_fas_correction(H.u[l - 1], pbar[l - 1], cells(l - 1), s);                       // 7

@@ -24,7 +24,7 @@ struct MarchAux {
 
 // Down step of a V-cycle level (Alg. 1 steps 1-3) in one pass: two smoothing sweeps of u, the
 // defect of the result restricted into fc, and the coarse correction uc0 cleared.
-// uin == nullptr: u is zero on input and is not read.
+// uin == nullptr (Lm = 0 only): u is zero on input and is not read.
 // Lm > 0: the level is in the MeshBlock layout with blocks of 2^Lm cells per side (the coarse
 // level below in the layout with blocks of 2^(Lm-1), or the dense root grid when Lm = 1).
 template <typename T>
@@ -46,7 +46,7 @@ void march_down_fas(const T* uin, T* uout, const T* f, T* fc, T* pbar, T* uc0, i
                     const LevelBC& bc, hipStream_t s);
 
 template <typename T>
-std::string march_fas_name(const LevelBC& bc);
+std::string march_down1_name(bool zero, const LevelBC& bc);   // FAS, or from zero
 
 // Names of the kernels as the profiler lists them (the wall form follows bc's kinds; blk:
 // MeshBlock layout).

@@ -22,8 +22,21 @@
 // even, chunks start at multiples of 6 and the ring has 6 planes, so the parity of the plane a
 // stage works on, and which cell of a lane's x-pair is red in each row, are template constants.
 // A stage then updates exactly one cell per row with no operand selection: two cross-lane moves
-// (DPP wave shifts) for the x-neighbour, in-lane rows or one LDS exchange of the band-edge rows
+// (DPP wave shifts) for the x-neighbour, in-lane rows or an LDS exchange of the band-edge rows
 // for y, ring planes for z.
+//
+// What bounds it: HBM at 512^3 (3.5 GB a leg at 4.2 TB/s), at 256^3 and below the step's chain of
+// LDS, barriers and dependent FP64 operations with two waves per SIMD.  Hence
+//  * one barrier for the four sweep stages: the y neighbours a stage reads beyond its band have
+//    the colour that no stage of this step changes on that plane, so all four stages' edge rows go
+//    out at the step's start, and the inner rows are done while they travel (the defect stage's
+//    red cells need one more);
+//  * no branch around a load or its take-up, and the step's stores after the take-up: loads and
+//    stores complete in one order, so a wait for loads behind stores, or at a join of paths, waits
+//    for the stores to reach memory.
+// Measured with five barriers and stores before the take-up, and now (us per leg down / up):
+// 128^3 39 / 34 -> 32 / 32; V-cycles at 256^3 386 -> 351 periodic, 451 -> 394 between z walls,
+// 522 -> 488 fixed; at 512^3 2285 -> 2070 and 2610 -> 2444 (periodic equal, at 2000).
 //
 // The defect stage needs the final state of both neighbouring planes.  Black cells of P-4 have
 // only red neighbours, final after red sweep 2; red cells of P-4 get their in-plane and lower
@@ -37,9 +50,10 @@
 //   y: with 52-row output tiles and a halo of 6 the rows beyond y = 0 and y = n-1 are always
 //      rows 1 and 2 of the same lane as their active neighbour; before each stage the ghost
 //      cells the stage reads are set to kappa times that neighbour (in-lane);
-//   z: the ring plane beyond z = 0 or z = n-1 is set the same way before a stage on the
-//      boundary plane.
-// Cells outside the domain are loaded from their periodic image (every address in range, no
+//   z: planes outside are zero and stay so (their updates have weight zero), and on the first
+//      and last plane the factor of the cell's own value is 6 - kappa (uniform: no instruction
+//      more than inside).
+// Cells outside in x or y are loaded from their periodic image (every address in range, no
 // predicated loads) and swept like the others; no active cell reads them.  The coarse
 // correction's taps (homogeneous conditions) are clamped to the domain with the sign of each
 // face's rule.
@@ -77,7 +91,6 @@ struct MarchArgs {
   LevelBC bcc;       // up: coarse level (homogeneous)
   int n, L, xo, yo, zc, tiles_x, tiles_y, ntiles;
   int set;           // tiles of this launch: 0 all, 1 the interior ones, 2 the ring at the walls
-  int zero_in;
   int Lm;            // BLK: log2 of the MeshBlock side on this level (the coarse level: Lm - 1)
   double h2, ih2, omega;
 };
@@ -92,43 +105,46 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // Whole-wave shift by one lane through DPP: wave_shr:1 gives lane i the value of lane i-1,
-// wave_shl:1 the value of lane i+1.  UNTIED: lanes without a source read zero (bound control),
-// which leaves the destination untied from the source (no copy before each move; used by the
-// all-periodic passes); otherwise they keep their own value (the non-periodic passes, whose
-// register allocation fares better with it).  Those lanes, and the edge lanes of each
-// half-wave, hold the outermost columns of a tile, inside its halo.
+// wave_shl:1 the value of lane i+1.  Lanes without a source read zero (bound control), which leaves
+// the destination untied from the source (no copy before each move).  Those lanes, and the edge
+// lanes of each half-wave, hold the outermost columns of a tile, inside its halo.
 constexpr int kDppWaveShr1 = 0x138;
 constexpr int kDppWaveShl1 = 0x130;
 
-template <int CTRL, bool UNTIED>
-__device__ __forceinline__ int dpp_move32(int v) {
-  if constexpr (UNTIED) return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
-  else return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false);
-}
-template <int CTRL, bool UNTIED>
+template <int CTRL>
 __device__ __forceinline__ float dpp_move(float v) {
-  return __builtin_bit_cast(float, dpp_move32<CTRL, UNTIED>(__builtin_bit_cast(int, v)));
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
 }
-template <int CTRL, bool UNTIED>
+template <int CTRL>
 __device__ __forceinline__ double dpp_move(double v) {
   const long long b = __builtin_bit_cast(long long, v);
-  const int lo2 = dpp_move32<CTRL, UNTIED>((int)(b & 0xffffffffLL));
-  const int hi2 = dpp_move32<CTRL, UNTIED>((int)(b >> 32));
+  const int lo2 = __builtin_amdgcn_mov_dpp((int)(b & 0xffffffffLL), CTRL, 0xf, 0xf, true);
+  const int hi2 = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
   return __builtin_bit_cast(double, ((long long)hi2 << 32) | (long long)(unsigned)lo2);
 }
-template <bool UNTIED, typename T>
+template <typename T>
 __device__ __forceinline__ T from_left(T v) {   // value of lane - 1
-  return dpp_move<kDppWaveShr1, UNTIED>(v);
+  return dpp_move<kDppWaveShr1>(v);
 }
-template <bool UNTIED, typename T>
+template <typename T>
 __device__ __forceinline__ T from_right(T v) {  // value of lane + 1
-  return dpp_move<kDppWaveShl1, UNTIED>(v);
+  return dpp_move<kDppWaveShl1>(v);
 }
 
 // Ghost rule of a face as ghost = kappa * adjacent: zero gradient 1, fixed (and multipole) -1.
 template <typename T>
 __device__ __forceinline__ T kappa_of(const LevelBC& bc, int face) {
   return bc.kind[face] == BC_ZERO_GRADIENT ? (T)1 : (T)-1;
+}
+
+// The 2 x 8 values are in registers here, the loads that made them complete.
+template <typename T>
+__device__ __forceinline__ void arrived(const T (&a)[kR][2], const T (&b)[kR][2]) {
+  static_assert(kR == 4, "four rows");
+  asm volatile("" ::"v"(a[0][0]), "v"(a[0][1]), "v"(a[1][0]), "v"(a[1][1]), "v"(a[2][0]), "v"(a[2][1]), "v"(a[3][0]),
+               "v"(a[3][1]), "v"(b[0][0]), "v"(b[0][1]), "v"(b[1][0]), "v"(b[1][1]), "v"(b[2][0]), "v"(b[2][1]),
+               "v"(b[3][0]), "v"(b[3][1])
+               : "memory");
 }
 
 template <typename T>
@@ -159,14 +175,15 @@ constexpr int cfg_W() {
 
 // WALLS: 0 = every face of the level is periodic (no boundary code compiled in); 1 = walls
 // only across z (x and y periodic, or a tile that reaches no x or y wall with its halo: no x/y
-// wall code compiled in); 2 = walls on any axis.  The launcher picks per tile.  BLK: the level is in the MeshBlock layout (blocks of 2^A.Lm cells, Morton order);
+// wall code compiled in); 2 = walls on any axis.  The launcher picks per tile.  ZIN: u is zero on
+// input and not read.  BLK: the level is in the MeshBlock layout (blocks of 2^A.Lm cells, Morton order);
 // the tile streams across block boundaries as across a dense array (an x-pair never straddles
 // two blocks), and the coarse level is in the layout below (blocks of 2^(A.Lm-1) cells, or the
 // dense root grid when that is one cell).
 // FAS (down only, Alg. 3 steps 2-4): the restriction also writes the restricted potential
 // phibar (mean of the 8 children of the pass's result) into A.pbar and starts the coarse level
 // from it (uc0 = phibar instead of 0).
-template <typename T, int W, bool UP, bool NORM, int WALLS, bool BLK, bool FAS>
+template <typename T, int W, bool UP, bool NORM, int WALLS, bool BLK, bool FAS, bool ZIN>
 __device__ __forceinline__ void march_body(const MarchArgs& A) {
   constexpr bool PER = WALLS == 0;                // every face periodic
   constexpr bool XYW = WALLS == 2;                // x or y walls may be in reach
@@ -174,9 +191,10 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
   constexpr bool DEF = !UP;                       // down: restricted defect
   constexpr bool DSTAGE = DEF || NORM;            // a defect stage after the sweeps
   constexpr int HZ = DSTAGE ? 5 : 4;              // planes marched before (and after) the chunk
-  __shared__ Pair<T> xch[2][NB][2][SL];
+  __shared__ T xe[4][NB][2][SL];                  // per stage: the bands' first and last rows
+  __shared__ T xd[DSTAGE ? NB : 1][2][SL];        // the same of the defect stage's black cells
   __shared__ Pair<T> fl[kFSlots][R][NT];
-  // non-periodic: the red cells' partial defects carried to the next step (registers are short)
+  // the red cells' partial defects carried to the next step, where registers are short
   __shared__ T dredl[PER ? 1 : R][PER ? 1 : NT];
 
   const int tid = threadIdx.x;
@@ -238,9 +256,9 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
     const int xag = xa & nm;
     const bool out_x = xa >= xs && xa < xs + A.xo && xa < n;
     // the lane whose even cell is x = 0, whose odd cell is x = n-1 (beside a wall)
-    const bool wx0 = XYW && !px && xa == 0;
+    [[maybe_unused]] const bool wx0 = XYW && !px && xa == 0;
     [[maybe_unused]] const bool in_x = px || (xa >= 0 && xa < n);
-    const bool wx1 = XYW && !px && xa == n - 2;
+    [[maybe_unused]] const bool wx1 = XYW && !px && xa == n - 2;
 
     const int ys = ty * A.yo;                    // first output row (even)
     int yv[R], ygv[R];
@@ -289,14 +307,26 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
     const int nsteps = (zend - z0) + 2 * HZ;
     // rows 1 and 2 of this lane are the ghost row beyond y = 0 and its active neighbour, or the
     // active row y = n-1 and the ghost beyond it
+    const T kx0 = kappa_of<T>(A.bc, 0), kx1 = kappa_of<T>(A.bc, 1), ky0 = kappa_of<T>(A.bc, 2);
+    const T ky1 = kappa_of<T>(A.bc, 3);
     const bool gy0 = XYW && !py && yv[1] == -1;
     const bool gy1 = XYW && !py && yv[2] == n;
-    // does any cell of this wave sit beside a wall in x or y?
+    // does any cell of this wave sit beside a wall in y?
     const int wy0 = ys - kHalo + w * 2 * R, wy1 = wy0 + 2 * R - 1;
-    const bool wave_x = XYW && !px && (xs - kHalo < 0 || xs - kHalo + kTX - 1 >= n);
     const bool wave_y = XYW && !py && (wy0 < 0 || wy1 >= n);
-    const T kx0 = kappa_of<T>(A.bc, 0), kx1 = kappa_of<T>(A.bc, 1), ky0 = kappa_of<T>(A.bc, 2);
-    const T ky1 = kappa_of<T>(A.bc, 3), kz0 = kappa_of<T>(A.bc, 4), kz1 = kappa_of<T>(A.bc, 5);
+    // plane p: 6 less the z walls' factors, and the weight of an update (0 outside the domain)
+    struct PlaneW {
+      T c6, wz;
+    };
+    const T w6 = omega * inv6;
+    auto plane_w = [&](int p) __attribute__((always_inline)) {
+      PlaneW v;
+      v.c6 = (T)6;
+      if (!pz && p == 0) v.c6 -= kappa_of<T>(A.bc, 4);
+      if (!pz && p == nm) v.c6 -= kappa_of<T>(A.bc, 5);
+      v.wz = pz || (unsigned)p < (unsigned)n ? w6 : (T)0;
+      return v;
+    };
     // up: the coarse correction's rules (homogeneous conditions)
     const T kcx0 = kappa_of<T>(A.bcc, 0), kcx1 = kappa_of<T>(A.bcc, 1), kcy0 = kappa_of<T>(A.bcc, 2);
     const T kcy1 = kappa_of<T>(A.bcc, 3), kcz0 = kappa_of<T>(A.bcc, 4), kcz1 = kappa_of<T>(A.bcc, 5);
@@ -304,8 +334,7 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
     T u[kRing][R][2];
     T pu[R][2], pf[R][2];      // prefetched u of plane P+1 and f of plane P
     T fr[R][2];                // f of plane P-1
-    T dred[PER ? R : 1];       // red cells' partial defects of plane P-4 (completed next step)
-    // (non-periodic: in LDS)
+    T dred[PER ? R : 1];      // red cells' partial defects of plane P-4 (completed next step)
     auto dred_get = [&](int r) __attribute__((always_inline)) -> T { return PER ? dred[PER ? r : 0] : dredl[PER ? 0 : r][PER ? 0 : tid]; };
     auto dred_set = [&](int r, T v) __attribute__((always_inline)) {
       if constexpr (PER) dred[r] = v;
@@ -332,6 +361,18 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
       for (int j = 0; j < R / 2; ++j) stash_u[j] = (T)0;
     }
 
+    // u of plane P as loaded (and corrected): zero outside the domain
+    auto keep_in = [&](int P) __attribute__((always_inline)) {
+      if constexpr (!PER) {
+        const bool in_z = pz || (unsigned)P < (unsigned)n;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          pu[r][0] = in_z ? pu[r][0] : (T)0;
+          pu[r][1] = in_z ? pu[r][1] : (T)0;
+        }
+      }
+    };
+
     // ---- loads of u on plane P (unless zero on input) and f on plane P-1 (the plane the red
     // stage of the next step works on); up: the coarse taps
     // of plane P
@@ -339,38 +380,17 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
     // lower one and load the upper, 2 (P even) keep the pair of P-1
     auto load_plane = [&](int P, auto cTAPS) __attribute__((always_inline)) {
       const int Pg = P & nm, Pfg = (P - 1) & nm;
-      if constexpr (PER) {
-        // (the range tests are trivially true here; written out, they keep the compiler's
-        // register allocation of the periodic passes at its best)
-        const bool in_z = pz || (P >= 0 && P < n);
-        const bool in_zf = pz || (P - 1 >= 0 && P - 1 < n);
+      // no branch around a load: at a join the waits on it would turn conservative
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          if (in_x && in_y[r] && in_z && !A.zero_in) {
-            const Pair<T> vu = *reinterpret_cast<const Pair<T>*>(uin + fidr(r, Pg));
-            pu[r][0] = vu.a; pu[r][1] = vu.b;
-          } else {
-            pu[r][0] = pu[r][1] = (T)0;
-          }
-          if (in_x && in_y[r] && in_zf) {
-            const Pair<T> vf = *reinterpret_cast<const Pair<T>*>(fin + fidr(r, Pfg));
-            pf[r][0] = vf.a; pf[r][1] = vf.b;
-          } else {
-            pf[r][0] = pf[r][1] = (T)0;
-          }
+      for (int r = 0; r < R; ++r) {
+        if constexpr (!ZIN) {
+          const Pair<T> vu = *reinterpret_cast<const Pair<T>*>(uin + fidr(r, Pg));
+          pu[r][0] = vu.a; pu[r][1] = vu.b;
+        } else {
+          pu[r][0] = pu[r][1] = (T)0;
         }
-      } else {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          if (!A.zero_in) {
-            const Pair<T> vu = *reinterpret_cast<const Pair<T>*>(uin + fidr(r, Pg));
-            pu[r][0] = vu.a; pu[r][1] = vu.b;
-          } else {
-            pu[r][0] = pu[r][1] = (T)0;
-          }
-          const Pair<T> vf = *reinterpret_cast<const Pair<T>*>(fin + fidr(r, Pfg));
-          pf[r][0] = vf.a; pf[r][1] = vf.b;
-        }
+        const Pair<T> vf = *reinterpret_cast<const Pair<T>*>(fin + fidr(r, Pfg));
+        pf[r][0] = vf.a; pf[r][1] = vf.b;
       }
       if constexpr (UP) {
         // Trilinear prolongation (weights 1/4, 3/4 per axis) of the coarse correction: the
@@ -442,21 +462,18 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
         for (int r = 0; r < R; ++r) {
           const int j = r >> 1;
           const T c = (r & 1) ? (T)0.75 * czv[j + 1] + (T)0.25 * czv[j + 2] : (T)0.25 * czv[j] + (T)0.75 * czv[j + 1];
-          const T cl = from_left<PER>(c), cr = from_right<PER>(c);
+          const T cl = from_left(c), cr = from_right(c);
           pu[r][0] += (T)0.25 * cl + (T)0.75 * c;
           pu[r][1] += (T)0.75 * c + (T)0.25 * cr;
         }
       }
     };
 
-    int xbuf = 0;
-
-    // ---- ghost cells read by the active cells of colour COL (0 red, 1 black, 2 both) of plane p
-    // (parity PAR, in uc; the planes beside it in um, up): y ghost rows and z ghost planes set
-    // to kappa times those cells' current values (x walls are taken in the stencil)
-    auto refresh = [&](auto cCOL, auto cPAR, T (&um)[R][2], T (&uc)[R][2], T (&up)[R][2], int p)
-                       __attribute__((always_inline)) {
-      if constexpr (!PER) {
+    // ---- y walls: the ghost cells read by the active cells of colour COL (0 red, 1 black, 2
+    // both) of the plane in uc (parity PAR), set to kappa times those cells' current values
+    // (x walls are taken in the stencil)
+    auto refresh = [&](auto cCOL, auto cPAR, T (&uc)[R][2]) __attribute__((always_inline)) {
+      if constexpr (XYW) {
         constexpr int COL = decltype(cCOL)::value, PAR = decltype(cPAR)::value;
         // does cell e of row r have a colour being refreshed?
         auto sel = [](int r, int e) constexpr { return COL == 2 || ((r + PAR + COL) & 1) == e; };
@@ -469,67 +486,61 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
               if (gy1) uc[2][e] = ky1 * uc[1][e];
           });
         }
-        // (two separate blocks: a store through a pointer chosen between the two ring planes
-        // would move the ring out of registers)
-        if (!pz && p == 0) {
-          static_for<R>([&](auto rr) __attribute__((always_inline)) {
-            constexpr int r = decltype(rr)::value;
-            static_for<2>([&](auto ee) __attribute__((always_inline)) {
-              constexpr int e = decltype(ee)::value;
-              if constexpr (sel(r, e)) um[r][e] = kz0 * uc[r][e];
-            });
-          });
-        }
-        if (!pz && p == nm) {
-          static_for<R>([&](auto rr) __attribute__((always_inline)) {
-            constexpr int r = decltype(rr)::value;
-            static_for<2>([&](auto ee) __attribute__((always_inline)) {
-              constexpr int e = decltype(ee)::value;
-              if constexpr (sel(r, e)) up[r][e] = kz1 * uc[r][e];
-            });
-          });
-        }
       }
     };
 
-    // ---- one colour C (0 red, 1 black) of the RB-SOR update (eqs. rbsor1-2) on plane p of
-    // parity PAR held in uc, its z-neighbour planes in um (p-1) and up (p+1); f from the
-    // registers (FS < 0) or LDS slot FS
-    auto colour = [&](auto cC, auto cPAR, auto cFS, T (&um)[R][2], T (&uc)[R][2], T (&up)[R][2],
-                      int p) __attribute__((always_inline)) {
-      constexpr int C = decltype(cC)::value, PAR = decltype(cPAR)::value, FS = decltype(cFS)::value;
-      refresh(cC, cPAR, um, uc, up, p);
-      // the band-edge rows' cells of the other colour, for the bands below and above
+    // ---- the y neighbours of a band's first and last rows, of the stage on plane P - 1 - S: cells of
+    // the other colour, which no stage of this step changes (S = 0: as loaded; else set a step
+    // ago), so all four stages' rows go out at the step's start under one barrier
+    auto edges_out = [&](auto cS, auto cPAR, T (&uc)[R][2]) __attribute__((always_inline)) {
+      constexpr int S = decltype(cS)::value, PAR = decltype(cPAR)::value, C = S & 1;
       constexpr int q0 = (PAR + C) & 1, qL = (R - 1 + PAR + C) & 1;
-      T* xt = reinterpret_cast<T*>(&xch[xbuf][0][0][0]);
-      xt[(band * 2 + 0) * SL + xl] = uc[0][q0 ^ 1];
-      xt[(band * 2 + 1) * SL + xl] = uc[R - 1][qL ^ 1];
-      __syncthreads();
-      const T below = xt[((band > 0 ? band - 1 : band) * 2 + 1) * SL + xl];
-      const T above = xt[((band < NB - 1 ? band + 1 : band) * 2 + 0) * SL + xl];
-      xbuf ^= 1;
+      xe[S][band][0][xl] = uc[0][q0 ^ 1];
+      xe[S][band][1][xl] = uc[R - 1][qL ^ 1];
+    };
+    const int bandb = band > 0 ? band - 1 : band, banda = band < NB - 1 ? band + 1 : band;
+
+    // ---- stage S: one colour (red for even S, else black) of the RB-SOR update (eqs. rbsor1-2) on
+    // plane p of parity PAR held in uc, its z-neighbour planes in um (p-1) and up (p+1); f from
+    // the registers (FS < 0) or LDS slot FS.  INNER: the rows whose y neighbours are this
+    // lane's, else the band's first and last row
+    auto colour = [&](auto cS, auto cPAR, auto cFS, auto cIN, T (&um)[R][2], T (&uc)[R][2], T (&up)[R][2],
+                      int p) __attribute__((always_inline)) {
+      constexpr int S = decltype(cS)::value, C = S & 1, PAR = decltype(cPAR)::value, FS = decltype(cFS)::value;
+      constexpr bool INNER = decltype(cIN)::value;
+      T below = (T)0, above = (T)0;
+      if constexpr (INNER) {
+        refresh(std::integral_constant<int, C>{}, cPAR, uc);
+      } else {
+        below = xe[S][bandb][1][xl];
+        above = xe[S][banda][0][xl];
+      }
+      [[maybe_unused]] const PlaneW pw = plane_w(p);
       static_for<R>([&](auto rr) __attribute__((always_inline)) {
         constexpr int r = decltype(rr)::value;
-        constexpr int q = (r + PAR + C) & 1;      // the cell of this colour in row r
-        const T c = uc[r][q];
-        T xm, xp, ym, yp;
-        if constexpr (q == 0) {
-          xm = from_left<PER>(uc[r][1]);
-          xp = uc[r][1];
-          if constexpr (XYW) xm = wx0 ? kx0 * c : xm;
-        } else {
-          xm = uc[r][0];
-          xp = from_right<PER>(uc[r][0]);
-          if constexpr (XYW) xp = wx1 ? kx1 * c : xp;
+        if constexpr (INNER == (r > 0 && r < R - 1)) {
+          constexpr int q = (r + PAR + C) & 1;      // the cell of this colour in row r
+          const T c = uc[r][q];
+          T xm, xp, ym, yp;
+          if constexpr (q == 0) {
+            xm = from_left(uc[r][1]);
+            xp = uc[r][1];
+            if constexpr (XYW) xm = wx0 ? kx0 * c : xm;
+          } else {
+            xm = uc[r][0];
+            xp = from_right(uc[r][0]);
+            if constexpr (XYW) xp = wx1 ? kx1 * c : xp;
+          }
+          if constexpr (r > 0) ym = uc[r - 1][q]; else ym = below;
+          if constexpr (r < R - 1) yp = uc[r + 1][q]; else yp = above;
+          const T zm = um[r][q], zp = up[r][q];
+          T fv;
+          if constexpr (FS < 0) fv = fr[r][q];
+          else fv = q ? fl[FS][r][tid].b : fl[FS][r][tid].a;
+          const T nbs = ((((xm + xp) + ym) + yp) + zm) + zp;
+          if constexpr (PER) uc[r][q] = c + omega * ((nbs - h2 * fv) * inv6 - c);
+          else uc[r][q] = c + pw.wz * ((nbs - h2 * fv) - pw.c6 * c);
         }
-        if constexpr (r > 0) ym = uc[r - 1][q]; else ym = below;
-        if constexpr (r < R - 1) yp = uc[r + 1][q]; else yp = above;
-        const T zm = um[r][q], zp = up[r][q];
-        T fv;
-        if constexpr (FS < 0) fv = fr[r][q];
-        else fv = q ? fl[FS][r][tid].b : fl[FS][r][tid].a;
-        const T nbs = ((((xm + xp) + ym) + yp) + zm) + zp;
-        uc[r][q] = c + omega * ((nbs - h2 * fv) * inv6 - c);
       });
     };
 
@@ -540,60 +551,59 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
     auto defect = [&](auto cPAR, auto cFS, T (&um)[R][2], T (&uc)[R][2], T (&up)[R][2], int p)
                       __attribute__((always_inline)) {
       constexpr int PAR = decltype(cPAR)::value, FS = decltype(cFS)::value;
-      refresh(std::integral_constant<int, 2>{}, cPAR, um, uc, up, p);
-      Pair<T>* xq = &xch[xbuf][0][0][0];
-      xq[(band * 2 + 0) * SL + xl] = Pair<T>{uc[0][0], uc[0][1]};
-      xq[(band * 2 + 1) * SL + xl] = Pair<T>{uc[R - 1][0], uc[R - 1][1]};
-      __syncthreads();
-      const Pair<T> vb = xq[((band > 0 ? band - 1 : band) * 2 + 1) * SL + xl];
-      const Pair<T> va = xq[((band < NB - 1 ? band + 1 : band) * 2 + 0) * SL + xl];
-      xbuf ^= 1;
-      const T below[2] = {vb.a, vb.b}, above[2] = {va.a, va.b};
-      const bool bnd_z1 = !PER && !pz && p == nm;
-      // plane p-1: its red cells' upper neighbour is final now (unless p-1 is the top plane of
-      // a non-periodic axis, whose ghost was taken at once)
-      const bool top_prev = !pz && p - 1 == nm;
+      refresh(std::integral_constant<int, 2>{}, cPAR, uc);
+      const T c6 = PER ? (T)6 : plane_w(p).c6;
+      // the red cells' y neighbours beyond the band: black, set in this step
+      xd[band][0][xl] = uc[0][PAR ? 0 : 1];
+      xd[band][1][xl] = uc[R - 1][(R - 1 + PAR + 1) & 1];
+      // plane p-1: its red cells' upper neighbour is final now
       const bool out_prev = p - 1 >= z0 && p - 1 < zend;
       const bool out_cur = p >= z0 && p < zend;
       T dprev[R], dblk[R];
       static_for<R>([&](auto rr) __attribute__((always_inline)) {
         constexpr int r = decltype(rr)::value;
         constexpr int qr_prev = (r + PAR + 1) & 1;   // red cell of row r on plane p-1 (parity PAR^1)
-        const T dr = dred_get(r);
-        dprev[r] = top_prev ? dr : dr - ih2 * uc[r][qr_prev];
+        dprev[r] = dred_get(r) - ih2 * uc[r][qr_prev];
       });
-      static_for<R>([&](auto rr) __attribute__((always_inline)) {
+      // the cell of row r that is red (RED, without its upper neighbour: added at the next step) or
+      // black; ynb: its y neighbour beyond the band
+      auto cell = [&](auto rr, auto cRED, T ynb) __attribute__((always_inline)) {
         constexpr int r = decltype(rr)::value;
-        const Pair<T> fp = fl[FS][r][tid];
-        const T fpair[2] = {fp.a, fp.b};
-        // q = 0: the black cell, whole; q = 1: the red cell, without its upper neighbour
-        static_for<2>([&](auto qq) __attribute__((always_inline)) {
-          constexpr int black = decltype(qq)::value == 0;
-          constexpr int q = (r + PAR + (black ? 1 : 0)) & 1;
-          const T c = uc[r][q];
-          T xm, xp, ym, yp;
-          if constexpr (q == 0) {
-            xm = from_left<PER>(uc[r][1]);
-            xp = uc[r][1];
-            if constexpr (XYW) xm = wx0 ? kx0 * c : xm;
-          } else {
-            xm = uc[r][0];
-            xp = from_right<PER>(uc[r][0]);
-            if constexpr (XYW) xp = wx1 ? kx1 * c : xp;
-          }
-          if constexpr (r > 0) ym = uc[r - 1][q]; else ym = below[q];
-          if constexpr (r < R - 1) yp = uc[r + 1][q]; else yp = above[q];
-          const T zm = um[r][q], zp = up[r][q];
-          const T s5 = (((xm + xp) + ym) + yp) + zm;
-          if constexpr (black) {
-            dblk[r] = fpair[q] - ((s5 + zp) - (T)6 * c) * ih2;
-          } else {
-            // the upper neighbour of a red cell on the top plane of a non-periodic axis is the
-            // ghost plane (set now); elsewhere it is added at the next step
-            dred_set(r, bnd_z1 ? fpair[q] - ((s5 + zp) - (T)6 * c) * ih2 : fpair[q] - (s5 - (T)6 * c) * ih2);
-          }
-        });
+        constexpr bool red = decltype(cRED)::value;
+        constexpr int q = (r + PAR + (red ? 0 : 1)) & 1;
+        const T c = uc[r][q];
+        const T fv = q ? fl[FS][r][tid].b : fl[FS][r][tid].a;
+        T xm, xp, ym, yp;
+        if constexpr (q == 0) {
+          xm = from_left(uc[r][1]);
+          xp = uc[r][1];
+          if constexpr (XYW) xm = wx0 ? kx0 * c : xm;
+        } else {
+          xm = uc[r][0];
+          xp = from_right(uc[r][0]);
+          if constexpr (XYW) xp = wx1 ? kx1 * c : xp;
+        }
+        if constexpr (r > 0) ym = uc[r - 1][q]; else ym = ynb;
+        if constexpr (r < R - 1) yp = uc[r + 1][q]; else yp = ynb;
+        const T s5 = (((xm + xp) + ym) + yp) + um[r][q];
+        if constexpr (red) dred_set(r, fv - (s5 - c6 * c) * ih2);
+        else dblk[r] = fv - ((s5 + up[r][q]) - c6 * c) * ih2;
+      };
+      using Red = std::true_type;
+      using Black = std::false_type;
+      using I0 = std::integral_constant<int, 0>;
+      using IL = std::integral_constant<int, R - 1>;
+      static_for<R - 2>([&](auto rr) __attribute__((always_inline)) {
+        using Ir = std::integral_constant<int, decltype(rr)::value + 1>;
+        cell(Ir{}, Black{}, (T)0);
+        cell(Ir{}, Red{}, (T)0);
       });
+      // (the black cells' y neighbours beyond the band are those of the last black stage)
+      cell(I0{}, Black{}, xe[3][bandb][1][xl]);
+      cell(IL{}, Black{}, xe[3][banda][0][xl]);
+      __syncthreads();
+      cell(I0{}, Red{}, xd[bandb][1][xl]);
+      cell(IL{}, Red{}, xd[banda][0][xl]);
       if constexpr (NORM) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -605,10 +615,8 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
       }
       if constexpr (DEF) {
         // plane p-1 is complete: its row-pair sums (black part from the previous step); the
-        // even plane of a coarse plane waits in stash, the odd one writes the coarse cell
+        // even plane of a coarse plane waits in stash, the odd one makes the coarse cell there
         constexpr int par_prev = PAR ^ 1;
-        T* __restrict__ fcp = reinterpret_cast<T*>(A.fc);
-        T* __restrict__ ucp = reinterpret_cast<T*>(A.uc0);
 #pragma unroll
         for (int j = 0; j < R / 2; ++j) {
           const T sprev = pend[j] + (dprev[2 * j] + dprev[2 * j + 1]);
@@ -619,17 +627,8 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
             stash[j] = sprev;
             if constexpr (FAS) stash_u[j] = suprev;
           } else {
-            if (out_prev && out_x && out_y[2 * j]) {
-              const size_t ci = cdx(xag >> 1, ygv[2 * j] >> 1, (p - 1) >> 1);
-              fcp[ci] = (stash[j] + sprev) * (T)0.125;
-              if constexpr (FAS) {
-                const T pb = (stash_u[j] + suprev) * (T)0.125;
-                reinterpret_cast<T*>(A.pbar)[ci] = pb;
-                ucp[ci] = pb;
-              } else {
-                ucp[ci] = (T)0;
-              }
-            }
+            stash[j] = (stash[j] + sprev) * (T)0.125;
+            if constexpr (FAS) stash_u[j] = (stash_u[j] + suprev) * (T)0.125;
           }
           pend[j] = dblk[2 * j] + dblk[2 * j + 1];
         }
@@ -638,11 +637,13 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
 
     load_plane(zstart, std::integral_constant<int, 0>{});
     prolong_apply(zstart, std::integral_constant<int, HZ & 1>{});
+    keep_in(zstart);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       u[0][r][0] = pu[r][0]; u[0][r][1] = pu[r][1];
       fr[r][0] = pf[r][0]; fr[r][1] = pf[r][1];
     }
+    arrived(u[0], fr);
     // one pipeline step: the plane in ring slot K is P = zstart + t, t = g + K with g a
     // multiple of 6, so P - j sits in slot (K - j) mod 6, has parity (HZ + K + j) mod 2, and
     // its f is in LDS slot (K - HZ - j) mod 3 (z0 is a multiple of 6)
@@ -651,12 +652,16 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
       const int t = g + K;
       if (t >= nsteps) return;
       const int P = zstart + t;
-      // prefetch; consumed at the end of the step
-      if (t + 1 < nsteps) load_plane(P + 1, std::integral_constant<int, ((HZ + K + 1) & 1) ? 1 : 2>{});
+      // prefetch; consumed at the end of the step (after the last plane: that plane again, unused --
+      // a branch here and at the take-up would make the waits at its join cover the stores)
+      const int Pn = t + 1 < nsteps ? P + 1 : P - 1;
+      load_plane(Pn, std::integral_constant<int, ((HZ + K + 1) & 1) ? 1 : 2>{});
       constexpr int s0 = K, s1 = (K + 5) % 6, s2 = (K + 4) % 6, s3 = (K + 3) % 6, s4 = (K + 2) % 6,
                     s5 = (K + 1) % 6;
       using I0 = std::integral_constant<int, 0>;
       using I1 = std::integral_constant<int, 1>;
+      using I2 = std::integral_constant<int, 2>;
+      using I3 = std::integral_constant<int, 3>;
       using Par1 = std::integral_constant<int, (HZ + K + 1) & 1>;
       using Par2 = std::integral_constant<int, (HZ + K + 2) & 1>;
       using Par3 = std::integral_constant<int, (HZ + K + 3) & 1>;
@@ -665,12 +670,35 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
       using Fs2 = std::integral_constant<int, ((K - HZ - 2) % 3 + 6) % 3>;
       using Fs3 = std::integral_constant<int, ((K - HZ - 3) % 3 + 6) % 3>;
       using Fs4 = std::integral_constant<int, ((K - HZ - 4) % 3 + 6) % 3>;
-      colour(I0{}, Par1{}, FsReg{}, u[s2], u[s1], u[s0], P - 1);   // red, sweep 1
-      colour(I1{}, Par2{}, Fs2{}, u[s3], u[s2], u[s1], P - 2);     // black, sweep 1
-      colour(I0{}, Par3{}, Fs3{}, u[s4], u[s3], u[s2], P - 3);     // red, sweep 2
-      colour(I1{}, Par4{}, Fs4{}, u[s5], u[s4], u[s3], P - 4);     // black, sweep 2
+      edges_out(I0{}, Par1{}, u[s1]);
+      edges_out(I1{}, Par2{}, u[s2]);
+      edges_out(I2{}, Par3{}, u[s3]);
+      edges_out(I3{}, Par4{}, u[s4]);
+      auto stages = [&](auto cIN) __attribute__((always_inline)) {
+        colour(I0{}, Par1{}, FsReg{}, cIN, u[s2], u[s1], u[s0], P - 1);   // red, sweep 1
+        colour(I1{}, Par2{}, Fs2{}, cIN, u[s3], u[s2], u[s1], P - 2);     // black, sweep 1
+        colour(I2{}, Par3{}, Fs3{}, cIN, u[s4], u[s3], u[s2], P - 3);     // red, sweep 2
+        colour(I3{}, Par4{}, Fs4{}, cIN, u[s5], u[s4], u[s3], P - 4);     // black, sweep 2
+      };
+      stages(std::true_type{});
+      __syncthreads();
+      stages(std::false_type{});
       if constexpr (DSTAGE) defect(Par4{}, Fs4{}, u[s5], u[s4], u[s3], P - 4);
-      // plane P-4 is final: out
+      else __syncthreads();   // (with a defect stage: its barrier) xe is free for the next step
+      prolong_apply(Pn, std::integral_constant<int, (HZ + K + 1) & 1>{});
+      keep_in(Pn);
+      // u(P+1) enters the ring in the slot of P-5; f(P-1) moves to the LDS slot of P-4 (done
+      // with), f(P) into the registers
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        u[s5][r][0] = pu[r][0]; u[s5][r][1] = pu[r][1];
+        fl[Fs4::value][r][tid] = Pair<T>{fr[r][0], fr[r][1]};
+        fr[r][0] = pf[r][0]; fr[r][1] = pf[r][1];
+      }
+      // Plane P-4 is final, and on odd planes P-5 its coarse cells: out, once the loads of plane P+1
+      // are in (loads and stores complete in one order, so a wait for the loads further on would
+      // wait for these stores)
+      arrived(u[s5], fr);
       {
         const int p = P - 4;
         if (p >= z0 && p < zend && out_x) {
@@ -684,15 +712,19 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
             }
         }
       }
-      if (t + 1 < nsteps) {
-        prolong_apply(P + 1, std::integral_constant<int, (HZ + K + 1) & 1>{});
-        // u(P+1) enters the ring in the slot of P-5; f(P-1) moves to the LDS slot of P-4 (done
-        // with), f(P) into the registers
+      if constexpr (DEF && ((HZ + K + 5) & 1) != 0) {
+        const int p = P - 5;
+        if (p >= z0 && p < zend && out_x) {
+          T* __restrict__ fcp = reinterpret_cast<T*>(A.fc);
+          T* __restrict__ ucp = reinterpret_cast<T*>(A.uc0);
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          u[s5][r][0] = pu[r][0]; u[s5][r][1] = pu[r][1];
-          fl[Fs4::value][r][tid] = Pair<T>{fr[r][0], fr[r][1]};
-          fr[r][0] = pf[r][0]; fr[r][1] = pf[r][1];
+          for (int j = 0; j < R / 2; ++j)
+            if (out_y[2 * j]) {
+              const size_t ci = cdx(xag >> 1, ygv[2 * j] >> 1, p >> 1);
+              fcp[ci] = stash[j];
+              if constexpr (FAS) reinterpret_cast<T*>(A.pbar)[ci] = stash_u[j];
+              ucp[ci] = FAS ? stash_u[j] : (T)0;
+            }
         }
       }
     };
@@ -707,7 +739,7 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
   }
   if constexpr (NORM) {
     // the exchange buffer is free once every wave has left the march
-    double* red = reinterpret_cast<double*>(&xch[0][0][0][0]);
+    double* red = reinterpret_cast<double*>(&xe[0][0][0][0]);
     acc = wave_sum(acc);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
@@ -722,13 +754,19 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
 
 template <typename T, int W, bool UP, bool NORM, int WALLS, bool BLK>
 __global__ void __launch_bounds__(kLanes* W) k_march(MarchArgs A) {
-  march_body<T, W, UP, NORM, WALLS, BLK, false>(A);
+  march_body<T, W, UP, NORM, WALLS, BLK, false, false>(A);
 }
 
 // The down pass of a Full Approximation Scheme cycle (dense FP64 levels).
 template <typename T, int W, int WALLS>
 __global__ void __launch_bounds__(kLanes* W) k_march_fas(MarchArgs A) {
-  march_body<T, W, false, false, WALLS, false, true>(A);
+  march_body<T, W, false, false, WALLS, false, true, false>(A);
+}
+
+// The down pass from u = 0, which is not read (the first leg of a mixed-precision correction).
+template <typename T, int W, int WALLS>
+__global__ void __launch_bounds__(kLanes* W) k_march_zero(MarchArgs A) {
+  march_body<T, W, false, false, WALLS, false, false, true>(A);
 }
 
 constexpr int kCUs = 256;
@@ -788,23 +826,23 @@ void launch_march(MarchArgs A, hipStream_t s, const MarchAux* aux) {
   A.tiles_y = (A.n + A.yo - 1) / A.yo;
   A.set = 0;
   int zi = 0, zr = 0;
-  if (sizeof(T) == 8 && !per && !xyper && aux && aux->s2 && A.tiles_x >= 3 && A.tiles_y >= 3 &&
-      march_split_plan(A.n, (A.tiles_x - 2) * (A.tiles_y - 2), 2 * A.tiles_x + 2 * (A.tiles_y - 2), HZ, zi, zr)) {
+  const int nint = (A.tiles_x - 2) * (A.tiles_y - 2), nring = 2 * A.tiles_x + 2 * (A.tiles_y - 2);
+  if (sizeof(T) == 8 && !per && !xyper && aux && aux->s2 && A.tiles_x >= 3 && A.tiles_y >= 3 && nint > nring &&
+      march_split_plan(A.n, nint, nring, HZ, zi, zr)) {
     // FP64 with x or y walls: the interior tiles (their halos reach no x or y wall) march in
     // the z-walls-only form on this stream, the ring of wall tiles in the full form on the
     // second stream, concurrently (fork and join through events); the ring's partials follow
-    // the interior's.  (Measured at 512^3: down 1.18 -> 1.05 ms, up with the norm 1.54 ->
-    // 1.36 ms.  Less than the two forms' own rates promise: the two sets march at different z,
-    // so halo re-reads between them miss L2.  FP32, without spills in the full form, is
-    // slower split: 0.52 -> 0.57 ms.)
+    // the interior's.  Where the interior tiles are the more: at 512^3 (64 against 36) a V-cycle
+    // takes 2444 us so and 2593 in one launch, at 256^3 (9 against 16) 507 and 488.  (FP32's full
+    // form, well within its registers, is slower split: 0.52 -> 0.57 ms at 512^3.)
     MarchArgs Ai = A, Ar = A;
     Ai.set = 1;
     Ai.zc = zi;
-    Ai.ntiles = (A.tiles_x - 2) * (A.tiles_y - 2) * ((A.n + zi - 1) / zi);
+    Ai.ntiles = nint * ((A.n + zi - 1) / zi);
     const int gi = (Ai.ntiles + 7) / 8 * 8;
     Ar.set = 2;
     Ar.zc = zr;
-    Ar.ntiles = (2 * A.tiles_x + 2 * (A.tiles_y - 2)) * ((A.n + zr - 1) / zr);
+    Ar.ntiles = nring * ((A.n + zr - 1) / zr);
     const int gr = (Ar.ntiles + 7) / 8 * 8;
     Ai.sink.total = Ar.sink.total = gi + gr;
     Ar.sink.first = gi;
@@ -831,9 +869,10 @@ void launch_march(MarchArgs A, hipStream_t s, const MarchAux* aux) {
   else launch_maybe_timed(k_march<T, W, UP, NORM, 2, BLK>, dim3(grid), dim3(kLanes * W), 0, s, A);
 }
 
-// The FAS down pass: one launch over every tile, the wall form chosen by the level's faces.
-template <typename T>
-void launch_march_fas(MarchArgs A, hipStream_t s) {
+// The down passes of FAS and from zero: one launch over every tile, the wall form chosen by the
+// level's faces.
+template <typename T, bool ZERO>
+void launch_march_down1(MarchArgs A, hipStream_t s) {
   bool per = true, xyper = true;
   for (int f = 0; f < 6; ++f) per = per && A.bc.kind[f] == BC_PERIODIC;
   for (int f = 0; f < 4; ++f) xyper = xyper && A.bc.kind[f] == BC_PERIODIC;
@@ -847,9 +886,15 @@ void launch_march_fas(MarchArgs A, hipStream_t s) {
   A.zc = march_zchunk(A.n, A.tiles_x * A.tiles_y, 5);
   A.ntiles = A.tiles_x * A.tiles_y * ((A.n + A.zc - 1) / A.zc);
   const int grid = (A.ntiles + 7) / 8 * 8;
-  if (per) launch_maybe_timed(k_march_fas<T, W, 0>, dim3(grid), dim3(kLanes * W), 0, s, A);
-  else if (xyper) launch_maybe_timed(k_march_fas<T, W, 1>, dim3(grid), dim3(kLanes * W), 0, s, A);
-  else launch_maybe_timed(k_march_fas<T, W, 2>, dim3(grid), dim3(kLanes * W), 0, s, A);
+  if constexpr (ZERO) {
+    if (per) launch_maybe_timed(k_march_zero<T, W, 0>, dim3(grid), dim3(kLanes * W), 0, s, A);
+    else if (xyper) launch_maybe_timed(k_march_zero<T, W, 1>, dim3(grid), dim3(kLanes * W), 0, s, A);
+    else launch_maybe_timed(k_march_zero<T, W, 2>, dim3(grid), dim3(kLanes * W), 0, s, A);
+  } else {
+    if (per) launch_maybe_timed(k_march_fas<T, W, 0>, dim3(grid), dim3(kLanes * W), 0, s, A);
+    else if (xyper) launch_maybe_timed(k_march_fas<T, W, 1>, dim3(grid), dim3(kLanes * W), 0, s, A);
+    else launch_maybe_timed(k_march_fas<T, W, 2>, dim3(grid), dim3(kLanes * W), 0, s, A);
+  }
 }
 
 template <typename T>
@@ -863,7 +908,6 @@ MarchArgs base_args(const T* uin, T* uout, const T* f, int n, double h, double o
   A.h2 = h * h;
   A.ih2 = 1.0 / (h * h);
   A.omega = omega;
-  A.zero_in = uin == nullptr;
   return A;
 }
 
@@ -877,6 +921,7 @@ void march_down(const T* uin, T* uout, const T* f, T* fc, T* uc0, int n, double 
   A.uc0 = uc0;
   A.Lm = Lm;
   if (Lm > 0) launch_march<T, false, false, true>(A, s, aux);
+  else if (!uin) launch_march_down1<T, true>(A, s);
   else launch_march<T, false, false, false>(A, s, aux);
 }
 
@@ -887,7 +932,7 @@ void march_down_fas(const T* uin, T* uout, const T* f, T* fc, T* pbar, T* uc0, i
   A.fc = fc;
   A.pbar = pbar;
   A.uc0 = uc0;
-  launch_march_fas<T>(A, s);
+  launch_march_down1<T, false>(A, s);
 }
 
 template <typename T>
@@ -908,11 +953,11 @@ void march_up(const T* uin, T* uout, const T* f, const T* ec, const LevelBC& bcc
 }
 
 template <typename T>
-std::string march_fas_name(const LevelBC& bc) {
+std::string march_down1_name(bool zero, const LevelBC& bc) {
   bool per = true, xyper = true;
   for (int f = 0; f < 6; ++f) per = per && bc.kind[f] == BC_PERIODIC;
   for (int f = 0; f < 4; ++f) xyper = xyper && bc.kind[f] == BC_PERIODIC;
-  return std::string("k_march_fas<") + (sizeof(T) == 8 ? "double" : "float") + ", " + std::to_string(cfg_W<T>()) +
+  return std::string(zero ? "k_march_zero<" : "k_march_fas<") + (sizeof(T) == 8 ? "double" : "float") + ", " + std::to_string(cfg_W<T>()) +
          ", " + std::to_string(per ? 0 : (xyper ? 1 : 2)) + ">";
 }
 
@@ -935,7 +980,7 @@ template void march_down<MG_MARCH_T>(const MG_MARCH_T*, MG_MARCH_T*, const MG_MA
 template void march_up<MG_MARCH_T>(const MG_MARCH_T*, MG_MARCH_T*, const MG_MARCH_T*, const MG_MARCH_T*, const LevelBC&,
                                    const SumSink*, int, double, double, const LevelBC&, hipStream_t, int, const MarchAux*);
 template std::string march_name<MG_MARCH_T>(bool, bool, const LevelBC&, bool);
-template std::string march_fas_name<MG_MARCH_T>(const LevelBC&);
+template std::string march_down1_name<MG_MARCH_T>(bool, const LevelBC&);
 template void march_down_fas<MG_MARCH_T>(const MG_MARCH_T*, MG_MARCH_T*, const MG_MARCH_T*, MG_MARCH_T*, MG_MARCH_T*,
                                          MG_MARCH_T*, int, double, double, const LevelBC&, hipStream_t);
 
