@@ -19,7 +19,7 @@
 // registers (a ring), f of plane P-1 in registers and of P-2..P-4 in per-thread LDS slots.
 //
 // The colour pattern is a compile-time constant: tile origins, halos and z-chunk starts are
-// even, chunks start at multiples of 6 and the ring has 6 planes, so the parity of the plane a
+// even and the ring has 6 planes, so the parity of the plane a
 // stage works on, and which cell of a lane's x-pair is red in each row, are template constants.
 // A stage then updates exactly one cell per row with no operand selection: two cross-lane moves
 // (DPP wave shifts) for the x-neighbour, in-lane rows or an LDS exchange of the band-edge rows
@@ -34,9 +34,11 @@
 //  * no branch around a load or its take-up, and the step's stores after the take-up: loads and
 //    stores complete in one order, so a wait for loads behind stores, or at a join of paths, waits
 //    for the stores to reach memory.
-// Measured with five barriers and stores before the take-up, and now (us per leg down / up):
-// 128^3 39 / 34 -> 32 / 32; V-cycles at 256^3 386 -> 351 periodic, 451 -> 394 between z walls,
-// 522 -> 488 fixed; at 512^3 2285 -> 2070 and 2610 -> 2444 (periodic equal, at 2000).
+//  * addresses are a uniform plane base and a 32-bit offset, coarse taps take their walls' signs
+//    when they are used, not as they are loaded.
+// Measured before these and now: 128^3 periodic legs 39 / 34 -> 32 / 32 us; V-cycles at 256^3
+// 386 -> 337 us periodic, 451 -> 378 between z walls, 522 -> 442 fixed; at 512^3 2285 -> 2030 and
+// 2610 -> 2243 (periodic 2000 -> 1953).  Loading two planes ahead: FP32 equal, FP64 spills.
 //
 // The defect stage needs the final state of both neighbouring planes.  Black cells of P-4 have
 // only red neighbours, final after red sweep 2; red cells of P-4 get their in-plane and lower
@@ -145,6 +147,14 @@ __device__ __forceinline__ void arrived(const T (&a)[kR][2], const T (&b)[kR][2]
                "v"(a[3][1]), "v"(b[0][0]), "v"(b[0][1]), "v"(b[1][0]), "v"(b[1][1]), "v"(b[2][0]), "v"(b[2][1]),
                "v"(b[3][0]), "v"(b[3][1])
                : "memory");
+}
+
+// v with its sign bit flipped by `bit`
+__device__ __forceinline__ float with_sign(float v, unsigned bit) {
+  return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, v) ^ bit);
+}
+__device__ __forceinline__ double with_sign(double v, unsigned bit) {
+  return __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, v) ^ ((unsigned long long)bit << 32));
 }
 
 template <typename T>
@@ -278,30 +288,44 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
 #pragma unroll
       for (int r = 0; r < R; ++r) rxy[r] = blk_xy(A.Lm, xag, ygv[r]);
     }
-    // storage index of row r of this lane on plane z
-    auto fidr = [&](int r, int z) __attribute__((always_inline)) -> size_t {
-      if constexpr (BLK) return (size_t)(rxy[r] + blk_z(A.Lm, z));
-      else return cidx(L, xag, ygv[r], z);
+    // dense layout: each row's byte offset within a plane (below 2^25 up to 2048^2 cells), so that
+    // an address is a uniform plane base and a 32-bit offset, with no arithmetic per load
+    unsigned rb[BLK ? 1 : R];
+    if constexpr (!BLK) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) rb[r] = (unsigned)(((ygv[r] << L) | xag) * (int)sizeof(T));
+    }
+    // row r of this lane on plane z of array p
+    auto at = [&](const T* p, int r, int z) __attribute__((always_inline)) -> const T* {
+      if constexpr (BLK) return p + (size_t)(rxy[r] + blk_z(A.Lm, z));
+      else return reinterpret_cast<const T*>(reinterpret_cast<const char*>(p + ((size_t)z << (2 * L))) + rb[r]);
     };
     // up, MeshBlock layout: the x-y part of the coarse taps' storage indices (rows Y0-1 ..
     // Y0+2 of the lane's coarse column, wrapped or clamped as the taps take them); the coarse
     // level is in blocks of 2^(Lm-1) cells, or the dense root grid when Lm = 1
     constexpr int NTAP = R / 2 + 2;
     unsigned cxy[UP ? NTAP : 1];
+    unsigned sgn[UP && XYW ? NTAP : 1];   // the sign of the walls' rule of a clamped tap, as its bit
     if constexpr (UP) {
       const int nc = n >> 1, Lc = L - 1;
       int X = (px ? xag : xa) >> 1;
+      const bool minus_x = XYW && ((X < 0 && kappa_of<T>(A.bcc, 0) < 0) || (X >= nc && kappa_of<T>(A.bcc, 1) < 0));
       if constexpr (XYW) X = min(max(X, 0), nc - 1);
       const int Y0 = (py ? ygv[0] : yv[0]) >> 1;
 #pragma unroll
       for (int i = 0; i < NTAP; ++i) {
         int Y = Y0 - 1 + i;
         if (py) Y &= nc - 1;
-        if constexpr (XYW) Y = min(max(Y, 0), nc - 1);
-        cxy[i] = !BLK || A.Lm == 1 ? (unsigned)((Y << Lc) | X) : blk_xy(A.Lm - 1, X, Y);
+        if constexpr (XYW) {
+          const bool minus_y = (Y < 0 && kappa_of<T>(A.bcc, 2) < 0) || (Y >= nc && kappa_of<T>(A.bcc, 3) < 0);
+          sgn[i] = minus_x != minus_y ? 0x80000000u : 0u;
+          Y = min(max(Y, 0), nc - 1);
+        }
+        if constexpr (BLK) cxy[i] = A.Lm == 1 ? (unsigned)((Y << Lc) | X) : blk_xy(A.Lm - 1, X, Y);
+        else cxy[i] = (unsigned)(((Y << Lc) | X) * (int)sizeof(T));   // in bytes
       }
     }
-    const int z0 = cz * A.zc;                    // a multiple of 6
+    const int z0 = cz * A.zc;                    // even
     const int zend = min(z0 + A.zc, n);
     const int zstart = z0 - HZ;
     const int nsteps = (zend - z0) + 2 * HZ;
@@ -328,8 +352,7 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
       return v;
     };
     // up: the coarse correction's rules (homogeneous conditions)
-    const T kcx0 = kappa_of<T>(A.bcc, 0), kcx1 = kappa_of<T>(A.bcc, 1), kcy0 = kappa_of<T>(A.bcc, 2);
-    const T kcy1 = kappa_of<T>(A.bcc, 3), kcz0 = kappa_of<T>(A.bcc, 4), kcz1 = kappa_of<T>(A.bcc, 5);
+    const T kcz0 = kappa_of<T>(A.bcc, 4), kcz1 = kappa_of<T>(A.bcc, 5);
 
     T u[kRing][R][2];
     T pu[R][2], pf[R][2];      // prefetched u of plane P+1 and f of plane P
@@ -378,20 +401,22 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
     // of plane P
     // cTAPS (up): 0 load both coarse planes of P, 1 (P odd) keep the upper plane of P-1 as the
     // lower one and load the upper, 2 (P even) keep the pair of P-1
-    auto load_plane = [&](int P, auto cTAPS) __attribute__((always_inline)) {
+    auto load_plane = [&](int P) __attribute__((always_inline)) {
       const int Pg = P & nm, Pfg = (P - 1) & nm;
       // no branch around a load: at a join the waits on it would turn conservative
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         if constexpr (!ZIN) {
-          const Pair<T> vu = *reinterpret_cast<const Pair<T>*>(uin + fidr(r, Pg));
+          const Pair<T> vu = *reinterpret_cast<const Pair<T>*>(at(uin, r, Pg));
           pu[r][0] = vu.a; pu[r][1] = vu.b;
         } else {
           pu[r][0] = pu[r][1] = (T)0;
         }
-        const Pair<T> vf = *reinterpret_cast<const Pair<T>*>(fin + fidr(r, Pfg));
+        const Pair<T> vf = *reinterpret_cast<const Pair<T>*>(at(fin, r, Pfg));
         pf[r][0] = vf.a; pf[r][1] = vf.b;
       }
+    };
+    auto load_taps = [&](int P, auto cTAPS) __attribute__((always_inline)) {
       if constexpr (UP) {
         // Trilinear prolongation (weights 1/4, 3/4 per axis) of the coarse correction: the
         // lane's coarse column X, coarse rows Y0-1 .. Y0+2 (rows 2j, 2j+1 of the band take
@@ -414,25 +439,12 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
           int Y = Y0 - 1 + i;
           if (py) Y &= nc - 1;
           if (pz) zz &= nc - 1;
-          // the lane's x-y part (wrapped, or clamped into the domain) plus the plane's z part;
-          // every face periodic: the wrapped indices are in range (no ghost code compiled);
-          // otherwise the sign of the wall's rule when clamped (selects: no branches around
-          // the load)
+          // the lane's x-y part (wrapped, or clamped into the domain) plus the plane's z part
           const int Zc = PER ? zz : min(max(zz, 0), nc - 1);
-          const size_t ci = (size_t)cxy[i] + (!BLK || A.Lm == 1 ? ((size_t)Zc << (2 * Lc)) : (size_t)blk_z(A.Lm - 1, Zc));
-          if constexpr (PER) {
-            return ec[ci];
-          } else if constexpr (!XYW) {
-            // x and y taps wrapped into the domain: only a z wall's sign (the same value as
-            // the general form, whose x and y factors are 1 here)
-            const T sz = zz < 0 ? kcz0 : (zz >= nc ? kcz1 : (T)1);
-            return sz * ec[ci];
-          } else {
-            const T sx = X < 0 ? kcx0 : (X >= nc ? kcx1 : (T)1);
-            const T sy = Y < 0 ? kcy0 : (Y >= nc ? kcy1 : (T)1);
-            const T sz = zz < 0 ? kcz0 : (zz >= nc ? kcz1 : (T)1);
-            return (sx * sy) * (sz * ec[ci]);
-          }
+          const T* ep;
+          if constexpr (BLK) ep = ec + ((size_t)cxy[i] + (A.Lm == 1 ? ((size_t)Zc << (2 * Lc)) : (size_t)blk_z(A.Lm - 1, Zc)));
+          else ep = reinterpret_cast<const T*>(reinterpret_cast<const char*>(ec + ((size_t)Zc << (2 * Lc))) + cxy[i]);
+          return *ep;   // (as stored: the walls' signs when it is used, so that nothing waits here)
         };
         if constexpr (TAPS == 0) {
 #pragma unroll
@@ -454,10 +466,21 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
     auto prolong_apply = [&](int P, auto cPAR) __attribute__((always_inline)) {
       if constexpr (UP) {
         constexpr int PARP = decltype(cPAR)::value;
-        const T wz0 = PARP ? (T)0.75 : (T)0.25, wz1 = PARP ? (T)0.25 : (T)0.75;
+        T wz0 = PARP ? (T)0.75 : (T)0.25, wz1 = PARP ? (T)0.25 : (T)0.75;
+        if constexpr (!PER) {
+          // (only the lower plane can lie below the domain, only the upper one above it)
+          const int zlo = ((pz ? (P & nm) : P) + (PARP ? 0 : -1)) >> 1;
+          if (!pz && zlo < 0) wz0 *= kcz0;
+          if (!pz && zlo < -1) wz1 *= kcz0;
+          if (!pz && zlo >= (n >> 1)) wz0 *= kcz1;
+          if (!pz && zlo + 1 >= (n >> 1)) wz1 *= kcz1;
+        }
         T czv[NTAP];
 #pragma unroll
-        for (int i = 0; i < NTAP; ++i) czv[i] = wz0 * pc[i][0] + wz1 * pc[i][1];
+        for (int i = 0; i < NTAP; ++i) {
+          czv[i] = wz0 * pc[i][0] + wz1 * pc[i][1];
+          if constexpr (XYW) czv[i] = with_sign(czv[i], sgn[i]);
+        }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           const int j = r >> 1;
@@ -635,7 +658,8 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
       }
     };
 
-    load_plane(zstart, std::integral_constant<int, 0>{});
+    load_plane(zstart);
+    load_taps(zstart, std::integral_constant<int, 0>{});
     prolong_apply(zstart, std::integral_constant<int, HZ & 1>{});
     keep_in(zstart);
 #pragma unroll
@@ -645,8 +669,8 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
     }
     arrived(u[0], fr);
     // one pipeline step: the plane in ring slot K is P = zstart + t, t = g + K with g a
-    // multiple of 6, so P - j sits in slot (K - j) mod 6, has parity (HZ + K + j) mod 2, and
-    // its f is in LDS slot (K - HZ - j) mod 3 (z0 is a multiple of 6)
+    // multiple of 6, so P - j sits in slot (K - j) mod 6, has parity (HZ + K + j) mod 2 (z0 is even),
+    // and its f is in LDS slot (K - HZ - j) mod 3
     auto step = [&](int g, auto kk) __attribute__((always_inline)) {
       constexpr int K = decltype(kk)::value;
       const int t = g + K;
@@ -655,7 +679,8 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
       // prefetch; consumed at the end of the step (after the last plane: that plane again, unused --
       // a branch here and at the take-up would make the waits at its join cover the stores)
       const int Pn = t + 1 < nsteps ? P + 1 : P - 1;
-      load_plane(Pn, std::integral_constant<int, ((HZ + K + 1) & 1) ? 1 : 2>{});
+      load_plane(Pn);
+      load_taps(Pn, std::integral_constant<int, ((HZ + K + 1) & 1) ? 1 : 2>{});
       constexpr int s0 = K, s1 = (K + 5) % 6, s2 = (K + 4) % 6, s3 = (K + 3) % 6, s4 = (K + 2) % 6,
                     s5 = (K + 1) % 6;
       using I0 = std::integral_constant<int, 0>;
@@ -708,7 +733,7 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
             if (out_y[r]) {
               typedef T ntv2 __attribute__((ext_vector_type(2)));
               const ntv2 v = {u[s4][r][0], u[s4][r][1]};
-              __builtin_nontemporal_store(v, reinterpret_cast<ntv2*>(uout + fidr(r, pg)));
+              __builtin_nontemporal_store(v, reinterpret_cast<ntv2*>(const_cast<T*>(at(uout, r, pg))));
             }
         }
       }
@@ -771,14 +796,13 @@ __global__ void __launch_bounds__(kLanes* W) k_march_zero(MarchArgs A) {
 
 constexpr int kCUs = 256;
 
-// Planes per workgroup: a multiple of 6 (the ring's period; chunks then start on planes whose
-// ring slot, parity and f slot are compile-time).  One workgroup per CU is resident (LDS), so
+// Planes per workgroup: even (chunks then start on planes of the parity compiled in).  One workgroup per CU is resident (LDS), so
 // the grid runs in rounds of kCUs workgroups; the chunk minimises rounds x (planes marched,
 // 2 hz halo planes included).
 int march_zchunk(int n, int tiles_xy, int hz) {
-  int best = (n + 5) / 6 * 6;
+  int best = n;
   long best_cost = -1;
-  for (int zc = 6; zc <= (n + 5) / 6 * 6; zc += 6) {
+  for (int zc = 6; zc <= n; zc += 2) {
     const long chunks = (n + zc - 1) / zc;
     if ((long)tiles_xy * chunks > (long)kMaxPartials * 32 - 8) continue;   // partials buffer
     const long rounds = ((long)tiles_xy * chunks + kCUs - 1) / kCUs;
@@ -797,10 +821,10 @@ bool march_split_plan(int n, int nint, int nring, int hz, int& zi, int& zr) {
   double best = -1.0;
   const long cap = (long)kMaxPartials * 32 - 8;
   for (int ci = 1; ci <= (n + 5) / 6; ++ci) {
-    const int zci = ((n + ci - 1) / ci + 5) / 6 * 6;
+    const int zci = ((n + ci - 1) / ci + 1) / 2 * 2;
     const long ni = (long)nint * ((n + zci - 1) / zci);
     for (int cr = 1; cr <= (n + 5) / 6; ++cr) {
-      const int zcr = ((n + cr - 1) / cr + 5) / 6 * 6;
+      const int zcr = ((n + cr - 1) / cr + 1) / 2 * 2;
       const long nr = (long)nring * ((n + zcr - 1) / zcr);
       const long tot = ((ni + 7) / 8 + (nr + 7) / 8) * 8;
       if (tot > kCUs || tot > cap) continue;
@@ -833,7 +857,7 @@ void launch_march(MarchArgs A, hipStream_t s, const MarchAux* aux) {
     // the z-walls-only form on this stream, the ring of wall tiles in the full form on the
     // second stream, concurrently (fork and join through events); the ring's partials follow
     // the interior's.  Where the interior tiles are the more: at 512^3 (64 against 36) a V-cycle
-    // takes 2444 us so and 2593 in one launch, at 256^3 (9 against 16) 507 and 488.  (FP32's full
+    // takes 2243 us so and 2338 in one launch, at 256^3 (9 against 16) 445 and 442.  (FP32's full
     // form, well within its registers, is slower split: 0.52 -> 0.57 ms at 512^3.)
     MarchArgs Ai = A, Ar = A;
     Ai.set = 1;
