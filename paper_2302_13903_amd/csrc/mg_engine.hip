@@ -132,7 +132,7 @@ struct mg_ctx {
   // large-level smoothing: 1 = temporally blocked passes (two sweeps per pass over HBM),
   // 0 = one sweep per pass; -1 = the built-in default
   int tblock[2] = {-1, -1};
-  // V(2,2) legs as two-sweep streaming passes (down: two sweeps + restricted defect; up:
+  // legs of one or two sweeps as streaming passes (down: sweeps + restricted defect; up:
   // prolongation + two sweeps [+ norm]): 0 = off, 1 = on levels whose faces are all periodic,
   // 2 = on every level; -1 = the built-in default (2)
   int march[2] = {-1, -1};
@@ -318,7 +318,7 @@ struct Hier {
   double omega = 1.15;
 };
 
-// Smallest level side on which the two-sweep passes run, or the one-sweep passes' threshold
+// Smallest level side on which the streaming passes run, or the one-sweep passes' threshold
 // ("fusedmin") when that was set larger.  At 128^3 the passes are taken in FP64 on an all-periodic
 // level only (40 + 34 us for the two legs against 38 + 46 us as region tiles); with walls the
 // tiles win (43 + 56 us against 84 + 96 us), and in FP32 (24 + 25 us against 40 + 39 us with walls;
@@ -331,7 +331,7 @@ int march_min_n(const mg_ctx* c, const LevelBC& bc) {
   return std::max(per ? kMarchMinN : 2 * kMarchMinN, v);
 }
 
-// Does a MeshBlock level of 2^l cells per side fit the two-sweep passes' 32-bit block index?
+// Does a MeshBlock level of 2^l cells per side fit the streaming passes' 32-bit block index?
 inline bool blk_march_fits(int l) { return 3 * l < 32; }
 
 struct Solver {
@@ -366,7 +366,7 @@ struct Solver {
   // next top-level vcycle / vcycle_blk skips it
   bool down_done = false;
 
-  // The down leg of dense level l of a V(2,2) cycle in one launch: the two-sweep pass
+  // The down leg of dense level l of a V-cycle in one launch: the streaming pass
   // (march) or the region-tile leg.  It reads u and f and writes only u2 and the coarse
   // level's source and correction.  zin: u is zero and not read.
   template <typename T>
@@ -375,25 +375,25 @@ struct Solver {
     const double cellsT = (double)cells(l) * sizeof(T);
     if (timed) kernel_begin(true);
     if (march) {
-      march_down<T>(zin ? nullptr : H.u[l], H.u2[l], H.f[l], H.f[l - 1], H.u[l - 1], n, H.h[l], H.omega, bc, s, 0,
+      march_down<T>(zin ? nullptr : H.u[l], H.u2[l], H.f[l], H.f[l - 1], H.u[l - 1], n, H.npre, H.h[l], H.omega, bc, s, 0,
                     aux_of());
       // algorithmic bytes: u and f read, u written, coarse source and correction written
       if (timed)
-        kernel_end(zin ? march_down1_name<T>(true, bc) : march_name<T>(false, false, bc), 3 * cellsT + cellsT / 4);
+        kernel_end(zin ? march_down1_name<T>(H.npre, true, bc) : march_name<T>(H.npre, false, false, bc), 3 * cellsT + cellsT / 4);
     } else {
       tile_down<T>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], nullptr, H.u[l - 1], n, 0, H.npre, H.h[l], H.omega, bc, s);
       if (timed) kernel_end(tile_name<T>(H.npre, false, bc, n), 3 * cellsT + cellsT / 4);
     }
   }
-  // The same for MeshBlock level l (big: the two-sweep pass across blocks).
+  // The same for MeshBlock level l (big: the streaming pass across blocks).
   template <typename T>
   void blk_down_leg(Hier<T>& H, int l, const LevelBC& bc, bool big, bool timed) {
     const int nl = 1 << l, Lm = l - Lb;
     const double cellsT = (double)cells(l) * sizeof(T);
     if (timed) kernel_begin(true);
-    if (big) march_down<T>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], H.u[l - 1], nl, H.h[l], H.omega, bc, s, Lm, aux_of());
+    if (big) march_down<T>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], H.u[l - 1], nl, H.npre, H.h[l], H.omega, bc, s, Lm, aux_of());
     else tile_down<T>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], nullptr, H.u[l - 1], nl, Lm, H.npre, H.h[l], H.omega, bc, s);
-    if (timed) kernel_end(big ? march_name<T>(false, false, bc, true) : tile_name<T>(H.npre, false, bc, nl),
+    if (timed) kernel_end(big ? march_name<T>(H.npre, false, false, bc, true) : tile_name<T>(H.npre, false, bc, nl),
                           3 * cellsT + cellsT / 4);
   }
 
@@ -508,12 +508,13 @@ struct Solver {
     return sizeof(T) == 8 ? 2 : 0;
   }
 
-  // Does level l run its V(2,2) legs as the two-sweep streaming passes (down: two sweeps and
+  // Does level l run its legs as the streaming passes of one or two sweeps (down: the sweeps and
   // the restricted defect in one pass; up: prolongation, two sweeps and the norm in one)?
   template <typename T>
   bool march_on(const Hier<T>& H, int l, const LevelBC& bc) const {
     const int mode = c->march[sizeof(T) == 8 ? 0 : 1] < 0 ? 2 : c->march[sizeof(T) == 8 ? 0 : 1];
-    if (mode == 0 || !use_fused || !H.u2[l] || l == H.T_top || Lb >= 0 || H.npre != 2 || H.npost != 2) return false;
+    if (mode == 0 || !use_fused || !H.u2[l] || l == H.T_top || Lb >= 0) return false;
+    if (!march_sweeps_ok(H.npre) || !march_sweeps_ok(H.npost)) return false;
     if ((1 << l) < march_min_n<T>(c, bc) || tblock_on<T>()) return false;
     if (mode == 1)
       for (int f = 0; f < 6; ++f)
@@ -524,20 +525,20 @@ struct Solver {
   // the second stream of the split passes (null: one launch per pass)
   const MarchAux* aux_of() const { return c->split == 0 ? nullptr : &c->aux; }
 
-  // May MeshBlock level l run the two-sweep streaming passes (the "march" setting for its
+  // May MeshBlock level l run the streaming passes (the "march" setting for its
   // faces)?  Those passes index the block layout in 32 bits, so the level must hold fewer than
   // 2^32 cells (every level up to 1024^3); larger ones take the block streaming sweeps.
   template <typename T>
   bool march_blk_on(const Hier<T>& H, int l, const LevelBC& bc) const {
     const int mode = c->march[sizeof(T) == 8 ? 0 : 1] < 0 ? 2 : c->march[sizeof(T) == 8 ? 0 : 1];
-    if (mode == 0 || H.npre != 2 || H.npost != 2 || !blk_march_fits(l)) return false;
+    if (mode == 0 || !march_sweeps_ok(H.npre) || !march_sweeps_ok(H.npost) || !blk_march_fits(l)) return false;
     if (mode == 1)
       for (int f = 0; f < 6; ++f)
         if (bc.kind[f] != BC_PERIODIC) return false;
     return true;
   }
 
-  // Does level l (side n) run its V(2,2) legs as region-tile launches (one per leg)?
+  // Does level l (side n) run its legs as region-tile launches (one per leg)?
   template <typename T>
   bool tile_on(const Hier<T>& H, int l) const {
     const int v = c->tile[sizeof(T) == 8 ? 0 : 1];
@@ -548,7 +549,7 @@ struct Solver {
 
   // FP64, dense: can the first pre-sweep of the finest level's V-cycle run as a head pass (a
   // one-sweep streaming pass that also takes the residual norm of its input)?  Not when the
-  // finest level runs the two-sweep passes, whose up pass takes the norm of the cycle's result.
+  // finest level runs the streaming legs, whose up pass takes the norm of the cycle's result.
   bool head_possible(const Hier<double>& H) const {
     const int L = H.L;
     return use_fused && H.u2[L] && L != H.T_top && Lb < 0 && (1 << L) >= fused_min_n64 && !tblock_on<double>() &&
@@ -601,8 +602,8 @@ struct Solver {
     const bool timed = top_call && l == H.L && ktiming;
     const double cellsT = (double)cells(l) * sizeof(T);
     if (march_on<T>(H, l, bc)) {
-      // V(2,2) in two streaming passes: down (two sweeps, restricted defect, coarse correction
-      // cleared), the coarse recursion, up (prolonged correction, two sweeps, and the norm of
+      // one or two sweeps per leg in two streaming passes: down (sweeps, restricted defect, coarse correction
+      // cleared), the coarse recursion, up (prolonged correction, sweeps, and the norm of
       // the result when asked); the result lands back in u[l] after the two ping-pongs
       const bool zin = top_call && zero_start;
       if (top_call && down_done) down_done = false;   // queued ahead of the stopping test
@@ -611,9 +612,9 @@ struct Solver {
       const bool norm = want_norm && sizeof(T) == 8;
       const SumSink sink = norm ? norm_sink() : SumSink{};
       if (timed) kernel_begin(true);
-      march_up<T>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, norm ? &sink : nullptr, n, h, H.omega, bc, s, 0, aux_of());
+      march_up<T>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, norm ? &sink : nullptr, n, H.npost, h, H.omega, bc, s, 0, aux_of());
       // algorithmic bytes: u, f and the coarse correction read, u written
-      if (timed) kernel_end(march_name<T>(true, norm, bc), 3 * cellsT + cellsT / 8);
+      if (timed) kernel_end(march_name<T>(H.npost, true, norm, bc), 3 * cellsT + cellsT / 8);
       return norm;
     }
     if (n < (sizeof(T) == 8 ? fused_min_n64 : fused_min_n32) && tile_on<T>(H, l)) {
@@ -787,7 +788,7 @@ struct Solver {
 
   // done: pre-sweeps of the top level already run by the head pass (result in u2).  want_norm
   // (top level): the sum of squared defects of the result may be left in scal[2] (by the
-  // two-sweep up pass, the tile leg or the tail); returns whether it was.
+  // streaming up pass, the tile leg or the tail); returns whether it was.
   bool fas_cycle(Hier<double>& H, double* const* pbar, int l, int done = 0, bool want_norm = false) {
     if (done == 0 && l <= H.T_top) {
       // The levels <= 16^3 in one workgroup, in correction form: below level l, FAS solves for
@@ -802,26 +803,26 @@ struct Solver {
     const bool timed = timed_top && l == H.L && ktiming;
     const double cellsT = (double)cells(l) * sizeof(double);
     if (done == 0 && march_on<double>(H, l, bc)) {
-      // V(2,2) legs as the two-sweep passes: down (two sweeps, restricted defect, phibar, the
+      // legs as the streaming passes: down (sweeps, restricted defect, phibar, the
       // coarse level started from it), steps 5-7 on the coarse level, up (the prolonged
       // correction psi - phibar, two sweeps, and the norm of the result when asked)
       if (timed) kernel_begin(true);
-      march_down_fas<double>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], pbar[l - 1], H.u[l - 1], n, H.h[l], H.omega, bc, s);
+      march_down_fas<double>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], pbar[l - 1], H.u[l - 1], n, H.npre, H.h[l], H.omega, bc, s);
       // algorithmic bytes: u and f read, u written, three coarse arrays written
-      if (timed) kernel_end(march_down1_name<double>(false, bc), 3 * cellsT + 3 * cellsT / 8);
+      if (timed) kernel_end(march_down1_name<double>(H.npre, false, bc), 3 * cellsT + 3 * cellsT / 8);
       launch_fas_source(pbar[l - 1], H.f[l - 1], n / 2, H.h[l - 1], H.hom, s);               // 5
       fas_cycle(H, pbar, l - 1);                                                             // 6
       launch_fas_correction(H.u[l - 1], pbar[l - 1], cells(l - 1), s);                       // 7
       const SumSink sink = want_norm ? norm_sink() : SumSink{};
       const bool norm = want_norm;
       if (timed) kernel_begin(true);
-      march_up<double>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, norm ? &sink : nullptr, n, H.h[l], H.omega, bc, s, 0,
+      march_up<double>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, norm ? &sink : nullptr, n, H.npost, H.h[l], H.omega, bc, s, 0,
                        aux_of());
-      if (timed) kernel_end(march_name<double>(true, norm, bc), 3 * cellsT + cellsT / 8);
+      if (timed) kernel_end(march_name<double>(H.npost, true, norm, bc), 3 * cellsT + cellsT / 8);
       return norm;
     }
     if (done == 0 && n < fused_min_n64 && tile_on<double>(H, l)) {
-      // a small level: each V(2,2) leg in one region-tile launch -- down (two sweeps,
+      // a small level: each leg in one region-tile launch -- down (sweeps,
       // restricted defect, phibar, the coarse level started from it), steps 5-7 on the coarse
       // level, up (the prolonged correction psi - phibar, two sweeps, the norm when asked)
       if (timed) kernel_begin(true);
@@ -973,7 +974,7 @@ struct Solver {
     const int vz = c->blk_zmarch[sizeof(T) == 8 ? 0 : 1];
     const bool big = vz != 0 && nl >= march_min_n<T>(c, bc) && march_blk_on<T>(H, l, bc);
     if (big || tile_on<T>(H, l)) {
-      // each leg of the block level in one launch over all blocks: the two-sweep streaming
+      // each leg of the block level in one launch over all blocks: the streaming
       // passes on the large levels, region tiles below
       const bool timed = timed_top && l == H.L && ktiming;
       const double cellsT = (double)cells(l) * sizeof(T);
@@ -983,11 +984,11 @@ struct Solver {
       const bool norm = want_norm && sizeof(T) == 8;
       const SumSink sink = norm ? norm_sink() : SumSink{};
       if (timed) kernel_begin(true);
-      if (big) march_up<T>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, norm ? &sink : nullptr, nl, H.h[l], H.omega, bc, s, Lm,
+      if (big) march_up<T>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, norm ? &sink : nullptr, nl, H.npost, H.h[l], H.omega, bc, s, Lm,
                            aux_of());
       else tile_up<T>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, norm ? &sink : nullptr, nl, Lm, H.npost, H.h[l], H.omega, bc, s);
       if (timed)
-        kernel_end(big ? march_name<T>(true, norm, bc, true) : tile_name<T>(H.npost, true, bc, nl),
+        kernel_end(big ? march_name<T>(H.npost, true, norm, bc, true) : tile_name<T>(H.npost, true, bc, nl),
                    3 * cellsT + cellsT / 8);
       return norm;
     }
@@ -1494,7 +1495,7 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
       }
       if (fas) {
         // as below: the head pass of the next cycle measures this cycle's result (or the
-        // two-sweep up pass does)
+        // streaming up pass does)
         const bool normed = S.fas_cycle(H64, pbar, L, head_mode ? 1 : 0, !head_mode);
         S.head_done = false;
         if (head_mode && cyc + 1 < ncyc) S.head(H64, bcL);
@@ -1728,8 +1729,8 @@ int autotune_blocks(mg_ctx* c, const mg_params* p, int Lb, int reps) {
       LevelBC hom = bc;
       (void)hipEventRecord(e0, s);
       for (int r = 0; r < reps; ++r) {
-        march_down<T>(buf[0], buf[1], buf[2], fc, uc, 1 << l, h, p->omega, bc, s, Lm);
-        (void)march_up<T>(buf[1], buf[0], buf[2], uc, hom, nullptr, 1 << l, h, p->omega, bc, s, Lm);
+        march_down<T>(buf[0], buf[1], buf[2], fc, uc, 1 << l, 2, h, p->omega, bc, s, Lm);
+        (void)march_up<T>(buf[1], buf[0], buf[2], uc, hom, nullptr, 1 << l, 2, h, p->omega, bc, s, Lm);
       }
       (void)hipEventRecord(e1, s);
       HIP_CHECK(c, hipEventSynchronize(e1));
@@ -2024,13 +2025,13 @@ int op_smooth(mg_ctx* c, int n, double h, double omega, int sweeps, bool zero_in
   return op_epilogue(c);
 }
 
-// Do the operator entry points run a V(2,2) leg of this level as one two-sweep streaming pass
+// Do the operator entry points run a leg of this level as one streaming pass
 // (the context's "march" setting, as in the solver; any level the passes support)?
 template <typename T>
 bool op_march(const mg_ctx* c, int n, int sweeps, const LevelBC& b) {
   const int v = c->march[sizeof(T) == 8 ? 0 : 1];
   const int mode = v < 0 ? 2 : v;
-  if (mode == 0 || sweeps != 2 || n < march_min_n<T>(c, b)) return false;
+  if (mode == 0 || !march_sweeps_ok(sweeps) || n < march_min_n<T>(c, b)) return false;
   if (mode == 1)
     for (int f = 0; f < 6; ++f)
       if (b.kind[f] != BC_PERIODIC) return false;
@@ -2074,7 +2075,7 @@ bool op_leg_scratch(mg_ctx* c, int n, double h, LevelBC* b, T** tmp, const T** f
   return true;
 }
 
-// Do the operator entry points run a V(2,2) leg of this level as one region-tile launch (the
+// Do the operator entry points run a leg of this level as one region-tile launch (the
 // context's "tile" setting, on the levels the solver uses them for: 32^3 .. 128^3, below the
 // streaming passes)?
 template <typename T>
@@ -2098,7 +2099,7 @@ int op_down(mg_ctx* c, int n, double h, double omega, int npre, const mg_level_b
     T* tmp = nullptr;
     const T* fv = f;
     if (op_leg_scratch<T>(c, n, h, &hb, &tmp, &fv, s, &st)) {
-      if (march) march_down<T>(u, tmp, fv, fc, uc, n, h, omega, hb, s);
+      if (march) march_down<T>(u, tmp, fv, fc, uc, n, npre, h, omega, hb, s);
       else tile_down<T>(u, tmp, fv, fc, nullptr, uc, n, 0, npre, h, omega, hb, s);
       HIP_CHECK(c, hipMemcpyAsync(u, tmp, cells(ilog2(n)) * sizeof(T), hipMemcpyDeviceToDevice, s));
       return op_epilogue(c);
@@ -2146,7 +2147,7 @@ int op_up(mg_ctx* c, int n, double h, double omega, int npost, const mg_level_bc
     T* tmp = nullptr;
     const T* fv = f;
     if (op_leg_scratch<T>(c, n, h, &hb, &tmp, &fv, s, &st)) {
-      if (march) march_up<T>(u, tmp, fv, uc, bcc, nullptr, n, h, omega, hb, s);
+      if (march) march_up<T>(u, tmp, fv, uc, bcc, nullptr, n, npost, h, omega, hb, s);
       else tile_up<T>(u, tmp, fv, uc, bcc, nullptr, n, 0, npost, h, omega, hb, s);
       HIP_CHECK(c, hipMemcpyAsync(u, tmp, cells(ilog2(n)) * sizeof(T), hipMemcpyDeviceToDevice, s));
       return op_epilogue(c);

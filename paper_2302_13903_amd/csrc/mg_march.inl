@@ -61,6 +61,10 @@
 // face's rule.
 #include "mg_march.h"
 
+#if !defined(MG_MARCH_T) || !defined(MG_MARCH_NS)
+#error "define MG_MARCH_T and MG_MARCH_NS (the precision and the sweeps per pass this translation unit instantiates)"
+#endif
+
 #include <algorithm>
 #include <cstring>
 #include <type_traits>
@@ -76,8 +80,10 @@ constexpr int kLanes = 64;
 constexpr int kR = 4;          // rows per lane (a band)
 constexpr int kSL = 32;        // lanes per x segment (a half-wave)
 constexpr int kTX = 2 * kSL;   // tile width
-constexpr int kRing = 6;       // u planes held per lane
-constexpr int kFSlots = 3;     // f planes held in LDS per lane
+constexpr int kNS = MG_MARCH_NS;         // sweeps per pass
+constexpr int kStages = 2 * kNS;         // colour updates
+constexpr int kRing = kStages + 2;       // u planes held per lane
+constexpr int kFSlots = kStages - 1;     // f planes held in LDS per lane
 constexpr int kHalo = 6;       // tile overlap in x and y
 
 struct MarchArgs {
@@ -178,10 +184,7 @@ __device__ __forceinline__ unsigned blk_z(int Lm, int k) {
 
 // Waves per workgroup: 8 (a 64 x 64 tile, 2 waves per SIMD with up to 256 registers per lane;
 // FP32 on 16 waves, a 64 x 128 tile, needs more than the 128 registers that leaves per lane).
-template <typename T>
-constexpr int cfg_W() {
-  return 8;
-}
+constexpr int kWaves = kMarchWaves;
 
 // WALLS: 0 = every face of the level is periodic (no boundary code compiled in); 1 = walls
 // only across z (x and y periodic, or a tile that reaches no x or y wall with its halo: no x/y
@@ -197,15 +200,16 @@ template <typename T, int W, bool UP, bool NORM, int WALLS, bool BLK, bool FAS, 
 __device__ __forceinline__ void march_body(const MarchArgs& A) {
   constexpr bool PER = WALLS == 0;                // every face periodic
   constexpr bool XYW = WALLS == 2;                // x or y walls may be in reach
+  constexpr bool DREG = PER || kNS == 1;          // registers to carry the red partial defects in
   constexpr int R = kR, SL = kSL, NB = 2 * W, NT = kLanes * W;
   constexpr bool DEF = !UP;                       // down: restricted defect
   constexpr bool DSTAGE = DEF || NORM;            // a defect stage after the sweeps
-  constexpr int HZ = DSTAGE ? 5 : 4;              // planes marched before (and after) the chunk
-  __shared__ T xe[4][NB][2][SL];                  // per stage: the bands' first and last rows
+  constexpr int HZ = kStages + (DSTAGE ? 1 : 0);  // planes marched before (and after) the chunk
+  __shared__ T xe[kStages][NB][2][SL];                  // per stage: the bands' first and last rows
   __shared__ T xd[DSTAGE ? NB : 1][2][SL];        // the same of the defect stage's black cells
   __shared__ Pair<T> fl[kFSlots][R][NT];
   // the red cells' partial defects carried to the next step, where registers are short
-  __shared__ T dredl[PER ? 1 : R][PER ? 1 : NT];
+  __shared__ T dredl[DREG ? 1 : R][DREG ? 1 : NT];
 
   const int tid = threadIdx.x;
   const int lane = tid & (kLanes - 1);
@@ -357,10 +361,10 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
     T u[kRing][R][2];
     T pu[R][2], pf[R][2];      // prefetched u of plane P+1 and f of plane P
     T fr[R][2];                // f of plane P-1
-    T dred[PER ? R : 1];      // red cells' partial defects of plane P-4 (completed next step)
-    auto dred_get = [&](int r) __attribute__((always_inline)) -> T { return PER ? dred[PER ? r : 0] : dredl[PER ? 0 : r][PER ? 0 : tid]; };
+    T dred[DREG ? R : 1];      // red cells' partial defects of plane P-4 (completed next step)
+    auto dred_get = [&](int r) __attribute__((always_inline)) -> T { return DREG ? dred[DREG ? r : 0] : dredl[DREG ? 0 : r][DREG ? 0 : tid]; };
     auto dred_set = [&](int r, T v) __attribute__((always_inline)) {
-      if constexpr (PER) dred[r] = v;
+      if constexpr (DREG) dred[r] = v;
       else dredl[r][tid] = v;
     };
     T pend[R / 2], stash[R / 2];   // down: row-pair defect sums (black cells of P-4; even plane)
@@ -622,8 +626,8 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
         cell(Ir{}, Red{}, (T)0);
       });
       // (the black cells' y neighbours beyond the band are those of the last black stage)
-      cell(I0{}, Black{}, xe[3][bandb][1][xl]);
-      cell(IL{}, Black{}, xe[3][banda][0][xl]);
+      cell(I0{}, Black{}, xe[kStages - 1][bandb][1][xl]);
+      cell(IL{}, Black{}, xe[kStages - 1][banda][0][xl]);
       __syncthreads();
       cell(I0{}, Red{}, xd[bandb][1][xl]);
       cell(IL{}, Red{}, xd[banda][0][xl]);
@@ -681,64 +685,62 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
       const int Pn = t + 1 < nsteps ? P + 1 : P - 1;
       load_plane(Pn);
       load_taps(Pn, std::integral_constant<int, ((HZ + K + 1) & 1) ? 1 : 2>{});
-      constexpr int s0 = K, s1 = (K + 5) % 6, s2 = (K + 4) % 6, s3 = (K + 3) % 6, s4 = (K + 2) % 6,
-                    s5 = (K + 1) % 6;
-      using I0 = std::integral_constant<int, 0>;
-      using I1 = std::integral_constant<int, 1>;
-      using I2 = std::integral_constant<int, 2>;
-      using I3 = std::integral_constant<int, 3>;
-      using Par1 = std::integral_constant<int, (HZ + K + 1) & 1>;
-      using Par2 = std::integral_constant<int, (HZ + K + 2) & 1>;
-      using Par3 = std::integral_constant<int, (HZ + K + 3) & 1>;
-      using Par4 = std::integral_constant<int, (HZ + K + 4) & 1>;
-      using FsReg = std::integral_constant<int, -1>;
-      using Fs2 = std::integral_constant<int, ((K - HZ - 2) % 3 + 6) % 3>;
-      using Fs3 = std::integral_constant<int, ((K - HZ - 3) % 3 + 6) % 3>;
-      using Fs4 = std::integral_constant<int, ((K - HZ - 4) % 3 + 6) % 3>;
-      edges_out(I0{}, Par1{}, u[s1]);
-      edges_out(I1{}, Par2{}, u[s2]);
-      edges_out(I2{}, Par3{}, u[s3]);
-      edges_out(I3{}, Par4{}, u[s4]);
+      // ring slot and parity of plane P - j, LDS slot of its f
+      auto slot = [](int j) constexpr { return (K - j + 2 * kRing) % kRing; };
+      auto fslot = [](int j) constexpr { return (K - HZ - j + 12 * kFSlots) % kFSlots; };
+      auto up_u = [&](auto jj) __attribute__((always_inline)) -> T (&)[R][2] { return u[slot(decltype(jj)::value)]; };
+      using ParL = std::integral_constant<int, (HZ + K + kStages) & 1>;
+      using FsL = std::integral_constant<int, fslot(kStages)>;
+      static_for<kStages>([&](auto ss) __attribute__((always_inline)) {
+        constexpr int S = decltype(ss)::value;
+        edges_out(ss, std::integral_constant<int, (HZ + K + S + 1) & 1>{}, up_u(std::integral_constant<int, S + 1>{}));
+      });
       auto stages = [&](auto cIN) __attribute__((always_inline)) {
-        colour(I0{}, Par1{}, FsReg{}, cIN, u[s2], u[s1], u[s0], P - 1);   // red, sweep 1
-        colour(I1{}, Par2{}, Fs2{}, cIN, u[s3], u[s2], u[s1], P - 2);     // black, sweep 1
-        colour(I2{}, Par3{}, Fs3{}, cIN, u[s4], u[s3], u[s2], P - 3);     // red, sweep 2
-        colour(I3{}, Par4{}, Fs4{}, cIN, u[s5], u[s4], u[s3], P - 4);     // black, sweep 2
+        // red, black (, red, black): stage S on plane P - 1 - S
+        static_for<kStages>([&](auto ss) __attribute__((always_inline)) {
+          constexpr int S = decltype(ss)::value;
+          colour(ss, std::integral_constant<int, (HZ + K + S + 1) & 1>{},
+                 std::integral_constant<int, S == 0 ? -1 : fslot(S + 1)>{}, cIN,
+                 up_u(std::integral_constant<int, S + 2>{}), up_u(std::integral_constant<int, S + 1>{}),
+                 up_u(std::integral_constant<int, S>{}), P - 1 - S);
+        });
       };
       stages(std::true_type{});
       __syncthreads();
       stages(std::false_type{});
-      if constexpr (DSTAGE) defect(Par4{}, Fs4{}, u[s5], u[s4], u[s3], P - 4);
+      if constexpr (DSTAGE)
+        defect(ParL{}, FsL{}, u[slot(kStages + 1)], u[slot(kStages)], u[slot(kStages - 1)], P - kStages);
       else __syncthreads();   // (with a defect stage: its barrier) xe is free for the next step
       prolong_apply(Pn, std::integral_constant<int, (HZ + K + 1) & 1>{});
       keep_in(Pn);
-      // u(P+1) enters the ring in the slot of P-5; f(P-1) moves to the LDS slot of P-4 (done
-      // with), f(P) into the registers
+      // u(P+1) enters the ring in the slot of the oldest plane; f(P-1) moves to the LDS slot of the
+      // last stage's plane (done with), f(P) into the registers
+      constexpr int so = slot(kStages + 1), sl = slot(kStages);
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        u[s5][r][0] = pu[r][0]; u[s5][r][1] = pu[r][1];
-        fl[Fs4::value][r][tid] = Pair<T>{fr[r][0], fr[r][1]};
+        u[so][r][0] = pu[r][0]; u[so][r][1] = pu[r][1];
+        fl[FsL::value][r][tid] = Pair<T>{fr[r][0], fr[r][1]};
         fr[r][0] = pf[r][0]; fr[r][1] = pf[r][1];
       }
-      // Plane P-4 is final, and on odd planes P-5 its coarse cells: out, once the loads of plane P+1
+      // The last stage's plane is final, and on odd planes the one before's coarse cells: out, once the loads of plane P+1
       // are in (loads and stores complete in one order, so a wait for the loads further on would
       // wait for these stores)
-      arrived(u[s5], fr);
+      arrived(u[so], fr);
       {
-        const int p = P - 4;
+        const int p = P - kStages;
         if (p >= z0 && p < zend && out_x) {
           const int pg = p & nm;
 #pragma unroll
           for (int r = 0; r < R; ++r)
             if (out_y[r]) {
               typedef T ntv2 __attribute__((ext_vector_type(2)));
-              const ntv2 v = {u[s4][r][0], u[s4][r][1]};
+              const ntv2 v = {u[sl][r][0], u[sl][r][1]};
               __builtin_nontemporal_store(v, reinterpret_cast<ntv2*>(const_cast<T*>(at(uout, r, pg))));
             }
         }
       }
-      if constexpr (DEF && ((HZ + K + 5) & 1) != 0) {
-        const int p = P - 5;
+      if constexpr (DEF && ((HZ + K + kStages + 1) & 1) != 0) {
+        const int p = P - kStages - 1;
         if (p >= z0 && p < zend && out_x) {
           T* __restrict__ fcp = reinterpret_cast<T*>(A.fc);
           T* __restrict__ ucp = reinterpret_cast<T*>(A.uc0);
@@ -754,12 +756,7 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
       }
     };
     for (int g = 0; g < nsteps; g += kRing) {
-      step(g, std::integral_constant<int, 0>{});
-      step(g, std::integral_constant<int, 1>{});
-      step(g, std::integral_constant<int, 2>{});
-      step(g, std::integral_constant<int, 3>{});
-      step(g, std::integral_constant<int, 4>{});
-      step(g, std::integral_constant<int, 5>{});
+      static_for<kRing>([&](auto kk) __attribute__((always_inline)) { step(g, kk); });
     }
   }
   if constexpr (NORM) {
@@ -777,19 +774,19 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
   }
 }
 
-template <typename T, int W, bool UP, bool NORM, int WALLS, bool BLK>
+template <typename T, int W, bool UP, bool NORM, int WALLS, bool BLK, int NS>
 __global__ void __launch_bounds__(kLanes* W) k_march(MarchArgs A) {
   march_body<T, W, UP, NORM, WALLS, BLK, false, false>(A);
 }
 
 // The down pass of a Full Approximation Scheme cycle (dense FP64 levels).
-template <typename T, int W, int WALLS>
+template <typename T, int W, int WALLS, int NS>
 __global__ void __launch_bounds__(kLanes* W) k_march_fas(MarchArgs A) {
   march_body<T, W, false, false, WALLS, false, true, false>(A);
 }
 
 // The down pass from u = 0, which is not read (the first leg of a mixed-precision correction).
-template <typename T, int W, int WALLS>
+template <typename T, int W, int WALLS, int NS>
 __global__ void __launch_bounds__(kLanes* W) k_march_zero(MarchArgs A) {
   march_body<T, W, false, false, WALLS, false, false, true>(A);
 }
@@ -841,8 +838,8 @@ void launch_march(MarchArgs A, hipStream_t s, const MarchAux* aux) {
   for (int f = 0; f < 6; ++f) per = per && A.bc.kind[f] == BC_PERIODIC;
   bool xyper = true;
   for (int f = 0; f < 4; ++f) xyper = xyper && A.bc.kind[f] == BC_PERIODIC;
-  constexpr int W = cfg_W<T>();
-  constexpr int HZ = (!UP || NORM) ? 5 : 4;
+  constexpr int W = kWaves;
+  constexpr int HZ = kStages + (!UP || NORM ? 1 : 0);
   A.L = ilog2(A.n);
   A.xo = kTX - 2 * kHalo;
   A.yo = kR * 2 * W - 2 * kHalo;
@@ -876,8 +873,8 @@ void launch_march(MarchArgs A, hipStream_t s, const MarchAux* aux) {
     if (timed) (void)hipEventRecord(lt.e0, s);
     (void)hipEventRecord(aux->fork, s);
     (void)hipStreamWaitEvent(aux->s2, aux->fork, 0);
-    hipLaunchKernelGGL((k_march<T, W, UP, NORM, 2, BLK>), dim3(gr), dim3(kLanes * W), 0, aux->s2, Ar);
-    hipLaunchKernelGGL((k_march<T, W, UP, NORM, 1, BLK>), dim3(gi), dim3(kLanes * W), 0, s, Ai);
+    hipLaunchKernelGGL((k_march<T, W, UP, NORM, 2, BLK, kNS>), dim3(gr), dim3(kLanes * W), 0, aux->s2, Ar);
+    hipLaunchKernelGGL((k_march<T, W, UP, NORM, 1, BLK, kNS>), dim3(gi), dim3(kLanes * W), 0, s, Ai);
     (void)hipEventRecord(aux->join, aux->s2);
     (void)hipStreamWaitEvent(s, aux->join, 0);
     if (timed) (void)hipEventRecord(lt.e1, s);
@@ -888,9 +885,9 @@ void launch_march(MarchArgs A, hipStream_t s, const MarchAux* aux) {
   A.ntiles = A.tiles_x * A.tiles_y * chunks;
   const int grid = (A.ntiles + 7) / 8 * 8;
   A.sink.total = grid;
-  if (per) launch_maybe_timed(k_march<T, W, UP, NORM, 0, BLK>, dim3(grid), dim3(kLanes * W), 0, s, A);
-  else if (xyper) launch_maybe_timed(k_march<T, W, UP, NORM, 1, BLK>, dim3(grid), dim3(kLanes * W), 0, s, A);
-  else launch_maybe_timed(k_march<T, W, UP, NORM, 2, BLK>, dim3(grid), dim3(kLanes * W), 0, s, A);
+  if (per) launch_maybe_timed(k_march<T, W, UP, NORM, 0, BLK, kNS>, dim3(grid), dim3(kLanes * W), 0, s, A);
+  else if (xyper) launch_maybe_timed(k_march<T, W, UP, NORM, 1, BLK, kNS>, dim3(grid), dim3(kLanes * W), 0, s, A);
+  else launch_maybe_timed(k_march<T, W, UP, NORM, 2, BLK, kNS>, dim3(grid), dim3(kLanes * W), 0, s, A);
 }
 
 // The down passes of FAS and from zero: one launch over every tile, the wall form chosen by the
@@ -900,24 +897,24 @@ void launch_march_down1(MarchArgs A, hipStream_t s) {
   bool per = true, xyper = true;
   for (int f = 0; f < 6; ++f) per = per && A.bc.kind[f] == BC_PERIODIC;
   for (int f = 0; f < 4; ++f) xyper = xyper && A.bc.kind[f] == BC_PERIODIC;
-  constexpr int W = cfg_W<T>();
+  constexpr int W = kWaves;
   A.L = ilog2(A.n);
   A.xo = kTX - 2 * kHalo;
   A.yo = kR * 2 * W - 2 * kHalo;
   A.tiles_x = (A.n + A.xo - 1) / A.xo;
   A.tiles_y = (A.n + A.yo - 1) / A.yo;
   A.set = 0;
-  A.zc = march_zchunk(A.n, A.tiles_x * A.tiles_y, 5);
+  A.zc = march_zchunk(A.n, A.tiles_x * A.tiles_y, kStages + 1);
   A.ntiles = A.tiles_x * A.tiles_y * ((A.n + A.zc - 1) / A.zc);
   const int grid = (A.ntiles + 7) / 8 * 8;
   if constexpr (ZERO) {
-    if (per) launch_maybe_timed(k_march_zero<T, W, 0>, dim3(grid), dim3(kLanes * W), 0, s, A);
-    else if (xyper) launch_maybe_timed(k_march_zero<T, W, 1>, dim3(grid), dim3(kLanes * W), 0, s, A);
-    else launch_maybe_timed(k_march_zero<T, W, 2>, dim3(grid), dim3(kLanes * W), 0, s, A);
+    if (per) launch_maybe_timed(k_march_zero<T, W, 0, kNS>, dim3(grid), dim3(kLanes * W), 0, s, A);
+    else if (xyper) launch_maybe_timed(k_march_zero<T, W, 1, kNS>, dim3(grid), dim3(kLanes * W), 0, s, A);
+    else launch_maybe_timed(k_march_zero<T, W, 2, kNS>, dim3(grid), dim3(kLanes * W), 0, s, A);
   } else {
-    if (per) launch_maybe_timed(k_march_fas<T, W, 0>, dim3(grid), dim3(kLanes * W), 0, s, A);
-    else if (xyper) launch_maybe_timed(k_march_fas<T, W, 1>, dim3(grid), dim3(kLanes * W), 0, s, A);
-    else launch_maybe_timed(k_march_fas<T, W, 2>, dim3(grid), dim3(kLanes * W), 0, s, A);
+    if (per) launch_maybe_timed(k_march_fas<T, W, 0, kNS>, dim3(grid), dim3(kLanes * W), 0, s, A);
+    else if (xyper) launch_maybe_timed(k_march_fas<T, W, 1, kNS>, dim3(grid), dim3(kLanes * W), 0, s, A);
+    else launch_maybe_timed(k_march_fas<T, W, 2, kNS>, dim3(grid), dim3(kLanes * W), 0, s, A);
   }
 }
 
@@ -937,8 +934,8 @@ MarchArgs base_args(const T* uin, T* uout, const T* f, int n, double h, double o
 
 }  // namespace
 
-template <typename T>
-void march_down(const T* uin, T* uout, const T* f, T* fc, T* uc0, int n, double h, double omega, const LevelBC& bc,
+template <typename T, int NS>
+void march_down_ns(const T* uin, T* uout, const T* f, T* fc, T* uc0, int n, double h, double omega, const LevelBC& bc,
                 hipStream_t s, int Lm, const MarchAux* aux) {
   MarchArgs A = base_args(uin, uout, f, n, h, omega, bc);
   A.fc = fc;
@@ -949,8 +946,8 @@ void march_down(const T* uin, T* uout, const T* f, T* fc, T* uc0, int n, double 
   else launch_march<T, false, false, false>(A, s, aux);
 }
 
-template <typename T>
-void march_down_fas(const T* uin, T* uout, const T* f, T* fc, T* pbar, T* uc0, int n, double h, double omega,
+template <typename T, int NS>
+void march_down_fas_ns(const T* uin, T* uout, const T* f, T* fc, T* pbar, T* uc0, int n, double h, double omega,
                     const LevelBC& bc, hipStream_t s) {
   MarchArgs A = base_args(uin, uout, f, n, h, omega, bc);
   A.fc = fc;
@@ -959,8 +956,8 @@ void march_down_fas(const T* uin, T* uout, const T* f, T* fc, T* pbar, T* uc0, i
   launch_march_down1<T, false>(A, s);
 }
 
-template <typename T>
-void march_up(const T* uin, T* uout, const T* f, const T* ec, const LevelBC& bcc, const SumSink* sink, int n, double h,
+template <typename T, int NS>
+void march_up_ns(const T* uin, T* uout, const T* f, const T* ec, const LevelBC& bcc, const SumSink* sink, int n, double h,
               double omega, const LevelBC& bc, hipStream_t s, int Lm, const MarchAux* aux) {
   MarchArgs A = base_args(uin, uout, f, n, h, omega, bc);
   A.ec = ec;
@@ -976,36 +973,13 @@ void march_up(const T* uin, T* uout, const T* f, const T* ec, const LevelBC& bcc
   }
 }
 
-template <typename T>
-std::string march_down1_name(bool zero, const LevelBC& bc) {
-  bool per = true, xyper = true;
-  for (int f = 0; f < 6; ++f) per = per && bc.kind[f] == BC_PERIODIC;
-  for (int f = 0; f < 4; ++f) xyper = xyper && bc.kind[f] == BC_PERIODIC;
-  return std::string(zero ? "k_march_zero<" : "k_march_fas<") + (sizeof(T) == 8 ? "double" : "float") + ", " + std::to_string(cfg_W<T>()) +
-         ", " + std::to_string(per ? 0 : (xyper ? 1 : 2)) + ">";
-}
-
-template <typename T>
-std::string march_name(bool up, bool norm, const LevelBC& bc, bool blk) {
-  auto b = [](bool v) { return std::string(v ? "true" : "false"); };
-  bool per = true, xyper = true;
-  for (int f = 0; f < 6; ++f) per = per && bc.kind[f] == BC_PERIODIC;
-  for (int f = 0; f < 4; ++f) xyper = xyper && bc.kind[f] == BC_PERIODIC;
-  const int walls = per ? 0 : (xyper ? 1 : 2);
-  return std::string("k_march<") + (sizeof(T) == 8 ? "double" : "float") + ", " + std::to_string(cfg_W<T>()) + ", " +
-         b(up) + ", " + b(up && norm) + ", " + std::to_string(walls) + ", " + b(blk) + ">";
-}
-
-#ifndef MG_MARCH_T
-#error "define MG_MARCH_T (the precision this translation unit instantiates)"
-#endif
-template void march_down<MG_MARCH_T>(const MG_MARCH_T*, MG_MARCH_T*, const MG_MARCH_T*, MG_MARCH_T*, MG_MARCH_T*, int,
-                                     double, double, const LevelBC&, hipStream_t, int, const MarchAux*);
-template void march_up<MG_MARCH_T>(const MG_MARCH_T*, MG_MARCH_T*, const MG_MARCH_T*, const MG_MARCH_T*, const LevelBC&,
-                                   const SumSink*, int, double, double, const LevelBC&, hipStream_t, int, const MarchAux*);
-template std::string march_name<MG_MARCH_T>(bool, bool, const LevelBC&, bool);
-template std::string march_down1_name<MG_MARCH_T>(bool, const LevelBC&);
-template void march_down_fas<MG_MARCH_T>(const MG_MARCH_T*, MG_MARCH_T*, const MG_MARCH_T*, MG_MARCH_T*, MG_MARCH_T*,
-                                         MG_MARCH_T*, int, double, double, const LevelBC&, hipStream_t);
+template void march_down_ns<MG_MARCH_T, kNS>(const MG_MARCH_T*, MG_MARCH_T*, const MG_MARCH_T*, MG_MARCH_T*, MG_MARCH_T*,
+                                             int, double, double, const LevelBC&, hipStream_t, int, const MarchAux*);
+template void march_up_ns<MG_MARCH_T, kNS>(const MG_MARCH_T*, MG_MARCH_T*, const MG_MARCH_T*, const MG_MARCH_T*,
+                                           const LevelBC&, const SumSink*, int, double, double, const LevelBC&,
+                                           hipStream_t, int, const MarchAux*);
+template void march_down_fas_ns<MG_MARCH_T, kNS>(const MG_MARCH_T*, MG_MARCH_T*, const MG_MARCH_T*, MG_MARCH_T*,
+                                                 MG_MARCH_T*, MG_MARCH_T*, int, double, double, const LevelBC&,
+                                                 hipStream_t);
 
 }  // namespace mg

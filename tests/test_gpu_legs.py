@@ -139,3 +139,53 @@ def test_legs_with_face_values_under_a_budget(mg, n, f32):
     su = max(float(u.abs().max()), h * h * float(f.abs().max())) + 2 * max(float(b.abs().max()) for b in bext if b is not None)
     assert np.abs(out[0][0] - out[1][0]).max() <= 2 * eps * 6 * su
     assert np.abs(out[0][1] - out[1][1]).max() <= 2 * eps * (float(f.abs().max()) + 12 * su / h ** 2)
+
+
+@pytest.mark.parametrize("f32", [False, True], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("n,kind", [(128, "periodic"), (256, "layer"), (256, "fixed"), (256, "mixed")])
+def test_streaming_legs_of_one_sweep(mg, n, kind, f32):
+    """The streaming passes with one sweep per leg (bounds as for the tile legs)."""
+    kinds = KINDS[kind]
+    hom = [k if k in (PERIODIC, ZERO_GRADIENT) else FIXED for k in kinds]
+    print(f"streaming legs n={n} {kind} f32={f32}", flush=True)
+    rng = np.random.default_rng(n)
+    u, e = rng.standard_normal((n,) * 3), rng.standard_normal((n // 2,) * 3)
+    f = rng.standard_normal((n,) * 3) * n * n
+    bext = [rng.standard_normal((n + 2,) * 2) if k == FIXED else None for k in kinds]
+    dt, h = (torch.float32 if f32 else torch.float64), 1.0 / n
+    if f32:
+        u, e, f = (a.astype(np.float32).astype(np.float64) for a in (u, e, f))
+    dbext = [None if b is None else dev(b) for b in bext]
+    ctx = mg.Context(0)
+    ctx.set_tuning("fusedmin fp32 128\n")
+    su = max(np.abs(u).max(), np.abs(e).max(), h * h * np.abs(f).max()) + 2 * max([0.0] + [np.abs(b).max() for b in bext if b is not None])
+    eps = 40 * float(np.finfo(np.float32).eps) if f32 else 1e-13
+    down, up = (mg.mg_op_down_f32, mg.mg_op_up_f32) if f32 else (mg.mg_op_down, mg.mg_op_up)
+
+    ref = sweeps(u, f, h, kinds, bext, 1)
+    ref_fc = oracle.restrict(oracle.defect(ref, f, h, kinds, bext))
+    du, fc, uc = dev(u, dt), dev(e, dt), dev(e, dt)
+    down(du, dev(f, dt), fc, uc, h, OMEGA, 1, kinds, dbext, ctx=ctx)
+    assert np.abs(host(du) - ref).max() <= eps * 6 * su
+    assert np.abs(host(fc) - ref_fc).max() <= eps * (np.abs(f).max() + 12 * su / h ** 2)
+    assert float(uc.abs().max()) == 0.0
+
+    ref = sweeps(oracle.prolong_add(e, u, hom), f, h, kinds, bext, 1)
+    du = dev(u, dt)
+    up(du, dev(f, dt), dev(e, dt), h, OMEGA, 1, kinds, dbext, hom, ctx=ctx)
+    assert np.abs(host(du) - ref).max() <= eps * 12 * su
+
+
+@pytest.mark.parametrize("kind", ["periodic", "mixed"])
+def test_one_sweep_cycles_agree_across_layouts_and_schemes(mg, kind):
+    """V(1,1) cycles on 256^3: the block layout gives the dense potential and history, and so does
+    the Full Approximation Scheme, as every whole-solve check: phi to 1e-10."""
+    n, kinds = 256, KINDS[kind]
+    rho = dev(wl.gaussian_clumps(n, 5, n_clumps=6))
+    a, ha, _ = mg.solve(rho, 1.0 / n, kinds, fixed_cycles=3, npre=1, npost=1)
+    b, hb, _ = mg.solve(mg.to_blocks(rho, 16), 1.0 / n, kinds, fixed_cycles=3, npre=1, npost=1, layout="blocks")
+    c, hc, _ = mg.solve(rho, 1.0 / n, kinds, fixed_cycles=3, npre=1, npost=1, scheme="fas")
+    a = host(a)
+    assert rel(host(mg.from_blocks(b, n, 16)), a) < 1e-10 and rel(host(c), a) < 1e-10
+    for h in (hb, hc):
+        assert len(h) == len(ha) and all(abs(x - y) <= 1e-6 * y for x, y in zip(h, ha))
