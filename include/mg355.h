@@ -154,13 +154,13 @@ int mg_autotune(mg_ctx *ctx, const mg_params *p, int reps);
  * "tail fp64|fp32 l" (highest level, 1..4, solved by the single-workgroup LDS tail) and
  * "tb fp64|fp32 0|1" (1: large-level sweeps two per pass over HBM) and "blkz fp64|fp32 0|1"
  * (MeshBlock layout, 1: streaming passes across blocks on the large block levels) and
- * "march fp64|fp32 0|1|2" (V(2,2) legs of the levels >= 256^3 -- all-periodic FP64 ones from 128^3 --, or >= the
- * fusedmin size when that was set larger, as two streaming passes -- down: two sweeps + restricted defect; up:
- * prolongation + two sweeps + norm -- 0 off, 1 when every face is periodic, 2 always (default))
+ * "march fp64|fp32 0|1|2" (legs of one or two sweeps on the levels >= 128^3, or >= the fusedmin size
+ * when that was set larger, as two streaming passes -- down: sweeps + restricted defect; up:
+ * prolongation + sweeps + norm -- 0 off, 1 when every face is periodic, 2 always (default))
  * and "tile fp64|fp32 0|1" (1, the default: with one or two sweeps per leg, each leg of the
  * levels 32^3 .. 128^3 that the streaming passes do not take runs as one region-tile launch) and "split fp64 0|1"
- * (1, the default: an FP64 streaming pass of a level with x or y walls runs its interior tiles
- * and its wall tiles as two launches on the context's second stream and the caller's, joined
+ * (1, the default: an FP64 streaming pass of a level with x or y walls whose interior tiles are
+ * the more runs them and its wall tiles as two launches on the context's second stream and the caller's, joined
  * before the pass returns; 0: one launch; the serving runtime sets 0) and "inner fp32 k"
  * (precision MG_PREC_MIXED on grids above the LDS tail: k = 1..4 FP32 V-cycles per outer
  * defect-correction step, each outer step then contracting the residual as k V-cycles do;
@@ -375,15 +375,15 @@ int mg_op_coarsest(mg_ctx *ctx, double h, const mg_level_bc *bc, double *u, cons
 
 /* Fused down step of a V-cycle level (Alg. 1 steps 1-3): `npre` smoothing sweeps of u,
  * then fc = restriction of the defect f - L u; uc = 0.  u, f: device n^3; fc, uc: (n/2)^3.
- * The kernels follow the context's schedule as the solver does: with npre = 2 on n >= 128 and
- * the "march" setting allowing it, one two-sweep streaming pass; otherwise the defect fused
+ * The kernels follow the context's schedule as the solver does: with npre = 1 or 2 on n >= 128
+ * and the "march" setting allowing it, one streaming pass; otherwise the defect fused
  * into the last sweep or as its own pass ("pass" lines of mg_tuning_set). */
 int mg_op_down(mg_ctx *ctx, int n, double h, double omega, int npre, const mg_level_bc *bc,
                double *u, const double *f, double *fc, double *uc, void *stream);
 
 /* Fused up step of a V-cycle level (Alg. 1 steps 5-7): u += trilinear(uc) with uc's ghosts
- * from bc_coarse, then `npost` smoothing sweeps with bc (with npost = 2 on n >= 128 and the
- * "march" setting allowing it, in one two-sweep streaming pass). */
+ * from bc_coarse, then `npost` smoothing sweeps with bc (with npost = 1 or 2 on n >= 128
+ * and the "march" setting allowing it, in one streaming pass). */
 int mg_op_up(mg_ctx *ctx, int n, double h, double omega, int npost, const mg_level_bc *bc,
              const mg_level_bc *bc_coarse, double *u, const double *f, const double *uc,
              void *stream);

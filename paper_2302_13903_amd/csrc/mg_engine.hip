@@ -136,8 +136,7 @@ struct mg_ctx {
   // prolongation + two sweeps [+ norm]): 0 = off, 1 = on levels whose faces are all periodic,
   // 2 = on every level; -1 = the built-in default (2)
   int march[2] = {-1, -1};
-  // V(2,2) legs of the levels 32^3 .. 128^3 (and the MeshBlock levels below the streaming
-  // passes) as one region-tile launch each: 1 = on (default), 0 = per-operator launches
+  // legs of the levels 32^3 .. 128^3 (and the MeshBlock levels) below the streaming passes as one region-tile launch each: 1 = on (default), 0 = per-operator launches
   int tile[2] = {-1, -1};
 };
 
@@ -319,16 +318,13 @@ struct Hier {
 };
 
 // Smallest level side on which the streaming passes run, or the one-sweep passes' threshold
-// ("fusedmin") when that was set larger.  At 128^3 the passes are taken in FP64 on an all-periodic
-// level only (40 + 34 us for the two legs against 38 + 46 us as region tiles); with walls the
-// tiles win (43 + 56 us against 84 + 96 us), and in FP32 (24 + 25 us against 40 + 39 us with walls;
-// 25 us a leg either way without).
+// ("fusedmin") when that was set larger.  At 128^3 a V-cycle takes, as streaming passes and as
+// region tiles: FP64 V(1,1) 96 and 114 us fixed, V(2,2) 150 and 151 us fixed, 110 and 120 us
+// periodic; mixed V(2,2) 162 and 173 us fixed, 137 and 150 us periodic.  At 64^3 a pass has
+// four tiles of columns and too few planes.
 template <typename T>
-int march_min_n(const mg_ctx* c, const LevelBC& bc) {
-  const int v = c->fused_min_n[sizeof(T) == 8 ? 0 : 1];
-  bool per = sizeof(T) == 8;
-  for (int f = 0; f < 6; ++f) per = per && bc.kind[f] == BC_PERIODIC;
-  return std::max(per ? kMarchMinN : 2 * kMarchMinN, v);
+int march_min_n(const mg_ctx* c) {
+  return std::max(kMarchMinN, c->fused_min_n[sizeof(T) == 8 ? 0 : 1]);
 }
 
 // Does a MeshBlock level of 2^l cells per side fit the streaming passes' 32-bit block index?
@@ -412,7 +408,7 @@ struct Solver {
       else return false;
     } else {
       if (L <= Lb) return false;
-      const bool big = c->blk_zmarch[0] != 0 && (1 << L) >= march_min_n<double>(c, bc) && march_blk_on<double>(H, L, bc);
+      const bool big = c->blk_zmarch[0] != 0 && (1 << L) >= march_min_n<double>(c) && march_blk_on<double>(H, L, bc);
       if (!big && !tile_on<double>(H, L)) return false;
       blk_down_leg<double>(H, L, bc, big, timed);
     }
@@ -515,7 +511,7 @@ struct Solver {
     const int mode = c->march[sizeof(T) == 8 ? 0 : 1] < 0 ? 2 : c->march[sizeof(T) == 8 ? 0 : 1];
     if (mode == 0 || !use_fused || !H.u2[l] || l == H.T_top || Lb >= 0) return false;
     if (!march_sweeps_ok(H.npre) || !march_sweeps_ok(H.npost)) return false;
-    if ((1 << l) < march_min_n<T>(c, bc) || tblock_on<T>()) return false;
+    if ((1 << l) < march_min_n<T>(c) || tblock_on<T>()) return false;
     if (mode == 1)
       for (int f = 0; f < 6; ++f)
         if (bc.kind[f] != BC_PERIODIC) return false;
@@ -972,7 +968,7 @@ struct Solver {
     const int Lm = l - Lb;
     const int nl = 1 << l;
     const int vz = c->blk_zmarch[sizeof(T) == 8 ? 0 : 1];
-    const bool big = vz != 0 && nl >= march_min_n<T>(c, bc) && march_blk_on<T>(H, l, bc);
+    const bool big = vz != 0 && nl >= march_min_n<T>(c) && march_blk_on<T>(H, l, bc);
     if (big || tile_on<T>(H, l)) {
       // each leg of the block level in one launch over all blocks: the streaming
       // passes on the large levels, region tiles below
@@ -1721,7 +1717,7 @@ int autotune_blocks(mg_ctx* c, const mg_params* p, int Lb, int reps) {
           if (ms < best_ms) { best_ms = ms; best = t; }
         }
     c->blk_tune[(sizeof(T) == 8 ? 0 : 1000) + 100 * Lm + Lb] = best;
-    if (l == L && p->npre == 2 && p->npost == 2 && (1 << l) >= march_min_n<T>(c, bc) && blk_march_fits(l)) {
+    if (l == L && p->npre == 2 && p->npost == 2 && (1 << l) >= march_min_n<T>(c) && blk_march_fits(l)) {
       // V(2,2) on the finest block level: both legs as the two-sweep streaming passes across
       // blocks against the four halo-tile sweeps alone (a lower bound on that schedule)
       T* fc = buf[3];
@@ -2031,7 +2027,7 @@ template <typename T>
 bool op_march(const mg_ctx* c, int n, int sweeps, const LevelBC& b) {
   const int v = c->march[sizeof(T) == 8 ? 0 : 1];
   const int mode = v < 0 ? 2 : v;
-  if (mode == 0 || !march_sweeps_ok(sweeps) || n < march_min_n<T>(c, b)) return false;
+  if (mode == 0 || !march_sweeps_ok(sweeps) || n < march_min_n<T>(c)) return false;
   if (mode == 1)
     for (int f = 0; f < 6; ++f)
       if (b.kind[f] != BC_PERIODIC) return false;

@@ -1,19 +1,20 @@
-// mg_march.inl -- two-sweep streaming passes of the large levels (the bandwidth path); included
-// once per precision by mg_march_f64.hip and mg_march_f32.hip.
+// mg_march.inl -- streaming passes of the large levels (the bandwidth path), one or two sweeps each;
+// included per precision and sweep count by mg_march_f64_1.hip and its siblings.
 //
 // One launch = the whole work of a V-cycle leg on one level, with u and f crossing HBM once:
-//   down (Alg. 1 steps 1-3): two red-black SOR sweeps (eqs. rbsor1-2), then the defect
+//   down (Alg. 1 steps 1-3): two (or one) red-black SOR sweeps (eqs. rbsor1-2), then the defect
 //        f - L u of the result (eq. defect) restricted to the coarse level (eq. restriction)
 //        and the coarse correction cleared;
 //   up   (Alg. 1 steps 5-7): u += trilinear prolongation of the coarse correction (eq.
-//        trilinear) as u is loaded, then two sweeps, optionally followed by the defect of the
+//        trilinear) as u is loaded, then the sweeps, optionally followed by the defect of the
 //        result summed as squares (the convergence norm of Sec. 2.3.7);
 //   FAS down (Alg. 3 steps 2-4, k_march_fas): the down leg with the swept u restricted beside
 //        the defect (phibar, also the coarse level's starting iterate).
 //
 // Work layout.  A workgroup of W = 8 waves owns a tile of 64 x 64 cells in x-y and marches a
 // chunk of z planes.  Each half-wave holds a band of R = 4 rows, each lane the x-pair (2l, 2l+1)
-// of those rows.  At the step that loads plane P the stages run on older planes:
+// of those rows.  At the step that loads plane P the stages run on older planes (two sweeps; one
+// sweep has the first two stages, a ring of four planes and one LDS slot):
 //   red sweep 1 on P-1, black 1 on P-2, red 2 on P-3, black 2 on P-4, defect on P-4,
 // so every stage reads its z-neighbours in the colour state it needs.  u of six planes lives in
 // registers (a ring), f of plane P-1 in registers and of P-2..P-4 in per-thread LDS slots.
@@ -37,8 +38,8 @@
 //  * addresses are a uniform plane base and a 32-bit offset, coarse taps take their walls' signs
 //    when they are used, not as they are loaded.
 // Measured before these and now: 128^3 periodic legs 39 / 34 -> 32 / 32 us; V-cycles at 256^3
-// 386 -> 337 us periodic, 451 -> 378 between z walls, 522 -> 442 fixed; at 512^3 2285 -> 2030 and
-// 2610 -> 2243 (periodic 2000 -> 1953).  Loading two planes ahead: FP32 equal, FP64 spills.
+// 386 -> 333 us periodic, 451 -> 352 between z walls, 522 -> 413 fixed; at 512^3 2285 -> 2005 and
+// 2610 -> 2193 (periodic 2000 -> 1953).  Loading two planes ahead: FP32 equal, FP64 spills.
 //
 // The defect stage needs the final state of both neighbouring planes.  Black cells of P-4 have
 // only red neighbours, final after red sweep 2; red cells of P-4 get their in-plane and lower
@@ -276,40 +277,40 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
 
     const int ys = ty * A.yo;                    // first output row (even)
     int yv[R], ygv[R];
-    bool out_y[R];
     [[maybe_unused]] bool in_y[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int y = ys - kHalo + band * R + r;
       yv[r] = y;
       ygv[r] = y & nm;
-      out_y[r] = y >= ys && y < ys + A.yo && y < n;
       in_y[r] = py || (y >= 0 && y < n);
     }
+    // rows 0, 1 and rows 2, 3: written by this lane?
+    const bool out[2] = {out_x && yv[0] >= ys && yv[0] < ys + A.yo && yv[0] < n,
+                         out_x && yv[2] >= ys && yv[2] < ys + A.yo && yv[2] < n};
     // MeshBlock layout: the x-y part of each row's storage index (the z part is added per plane)
     unsigned rxy[BLK ? R : 1];
     if constexpr (BLK) {
 #pragma unroll
       for (int r = 0; r < R; ++r) rxy[r] = blk_xy(A.Lm, xag, ygv[r]);
     }
-    // dense layout: each row's byte offset within a plane (below 2^25 up to 2048^2 cells), so that
+    // dense layout: the row pairs' byte offsets within a plane (below 2^25 up to 2048^2 cells; a
+    // pair neither wraps nor straddles a wall or the output's edge: all lie between rows 1 and 2), so that
     // an address is a uniform plane base and a 32-bit offset, with no arithmetic per load
-    unsigned rb[BLK ? 1 : R];
-    if constexpr (!BLK) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) rb[r] = (unsigned)(((ygv[r] << L) | xag) * (int)sizeof(T));
-    }
+    unsigned rb[2];
+    rb[0] = (unsigned)(((ygv[0] << L) | xag) * (int)sizeof(T));
+    rb[1] = (unsigned)(((ygv[2] << L) | xag) * (int)sizeof(T));
     // row r of this lane on plane z of array p
     auto at = [&](const T* p, int r, int z) __attribute__((always_inline)) -> const T* {
       if constexpr (BLK) return p + (size_t)(rxy[r] + blk_z(A.Lm, z));
-      else return reinterpret_cast<const T*>(reinterpret_cast<const char*>(p + ((size_t)z << (2 * L))) + rb[r]);
+      else return reinterpret_cast<const T*>(reinterpret_cast<const char*>(p + (((size_t)z << (2 * L)) + ((r & 1) << L))) + rb[r >> 1]);
     };
     // up, MeshBlock layout: the x-y part of the coarse taps' storage indices (rows Y0-1 ..
     // Y0+2 of the lane's coarse column, wrapped or clamped as the taps take them); the coarse
     // level is in blocks of 2^(Lm-1) cells, or the dense root grid when Lm = 1
     constexpr int NTAP = R / 2 + 2;
     unsigned cxy[UP ? NTAP : 1];
-    unsigned sgn[UP && XYW ? NTAP : 1];   // the sign of the walls' rule of a clamped tap, as its bit
+    unsigned sgn[UP && XYW ? NTAP / 2 : 1];   // the sign of the walls' rule of a clamped pair of taps, as its bit
     if constexpr (UP) {
       const int nc = n >> 1, Lc = L - 1;
       int X = (px ? xag : xa) >> 1;
@@ -322,7 +323,8 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
         if (py) Y &= nc - 1;
         if constexpr (XYW) {
           const bool minus_y = (Y < 0 && kappa_of<T>(A.bcc, 2) < 0) || (Y >= nc && kappa_of<T>(A.bcc, 3) < 0);
-          sgn[i] = minus_x != minus_y ? 0x80000000u : 0u;
+          // (a wall lies between taps 1 and 2, as between rows 1 and 2)
+          if (i % 2 == 0) sgn[i / 2] = minus_x != minus_y ? 0x80000000u : 0u;
           Y = min(max(Y, 0), nc - 1);
         }
         if constexpr (BLK) cxy[i] = A.Lm == 1 ? (unsigned)((Y << Lc) | X) : blk_xy(A.Lm - 1, X, Y);
@@ -483,7 +485,7 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
 #pragma unroll
         for (int i = 0; i < NTAP; ++i) {
           czv[i] = wz0 * pc[i][0] + wz1 * pc[i][1];
-          if constexpr (XYW) czv[i] = with_sign(czv[i], sgn[i]);
+          if constexpr (XYW) czv[i] = with_sign(czv[i], sgn[i / 2]);
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -632,11 +634,12 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
       cell(I0{}, Red{}, xd[bandb][1][xl]);
       cell(IL{}, Red{}, xd[banda][0][xl]);
       if constexpr (NORM) {
+        auto square = [](T v) { return (double)v * (double)v; };
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          if (out_x && out_y[r]) {
-            if (out_cur) acc += (double)dblk[r] * (double)dblk[r];
-            if (out_prev) acc += (double)dprev[r] * (double)dprev[r];
+        for (int j = 0; j < R / 2; ++j) {
+          if (out[j]) {
+            if (out_cur) acc += square(dblk[2 * j]) + square(dblk[2 * j + 1]);
+            if (out_prev) acc += square(dprev[2 * j]) + square(dprev[2 * j + 1]);
           }
         }
       }
@@ -728,11 +731,11 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
       arrived(u[so], fr);
       {
         const int p = P - kStages;
-        if (p >= z0 && p < zend && out_x) {
+        if (p >= z0 && p < zend) {
           const int pg = p & nm;
 #pragma unroll
           for (int r = 0; r < R; ++r)
-            if (out_y[r]) {
+            if (out[r >> 1]) {
               typedef T ntv2 __attribute__((ext_vector_type(2)));
               const ntv2 v = {u[sl][r][0], u[sl][r][1]};
               __builtin_nontemporal_store(v, reinterpret_cast<ntv2*>(const_cast<T*>(at(uout, r, pg))));
@@ -741,12 +744,12 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
       }
       if constexpr (DEF && ((HZ + K + kStages + 1) & 1) != 0) {
         const int p = P - kStages - 1;
-        if (p >= z0 && p < zend && out_x) {
+        if (p >= z0 && p < zend) {
           T* __restrict__ fcp = reinterpret_cast<T*>(A.fc);
           T* __restrict__ ucp = reinterpret_cast<T*>(A.uc0);
 #pragma unroll
           for (int j = 0; j < R / 2; ++j)
-            if (out_y[2 * j]) {
+            if (out[j]) {
               const size_t ci = cdx(xag >> 1, ygv[2 * j] >> 1, p >> 1);
               fcp[ci] = stash[j];
               if constexpr (FAS) reinterpret_cast<T*>(A.pbar)[ci] = stash_u[j];
@@ -854,7 +857,7 @@ void launch_march(MarchArgs A, hipStream_t s, const MarchAux* aux) {
     // the z-walls-only form on this stream, the ring of wall tiles in the full form on the
     // second stream, concurrently (fork and join through events); the ring's partials follow
     // the interior's.  Where the interior tiles are the more: at 512^3 (64 against 36) a V-cycle
-    // takes 2243 us so and 2338 in one launch, at 256^3 (9 against 16) 445 and 442.  (FP32's full
+    // takes 2193 us so and 2210 in one launch, at 256^3 (9 against 16) 415 and 413.  (FP32's full
     // form, well within its registers, is slower split: 0.52 -> 0.57 ms at 512^3.)
     MarchArgs Ai = A, Ar = A;
     Ai.set = 1;
