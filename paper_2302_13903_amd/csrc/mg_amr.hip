@@ -535,14 +535,22 @@ __global__ void k_coarsest(double* u, const double* f, Phys P, double h2) {
   if (sa != 6.0) u[gx(d, 0, 0, 0)] = (sb - h2 * f[gx(d, 0, 0, 0)]) / (6.0 - sa);
 }
 
-// ---- the small root levels (kRootTailN^3 cells and below) in one workgroup: the uniform FAS
-// V-cycle of the root grid from level q0 down to the single cell and back, every operator a
-// block-strided loop followed by a barrier (the levels are cached in the CU; its waves share
-// the L1, so a barrier orders their global-memory accesses).  Same bodies, same order of
+// ---- the coarse part of the refined hierarchy in one workgroup: the small root levels
+// (kRootTailN^3 cells and below), and the whole middle of a V-cycle -- the Octet levels (one cell
+// per MeshBlock of each refinement level) finest first, the root grid, the Octet levels coarsest
+// first.  Every operator is a block-strided loop followed by a barrier: same bodies, same order of
 // operations as the per-operator launches.
+//
+// What bounds it: some 170 phases of a few hundred cells, each a memory round trip and a barrier.  So
+// where they fit, u, phibar and the source of every level and one array of defects live in LDS
+// (the source replaces the restricted defect in place, cell by cell; the levels' starting u is
+// phibar) and only u goes back; larger meshes work in global memory, cached in the CU, whose waves
+// share the L1, so that a barrier orders their accesses.
+// MID_MEASURED
 constexpr int kRootTailN = 16;
-constexpr int kRootTailThreads = 1024;
-constexpr int kMaxRoot = 10;   // root levels 256^3 .. 1
+constexpr int kMaxRoot = 10;         // root levels 256^3 .. 1
+constexpr int kMidMaxCells = 4096;   // 16^3: per Octet patch, in global memory
+constexpr int kMidLds = 20000;       // doubles of LDS
 struct RootLvl {
   Dims d;
   double h;
@@ -552,76 +560,6 @@ struct RootLvl {
 struct RootSet {
   RootLvl l[kMaxRoot];
 };
-
-template <typename F>
-__device__ inline void forall(size_t work, F fn) {
-  for (size_t t = threadIdx.x; t < work; t += blockDim.x) fn(t);
-  __syncthreads();
-}
-
-__device__ void root_tail_run(const RootSet& S, int q0, int npre, int npost, double omega) {
-  const Hole none{};
-  auto smooth = [&](const RootLvl& L, int sweeps) {
-    for (int it = 0; it < sweeps; ++it)
-      for (int colour = 0; colour < 2; ++colour) {
-        forall(ghost_faces(L.d), [&](size_t t) { fill_phys_body(L.u, L.d, L.phys, 0, t); });
-        forall(smooth_items(L.d),
-               [&](size_t t) { smooth_body(L.u, L.f, L.d, 0, 0, 0, none, L.h * L.h, omega, colour, t); });
-      }
-  };
-  int q = q0;
-  // down: smooth, defect, FAS restriction of u and of the defect, coarse source
-  while (S.l[q].d.n[0] > 1) {
-    const RootLvl& L = S.l[q];
-    const RootLvl& C = S.l[q + 1];
-    smooth(L, npre);
-    forall(ghost_faces(L.d), [&](size_t t) { fill_phys_body(L.u, L.d, L.phys, 0, t); });
-    forall(cells(L.d), [&](size_t t) { lap_body(L.u, L.f, L.tmp, L.d, none, 1.0 / (L.h * L.h), -1.0, t); });
-    forall(cells(C.d), [&](size_t t) {
-      restrict_body(L.u, L.d, none, C.u, C.pbar, C.d, 0, 0, 0, C.d, t);
-      restrict_body(L.tmp, L.d, none, C.dres, nullptr, C.d, 0, 0, 0, C.d, t);
-    });
-    forall(ghost_faces(C.d), [&](size_t t) { fill_phys_body(C.pbar, C.d, C.phys, 0, t); });
-    forall(cells(C.d), [&](size_t t) { lap_body(C.pbar, C.dres, C.f, C.d, none, 1.0 / (C.h * C.h), 1.0, t); });
-    ++q;
-  }
-  // the single cell
-  if (threadIdx.x == 0) {
-    const RootLvl& L = S.l[q];
-    double sa = 0.0, sb = 0.0;
-    for (int face = 0; face < 6; ++face) {
-      if (L.phys.kind[face] == BC_PERIODIC || L.phys.kind[face] == BC_ZERO_GRADIENT) {
-        sa += 1.0;
-      } else {
-        sa -= 1.0;
-        sb += 2.0 * (L.phys.b[face] ? L.phys.b[face][0] : 0.0);
-      }
-    }
-    if (sa != 6.0) L.u[gx(L.d, 0, 0, 0)] = (sb - L.h * L.h * L.f[gx(L.d, 0, 0, 0)]) / (6.0 - sa);
-  }
-  __syncthreads();
-  // up: correction u - pbar, homogeneous ghosts, trilinear prolongation added, smooth
-  for (--q; q >= q0; --q) {
-    const RootLvl& L = S.l[q];
-    const RootLvl& C = S.l[q + 1];
-    forall(cells(C.d), [&](size_t t) { sub_body(C.u, C.pbar, C.tmp, C.d, none, t); });
-    forall(ghost_faces(C.d), [&](size_t t) { fill_phys_body(C.tmp, C.d, C.phys, 1, t); });
-    forall(cells(L.d), [&](size_t t) {
-      prolong_body(C.tmp, C.d, 0, 0, 0, L.u, L.d, 0, 0, 0, none, 0, 0, 0, L.d, 0, t);
-    });
-    smooth(L, npost);
-  }
-}
-
-__global__ void __launch_bounds__(kRootTailThreads) k_root_tail(RootSet S, int q0, int npre, int npost, double omega) {
-  root_tail_run(S, q0, npre, npost, omega);
-}
-
-// ---- the middle of a refined-mesh V-cycle in one workgroup: the Octet levels (one cell per
-// MeshBlock of each refinement level) finest first, the root grid, the Octet levels coarsest
-// first -- the same operators in the same order as the per-operator launches, for meshes
-// whose Octet patches and root grid are small
-constexpr int kMidMaxCells = 4096;   // 16^3: four cells per thread and operator
 struct OctL {
   Dims d;
   int o[3];
@@ -632,11 +570,134 @@ struct OctL {
 struct OctSet {
   OctL l[kMaxSet];
 };
+// places in LDS (in doubles) of each level's three arrays (u, phibar, source), Octet 0 = root 0, and of
+// the defects
+struct MidPlaces {
+  unsigned oct[kMaxSet], root[kMaxRoot], tmp;
+};
 
-static_assert(sizeof(OctSet) + sizeof(RootSet) + 64 <= 4096, "k_mid arguments are limited to 4 KiB");
+static_assert(sizeof(OctSet) + sizeof(RootSet) + sizeof(MidPlaces) + 64 <= 4096, "k_mid arguments are limited to 4 KiB");
 static_assert(kMpMaxBoxes >= MG_AMR_MAX_LEVELS + 1, "one multipole box per refinement level");
 
-__device__ inline Cons oct_cons(const OctL& F, double* uf, const OctL& C, const double* uc) {
+constexpr int mid_threads(bool lds) { return lds ? 512 : 1024; }
+
+template <typename F>
+__device__ __forceinline__ void forall(size_t work, F fn) {
+  for (size_t t = threadIdx.x; t < work; t += blockDim.x) fn(t);
+  __syncthreads();
+}
+
+// the arrays of one level as the phases see them (in LDS, f and dres are one array)
+struct Arr {
+  double *u, *f, *pbar, *dres, *tmp;
+};
+template <bool LDS>
+struct MidMem {
+  double* lds;
+  const MidPlaces& at;
+  __device__ __forceinline__ Arr arr(unsigned place, const Dims& d) const {
+    const unsigned g = (unsigned)ghosted_d(d);
+    return Arr{lds + place, lds + place + 2 * g, lds + place + g, lds + place + 2 * g, lds + at.tmp};
+  }
+  __device__ __forceinline__ Arr root(const RootSet& S, int q) const {
+    if constexpr (LDS) return arr(at.root[q], S.l[q].d);
+    else return Arr{S.l[q].u, S.l[q].f, S.l[q].pbar, S.l[q].dres, S.l[q].tmp};
+  }
+  __device__ __forceinline__ Arr oct(const OctSet& S, int l) const {
+    if constexpr (LDS) return arr(at.oct[l], S.l[l].d);
+    else return Arr{S.l[l].u, S.l[l].f, S.l[l].pbar, S.l[l].dres, S.l[l].tmp};
+  }
+};
+
+template <bool LDS>
+__device__ __forceinline__ void root_tail_run(const MidMem<LDS>& M, const RootSet& S, int q0, int npre, int npost,
+                                              double omega) {
+  const Hole none{};
+  auto smooth = [&](const RootLvl& L, const Arr& a, int sweeps) {
+    for (int it = 0; it < sweeps; ++it)
+      for (int colour = 0; colour < 2; ++colour) {
+        forall(ghost_faces(L.d), [&](size_t t) { fill_phys_body(a.u, L.d, L.phys, 0, t); });
+        forall(smooth_items(L.d),
+               [&](size_t t) { smooth_body(a.u, a.f, L.d, 0, 0, 0, none, L.h * L.h, omega, colour, t); });
+      }
+  };
+  int q = q0;
+  // down: smooth, defect, FAS restriction of u and of the defect, coarse source
+  while (S.l[q].d.n[0] > 1) {
+    const RootLvl& L = S.l[q];
+    const RootLvl& C = S.l[q + 1];
+    const Arr a = M.root(S, q), c = M.root(S, q + 1);
+    smooth(L, a, npre);
+    forall(ghost_faces(L.d), [&](size_t t) { fill_phys_body(a.u, L.d, L.phys, 0, t); });
+    forall(cells(L.d), [&](size_t t) { lap_body(a.u, a.f, a.tmp, L.d, none, 1.0 / (L.h * L.h), -1.0, t); });
+    forall(cells(C.d), [&](size_t t) {
+      restrict_body(a.u, L.d, none, c.u, c.pbar, C.d, 0, 0, 0, C.d, t);
+      restrict_body(a.tmp, L.d, none, c.dres, nullptr, C.d, 0, 0, 0, C.d, t);
+    });
+    forall(ghost_faces(C.d), [&](size_t t) { fill_phys_body(c.pbar, C.d, C.phys, 0, t); });
+    forall(cells(C.d), [&](size_t t) { lap_body(c.pbar, c.dres, c.f, C.d, none, 1.0 / (C.h * C.h), 1.0, t); });
+    ++q;
+  }
+  // the single cell
+  if (threadIdx.x == 0) {
+    const RootLvl& L = S.l[q];
+    const Arr a = M.root(S, q);
+    double sa = 0.0, sb = 0.0;
+    for (int face = 0; face < 6; ++face) {
+      if (L.phys.kind[face] == BC_PERIODIC || L.phys.kind[face] == BC_ZERO_GRADIENT) {
+        sa += 1.0;
+      } else {
+        sa -= 1.0;
+        sb += 2.0 * (L.phys.b[face] ? L.phys.b[face][0] : 0.0);
+      }
+    }
+    if (sa != 6.0) a.u[gx(L.d, 0, 0, 0)] = (sb - L.h * L.h * a.f[gx(L.d, 0, 0, 0)]) / (6.0 - sa);
+  }
+  __syncthreads();
+  // up: correction u - pbar, homogeneous ghosts, trilinear prolongation added, smooth
+  for (--q; q >= q0; --q) {
+    const RootLvl& L = S.l[q];
+    const RootLvl& C = S.l[q + 1];
+    const Arr a = M.root(S, q), c = M.root(S, q + 1);
+    forall(cells(C.d), [&](size_t t) { sub_body(c.u, c.pbar, c.tmp, C.d, none, t); });
+    forall(ghost_faces(C.d), [&](size_t t) { fill_phys_body(c.tmp, C.d, C.phys, 1, t); });
+    forall(cells(L.d), [&](size_t t) {
+      prolong_body(c.tmp, C.d, 0, 0, 0, a.u, L.d, 0, 0, 0, none, 0, 0, 0, L.d, 0, t);
+    });
+    smooth(L, a, npost);
+  }
+}
+
+// dst = src on the active cells of a ghosted array (between global memory and LDS)
+__device__ __forceinline__ void move_body(const double* src, double* dst, const Dims& d, size_t t) {
+  int x, y, z;
+  cell_of(t, d, x, y, z);
+  const size_t c = gx(d, x, y, z);
+  dst[c] = src[c];
+}
+
+// the root levels from q0: u improved by one V-cycle with the source in f
+template <bool LDS>
+__global__ void __launch_bounds__(mid_threads(LDS)) k_root_tail(RootSet S, MidPlaces at, int q0, int npre, int npost,
+                                                                 double omega) {
+  __shared__ double arena[LDS ? kMidLds : 1];
+  const MidMem<LDS> M{arena, at};
+  const RootLvl& T = S.l[q0];
+  if constexpr (LDS) {
+    const Arr a = M.root(S, q0);
+    forall(cells(T.d), [&](size_t t) {
+      move_body(T.u, a.u, T.d, t);
+      move_body(T.f, a.f, T.d, t);
+    });
+  }
+  root_tail_run<LDS>(M, S, q0, npre, npost, omega);
+  if constexpr (LDS) {
+    const Arr a = M.root(S, q0);
+    forall(cells(T.d), [&](size_t t) { move_body(a.u, T.u, T.d, t); });
+  }
+}
+
+__device__ __forceinline__ Cons oct_cons(const OctL& F, double* uf, const OctL& C, const double* uc) {
   Cons A;
   A.uf = uf;
   A.df = F.d;
@@ -659,56 +720,98 @@ __device__ inline size_t cons_most(const Dims& df) {
   return m;
 }
 
-__global__ void __launch_bounds__(kRootTailThreads) k_mid(OctSet O, RootSet R, int Lam, int npre, int npost,
-                                                          double omega) {
+// The middle of a V-cycle from Octet level `top`.  src == nullptr: as a part of a cycle that came
+// down from the MeshBlock levels (every level's phibar and restricted defect are there); else the
+// V-cycle of Octet level top itself, u there to be improved with the source src.
+template <bool LDS>
+__global__ void __launch_bounds__(mid_threads(LDS)) k_mid(OctSet O, RootSet R, MidPlaces at, int top, const double* src,
+                                                           int npre, int npost, double omega) {
+  __shared__ double arena[LDS ? kMidLds : 1];
+  const MidMem<LDS> M{arena, at};
   const Hole none{};
-  auto cons_all = [&](const Cons& A) {
-    const size_t m = cons_most(A.df);
-    forall(3 * m, [&](size_t t) { cons_body(A, (int)(t / m), t % m); });
+  auto cons_all = [&](const Cons& A) __attribute__((always_inline)) {
+    const unsigned m = (unsigned)cons_most(A.df);
+    // (constant axes: indexing by a variable one would go through scratch memory)
+    forall(3 * m, [&](size_t t) {
+      if (t < m) cons_body(A, 0, t);
+      else if (t < 2 * m) cons_body(A, 1, t - m);
+      else cons_body(A, 2, t - 2 * m);
+    });
   };
-  auto oct_smooth = [&](const OctL& P, const OctL& C, int sweeps) {
+  auto oct_smooth = [&](const OctL& P, const Arr& p, const OctL& C, const Arr& c, int sweeps) __attribute__((always_inline)) {
     for (int it = 0; it < sweeps; ++it)
       for (int colour = 0; colour < 2; ++colour) {
-        cons_all(oct_cons(P, P.u, C, C.u));
+        cons_all(oct_cons(P, p.u, C, c.u));
         forall(smooth_items(P.d), [&](size_t t) {
-          smooth_body(P.u, P.f, P.d, P.o[0], P.o[1], P.o[2], none, P.h * P.h, omega, colour, t);
+          smooth_body(p.u, p.f, P.d, P.o[0], P.o[1], P.o[2], none, P.h * P.h, omega, colour, t);
         });
       }
   };
+  if constexpr (LDS) {
+    for (int l = 0; l <= top; ++l) {
+      const OctL& P = O.l[l];
+      const Arr p = M.oct(O, l);
+      const bool start = l == top && src;   // u and f are given, not phibar and the restricted defect
+      for (size_t t = threadIdx.x; t < cells(P.d); t += blockDim.x) {
+        int x, y, z;
+        cell_of(t, P.d, x, y, z);
+        const size_t c = gx(P.d, x, y, z);
+        const double v = start ? P.u[c] : P.pbar[c];
+        p.u[c] = v;
+        p.pbar[c] = v;
+        p.f[c] = start ? src[c] : P.dres[c];
+      }
+    }
+    __syncthreads();
+  }
   // Octet levels, finest first
-  for (int l = Lam; l >= 1; --l) {
+  for (int l = top; l >= 1; --l) {
     const OctL& P = O.l[l];
     const OctL& C = O.l[l - 1];
-    cons_all(oct_cons(P, P.pbar, C, C.pbar));
-    forall(cells(P.d), [&](size_t t) { lap_body(P.pbar, P.dres, P.f, P.d, none, 1.0 / (P.h * P.h), 1.0, t); });
-    forall(ghosted_d(P.d), [&](size_t t) { P.u[t] = P.pbar[t]; });
-    oct_smooth(P, C, npre);
-    cons_all(oct_cons(P, P.u, C, C.u));
-    forall(cells(P.d), [&](size_t t) { lap_body(P.u, P.f, P.tmp, P.d, none, 1.0 / (P.h * P.h), -1.0, t); });
+    const Arr p = M.oct(O, l), c = M.oct(O, l - 1);
+    if (l < top || !src) {
+      cons_all(oct_cons(P, p.pbar, C, c.pbar));
+      forall(cells(P.d), [&](size_t t) { lap_body(p.pbar, p.dres, p.f, P.d, none, 1.0 / (P.h * P.h), 1.0, t); });
+      forall(ghosted_d(P.d), [&](size_t t) { p.u[t] = p.pbar[t]; });
+    } else if (!LDS) {
+      forall(cells(P.d), [&](size_t t) { move_body(src, p.f, P.d, t); });
+    }
+    oct_smooth(P, p, C, c, npre);
+    cons_all(oct_cons(P, p.u, C, c.u));
+    forall(cells(P.d), [&](size_t t) { lap_body(p.u, p.f, p.tmp, P.d, none, 1.0 / (P.h * P.h), -1.0, t); });
     const Dims nr{{P.d.n[0] / 2, P.d.n[1] / 2, P.d.n[2] / 2}};
     forall(cells(nr), [&](size_t t) {
-      restrict_body(P.u, P.d, none, C.pbar, C.u, C.d, C.hlo[0], C.hlo[1], C.hlo[2], nr, t);
-      restrict_body(P.tmp, P.d, none, C.dres, nullptr, C.d, C.hlo[0], C.hlo[1], C.hlo[2], nr, t);
+      restrict_body(p.u, P.d, none, c.pbar, c.u, C.d, C.hlo[0], C.hlo[1], C.hlo[2], nr, t);
+      restrict_body(p.tmp, P.d, none, c.dres, nullptr, C.d, C.hlo[0], C.hlo[1], C.hlo[2], nr, t);
     });
   }
   // root grid
   {
     const RootLvl& L = R.l[0];
-    forall(ghost_faces(L.d), [&](size_t t) { fill_phys_body(L.pbar, L.d, L.phys, 0, t); });
-    forall(cells(L.d), [&](size_t t) { lap_body(L.pbar, L.dres, L.f, L.d, none, 1.0 / (L.h * L.h), 1.0, t); });
-    forall(ghosted_d(L.d), [&](size_t t) { L.u[t] = L.pbar[t]; });
-    root_tail_run(R, 0, npre, npost, omega);
+    const Arr a = M.oct(O, 0);
+    forall(ghost_faces(L.d), [&](size_t t) { fill_phys_body(a.pbar, L.d, L.phys, 0, t); });
+    forall(cells(L.d), [&](size_t t) { lap_body(a.pbar, a.dres, a.f, L.d, none, 1.0 / (L.h * L.h), 1.0, t); });
+    forall(ghosted_d(L.d), [&](size_t t) { a.u[t] = a.pbar[t]; });
+    root_tail_run<LDS>(M, R, 0, npre, npost, omega);
   }
   // Octet levels, coarsest first
-  for (int l = 1; l <= Lam; ++l) {
+  for (int l = 1; l <= top; ++l) {
     const OctL& P = O.l[l];
     const OctL& C = O.l[l - 1];
-    forall(cells(C.d), [&](size_t t) { sub_body(C.u, C.pbar, C.tmp, C.d, none, t); });
-    if (l == 1) forall(ghost_faces(C.d), [&](size_t t) { fill_phys_body(C.tmp, C.d, R.l[0].phys, 1, t); });
+    const Arr p = M.oct(O, l), c = M.oct(O, l - 1);
+    forall(cells(C.d), [&](size_t t) { sub_body(c.u, c.pbar, c.tmp, C.d, none, t); });
+    if (l == 1) forall(ghost_faces(C.d), [&](size_t t) { fill_phys_body(c.tmp, C.d, R.l[0].phys, 1, t); });
     forall(cells(P.d), [&](size_t t) {
-      prolong_body(C.tmp, C.d, C.o[0], C.o[1], C.o[2], P.u, P.d, P.o[0], P.o[1], P.o[2], none, 0, 0, 0, P.d, 0, t);
+      prolong_body(c.tmp, C.d, C.o[0], C.o[1], C.o[2], p.u, P.d, P.o[0], P.o[1], P.o[2], none, 0, 0, 0, P.d, 0, t);
     });
-    oct_smooth(P, C, npost);
+    oct_smooth(P, p, C, c, npost);
+  }
+  if constexpr (LDS) {
+    for (int l = 0; l <= top; ++l) {
+      const OctL& P = O.l[l];
+      const Arr p = M.oct(O, l);
+      for (size_t t = threadIdx.x; t < cells(P.d); t += blockDim.x) move_body(p.u, P.u, P.d, t);
+    }
   }
 }
 
@@ -1014,11 +1117,31 @@ struct AmrRun {
     return S;
   }
 
+  // Lays the Octet levels 0..top (none: top < 0) and the root levels from q on in LDS; do they fit?
+  bool mid_places(int top, int q, MidPlaces& at) const {
+    size_t off = 0, most = 0;
+    auto place = [&](const Dims& d) {
+      const size_t o = off;
+      off += 3 * ghosted(d);
+      most = std::max(most, ghosted(d));
+      return (unsigned)o;
+    };
+    for (int l = 0; l <= top; ++l) at.oct[l] = place(pl.P[l][0].d);
+    for (int i = q; i <= (int)pl.R.size() && i < kMaxRoot; ++i)
+      at.root[i] = i == 0 && top >= 0 ? at.oct[0] : place(i == 0 ? pl.P[0][0].d : pl.R[i - 1].d);
+    at.tmp = (unsigned)off;
+    return off + most <= (size_t)kMidLds;
+  }
+
   void root_fas(int q, PatchL& top, double* u, double* f) {
     // level q: q = 0 is the NB^3 root patch (u, f given), q >= 1 index into pl.R
     const int n = top.d.n[0];
     if (n <= kRootTailN && (int)pl.R.size() < kMaxRoot && u == top.u && f == top.f) {
-      hipLaunchKernelGGL(k_root_tail, dim3(1), dim3(kRootTailThreads), 0, s, root_set(), q, npre, npost, omega);
+      MidPlaces at{};
+      if (mid_places(-1, q, at))
+        hipLaunchKernelGGL(k_root_tail<true>, dim3(1), dim3(mid_threads(true)), 0, s, root_set(), at, q, npre, npost, omega);
+      else
+        hipLaunchKernelGGL(k_root_tail<false>, dim3(1), dim3(mid_threads(false)), 0, s, root_set(), at, q, npre, npost, omega);
       return;
     }
     if (n == 1) {
@@ -1074,11 +1197,26 @@ struct AmrRun {
       }
   }
 
-  // can the middle of a V-cycle (Octet levels, root grid) run in one workgroup?
-  bool mid_fits() const {
+  // The middle of a V-cycle (Octet levels from lam_top, root grid) in one workgroup, in LDS if it fits,
+  // in global memory if every patch is small (src: as k_mid's); false: neither
+  bool mid_one(int lam_top, const double* src) {
     if (pl.NB > kRootTailN || (int)pl.R.size() + 1 > kMaxRoot) return false;
-    for (int l = 0; l <= pl.Lam; ++l)
+    MidPlaces at{};
+    const bool lds = mid_places(lam_top, 0, at);
+    for (int l = 0; l <= lam_top && !lds; ++l)
       if (cells(pl.P[l][0].d) > (size_t)kMidMaxCells) return false;
+    OctSet O{};
+    for (int l = 0; l <= lam_top; ++l) {
+      const PatchL& p = pl.P[l][0];
+      O.l[l] = OctL{p.d, {p.o[0], p.o[1], p.o[2]}, p.h, p.u, p.f, p.pbar, p.dres, p.tmp,
+                    {p.hole.lo[0], p.hole.lo[1], p.hole.lo[2]}, {p.hole.hi[0], p.hole.hi[1], p.hole.hi[2]}};
+    }
+    if (lds)
+      hipLaunchKernelGGL(k_mid<true>, dim3(1), dim3(mid_threads(true)), 0, s, O, root_set(), at, lam_top, src, npre, npost,
+                         omega);
+    else
+      hipLaunchKernelGGL(k_mid<false>, dim3(1), dim3(mid_threads(false)), 0, s, O, root_set(), at, lam_top, src, npre, npost,
+                         omega);
     return true;
   }
 
@@ -1163,18 +1301,7 @@ struct AmrRun {
         copy(p.u, p.pbar, p.d);
       }
     }
-    if (kind == 0 && mid_fits()) {
-      // the Octet levels, the root grid and the Octet levels back in one workgroup
-      OctSet O{};
-      for (int l = 0; l <= Lam; ++l) {
-        const PatchL& p = pl.P[l][0];
-        O.l[l] = OctL{p.d, {p.o[0], p.o[1], p.o[2]}, p.h, p.u, p.f, p.pbar, p.dres, p.tmp,
-                      {p.hole.lo[0], p.hole.lo[1], p.hole.lo[2]}, {p.hole.hi[0], p.hole.hi[1], p.hole.hi[2]}};
-      }
-      hipLaunchKernelGGL(k_mid, dim3(1), dim3(kRootTailThreads), 0, s, O, root_set(), Lam, npre, npost, omega);
-    } else {
-      vcycle_middle(kind, lam_top);
-    }
+    if (!mid_one(lam_top, kind == 1 ? pl.P[lam_top][0].src : nullptr)) vcycle_middle(kind, lam_top);
     // ---- MeshBlock levels, up
     for (int k = 1; k <= kt; ++k) {
       Set<SubA> S{};
