@@ -337,6 +337,42 @@ struct RestrictA {
   int o[3];
   Dims nr;
 };
+// The step down of every patch in one launch, a coarse cell per thread: u restricted into phibar and
+// the coarse u, the defect f - L u of its eight children into the coarse source of FAS; covered
+// cells count as 0 in both.  (Apart, the defects cost a write and a read of every cell: on five
+// patches of 128^3 51 + 2 x 16 us, 59 us in one.)
+struct DownA {
+  const double *u, *f;
+  double *pbar, *uc, *dres;
+  Dims d, dc;
+  Hole H;
+  double ih2;
+};
+__global__ void __launch_bounds__(kB) k_down_set(Set<DownA> S) {
+  const DownA& A = S.a[blockIdx.y];
+  const Dims nr{{A.d.n[0] / 2, A.d.n[1] / 2, A.d.n[2] / 2}};
+  const size_t t = (size_t)blockIdx.x * kB + threadIdx.x;
+  if (t >= cells(nr)) return;
+  int X, Y, Z;
+  cell_of(t, nr, X, Y, Z);
+  double su = 0.0, sd = 0.0;
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        const int x = 2 * X + a, y = 2 * Y + b, z = 2 * Z + c;
+        if (covered(A.H, x, y, z)) continue;
+        const size_t i = gx(A.d, x, y, z);
+        const double v = A.u[i];
+        su += v;
+        sd += A.f[i] - (nbsum(A.u, A.d, A.H, x, y, z) - 6.0 * v) * A.ih2;
+      }
+  const size_t o = gx(A.dc, X, Y, Z);
+  A.pbar[o] = A.uc[o] = su / 8.0;
+  A.dres[o] = sd / 8.0;
+}
 __global__ void __launch_bounds__(kB) k_restrict_set(Set<RestrictA> S) {
   const RestrictA& A = S.a[blockIdx.y];
   restrict_body(A.uf, A.df, A.Hf, A.out1, A.out2, A.dc, A.o[0], A.o[1], A.o[2], A.nr,
@@ -408,10 +444,90 @@ struct ProlongA {
   int l[3];
   Dims span;
 };
-__global__ void __launch_bounds__(kB) k_prolong_set(Set<ProlongA> S, int mode) {
+// All eight children of one parent cell (modes 0 and 2, on levels of two or more cells per block,
+// where patches and holes hold whole octets): 27 parent values once instead of per child.  On
+// five patches of 128^3 30 us, and 119 us with a child per thread.
+template <bool CUBIC>
+__global__ void __launch_bounds__(kB) k_prolong_set(Set<ProlongA> S) {
   const ProlongA& A = S.a[blockIdx.y];
-  prolong_body(A.uc, A.dc, A.co[0], A.co[1], A.co[2], A.uf, A.df, A.fo[0], A.fo[1], A.fo[2], A.Hf, A.l[0], A.l[1], A.l[2],
-               A.span, mode, (size_t)blockIdx.x * kB + threadIdx.x);
+  const Dims dp{{A.df.n[0] / 2, A.df.n[1] / 2, A.df.n[2] / 2}};
+  const size_t t = (size_t)blockIdx.x * kB + threadIdx.x;
+  if (t >= cells(dp)) return;
+  int x, y, z;
+  cell_of(t, dp, x, y, z);
+  const bool cov = covered(A.Hf, 2 * x, 2 * y, 2 * z);
+  if (cov && !CUBIC) return;
+  const int X = A.fo[0] / 2 + x - A.co[0], Y = A.fo[1] / 2 + y - A.co[1], Z = A.fo[2] / 2 + z - A.co[2];
+  // (the weights of prolong_body)
+  auto lin = [](double cm, double c0, double cp, int up) {
+    if (CUBIC)
+      return up ? ((-3.0 / 32.0) * cm + (30.0 / 32.0) * c0) + (5.0 / 32.0) * cp
+                : ((5.0 / 32.0) * cm + (30.0 / 32.0) * c0) + (-3.0 / 32.0) * cp;
+    return up ? 0.75 * c0 + 0.25 * cp : 0.25 * cm + 0.75 * c0;
+  };
+  double tx[2][3][3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      const double* r = A.uc + gx(A.dc, X, Y + b - 1, Z + c - 1);
+      const double m = r[-1], o = r[0], p = r[1];
+      tx[0][c][b] = lin(m, o, p, 0);
+      tx[1][c][b] = lin(m, o, p, 1);
+    }
+#pragma unroll
+  for (int uy = 0; uy < 2; ++uy) {
+    double ty[2][3];
+#pragma unroll
+    for (int ux = 0; ux < 2; ++ux)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) ty[ux][c] = lin(tx[ux][c][0], tx[ux][c][1], tx[ux][c][2], uy);
+#pragma unroll
+    for (int uz = 0; uz < 2; ++uz) {
+      double* q = A.uf + gx(A.df, 2 * x, 2 * y + uy, 2 * z + uz);
+#pragma unroll
+      for (int ux = 0; ux < 2; ++ux) {
+        const double v = lin(ty[ux][0], ty[ux][1], ty[ux][2], uz);
+        if (CUBIC) q[ux] = cov ? 0.0 : v;
+        else q[ux] += v;
+      }
+    }
+  }
+}
+// The ghost shells of the finer patches (patch on blockIdx.y, mode 1) and, last, the physical ghosts
+// of the root patch.  On levels of two or more cells per block a shell's parents and their
+// neighbours are active cells or the covered layer beside them, so no part reads another's ghosts.
+__global__ void __launch_bounds__(kB) k_shell_set(Set<ProlongA> S, int nfine, double* u0, Dims d0, Phys P0, int hom0) {
+  size_t t = (size_t)blockIdx.x * kB + threadIdx.x;
+  if ((int)blockIdx.y == nfine) {
+    fill_phys_body(u0, d0, P0, hom0, t);
+    return;
+  }
+  const ProlongA& A = S.a[blockIdx.y];
+  // the cell of the six ghost faces (edges and corners more than once, with the same value)
+  const unsigned n0 = (unsigned)A.df.n[0] + 2, n1 = (unsigned)A.df.n[1] + 2, n2 = (unsigned)A.df.n[2] + 2;
+  const size_t f0 = (size_t)n1 * n2, f1 = (size_t)n0 * n2, f2 = (size_t)n0 * n1;
+  int x, y, z;
+  if (t < 2 * f0) {
+    const unsigned r = (unsigned)(t % f0);
+    x = t < f0 ? -1 : A.df.n[0];
+    y = (int)(r % n1) - 1;
+    z = (int)(r / n1) - 1;
+  } else if ((t -= 2 * f0) < 2 * f1) {
+    const unsigned r = (unsigned)(t % f1);
+    y = t < f1 ? -1 : A.df.n[1];
+    x = (int)(r % n0) - 1;
+    z = (int)(r / n0) - 1;
+  } else if ((t -= 2 * f1) < 2 * f2) {
+    const unsigned r = (unsigned)(t % f2);
+    z = t < f2 ? -1 : A.df.n[2];
+    x = (int)(r % n0) - 1;
+    y = (int)(r / n0) - 1;
+  } else {
+    return;
+  }
+  prolong_body(A.uc, A.dc, A.co[0], A.co[1], A.co[2], A.uf, A.df, A.fo[0], A.fo[1], A.fo[2], A.Hf, x, y, z,
+               Dims{{1, 1, 1}}, 1, 0);
 }
 
 // dst = src over the whole ghosted array
@@ -447,7 +563,8 @@ __global__ void __launch_bounds__(kB) k_sub_set(Set<SubA> S) {
 
 // kernel arguments are limited to 4 KiB
 static_assert(sizeof(Set<Cons>) <= 4096 && sizeof(Set<SmoothA>) <= 4096 && sizeof(Set<LapA>) <= 4096 &&
-                  sizeof(Set<RestrictA>) <= 4096 && sizeof(Set<ProlongA>) <= 4096 && sizeof(Set<SubA>) <= 4096,
+                  sizeof(Set<RestrictA>) <= 4096 && sizeof(Set<ProlongA>) + 256 <= 4096 && sizeof(Set<SubA>) <= 4096 &&
+                  sizeof(Set<DownA>) <= 4096,
               "batched launch arguments");
 
 // dense caller array <-> ghosted patch: a*src + c on active cells, 0 on covered cells
@@ -479,35 +596,44 @@ __global__ void __launch_bounds__(kB) k_load_ghosted(const double* __restrict__ 
   dst[c] = covered(H, x, y, z) ? 0.0 : src[c];
 }
 
-// per-block partial sums of g(v) over the active cells (what: 0 value, 1 square), fixed tree
-// Partial sums over the active cells of several patches in one launch: patch q (blockIdx.y)
-// uses its own nb blocks, block b summing cells b*kB + i + j*nb*kB into part[q * stride + b],
-// so each patch's partials and their order are fixed by its own size.
+// Sum over the active cells of every patch of w g, w the patch's weight (its cell volume) and g a value
+// (WHAT = 0), its square (1) or the square of the defect f - L u (2; ghosts filled before), in one
+// launch: blocks first[q] .. first[q + 1] of the grid work on patch q, the last to arrive adds up
+// the partials (in a fixed order).
 struct SumA {
-  const double* v;
+  const double *v, *f;
   Dims d;
   Hole H;
-  int nb;
+  double ih2, w;
 };
-__global__ void __launch_bounds__(kB) k_psum_set(Set<SumA> S, int what, double* __restrict__ part, int stride) {
-  const SumA& A = S.a[blockIdx.y];
-  if ((int)blockIdx.x >= A.nb) return;
-  __shared__ double sh[kB];
+struct SumBlocks {
+  int first[kMaxSet + 1];
+};
+template <int WHAT>
+__global__ void __launch_bounds__(kB) k_sum_set(Set<SumA> S, SumBlocks B, SumSink sink) {
+  __shared__ double red[kB / 64];
+  int q = 0;
+  while ((int)blockIdx.x >= B.first[q + 1]) ++q;
+  const SumA& A = S.a[q];
+  const size_t step = (size_t)(B.first[q + 1] - B.first[q]) * kB;
   double acc = 0.0;
-  for (size_t t = (size_t)blockIdx.x * kB + threadIdx.x; t < cells(A.d); t += (size_t)A.nb * kB) {
+  for (size_t t = (size_t)((int)blockIdx.x - B.first[q]) * kB + threadIdx.x; t < cells(A.d); t += step) {
     int x, y, z;
     cell_of(t, A.d, x, y, z);
     if (covered(A.H, x, y, z)) continue;
-    const double a = A.v[gx(A.d, x, y, z)];
-    acc += what ? a * a : a;
+    const size_t c = gx(A.d, x, y, z);
+    double a = A.v[c];
+    if (WHAT == 2) a = A.f[c] - (nbsum(A.v, A.d, A.H, x, y, z) - 6.0 * a) * A.ih2;
+    acc += WHAT ? a * a : a;
   }
-  sh[threadIdx.x] = acc;
+  acc = wave_sum(acc);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
   __syncthreads();
-  for (int s = kB / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[(size_t)blockIdx.y * stride + blockIdx.x] = sh[0];
+  double s = 0.0;
+  if (threadIdx.x == 0)
+    for (int i = 0; i < kB / 64; ++i) s += red[i];
+  __syncthreads();
+  finish_sum<kB>(sink, s * A.w, red);
 }
 
 // 2 x 2 area mean of a face array (n x n) -> (n/2 x n/2)
@@ -546,7 +672,7 @@ __global__ void k_coarsest(double* u, const double* f, Phys P, double h2) {
 // (the source replaces the restricted defect in place, cell by cell; the levels' starting u is
 // phibar) and only u goes back; larger meshes work in global memory, cached in the CU, whose waves
 // share the L1, so that a barrier orders their accesses.
-// MID_MEASURED
+// Five Octet levels of 8^3: 301 us in global memory (with its scratch traffic), 138 us in LDS.
 constexpr int kRootTailN = 16;
 constexpr int kMaxRoot = 10;         // root levels 256^3 .. 1
 constexpr int kMidMaxCells = 4096;   // 16^3: per Octet patch, in global memory
@@ -853,8 +979,8 @@ namespace {
 struct AmrRun {
   Plan pl;
   hipStream_t s;
-  double* part;
-  double* hpart;   // host copy of partials
+  SumSink sink;    // where sums go
+  double* host;    // one value of pinned host memory
   int kinds[6];
   int npre, npost;
   double omega;
@@ -952,20 +1078,17 @@ struct AmrRun {
       }
   }
 
-  // out[l] = a[l] + s L(arrays) at level k (ghosts filled first)
-  void lap_level(int k, int which, int a_sel, int out_sel, double sgn) {
-    fill_level(k, which);
+  // the FAS source of every patch at level k: f = dres + L phibar (ghosts filled first)
+  void source_level(int k) {
+    fill_level(k, 1);
     Set<LapA> S{};
     size_t most = 0;
     for (int l = 0; l <= pl.Lam; ++l) {
       PatchL& p = pl.P[l][k];
-      const double* u = which == 0 ? p.u : p.pbar;
-      const double* a = a_sel == 0 ? p.f : p.dres;
-      double* out = out_sel == 0 ? p.tmp : p.f;
-      S.a[l] = LapA{u, a, out, p.d, hole_of(p), 1.0 / (p.h * p.h)};
+      S.a[l] = LapA{p.pbar, p.dres, p.f, p.d, hole_of(p), 1.0 / (p.h * p.h)};
       most = std::max(most, cells(p.d));
     }
-    hipLaunchKernelGGL(k_lap_set, dim3(blocks(most), pl.Lam + 1), dim3(kB), 0, s, S, sgn);
+    hipLaunchKernelGGL(k_lap_set, dim3(blocks(most), pl.Lam + 1), dim3(kB), 0, s, S, 1.0);
   }
 
   static RestrictA restrict_args(const PatchL& fine, const double* src, bool mask, double* out1, double* out2,
@@ -982,20 +1105,30 @@ struct AmrRun {
     A.nr = Dims{{fine.d.n[0] / 2, fine.d.n[1] / 2, fine.d.n[2] / 2}};
     return A;
   }
-  // the restrictions of every patch from level k to k-1: u into pbar and u (masked: covered
-  // cells count as 0), the defect in tmp into dres
-  void restrict_level(int k) {
-    Set<RestrictA> Su{}, Sd{};
+  // the step down of every patch from level k to k-1: u into pbar and u, the defect into dres
+  void down_level(int k) {
+    fill_level(k, 0);
+    Set<DownA> S{};
     size_t most = 0;
-    const int o[3] = {0, 0, 0};
     for (int l = 0; l <= pl.Lam; ++l) {
       PatchL &p = pl.P[l][k], &c = pl.P[l][k - 1];
-      Su.a[l] = restrict_args(p, p.u, true, c.pbar, c.u, c, o);
-      Sd.a[l] = restrict_args(p, p.tmp, false, c.dres, nullptr, c, o);
-      most = std::max(most, cells(Su.a[l].nr));
+      S.a[l] = DownA{p.u, p.f, c.pbar, c.u, c.dres, p.d, c.d, hole_of(p), 1.0 / (p.h * p.h)};
+      most = std::max(most, cells(c.d));
     }
-    hipLaunchKernelGGL(k_restrict_set, dim3(blocks(most), pl.Lam + 1), dim3(kB), 0, s, Su);
-    hipLaunchKernelGGL(k_restrict_set, dim3(blocks(most), pl.Lam + 1), dim3(kB), 0, s, Sd);
+    hipLaunchKernelGGL(k_down_set, dim3(blocks(most), pl.Lam + 1), dim3(kB), 0, s, S);
+  }
+  static ProlongA prolong_args(const PatchL& c, const double* uc, const PatchL& p, double* uf) {
+    ProlongA A{};
+    A.uc = uc;
+    A.dc = c.d;
+    A.uf = uf;
+    A.df = p.d;
+    A.Hf = p.hole;
+    for (int a = 0; a < 3; ++a) {
+      A.co[a] = c.o[a];
+      A.fo[a] = p.o[a];
+    }
+    return A;
   }
   // every patch at level k-1 -> k: the prolongated correction tmp added to u (mode 0), or the
   // FMG start from u (mode 2)
@@ -1004,21 +1137,11 @@ struct AmrRun {
     size_t most = 0;
     for (int l = 0; l <= pl.Lam; ++l) {
       PatchL &c = pl.P[l][k - 1], &p = pl.P[l][k];
-      ProlongA& A = S.a[l];
-      A.uc = mode == 0 ? c.tmp : c.u;
-      A.dc = c.d;
-      A.uf = p.u;
-      A.df = p.d;
-      A.Hf = p.hole;
-      for (int a = 0; a < 3; ++a) {
-        A.co[a] = c.o[a];
-        A.fo[a] = p.o[a];
-        A.l[a] = 0;
-      }
-      A.span = p.d;
-      most = std::max(most, cells(p.d));
+      S.a[l] = prolong_args(c, mode == 0 ? c.tmp : c.u, p, p.u);
+      most = std::max(most, cells(p.d) / 8);
     }
-    hipLaunchKernelGGL(k_prolong_set, dim3(blocks(most), pl.Lam + 1), dim3(kB), 0, s, S, mode);
+    if (mode == 0) hipLaunchKernelGGL(k_prolong_set<false>, dim3(blocks(most), pl.Lam + 1), dim3(kB), 0, s, S);
+    else hipLaunchKernelGGL(k_prolong_set<true>, dim3(blocks(most), pl.Lam + 1), dim3(kB), 0, s, S);
   }
 
   void restrict_into(const PatchL& fine, const double* src, bool mask, double* out1, double* out2, const PatchL& coarse,
@@ -1042,6 +1165,33 @@ struct AmrRun {
   // the arrays tmp (corrections, homogeneous root conditions) or u (the solution, FMG)
   void normal_fill(int k, bool on_u = false) {
     auto arr = [&](PatchL& p) { return on_u ? p.u : p.tmp; };
+    if (k >= 1) {
+      // two or more cells per block: every patch's hole lies two cells or more inside it, so the
+      // covered layer beside a hole's faces (all that the prolongations read of it) and the shells
+      // depend on active cells alone, and all patches go in one launch each (a finer hole's
+      // cells count as 0: they reach only what nothing reads)
+      if (pl.Lam > 0) {
+        Set<RestrictA> R{};
+        size_t most = 0;
+        for (int l = 1; l <= pl.Lam; ++l) {
+          PatchL &f = pl.P[l][k], &c = pl.P[l - 1][k];
+          R.a[l - 1] = restrict_args(f, arr(f), true, arr(c), nullptr, c, c.hole.lo);
+          most = std::max(most, cells(R.a[l - 1].nr));
+        }
+        hipLaunchKernelGGL(k_restrict_set, dim3(blocks(most), pl.Lam), dim3(kB), 0, s, R);
+      }
+      Set<ProlongA> S{};
+      PatchL& r = pl.P[0][k];
+      size_t most = ghost_faces(r.d);
+      for (int l = 1; l <= pl.Lam; ++l) {
+        PatchL &f = pl.P[l][k], &c = pl.P[l - 1][k];
+        S.a[l - 1] = prolong_args(c, arr(c), f, arr(f));
+        most = std::max(most, ghost_faces(f.d));
+      }
+      hipLaunchKernelGGL(k_shell_set, dim3(blocks(most), pl.Lam + 1), dim3(kB), 0, s, S, pl.Lam, arr(r), r.d,
+                         phys_for(r.d.n[0], on_u ? false : true), on_u ? 0 : 1);
+      return;
+    }
     for (int l = pl.Lam; l >= 1; --l) {
       PatchL &f = pl.P[l][k], &c = pl.P[l - 1][k];
       restrict_into(f, arr(f), false, arr(c), nullptr, c, c.hole.lo);
@@ -1076,33 +1226,32 @@ struct AmrRun {
     return q;
   }
 
-  // cell-volume-weighted mean over the active cells of level k (all patches): one launch and
-  // one copy of the partials, summed on the host patch by patch in block order
+  // cell-volume-weighted mean over the active cells of level k of f's (which_arr = 1) or u's (0)
+  // values (what = 0) or squares (1), or of the squared defect of u (2)
   double volume_mean(int k, int which_arr, int what) {
     Set<SumA> S{};
-    int most = 1;
-    for (int l = 0; l <= pl.Lam; ++l) {
-      const PatchL& p = pl.P[l][k];
-      const double* v = which_arr == 0 ? p.u : which_arr == 1 ? p.f : p.tmp;
-      const int nb = (int)std::min<size_t>(kMaxPartials, std::max<size_t>(1, cells(p.d) / (kB * 4)));
-      S.a[l] = SumA{v, p.d, hole_of(p), nb};
-      most = std::max(most, nb);
-    }
-    hipLaunchKernelGGL(k_psum_set, dim3(most, pl.Lam + 1), dim3(kB), 0, s, S, what, part, kMaxPartials);
-    (void)hipMemcpyAsync(hpart, part, sizeof(double) * kMaxPartials * (pl.Lam + 1), hipMemcpyDeviceToHost, s);
-    (void)hipStreamSynchronize(s);
-    double sum = 0.0, vol = 0.0;
+    SumBlocks B{};
+    double vol = 0.0;
     for (int l = 0; l <= pl.Lam; ++l) {
       const PatchL& p = pl.P[l][k];
       const double w = p.h * p.h * p.h;
-      double acc = 0.0;
-      for (int i = 0; i < S.a[l].nb; ++i) acc += hpart[(size_t)l * kMaxPartials + i];
-      sum += w * acc;
+      const int nb = (int)std::min<size_t>(512, std::max<size_t>(1, cells(p.d) / (kB * 4)));
+      S.a[l] = SumA{which_arr == 0 ? p.u : p.f, p.f, p.d, hole_of(p), 1.0 / (p.h * p.h), w};
+      B.first[l + 1] = B.first[l] + nb;
       size_t act = cells(p.d);
       if (p.hole.on) act -= (size_t)(p.hole.hi[0] - p.hole.lo[0]) * (p.hole.hi[1] - p.hole.lo[1]) * (p.hole.hi[2] - p.hole.lo[2]);
       vol += w * (double)act;
     }
-    return sum / vol;
+    SumSink k1 = sink;
+    k1.first = 0;
+    k1.total = B.first[pl.Lam + 1];
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(k1.total), dim3(kB), 0, s, S, B, k1); };
+    if (what == 0) go(k_sum_set<0>);
+    else if (what == 1) go(k_sum_set<1>);
+    else go(k_sum_set<2>);
+    (void)hipMemcpyAsync(host, k1.out, sizeof(double), hipMemcpyDeviceToHost, s);
+    (void)hipStreamSynchronize(s);
+    return *host / vol;
   }
 
   // one uniform FAS V-cycle on the root grid (NB^3 down to one cell), physical conditions
@@ -1281,9 +1430,8 @@ struct AmrRun {
     // ---- MeshBlock levels, down
     for (int k = kt; k >= 1; --k) {
       smooth_level(k, npre);
-      lap_level(k, 0, 0, 0, -1.0);                      // tmp = f - L u
-      restrict_level(k);
-      if (k - 1 >= 1) lap_level(k - 1, 1, 1, 1, 1.0);   // f = dres + L pbar
+      down_level(k);
+      if (k - 1 >= 1) source_level(k - 1);
     }
     if (kind == 1) {
       // the uncovered cells of the coarser patches belong to this Octet level's composite
@@ -1380,8 +1528,8 @@ struct AmrRun {
   }
 
   double residual(double rms_f) {
-    lap_level(pl.K, 0, 0, 0, -1.0);
-    const double rd = std::sqrt(volume_mean(pl.K, 2, 1));
+    fill_level(pl.K, 0);
+    const double rd = std::sqrt(volume_mean(pl.K, 0, 2));
     return rms_f > 0 ? rd / rms_f : rd;
   }
 };
@@ -1466,7 +1614,7 @@ int mg_amr_patch_dims(const mg_amr_mesh* m, int lam, int dims[3]) {
 // Solve on the refined mesh.  The workspace is the caller's pool (*pool, *pool_cap bytes),
 // grown here when the mesh needs more (at most `room` bytes) and kept for the next call.
 int amr_solve_impl(int device, const mg_params* p, const mg_amr_mesh* m, const mg_bc* bc, const double* const* rho,
-                   double* const* phi, double* hist, int* n_hist, void* stream, double* part, double* hpart,
+                   double* const* phi, double* hist, int* n_hist, void* stream, const SumSink& sink, double* host,
                    double** pool, size_t* pool_cap, size_t room, std::string* err) {
   Plan pl;
   int st = amr_plan(m, pl, err);
@@ -1635,8 +1783,8 @@ int amr_solve_impl(int device, const mg_params* p, const mg_amr_mesh* m, const m
   AmrRun R;
   R.pl = pl;
   R.s = s;
-  R.part = part;
-  R.hpart = hpart;
+  R.sink = sink;
+  R.host = host;
   for (int f = 0; f < 6; ++f) R.kinds[f] = bc->kind[f] == MG_BC_MULTIPOLE ? MG_BC_FIXED : bc->kind[f];
   R.npre = p->npre;
   R.npost = p->npost;

@@ -140,11 +140,11 @@ struct mg_ctx {
   int tile[2] = {-1, -1};
 };
 
-// refined-mesh solve (mg_amr.hip); part: device partials (kMaxPartials x 32 doubles), hpart:
-// host partials (kMaxPartials x (MG_AMR_MAX_LEVELS + 1) doubles); *pool / *pool_cap: the
+// refined-mesh solve (mg_amr.hip); sink: where sums go, *host: one double of pinned host memory
+// they are read through; *pool / *pool_cap: the
 // caller's workspace, grown (up to `room` bytes) when the mesh needs more
 int amr_solve_impl(int device, const mg_params* p, const mg_amr_mesh* m, const mg_bc* bc, const double* const* rho,
-                   double* const* phi, double* hist, int* n_hist, void* stream, double* part, double* hpart,
+                   double* const* phi, double* hist, int* n_hist, void* stream, const SumSink& sink, double* host,
                    double** pool, size_t* pool_cap, size_t room, std::string* err);
 
 namespace {
@@ -2330,14 +2330,14 @@ int mg_amr_solve(mg_ctx* c, const mg_params* p, const mg_amr_mesh* mesh, const m
                  double* const* phi, double* hist, int* n_hist, void* stream) {
   if (!c) return MG_ERR_INVALID_ARG;
   if (n_hist) *n_hist = 0;
-  std::vector<double> hpart((size_t)kMaxPartials * (MG_AMR_MAX_LEVELS + 1));   // one row of partials per patch
   // what the budget leaves for the refined-mesh workspace (its current size included)
   size_t room = SIZE_MAX;
   if (c->hbm_budget) {
     const size_t other = kFixedBytes + c->ws_cap + c->op_scratch_cap;
     room = c->hbm_budget > other ? c->hbm_budget - other : 0;
   }
-  return amr_solve_impl(c->device, p, mesh, bc, rho, phi, hist, n_hist, stream, c->part, hpart.data(), &c->amr_ws,
+  return amr_solve_impl(c->device, p, mesh, bc, rho, phi, hist, n_hist, stream, sum_sink(c->part, c->scal, 2), c->hscal,
+                        &c->amr_ws,
                         &c->amr_ws_cap, room, &c->err);
 }
 
