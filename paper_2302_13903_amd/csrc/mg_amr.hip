@@ -14,9 +14,9 @@
 // correction is prolongated, the normal level boundary restricts the finer patch into the
 // covered coarse cells and prolongates the coarse patch into the finer patch's ghost shell.
 //
-// Every operator is one plain launch over a patch (the refined levels are small next to the
-// uniform path; this is the correctness-first form of the refined solver).  Arithmetic follows
-// the same expressions in the same order as the oracle, so results agree to rounding.
+// On the MeshBlock levels an operator is one launch over the patches of all refinement levels, the
+// Octet levels and the root grid are one launch altogether.  Arithmetic follows the same
+// expressions in the same order as the oracle, so results agree to rounding.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -45,6 +45,14 @@ inline size_t ghosted(const Dims& d) { return (size_t)(d.n[0] + 2) * (d.n[1] + 2
 __device__ inline size_t ghosted_d(const Dims& d) { return (size_t)(d.n[0] + 2) * (d.n[1] + 2) * (d.n[2] + 2); }
 __host__ __device__ inline size_t cells(const Dims& d) { return (size_t)d.n[0] * d.n[1] * d.n[2]; }
 inline unsigned blocks(size_t work) { return (unsigned)std::max<size_t>(1, (work + kB - 1) / kB); }
+// Work item of this thread where the items read their neighbours: workgroups go to the eight XCDs in
+// turn, so each XCD takes a contiguous eighth of the items (a grid of a multiple of 8) and its L2
+// holds the rows and planes they share: one colour of five patches of 128^3 47 us in plain order,
+// 43 us so (252 MB of u and f read and u written: 5.9 TB/s).
+__device__ inline size_t near_item() {
+  return (size_t)((blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3)) * kB + threadIdx.x;
+}
+inline unsigned blocks8(size_t work) { return (blocks(work) + 7) / 8 * 8; }
 // work items of one colour of k_smooth (x-pairs when the x extent is even)
 __host__ __device__ inline size_t smooth_items(const Dims& d) { return (d.n[0] & 1) ? cells(d) : cells(d) / 2; }
 
@@ -266,7 +274,7 @@ struct SmoothA {
 };
 __global__ void __launch_bounds__(kB) k_smooth_set(Set<SmoothA> S, double omega, int colour) {
   const SmoothA& A = S.a[blockIdx.y];
-  smooth_body(A.u, A.f, A.d, A.o[0], A.o[1], A.o[2], A.H, A.h2, omega, colour, (size_t)blockIdx.x * kB + threadIdx.x);
+  smooth_body(A.u, A.f, A.d, A.o[0], A.o[1], A.o[2], A.H, A.h2, omega, colour, near_item());
 }
 
 // ---- out = a + s L u on the active cells (defect: a = f, s = -1; FAS source: a = restricted
@@ -298,7 +306,7 @@ struct LapA {
 };
 __global__ void __launch_bounds__(kB) k_lap_set(Set<LapA> S, double s) {
   const LapA& A = S.a[blockIdx.y];
-  lap_body(A.u, A.a, A.out, A.d, A.H, A.ih2, s, (size_t)blockIdx.x * kB + threadIdx.x);
+  lap_body(A.u, A.a, A.out, A.d, A.H, A.ih2, s, near_item());
 }
 
 // ---- 8-cell mean (eq. restriction) of the fine patch into coarse cells [0, nr) written at
@@ -340,7 +348,7 @@ struct RestrictA {
 // The step down of every patch in one launch, a coarse cell per thread: u restricted into phibar and
 // the coarse u, the defect f - L u of its eight children into the coarse source of FAS; covered
 // cells count as 0 in both.  (Apart, the defects cost a write and a read of every cell: on five
-// patches of 128^3 51 + 2 x 16 us, 59 us in one.)
+// patches of 128^3 51 + 2 x 16 us, 57 us in one.)
 struct DownA {
   const double *u, *f;
   double *pbar, *uc, *dres;
@@ -351,7 +359,7 @@ struct DownA {
 __global__ void __launch_bounds__(kB) k_down_set(Set<DownA> S) {
   const DownA& A = S.a[blockIdx.y];
   const Dims nr{{A.d.n[0] / 2, A.d.n[1] / 2, A.d.n[2] / 2}};
-  const size_t t = (size_t)blockIdx.x * kB + threadIdx.x;
+  const size_t t = near_item();
   if (t >= cells(nr)) return;
   int X, Y, Z;
   cell_of(t, nr, X, Y, Z);
@@ -451,7 +459,7 @@ template <bool CUBIC>
 __global__ void __launch_bounds__(kB) k_prolong_set(Set<ProlongA> S) {
   const ProlongA& A = S.a[blockIdx.y];
   const Dims dp{{A.df.n[0] / 2, A.df.n[1] / 2, A.df.n[2] / 2}};
-  const size_t t = (size_t)blockIdx.x * kB + threadIdx.x;
+  const size_t t = near_item();
   if (t >= cells(dp)) return;
   int x, y, z;
   cell_of(t, dp, x, y, z);
@@ -615,9 +623,12 @@ __global__ void __launch_bounds__(kB) k_sum_set(Set<SumA> S, SumBlocks B, SumSin
   int q = 0;
   while ((int)blockIdx.x >= B.first[q + 1]) ++q;
   const SumA& A = S.a[q];
-  const size_t step = (size_t)(B.first[q + 1] - B.first[q]) * kB;
+  // each block a contiguous run of cells, each XCD neighbouring runs (as near_item)
+  const unsigned nb = (unsigned)(B.first[q + 1] - B.first[q]), b = blockIdx.x - (unsigned)B.first[q];
+  const unsigned mine = nb % 8 == 0 ? (b & 7u) * (nb >> 3) + (b >> 3) : b;
+  const size_t run = (cells(A.d) + nb - 1) / nb, end = min(cells(A.d), (mine + 1) * run);
   double acc = 0.0;
-  for (size_t t = (size_t)((int)blockIdx.x - B.first[q]) * kB + threadIdx.x; t < cells(A.d); t += step) {
+  for (size_t t = mine * run + threadIdx.x; t < end; t += kB) {
     int x, y, z;
     cell_of(t, A.d, x, y, z);
     if (covered(A.H, x, y, z)) continue;
@@ -672,7 +683,7 @@ __global__ void k_coarsest(double* u, const double* f, Phys P, double h2) {
 // (the source replaces the restricted defect in place, cell by cell; the levels' starting u is
 // phibar) and only u goes back; larger meshes work in global memory, cached in the CU, whose waves
 // share the L1, so that a barrier orders their accesses.
-// Five Octet levels of 8^3: 301 us in global memory (with its scratch traffic), 138 us in LDS.
+// Five Octet levels of 8^3: 301 us in global memory (with its scratch traffic), 128 us in LDS.
 constexpr int kRootTailN = 16;
 constexpr int kMaxRoot = 10;         // root levels 256^3 .. 1
 constexpr int kMidMaxCells = 4096;   // 16^3: per Octet patch, in global memory
@@ -705,7 +716,7 @@ struct MidPlaces {
 static_assert(sizeof(OctSet) + sizeof(RootSet) + sizeof(MidPlaces) + 64 <= 4096, "k_mid arguments are limited to 4 KiB");
 static_assert(kMpMaxBoxes >= MG_AMR_MAX_LEVELS + 1, "one multipole box per refinement level");
 
-constexpr int mid_threads(bool lds) { return lds ? 512 : 1024; }
+constexpr int kMidThreads = 1024;    // (in LDS 128 us; 138 with 512)
 
 template <typename F>
 __device__ __forceinline__ void forall(size_t work, F fn) {
@@ -804,7 +815,7 @@ __device__ __forceinline__ void move_body(const double* src, double* dst, const 
 
 // the root levels from q0: u improved by one V-cycle with the source in f
 template <bool LDS>
-__global__ void __launch_bounds__(mid_threads(LDS)) k_root_tail(RootSet S, MidPlaces at, int q0, int npre, int npost,
+__global__ void __launch_bounds__(kMidThreads) k_root_tail(RootSet S, MidPlaces at, int q0, int npre, int npost,
                                                                  double omega) {
   __shared__ double arena[LDS ? kMidLds : 1];
   const MidMem<LDS> M{arena, at};
@@ -850,7 +861,7 @@ __device__ inline size_t cons_most(const Dims& df) {
 // down from the MeshBlock levels (every level's phibar and restricted defect are there); else the
 // V-cycle of Octet level top itself, u there to be improved with the source src.
 template <bool LDS>
-__global__ void __launch_bounds__(mid_threads(LDS)) k_mid(OctSet O, RootSet R, MidPlaces at, int top, const double* src,
+__global__ void __launch_bounds__(kMidThreads) k_mid(OctSet O, RootSet R, MidPlaces at, int top, const double* src,
                                                            int npre, int npost, double omega) {
   __shared__ double arena[LDS ? kMidLds : 1];
   const MidMem<LDS> M{arena, at};
@@ -1074,7 +1085,7 @@ struct AmrRun {
     for (int it = 0; it < sweeps; ++it)
       for (int colour = 0; colour < 2; ++colour) {
         fill_level(k, 0);
-        hipLaunchKernelGGL(k_smooth_set, dim3(blocks(most), pl.Lam + 1), dim3(kB), 0, s, S, omega, colour);
+        hipLaunchKernelGGL(k_smooth_set, dim3(blocks8(most), pl.Lam + 1), dim3(kB), 0, s, S, omega, colour);
       }
   }
 
@@ -1088,7 +1099,7 @@ struct AmrRun {
       S.a[l] = LapA{p.pbar, p.dres, p.f, p.d, hole_of(p), 1.0 / (p.h * p.h)};
       most = std::max(most, cells(p.d));
     }
-    hipLaunchKernelGGL(k_lap_set, dim3(blocks(most), pl.Lam + 1), dim3(kB), 0, s, S, 1.0);
+    hipLaunchKernelGGL(k_lap_set, dim3(blocks8(most), pl.Lam + 1), dim3(kB), 0, s, S, 1.0);
   }
 
   static RestrictA restrict_args(const PatchL& fine, const double* src, bool mask, double* out1, double* out2,
@@ -1115,7 +1126,7 @@ struct AmrRun {
       S.a[l] = DownA{p.u, p.f, c.pbar, c.u, c.dres, p.d, c.d, hole_of(p), 1.0 / (p.h * p.h)};
       most = std::max(most, cells(c.d));
     }
-    hipLaunchKernelGGL(k_down_set, dim3(blocks(most), pl.Lam + 1), dim3(kB), 0, s, S);
+    hipLaunchKernelGGL(k_down_set, dim3(blocks8(most), pl.Lam + 1), dim3(kB), 0, s, S);
   }
   static ProlongA prolong_args(const PatchL& c, const double* uc, const PatchL& p, double* uf) {
     ProlongA A{};
@@ -1140,8 +1151,8 @@ struct AmrRun {
       S.a[l] = prolong_args(c, mode == 0 ? c.tmp : c.u, p, p.u);
       most = std::max(most, cells(p.d) / 8);
     }
-    if (mode == 0) hipLaunchKernelGGL(k_prolong_set<false>, dim3(blocks(most), pl.Lam + 1), dim3(kB), 0, s, S);
-    else hipLaunchKernelGGL(k_prolong_set<true>, dim3(blocks(most), pl.Lam + 1), dim3(kB), 0, s, S);
+    if (mode == 0) hipLaunchKernelGGL(k_prolong_set<false>, dim3(blocks8(most), pl.Lam + 1), dim3(kB), 0, s, S);
+    else hipLaunchKernelGGL(k_prolong_set<true>, dim3(blocks8(most), pl.Lam + 1), dim3(kB), 0, s, S);
   }
 
   void restrict_into(const PatchL& fine, const double* src, bool mask, double* out1, double* out2, const PatchL& coarse,
@@ -1288,9 +1299,9 @@ struct AmrRun {
     if (n <= kRootTailN && (int)pl.R.size() < kMaxRoot && u == top.u && f == top.f) {
       MidPlaces at{};
       if (mid_places(-1, q, at))
-        hipLaunchKernelGGL(k_root_tail<true>, dim3(1), dim3(mid_threads(true)), 0, s, root_set(), at, q, npre, npost, omega);
+        hipLaunchKernelGGL(k_root_tail<true>, dim3(1), dim3(kMidThreads), 0, s, root_set(), at, q, npre, npost, omega);
       else
-        hipLaunchKernelGGL(k_root_tail<false>, dim3(1), dim3(mid_threads(false)), 0, s, root_set(), at, q, npre, npost, omega);
+        hipLaunchKernelGGL(k_root_tail<false>, dim3(1), dim3(kMidThreads), 0, s, root_set(), at, q, npre, npost, omega);
       return;
     }
     if (n == 1) {
@@ -1361,10 +1372,10 @@ struct AmrRun {
                     {p.hole.lo[0], p.hole.lo[1], p.hole.lo[2]}, {p.hole.hi[0], p.hole.hi[1], p.hole.hi[2]}};
     }
     if (lds)
-      hipLaunchKernelGGL(k_mid<true>, dim3(1), dim3(mid_threads(true)), 0, s, O, root_set(), at, lam_top, src, npre, npost,
+      hipLaunchKernelGGL(k_mid<true>, dim3(1), dim3(kMidThreads), 0, s, O, root_set(), at, lam_top, src, npre, npost,
                          omega);
     else
-      hipLaunchKernelGGL(k_mid<false>, dim3(1), dim3(mid_threads(false)), 0, s, O, root_set(), at, lam_top, src, npre, npost,
+      hipLaunchKernelGGL(k_mid<false>, dim3(1), dim3(kMidThreads), 0, s, O, root_set(), at, lam_top, src, npre, npost,
                          omega);
     return true;
   }
