@@ -1718,7 +1718,7 @@ int autotune_blocks(mg_ctx* c, const mg_params* p, int Lb, int reps) {
         }
     c->blk_tune[(sizeof(T) == 8 ? 0 : 1000) + 100 * Lm + Lb] = best;
     if (l == L && p->npre == 2 && p->npost == 2 && (1 << l) >= march_min_n<T>(c) && blk_march_fits(l)) {
-      // V(2,2) on the finest block level: both legs as the two-sweep streaming passes across
+      // V(2,2) on the finest block level: both legs as the streaming passes across
       // blocks against the four halo-tile sweeps alone (a lower bound on that schedule)
       T* fc = buf[3];
       T* uc = buf[3] + cellsL / 8;

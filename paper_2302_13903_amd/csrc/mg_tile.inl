@@ -441,6 +441,11 @@ void launch_shape(const TileArgs& A, hipStream_t s) {
     default: launch_maybe_timed(k_tile_leg<T, NS, UP, WALLS, 1>, g, dim3(tile_threads(NS, 1)), 0, s, A); break;
   }
 }
+// Measured per launch, down / up, FP64 periodic: 64^3 9.5 / 11.2 us with two sweeps (six gathered
+// neighbours per update: 15.1 / 22.3), 6.3 / 7.3 with one; 32^3 6.5 / 6.8 (9.3 / 11.4) and 4.7 / 4.9;
+// FP32 with walls 64^3 6.8 / 9.0, 32^3 5.3 / 6.7.  At 128^3 47 / 49 us with walls, where the
+// streaming passes are faster (march_min_n).  Bound by the chain of LDS exchanges and barriers, one per
+// colour, of workgroups of one residency.
 template <typename T, int NS, bool UP>
 void launch_leg(const TileArgs& A, hipStream_t s) {
   if (A.per != 7) launch_shape<T, NS, UP, true>(A, s);

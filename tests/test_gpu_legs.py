@@ -189,3 +189,23 @@ def test_one_sweep_cycles_agree_across_layouts_and_schemes(mg, kind):
     assert rel(host(mg.from_blocks(b, n, 16)), a) < 1e-10 and rel(host(c), a) < 1e-10
     for h in (hb, hc):
         assert len(h) == len(ha) and all(abs(x - y) <= 1e-6 * y for x, y in zip(h, ha))
+
+
+@pytest.mark.parametrize("n,lb,lmax", [(8, 0, 4), (16, 0, 4), (32, 0, 3), (128, 0, 4), (256, 0, 4), (64, 3, 4), (64, 4, 2)])
+def test_moments_by_columns(mg, n, lb, lmax):
+    """Moments summed column by column (8, 16 and 32 cells, a whole side or a part) against the
+    oracle's, and the potential of a solve in blocks against the dense one.  A moment is a sum of
+    n^3 terms no larger than the mass's (the box has side 1): 1e-12 of the mass."""
+    rng = np.random.default_rng(n + lb)
+    rho = rng.random((n,) * 3)
+    kw = dict(lmax=lmax, fixed_cycles=3)
+    if lb:
+        a, _, _ = mg.solve(dev(rho), 1.0 / n, "multipole", **kw)
+        b, _, _ = mg.solve(mg.to_blocks(dev(rho), 1 << lb), 1.0 / n, "multipole", layout="blocks", block_n=1 << lb, **kw)
+        assert rel(host(mg.from_blocks(b, n, 1 << lb)), host(a)) < 1e-12
+        return
+    o_ref, q_ref = oracle.multipole_moments(rho, 1.0 / n, lmax=lmax)
+    o, q = mg.mg_multipole_moments(dev(rho), 1.0 / n, lmax=lmax)
+    nq = (lmax + 1) ** 2
+    assert np.abs(np.asarray(o) - np.asarray(o_ref)).max() < 1e-12
+    assert np.abs(np.asarray(q)[:nq] - np.asarray(q_ref)[:nq]).max() < 1e-12 * abs(q_ref[0])
