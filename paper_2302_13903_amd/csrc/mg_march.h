@@ -39,7 +39,7 @@ void march_down_fas_ns(const T* uin, T* uout, const T* f, T* fc, T* pbar, T* uc0
 inline bool march_sweeps_ok(int ns) { return ns == 1 || ns == 2; }
 
 // Down step of a V-cycle level (Alg. 1 steps 1-3) in one pass: ns smoothing sweeps of u, the
-// defect of the result restricted into fc, and the coarse correction uc0 cleared.
+// defect of the result restricted into fc, and the coarse correction uc0 (if any) cleared.
 // uin == nullptr (Lm = 0 only): u is zero on input and is not read.
 // Lm > 0: the level is in the MeshBlock layout with blocks of 2^Lm cells per side (the coarse
 // level below in the layout with blocks of 2^(Lm-1), or the dense root grid when Lm = 1).

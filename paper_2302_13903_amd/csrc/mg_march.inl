@@ -93,7 +93,7 @@ struct MarchArgs {
   const void* f;
   const void* ec;    // up: coarse correction (n/2)^3
   void* fc;          // down: restricted defect (n/2)^3
-  void* uc0;         // down: coarse correction to clear (FAS: to start from phibar)
+  void* uc0;         // down: coarse correction to clear, or null (FAS: to start from phibar)
   void* pbar;        // FAS down: the restricted potential phibar
   SumSink sink;      // norm: where the sum of squared defects goes
   LevelBC bc;        // this level
@@ -753,7 +753,7 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
               const size_t ci = cdx(xag >> 1, ygv[2 * j] >> 1, p >> 1);
               fcp[ci] = stash[j];
               if constexpr (FAS) reinterpret_cast<T*>(A.pbar)[ci] = stash_u[j];
-              ucp[ci] = FAS ? stash_u[j] : (T)0;
+              if (FAS || ucp) ucp[ci] = FAS ? stash_u[j] : (T)0;
             }
         }
       }

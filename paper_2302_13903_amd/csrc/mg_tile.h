@@ -27,7 +27,7 @@ inline bool tile_sweeps_ok(int ns) { return ns == 1 || ns == 2; }
 
 // Down step of a V-cycle level (Alg. 1 steps 1-3) in one launch: ns smoothing sweeps of u
 // (uin -> uout, distinct arrays), the defect restricted into fc and the coarse correction uc0
-// cleared.  Lm > 0: the level is in the MeshBlock layout with blocks of 2^Lm cells per side (the
+// (if any) cleared.  Lm > 0: the level is in the MeshBlock layout with blocks of 2^Lm cells per side (the
 // coarse level in the layout below, or the dense root grid when Lm = 1); Lm = 0: dense.
 // pbar != nullptr: the down step of a Full Approximation Scheme cycle (Alg. 3 steps 2-4) --
 // phibar (the mean of the 8 children of the swept u) is written to pbar and to uc0, the coarse

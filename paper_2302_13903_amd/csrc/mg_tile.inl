@@ -54,7 +54,7 @@ struct TileArgs {
   const void* f;
   const void* ec;    // up: coarse correction
   void* fc;          // down: restricted defect
-  void* uc0;         // down: coarse correction to clear (FAS: to start from phibar)
+  void* uc0;         // down: coarse correction to clear, or null (FAS: to start from phibar)
   void* pbar;        // FAS down (Alg. 3 steps 2-4), else null: receives phibar, the mean of the
                      // 8 children of the swept u, from which the coarse level then starts
   SumSink sink;      // up: where the sum of squared defects goes (part null: not wanted)
@@ -391,7 +391,7 @@ __global__ void __launch_bounds__(tile_threads(NS, SH), SH == 0 ? 4 : 1) k_tile_
           reinterpret_cast<T*>(A.pbar)[ci] = pb;
           uc0[ci] = pb;
         } else {
-          uc0[ci] = (T)0;
+          if (uc0) uc0[ci] = (T)0;
         }
       }
     } else {
