@@ -54,8 +54,8 @@
 //      rows 1 and 2 of the same lane as their active neighbour; before each stage the ghost
 //      cells the stage reads are set to kappa times that neighbour (in-lane);
 //   z: planes outside are zero and stay so (their updates have weight zero), and on the first
-//      and last plane the factor of the cell's own value is 6 - kappa (uniform: no instruction
-//      more than inside).
+//      and last plane kappa times the cell's own value joins its neighbours (kappa uniform and 0
+//      inside: one multiply-add an update).
 // Cells outside in x or y are loaded from their periodic image (every address in range, no
 // predicated loads) and swept like the others; no active cell reads them.  The coarse
 // correction's taps (homogeneous conditions) are clamped to the domain with the sign of each
@@ -344,17 +344,16 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
     // does any cell of this wave sit beside a wall in y?
     const int wy0 = ys - kHalo + w * 2 * R, wy1 = wy0 + 2 * R - 1;
     const bool wave_y = XYW && !py && (wy0 < 0 || wy1 >= n);
-    // plane p: 6 less the z walls' factors, and the weight of an update (0 outside the domain)
+    // plane p: the z walls' factors on the own value, and the weight of an update (0 outside the domain)
     struct PlaneW {
-      T c6, wz;
+      T kz, om;
     };
-    const T w6 = omega * inv6;
     auto plane_w = [&](int p) __attribute__((always_inline)) {
       PlaneW v;
-      v.c6 = (T)6;
-      if (!pz && p == 0) v.c6 -= kappa_of<T>(A.bc, 4);
-      if (!pz && p == nm) v.c6 -= kappa_of<T>(A.bc, 5);
-      v.wz = pz || (unsigned)p < (unsigned)n ? w6 : (T)0;
+      v.kz = (T)0;
+      if (!pz && p == 0) v.kz += kappa_of<T>(A.bc, 4);
+      if (!pz && p == nm) v.kz += kappa_of<T>(A.bc, 5);
+      v.om = pz || (unsigned)p < (unsigned)n ? omega : (T)0;
       return v;
     };
     // up: the coarse correction's rules (homogeneous conditions)
@@ -567,8 +566,9 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
           if constexpr (FS < 0) fv = fr[r][q];
           else fv = q ? fl[FS][r][tid].b : fl[FS][r][tid].a;
           const T nbs = ((((xm + xp) + ym) + yp) + zm) + zp;
+          // (one form of the update for every level, so that its rounding does not depend on the walls)
           if constexpr (PER) uc[r][q] = c + omega * ((nbs - h2 * fv) * inv6 - c);
-          else uc[r][q] = c + pw.wz * ((nbs - h2 * fv) - pw.c6 * c);
+          else uc[r][q] = c + pw.om * (((nbs + pw.kz * c) - h2 * fv) * inv6 - c);
         }
       });
     };
@@ -581,7 +581,7 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
                       __attribute__((always_inline)) {
       constexpr int PAR = decltype(cPAR)::value, FS = decltype(cFS)::value;
       refresh(std::integral_constant<int, 2>{}, cPAR, uc);
-      const T c6 = PER ? (T)6 : plane_w(p).c6;
+      const T c6 = PER ? (T)6 : (T)6 - plane_w(p).kz;
       // the red cells' y neighbours beyond the band: black, set in this step
       xd[band][0][xl] = uc[0][PAR ? 0 : 1];
       xd[band][1][xl] = uc[R - 1][(R - 1 + PAR + 1) & 1];
