@@ -407,7 +407,10 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
     // cTAPS (up): 0 load both coarse planes of P, 1 (P odd) keep the upper plane of P-1 as the
     // lower one and load the upper, 2 (P even) keep the pair of P-1
     auto load_plane = [&](int P) __attribute__((always_inline)) {
-      const int Pg = P & nm, Pfg = (P - 1) & nm;
+      // f of a plane beyond a z wall is that of the first plane inside: the plane's updates weigh
+      // nothing, but 0 times a value that is not finite is not 0, and so it reaches only cells
+      // that the same value reaches inside
+      const int Pg = P & nm, Pfg = pz ? (P - 1) & nm : min(max(P - 1, 0), nm);
       // no branch around a load: at a join the waits on it would turn conservative
 #pragma unroll
       for (int r = 0; r < R; ++r) {

@@ -1,0 +1,74 @@
+"""V-cycle legs at their faces: non-finite sources beside one wall, against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from oracle import FIXED, PERIODIC, ZERO_GRADIENT
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+KINDS = {
+    "layer": [PERIODIC] * 4 + [FIXED, ZERO_GRADIENT],
+    "fixed": [FIXED] * 6,
+    "mixed": [FIXED, ZERO_GRADIENT, PERIODIC, PERIODIC, ZERO_GRADIENT, FIXED],
+    "periodic": [PERIODIC] * 6,
+}
+OMEGA = 1.15
+
+
+@pytest.fixture(scope="module")
+def mg():
+    import paper_2302_13903_amd as m
+    return m
+
+
+def dev(a, dt=torch.float64):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0", dt)
+
+
+def host(t):
+    torch.cuda.synchronize()
+    return t.cpu().numpy().astype(np.float64)
+
+
+def homogeneous(kinds):
+    return [k if k in (PERIODIC, ZERO_GRADIENT) else FIXED for k in kinds]
+
+
+def sweeps(u, f, h, kinds, bext, count):
+    for _ in range(count):
+        u = oracle.smooth(u, f, h, OMEGA, kinds, bext)
+    return u
+
+
+@pytest.mark.parametrize("f32", [False, True], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("ns", [1, 2])
+@pytest.mark.parametrize("kind", list(KINDS))
+@pytest.mark.parametrize("n", [32, 64, 128])
+def test_non_finite_source_stays_at_its_wall(mg, n, kind, ns, f32):
+    """A NaN or an infinity in f beside one wall makes exactly the cells non-finite that the sweeps
+    carry it to: none beside the opposite wall, unless the axis is periodic."""
+    kinds = KINDS[kind]
+    print(f"non-finite source n={n} {kind} ns={ns} f32={f32}", flush=True)
+    rng = np.random.default_rng(n + ns)
+    u, e = rng.standard_normal((n,) * 3), rng.standard_normal((n // 2,) * 3)
+    f = rng.standard_normal((n,) * 3) * n * n
+    f[n - 1, n // 2, n // 3] = np.nan
+    f[0, n // 4, n - 1] = np.inf
+    f[n // 2, n - 1, 5] = -np.inf
+    f[n // 3, 7, 0] = np.nan
+    none, dt, h = [None] * 6, (torch.float32 if f32 else torch.float64), 1.0 / n
+    down, up = (mg.mg_op_down_f32, mg.mg_op_up_f32) if f32 else (mg.mg_op_down, mg.mg_op_up)
+    ctx = mg.Context(0)
+    with np.errstate(all="ignore"):
+        ref = sweeps(u, f, h, kinds, none, ns)
+        ref_fc = oracle.restrict(oracle.defect(ref, f, h, kinds, none))
+        ref_up = sweeps(oracle.prolong_add(e, u, homogeneous(kinds)), f, h, kinds, none, ns)
+    du, fc, uc = dev(u, dt), dev(e, dt), dev(e, dt)
+    down(du, dev(f, dt), fc, uc, h, OMEGA, ns, kinds, none, ctx=ctx)
+    assert np.array_equal(np.isfinite(host(du)), np.isfinite(ref))
+    assert np.array_equal(np.isfinite(host(fc)), np.isfinite(ref_fc))
+    du = dev(u, dt)
+    up(du, dev(f, dt), dev(e, dt), h, OMEGA, ns, kinds, none, homogeneous(kinds), ctx=ctx)
+    assert np.array_equal(np.isfinite(host(du)), np.isfinite(ref_up))
