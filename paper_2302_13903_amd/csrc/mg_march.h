@@ -41,6 +41,7 @@ inline bool march_sweeps_ok(int ns) { return ns == 1 || ns == 2; }
 // Down step of a V-cycle level (Alg. 1 steps 1-3) in one pass: ns smoothing sweeps of u, the
 // defect of the result restricted into fc, and the coarse correction uc0 (if any) cleared.
 // uin == nullptr (Lm = 0 only): u is zero on input and is not read.
+// Face values: in f (launch_fold_faces), or in bc with u read and Lm = 0.
 // Lm > 0: the level is in the MeshBlock layout with blocks of 2^Lm cells per side (the coarse
 // level below in the layout with blocks of 2^(Lm-1), or the dense root grid when Lm = 1).
 template <typename T>
@@ -52,7 +53,8 @@ void march_down(const T* uin, T* uout, const T* f, T* fc, T* uc0, int n, int ns,
 
 // Up step (Alg. 1 steps 5-7) in one pass: u += trilinear(ec) (ec's ghosts from bcc) as u is
 // loaded, then ns smoothing sweeps.  sink != nullptr: the sum of squared defects of the result
-// (the convergence norm, Sec. 2.3.7) goes there.
+// (the convergence norm, Sec. 2.3.7) goes there.  Face values: in f, or in bc without a sink and with
+// Lm = 0.
 template <typename T>
 void march_up(const T* uin, T* uout, const T* f, const T* ec, const LevelBC& bcc, const SumSink* sink, int n, int ns,
               double h, double omega, const LevelBC& bc, hipStream_t s, int Lm = 0, const MarchAux* aux = nullptr) {

@@ -47,7 +47,9 @@
 // stays at six planes.  Tiles overlap by a halo of 6 cells (5 stages of radius 1, rounded up to
 // even) and are recomputed, so tiles are independent and the result goes to another array.
 //
-// Non-periodic faces (Sec. 2.3.6): face values stand in f (launch_fold_faces), so a ghost is kappa
+// Non-periodic faces (Sec. 2.3.6): face values b enter the source of the cells beside them, as
+// f - 2 b / h^2 (in f already in a solve: launch_fold_faces; as f is taken up in the passes of the
+// operator entry points, whose f is the caller's: k_march_values), so a ghost is kappa
 // times the adjacent active cell's current value, +1 at a zero-gradient face and -1 at a fixed one:
 //   x: the lane holding x = 0 (x = n-1) takes kappa * c in place of its left (right) neighbour;
 //   y: with 52-row output tiles and a halo of 6 the rows beyond y = 0 and y = n-1 are always
@@ -197,7 +199,8 @@ constexpr int kWaves = kMarchWaves;
 // FAS (down only, Alg. 3 steps 2-4): the restriction also writes the restricted potential
 // phibar (mean of the 8 children of the pass's result) into A.pbar and starts the coarse level
 // from it (uc0 = phibar instead of 0).
-template <typename T, int W, bool UP, bool NORM, int WALLS, bool BLK, bool FAS, bool ZIN>
+// VALUES: the face values are in A.bc and not in f (null: none on that face).
+template <typename T, int W, bool UP, bool NORM, int WALLS, bool BLK, bool FAS, bool ZIN, bool VALUES>
 __device__ __forceinline__ void march_body(const MarchArgs& A) {
   constexpr bool PER = WALLS == 0;                // every face periodic
   constexpr bool XYW = WALLS == 2;                // x or y walls may be in reach
@@ -668,6 +671,55 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
       }
     };
 
+    // ---- face values into f of plane Q, just taken up (fr): a wave beside a wall loads them and waits
+    auto take_values = [&](int Q) __attribute__((always_inline)) {
+      if constexpr (VALUES) {
+        const double w = -2.0 * A.ih2;
+        // one face's values for a cell of each of the four rows, or for the two cells of a row: at `at`
+        // and onwards by step; the indices are made here each time (as loop invariants they would
+        // hold registers through the march)
+        auto fold = [&](T& fv, const double* at) __attribute__((always_inline)) { fv = (T)((double)fv + w * *at); };
+        auto row_of = [&](int r) __attribute__((always_inline)) {
+          int y = ygv[r];
+          asm volatile("" : "+v"(y));
+          return y;
+        };
+        int x = xag;
+        asm volatile("" : "+v"(x));
+        if constexpr (XYW) {
+          const size_t line = (size_t)((pz ? Q & nm : min(max(Q, 0), nm)) + 1) * (size_t)(n + 2) + 1;
+          auto x_face = [&](int face, int e) __attribute__((always_inline)) {
+            const double* b = A.bc.b[face] + line;
+#pragma unroll
+            for (int r = 0; r < R; r += 2) {
+              const double* at = b + row_of(r);   // (a row pair neither wraps nor straddles a wall)
+              fold(fr[r][e], at);
+              fold(fr[r + 1][e], at + 1);
+            }
+          };
+          auto y_face = [&](int face, int r) __attribute__((always_inline)) {
+            const double* at = A.bc.b[face] + line + x;
+            fold(fr[r][0], at);
+            fold(fr[r][1], at + 1);
+          };
+          if (wx0 && A.bc.b[0]) x_face(0, 0);
+          if (wx1 && A.bc.b[1]) x_face(1, 1);
+          if (gy0 && A.bc.b[2]) y_face(2, 2);
+          if (gy1 && A.bc.b[3]) y_face(3, 1);
+        }
+        auto z_face = [&](int face) __attribute__((always_inline)) {
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            const double* at = A.bc.b[face] + (size_t)(row_of(r) + 1) * (size_t)(n + 2) + 1 + x;
+            fold(fr[r][0], at);
+            fold(fr[r][1], at + 1);
+          }
+        };
+        if (!pz && Q == 0 && A.bc.b[4]) z_face(4);
+        if (!pz && Q == nm && A.bc.b[5]) z_face(5);
+      }
+    };
+
     load_plane(zstart);
     load_taps(zstart, std::integral_constant<int, 0>{});
     prolong_apply(zstart, std::integral_constant<int, HZ & 1>{});
@@ -678,6 +730,7 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
       fr[r][0] = pf[r][0]; fr[r][1] = pf[r][1];
     }
     arrived(u[0], fr);
+    take_values(zstart - 1);
     // one pipeline step: the plane in ring slot K is P = zstart + t, t = g + K with g a
     // multiple of 6, so P - j sits in slot (K - j) mod 6, has parity (HZ + K + j) mod 2 (z0 is even),
     // and its f is in LDS slot (K - HZ - j) mod 3
@@ -760,6 +813,7 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
             }
         }
       }
+      take_values(P);   // (last: before the stores the FP64 up pass spills 100-160 bytes, 1.4 times its time)
     };
     for (int g = 0; g < nsteps; g += kRing) {
       static_for<kRing>([&](auto kk) __attribute__((always_inline)) { step(g, kk); });
@@ -782,19 +836,25 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
 
 template <typename T, int W, bool UP, bool NORM, int WALLS, bool BLK, int NS>
 __global__ void __launch_bounds__(kLanes* W) k_march(MarchArgs A) {
-  march_body<T, W, UP, NORM, WALLS, BLK, false, false>(A);
+  march_body<T, W, UP, NORM, WALLS, BLK, false, false, false>(A);
+}
+
+// A leg with face values, f being the caller's (the operator entry points).
+template <typename T, int W, bool UP, int WALLS, int NS>
+__global__ void __launch_bounds__(kLanes* W) k_march_values(MarchArgs A) {
+  march_body<T, W, UP, false, WALLS, false, false, false, true>(A);
 }
 
 // The down pass of a Full Approximation Scheme cycle (dense FP64 levels).
 template <typename T, int W, int WALLS, int NS>
 __global__ void __launch_bounds__(kLanes* W) k_march_fas(MarchArgs A) {
-  march_body<T, W, false, false, WALLS, false, true, false>(A);
+  march_body<T, W, false, false, WALLS, false, true, false, false>(A);
 }
 
 // The down pass from u = 0, which is not read (the first leg of a mixed-precision correction).
 template <typename T, int W, int WALLS, int NS>
 __global__ void __launch_bounds__(kLanes* W) k_march_zero(MarchArgs A) {
-  march_body<T, W, false, false, WALLS, false, false, true>(A);
+  march_body<T, W, false, false, WALLS, false, false, true, false>(A);
 }
 
 constexpr int kCUs = 256;
@@ -896,10 +956,11 @@ void launch_march(MarchArgs A, hipStream_t s, const MarchAux* aux) {
   else launch_maybe_timed(k_march<T, W, UP, NORM, 2, BLK, kNS>, dim3(grid), dim3(kLanes * W), 0, s, A);
 }
 
-// The down passes of FAS and from zero: one launch over every tile, the wall form chosen by the
-// level's faces.
-template <typename T, bool ZERO>
-void launch_march_down1(MarchArgs A, hipStream_t s) {
+// The down passes of FAS and from zero, and the legs with face values: one launch over every tile,
+// the wall form chosen by the level's faces.
+enum class OneLaunch { kFas, kZero, kValuesDown, kValuesUp };
+template <typename T, OneLaunch FORM>
+void launch_march_one(MarchArgs A, hipStream_t s) {
   bool per = true, xyper = true;
   for (int f = 0; f < 6; ++f) per = per && A.bc.kind[f] == BC_PERIODIC;
   for (int f = 0; f < 4; ++f) xyper = xyper && A.bc.kind[f] == BC_PERIODIC;
@@ -910,10 +971,15 @@ void launch_march_down1(MarchArgs A, hipStream_t s) {
   A.tiles_x = (A.n + A.xo - 1) / A.xo;
   A.tiles_y = (A.n + A.yo - 1) / A.yo;
   A.set = 0;
-  A.zc = march_zchunk(A.n, A.tiles_x * A.tiles_y, kStages + 1);
+  A.zc = march_zchunk(A.n, A.tiles_x * A.tiles_y, kStages + (FORM == OneLaunch::kValuesUp ? 0 : 1));
   A.ntiles = A.tiles_x * A.tiles_y * ((A.n + A.zc - 1) / A.zc);
   const int grid = (A.ntiles + 7) / 8 * 8;
-  if constexpr (ZERO) {
+  if constexpr (FORM == OneLaunch::kValuesDown || FORM == OneLaunch::kValuesUp) {
+    // (values only count on faces that fix one, so some face is a wall)
+    constexpr bool UP = FORM == OneLaunch::kValuesUp;
+    if (xyper) launch_maybe_timed(k_march_values<T, W, UP, 1, kNS>, dim3(grid), dim3(kLanes * W), 0, s, A);
+    else launch_maybe_timed(k_march_values<T, W, UP, 2, kNS>, dim3(grid), dim3(kLanes * W), 0, s, A);
+  } else if constexpr (FORM == OneLaunch::kZero) {
     if (per) launch_maybe_timed(k_march_zero<T, W, 0, kNS>, dim3(grid), dim3(kLanes * W), 0, s, A);
     else if (xyper) launch_maybe_timed(k_march_zero<T, W, 1, kNS>, dim3(grid), dim3(kLanes * W), 0, s, A);
     else launch_maybe_timed(k_march_zero<T, W, 2, kNS>, dim3(grid), dim3(kLanes * W), 0, s, A);
@@ -938,6 +1004,16 @@ MarchArgs base_args(const T* uin, T* uout, const T* f, int n, double h, double o
   return A;
 }
 
+// Does bc hold face values?  (Arrays of faces that fix none are dropped.)
+bool take_face_values(LevelBC& bc) {
+  bool any = false;
+  for (int f = 0; f < 6; ++f) {
+    if (!bc_has_value(bc.kind[f])) bc.b[f] = nullptr;
+    any = any || bc.b[f];
+  }
+  return any;
+}
+
 }  // namespace
 
 template <typename T, int NS>
@@ -948,7 +1024,8 @@ void march_down_ns(const T* uin, T* uout, const T* f, T* fc, T* uc0, int n, doub
   A.uc0 = uc0;
   A.Lm = Lm;
   if (Lm > 0) launch_march<T, false, false, true>(A, s, aux);
-  else if (!uin) launch_march_down1<T, true>(A, s);
+  else if (!uin) launch_march_one<T, OneLaunch::kZero>(A, s);
+  else if (take_face_values(A.bc)) launch_march_one<T, OneLaunch::kValuesDown>(A, s);
   else launch_march<T, false, false, false>(A, s, aux);
 }
 
@@ -959,7 +1036,7 @@ void march_down_fas_ns(const T* uin, T* uout, const T* f, T* fc, T* pbar, T* uc0
   A.fc = fc;
   A.pbar = pbar;
   A.uc0 = uc0;
-  launch_march_down1<T, false>(A, s);
+  launch_march_one<T, OneLaunch::kFas>(A, s);
 }
 
 template <typename T, int NS>
@@ -973,6 +1050,8 @@ void march_up_ns(const T* uin, T* uout, const T* f, const T* ec, const LevelBC& 
   if (Lm > 0) {
     if (sink) launch_march<T, true, true, true>(A, s, aux);
     else launch_march<T, true, false, true>(A, s, aux);
+  } else if (!sink && take_face_values(A.bc)) {
+    launch_march_one<T, OneLaunch::kValuesUp>(A, s);
   } else {
     if (sink) launch_march<T, true, true, false>(A, s, aux);
     else launch_march<T, true, false, false>(A, s, aux);

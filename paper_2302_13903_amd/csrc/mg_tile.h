@@ -31,7 +31,7 @@ inline bool tile_sweeps_ok(int ns) { return ns == 1 || ns == 2; }
 // coarse level in the layout below, or the dense root grid when Lm = 1); Lm = 0: dense.
 // pbar != nullptr: the down step of a Full Approximation Scheme cycle (Alg. 3 steps 2-4) --
 // phibar (the mean of the 8 children of the swept u) is written to pbar and to uc0, the coarse
-// level's starting iterate.
+// level's starting iterate.  Face values: in f (launch_fold_faces), or in bc.
 template <typename T>
 void tile_down(const T* uin, T* uout, const T* f, T* fc, T* pbar, T* uc0, int n, int Lm, int ns, double h, double omega,
                const LevelBC& bc, hipStream_t s) {
@@ -54,7 +54,7 @@ template <typename T>
 std::string tile_name(int ns, bool up, const LevelBC& bc, int n) {
   const bool walls = bc.kind[0] != BC_PERIODIC || bc.kind[2] != BC_PERIODIC || bc.kind[4] != BC_PERIODIC;
   return std::string("k_tile_leg<") + (sizeof(T) == 8 ? "double" : "float") + ", " + std::to_string(ns) +
-         (up ? ", true" : ", false") + (walls ? ", true, " : ", false, ") + (n >= 64 ? "0>" : "1>");
+         (up ? ", true" : ", false") + (walls ? ", true, " : ", false, ") + (n >= 64 ? "0, false>" : "1, false>");
 }
 
 }  // namespace mg

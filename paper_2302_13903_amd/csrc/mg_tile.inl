@@ -24,8 +24,9 @@
 // of f in every pass; u and f here cross once.)  Levels and times: see launch_leg.
 //
 // u += (omega/6) r with r = (neighbours - h^2 f) - (6 - kappa) u = -h^2 times the defect, kappa
-// the ghosts' factors on the cell's own value (face values stand in f: launch_fold_faces); cells
-// outside the domain hold zero and are not updated (weight zero).  The up leg first stages the coarse correction under the tile (homogeneous ghosts: periodic wrap, or the boundary cell
+// the ghosts' factors on the cell's own value (face values b stand in f as f - 2 b / h^2: from the
+// start in a solve, launch_fold_faces; put there as f is loaded in the legs of the operator entry
+// points, whose f is the caller's); cells outside the domain hold zero and are not updated (weight zero).  The up leg first stages the coarse correction under the tile (homogeneous ghosts: periodic wrap, or the boundary cell
 // with the face's sign).  The level may be dense or in the MeshBlock layout (the same code with
 // the block-major index, whose x, y and z parts are disjoint bits; the coarse side of the lowest
 // block level is the dense root grid).
@@ -110,8 +111,9 @@ __device__ __forceinline__ T wall_factor(const LevelBC& bc, int face) {
 }
 
 // WALLS: some face of the level is not periodic.  Layout, norm and FAS (a coarse index, a sum or
-// two stores at the end of a leg) are the launch's, not the kernel's.
-template <typename T, int NS, bool UP, bool WALLS, int SH>
+// two stores at the end of a leg) are the launch's, not the kernel's.  VALUES: the face values are in
+// A.bc and not in f (null: none on that face).
+template <typename T, int NS, bool UP, bool WALLS, int SH, bool VALUES>
 __global__ void __launch_bounds__(tile_threads(NS, SH), SH == 0 ? 4 : 1) k_tile_leg(TileArgs A) {
   typedef T v2 __attribute__((ext_vector_type(2)));
   constexpr int H = 2 * NS + 1;
@@ -243,6 +245,24 @@ __global__ void __launch_bounds__(tile_threads(NS, SH), SH == 0 ? 4 : 1) k_tile_
       f0 = in0 ? f0 : (T)0;
       u1 = in1 ? u1 : (T)0;
       f1 = in1 ? f1 : (T)0;
+      if constexpr (VALUES) {
+        // 2 / h^2 times the values of the faces that cell k of the column touches
+        auto values = [&](int k) __attribute__((always_inline)) {
+          auto at = [&](int face, int t1, int t2) __attribute__((always_inline)) {
+            return A.bc.b[face][(size_t)(t2 + 1) * (size_t)(n + 2) + (size_t)(t1 + 1)];
+          };
+          double v = 0.0;
+          if (A.bc.b[0] && i == 0) v += at(0, j, k);
+          if (A.bc.b[1] && i == nm) v += at(1, j, k);
+          if (A.bc.b[2] && j == 0) v += at(2, i, k);
+          if (A.bc.b[3] && j == nm) v += at(3, i, k);
+          if (A.bc.b[4] && k == 0) v += at(4, i, j);
+          if (A.bc.b[5] && k == nm) v += at(5, i, j);
+          return 2.0 * A.ih2 * v;
+        };
+        if (in0) f0 = (T)((double)f0 - values(k0 & nm));
+        if (in1) f1 = (T)((double)f1 - values(k1 & nm));
+      }
     }
     R[q] = p ? u0 : u1;
     B[q] = p ? u1 : u0;
@@ -433,12 +453,12 @@ int regions(int n) {
 }
 
 // One launch of the leg in the region shape of level side n.
-template <typename T, int NS, bool UP, bool WALLS>
+template <typename T, int NS, bool UP, bool WALLS, bool VALUES>
 void launch_shape(const TileArgs& A, hipStream_t s) {
   const dim3 g(regions(A.n));
   switch (shape_of(A.n)) {
-    case 0: launch_maybe_timed(k_tile_leg<T, NS, UP, WALLS, 0>, g, dim3(tile_threads(NS, 0)), 0, s, A); break;
-    default: launch_maybe_timed(k_tile_leg<T, NS, UP, WALLS, 1>, g, dim3(tile_threads(NS, 1)), 0, s, A); break;
+    case 0: launch_maybe_timed(k_tile_leg<T, NS, UP, WALLS, 0, VALUES>, g, dim3(tile_threads(NS, 0)), 0, s, A); break;
+    default: launch_maybe_timed(k_tile_leg<T, NS, UP, WALLS, 1, VALUES>, g, dim3(tile_threads(NS, 1)), 0, s, A); break;
   }
 }
 // Measured per launch, down / up, FP64 periodic: 64^3 9.5 / 11.2 us with two sweeps (six gathered
@@ -447,9 +467,15 @@ void launch_shape(const TileArgs& A, hipStream_t s) {
 // streaming passes are faster (march_min_n).  Bound by the chain of LDS exchanges and barriers, one per
 // colour, of workgroups of one residency.
 template <typename T, int NS, bool UP>
-void launch_leg(const TileArgs& A, hipStream_t s) {
-  if (A.per != 7) launch_shape<T, NS, UP, true>(A, s);
-  else launch_shape<T, NS, UP, false>(A, s);
+void launch_leg(TileArgs A, hipStream_t s) {
+  bool values = false;
+  for (int f = 0; f < 6; ++f) {
+    if (!bc_has_value(A.bc.kind[f])) A.bc.b[f] = nullptr;
+    values = values || A.bc.b[f];
+  }
+  if (values) launch_shape<T, NS, UP, true, true>(A, s);
+  else if (A.per != 7) launch_shape<T, NS, UP, true, false>(A, s);
+  else launch_shape<T, NS, UP, false, false>(A, s);
 }
 
 }  // namespace

@@ -1,4 +1,5 @@
-"""V-cycle legs at their faces: non-finite sources beside one wall, against the oracle."""
+"""V-cycle legs at their faces: non-finite sources beside one wall, against the oracle; face values
+under a memory budget."""
 import numpy as np
 import pytest
 
@@ -72,3 +73,36 @@ def test_non_finite_source_stays_at_its_wall(mg, n, kind, ns, f32):
     du = dev(u, dt)
     up(du, dev(f, dt), dev(e, dt), h, OMEGA, ns, kinds, none, homogeneous(kinds), ctx=ctx)
     assert np.array_equal(np.isfinite(host(du)), np.isfinite(ref_up))
+
+
+@pytest.mark.parametrize("f32", [False, True], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("ns", [1, 2])
+@pytest.mark.parametrize("kind", ["layer", "fixed", "mixed"])
+@pytest.mark.parametrize("n", [32, 64, 128, 256])
+def test_face_values_need_no_more_memory(mg, n, kind, ns, f32):
+    """A leg with face values takes one level array of scratch: with a budget of that much it runs the
+    same kernels as without one, bitwise, and leaves f as it was.  A zero-gradient face ignores values."""
+    kinds = KINDS[kind]
+    print(f"valued legs n={n} {kind} ns={ns} f32={f32}", flush=True)
+    gen = torch.Generator(device="cuda:0").manual_seed(n + ns)
+    dt, h = (torch.float32 if f32 else torch.float64), 1.0 / n
+
+    def rand(shape, t):
+        return torch.randn(shape, generator=gen, dtype=t, device="cuda:0")
+
+    u, f, e = rand((n,) * 3, dt), rand((n,) * 3, dt) * n * n, rand((n // 2,) * 3, dt)
+    f0 = f.clone()
+    bext = [rand((n + 2,) * 2, torch.float64) if k == FIXED else None for k in kinds]
+    ignored = [rand((n + 2,) * 2, torch.float64) if k == ZERO_GRADIENT else b for k, b in zip(kinds, bext)]
+    down, up = (mg.mg_op_down_f32, mg.mg_op_up_f32) if f32 else (mg.mg_op_down, mg.mg_op_up)
+    budget = mg.mg_footprint_bytes(mg.params(2, 0.5)) + u.element_size() * n ** 3
+    out = []
+    for ctx, b in ((mg.Context(0), bext), (mg.Context(0, hbm_budget=budget), ignored)):
+        a, fc, uc = u.clone(), torch.zeros_like(e), torch.ones_like(e)
+        down(a, f, fc, uc, h, OMEGA, ns, kinds, b, ctx=ctx)
+        c = u.clone()
+        up(c, f, e, h, OMEGA, ns, kinds, b, homogeneous(kinds), ctx=ctx)
+        out.append((a, fc, c))
+    torch.cuda.synchronize()
+    assert torch.equal(f, f0)
+    assert all(torch.equal(x, y) for x, y in zip(*out))
