@@ -2066,6 +2066,10 @@ bool op_tile(const mg_ctx* c, int n, int sweeps) {
   return (v < 0 || v == 1) && tile_sweeps_ok(sweeps) && n >= kTileMinN && n <= kTileMaxN && n < kFusedDefaultMinN;
 }
 
+// May a leg that found no memory for its scratch run as per-operator launches, in place?  With one
+// sweep below the streaming passes' levels, whose legs needed no scratch before they were one launch.
+inline bool op_in_place(int n, int sweeps, int st) { return st == MG_ERR_OOM && sweeps == 1 && n < kFusedMinN; }
+
 // Down step (Alg. 1 steps 1-3) with the context's fusion schedule for this precision.
 template <typename T>
 int op_down(mg_ctx* c, int n, double h, double omega, int npre, const mg_level_bc* bc, T* u, const T* f, T* fc, T* uc,
@@ -2079,12 +2083,13 @@ int op_down(mg_ctx* c, int n, double h, double omega, int npre, const mg_level_b
   if (march || op_tile<T>(c, n, npre)) {
     double* mem = nullptr;
     st = op_scratch(c, cells(ilog2(n)) * sizeof(T), &mem);
-    if (st) return st;
-    T* const tmp = reinterpret_cast<T*>(mem);
-    if (march) march_down<T>(u, tmp, f, fc, uc, n, npre, h, omega, b, s);
-    else tile_down<T>(u, tmp, f, fc, nullptr, uc, n, 0, npre, h, omega, b, s);
-    HIP_CHECK(c, hipMemcpyAsync(u, tmp, cells(ilog2(n)) * sizeof(T), hipMemcpyDeviceToDevice, s));
-    return op_epilogue(c);
+    if (st && !op_in_place(n, npre, st)) return st;
+    if (T* const tmp = reinterpret_cast<T*>(mem)) {
+      if (march) march_down<T>(u, tmp, f, fc, uc, n, npre, h, omega, b, s);
+      else tile_down<T>(u, tmp, f, fc, nullptr, uc, n, 0, npre, h, omega, b, s);
+      HIP_CHECK(c, hipMemcpyAsync(u, tmp, cells(ilog2(n)) * sizeof(T), hipMemcpyDeviceToDevice, s));
+      return op_epilogue(c);
+    }
   }
   if (fused_supported<T>(n) && npre > 0) {
     double* tmp = nullptr;
@@ -2125,12 +2130,13 @@ int op_up(mg_ctx* c, int n, double h, double omega, int npost, const mg_level_bc
   if ((march || op_tile<T>(c, n, npost)) && hom_arrays_null(bcc)) {
     double* mem = nullptr;
     st = op_scratch(c, cells(ilog2(n)) * sizeof(T), &mem);
-    if (st) return st;
-    T* const tmp = reinterpret_cast<T*>(mem);
-    if (march) march_up<T>(u, tmp, f, uc, bcc, nullptr, n, npost, h, omega, b, s);
-    else tile_up<T>(u, tmp, f, uc, bcc, nullptr, n, 0, npost, h, omega, b, s);
-    HIP_CHECK(c, hipMemcpyAsync(u, tmp, cells(ilog2(n)) * sizeof(T), hipMemcpyDeviceToDevice, s));
-    return op_epilogue(c);
+    if (st && !op_in_place(n, npost, st)) return st;
+    if (T* const tmp = reinterpret_cast<T*>(mem)) {
+      if (march) march_up<T>(u, tmp, f, uc, bcc, nullptr, n, npost, h, omega, b, s);
+      else tile_up<T>(u, tmp, f, uc, bcc, nullptr, n, 0, npost, h, omega, b, s);
+      HIP_CHECK(c, hipMemcpyAsync(u, tmp, cells(ilog2(n)) * sizeof(T), hipMemcpyDeviceToDevice, s));
+      return op_epilogue(c);
+    }
   }
   if (fused_supported<T>(n) && npost > 0) {
     double* tmp = nullptr;

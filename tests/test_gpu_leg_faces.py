@@ -1,5 +1,5 @@
 """V-cycle legs at their faces: non-finite sources beside one wall, against the oracle; face values
-under a memory budget."""
+under a memory budget, and legs on a budget that holds no scratch."""
 import numpy as np
 import pytest
 
@@ -106,3 +106,33 @@ def test_face_values_need_no_more_memory(mg, n, kind, ns, f32):
     torch.cuda.synchronize()
     assert torch.equal(f, f0)
     assert all(torch.equal(x, y) for x, y in zip(*out))
+
+
+@pytest.mark.parametrize("f32", [False, True], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("kind", ["periodic", "mixed"])
+def test_one_sweep_without_scratch(mg, kind, f32):
+    """One sweep at 32^3 on a budget that holds no level array runs in place, as with memory (u to the
+    sums' rounding, 40 epsilons of the terms of either side); two sweeps are refused."""
+    n, kinds = 32, KINDS[kind]
+    print(f"legs without scratch {kind} f32={f32}", flush=True)
+    rng = np.random.default_rng(4)
+    dt, h = (torch.float32 if f32 else torch.float64), 1.0 / n
+    u, f = dev(rng.standard_normal((n,) * 3), dt), dev(rng.standard_normal((n,) * 3) * n * n, dt)
+    e = dev(rng.standard_normal((n // 2,) * 3), dt)
+    bext = [dev(rng.standard_normal((n + 2,) * 2)) if k == FIXED else None for k in kinds]
+    down, up = (mg.mg_op_down_f32, mg.mg_op_up_f32) if f32 else (mg.mg_op_down, mg.mg_op_up)
+    tight = mg.Context(0, hbm_budget=mg.mg_footprint_bytes(mg.params(2, 0.5)))
+    out = []
+    for ctx in (mg.Context(0), tight):
+        a, c, fc, uc = u.clone(), u.clone(), torch.zeros_like(e), torch.ones_like(e)
+        down(a, f, fc, uc, h, OMEGA, 1, kinds, bext, ctx=ctx)
+        up(c, f, e, h, OMEGA, 1, kinds, bext, homogeneous(kinds), ctx=ctx)
+        assert float(uc.abs().max()) == 0.0
+        out.append((host(a), host(fc), host(c)))
+    eps = 40 * float(torch.finfo(dt).eps)
+    su = 6 * max(float(u.abs().max()) + float(e.abs().max()), h * h * float(f.abs().max()),
+                 2 * max([0.0] + [float(b.abs().max()) for b in bext if b is not None]))
+    for x, y, scale in zip(*out, (su, float(f.abs().max()) + 12 * su / h ** 2, su)):
+        assert np.abs(x - y).max() <= 2 * eps * scale
+    with pytest.raises(mg.MgError, match="OOM"):
+        down(u.clone(), f, torch.zeros_like(e), torch.zeros_like(e), h, OMEGA, 2, kinds, bext, ctx=tight)
