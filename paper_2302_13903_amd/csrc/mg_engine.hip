@@ -1470,7 +1470,7 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
 
   // ---- V-cycles until the stopping test (Sec. 2.3.7)
   const int ncyc = p->fixed_cycles > 0 ? p->fixed_cycles : p->max_cycles;
-  std::vector<unsigned long long> clocks;
+  std::vector<unsigned long long> clocks;   // of the cycles; stays empty in the allocation-free form
   int status = p->fixed_cycles > 0 ? MG_OK : MG_NOT_CONVERGED;
   int slow = 0;
   double* phi_cur = phi;     // mixed mode alternates phi with its ping-pong partner
@@ -1559,7 +1559,7 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
         (void)S.down_ahead(H64, bcL);
       unsigned long long clock = 0;
       if (const int st = await_norm(c, scal, s, want, &d2, &clock); st != MG_OK) return st;
-      clocks.push_back(clock);
+      if (!mem.noalloc) clocks.push_back(clock);
       const double rn = rel(d2);
       if (r > 0 && rn > 0) rho_seen = std::min(1.0, rn / r);
       hist[nh++] = rn;
@@ -1601,7 +1601,7 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
   c->fmg_ms = ms(t1, clock_fmg);
   c->cycle_ms.clear();
   unsigned long long prev = clock_fmg;
-  for (size_t cyc = 0; cyc < clocks.size() && !mem.noalloc; ++cyc) {
+  for (size_t cyc = 0; cyc < clocks.size(); ++cyc) {
     c->cycle_ms.push_back(ms(prev, clocks[cyc]));
     prev = clocks[cyc];
   }
