@@ -213,8 +213,9 @@ int mg_solve_simple(mg_ctx *ctx, int n, const double *rho, int bc_kind, double d
                     double *hist, int *n_hist, void *stream);
 
 /* Timing of the last mg_solve on this context, from the device clock read on its stream:
- * *fmg_ms = set-up + FMG sweep; cycle_ms[c] = wall time of V-cycle c (including its
- * residual norm); *n = number of cycles (up to cap). */
+ * *setup_ms = set-up (source, face values, restrictions); *fmg_ms = FMG sweep and the first
+ * residual (MG_MODE_MGI: the residual alone); cycle_ms[c] = wall time of V-cycle c (including
+ * its residual norm); *n = number of cycles (up to cap). */
 int mg_last_timing(const mg_ctx *ctx, double *setup_ms, double *fmg_ms, double *cycle_ms,
                    int cap, int *n);
 

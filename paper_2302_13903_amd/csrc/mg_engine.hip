@@ -152,8 +152,9 @@ namespace {
 constexpr int kScal = 64;
 static_assert(kScal == kPubScalars, "publications copy every scalar");
 constexpr int kMpoleOff = 16;
-// device clock at the start of a solve and of its FMG sweep; arrivals of the sums (SumSink)
-constexpr int kClockStart = 48, kClockFmg = 49, kTicket = 50;
+// device clock at the start of a solve, at the end of its set-up and (where nothing is published) at
+// the norm last read; arrivals of the sums (SumSink)
+constexpr int kClockStart = 48, kClockFmg = 49, kTicket = 50, kClockRead = 51;
 
 SumSink sum_sink(double* part, double* scal, int out) {
   SumSink k;
@@ -1278,8 +1279,8 @@ struct SolveMem {
 // stream after 20 ms and every 20 ms from then on, so that a failed launch ends the wait with an
 // error; if the stream has finished and the number has not arrived (want = 0: nothing was
 // published), the scalars are read by a blocking copy and publishing is given up for good.
-// *clock: the device clock at the publication (0 when it was a copy).
-int await_norm(mg_ctx* c, const double* scal, hipStream_t s, unsigned long long want, double* out,
+// *clock: the device clock at the publication (or before the copy).
+int await_norm(mg_ctx* c, double* scal, hipStream_t s, unsigned long long want, double* out,
                unsigned long long* clock) {
   HIP_CHECK(c, hipGetLastError());
   auto arrived = [&]() {
@@ -1307,10 +1308,11 @@ int await_norm(mg_ctx* c, const double* scal, hipStream_t s, unsigned long long 
       __builtin_ia32_pause();
     }
   }
+  launch_clock(reinterpret_cast<unsigned long long*>(scal + kClockRead), s);
   HIP_CHECK(c, hipMemcpyAsync(c->hscal, scal, sizeof(double) * kScal, hipMemcpyDeviceToHost, s));
   HIP_CHECK(c, hipStreamSynchronize(s));
   *out = c->hscal[2];
-  *clock = 0;
+  *clock = __builtin_bit_cast(unsigned long long, c->hscal[kClockRead]);
   return MG_OK;
 }
 
@@ -1433,6 +1435,9 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
       S.fmg(H32);
       launch_f32_to_f64(H32.u[L], phi, n3, s);
     }
+  } else {
+    // (the FMG sweep's first launch takes the time by itself)
+    launch_clock(reinterpret_cast<unsigned long long*>(scal + kClockFmg), s);
   }
   // ---- residual of the start (Sec. 2.3.7); mixed: also its FP32 copy as the inner RHS.  FP64
   // on the fused path: taken by the head pass, which is also the first sweep of V-cycle 1
@@ -1454,7 +1459,7 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
   if (const int st = await_norm(c, scal, s, want, &d2, &clock_fmg); st != MG_OK) return st;
   double hs[kScal];
   for (int q = 0; q < kScal; ++q)
-    hs[q] = clock_fmg ? __builtin_bit_cast(double, __atomic_load_n(c->hpub + 8 + q, __ATOMIC_RELAXED)) : c->hscal[q];
+    hs[q] = c->pub_ok ? __builtin_bit_cast(double, __atomic_load_n(c->hpub + 8 + q, __ATOMIC_RELAXED)) : c->hscal[q];
   auto clock_of = [&](int q) { return __builtin_bit_cast(unsigned long long, hs[q]); };
   bool finite = std::isfinite(hs[0]) && std::isfinite(hs[1]);
   for (int f = 0; f < 6; ++f) finite = finite && hs[8 + f] == 0.0;
@@ -1595,8 +1600,7 @@ int solve_impl(mg_ctx* c, const mg_params* p, const mg_bc* bc, const double* rho
   auto ms = [&](unsigned long long a, unsigned long long b) {
     return a && b > a ? (double)(b - a) / (double)c->clock_khz : 0.0;
   };
-  const unsigned long long t0 = clock_of(kClockStart);
-  const unsigned long long t1 = clock_of(kClockFmg) ? clock_of(kClockFmg) : clock_fmg;   // no FMG sweep: at the residual
+  const unsigned long long t0 = clock_of(kClockStart), t1 = clock_of(kClockFmg);
   c->setup_ms = ms(t0, t1);
   c->fmg_ms = ms(t1, clock_fmg);
   c->cycle_ms.clear();

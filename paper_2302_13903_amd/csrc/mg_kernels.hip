@@ -534,6 +534,12 @@ void launch_begin(double* scal, int count, int at, hipStream_t s) {
   hipLaunchKernelGGL(k_begin, dim3(1), dim3(64), 0, s, scal, count, at);
 }
 
+__global__ void k_clock(unsigned long long* at) {
+  if (threadIdx.x == 0) *at = (unsigned long long)wall_clock64();
+}
+
+void launch_clock(unsigned long long* at, hipStream_t s) { hipLaunchKernelGGL(k_clock, dim3(1), dim3(64), 0, s, at); }
+
 // Publication of a sum that a launch without a sink left in device memory.
 __global__ void k_publish(const double* __restrict__ src, SumSink sink) {
   publish_scalars(sink.pub, sink.seq, src[0], sink.copy);

@@ -106,6 +106,8 @@ void launch_sum(const double* x, size_t n3, SumSink sink, hipStream_t s);
 void launch_sum_partials(int np, SumSink sink, hipStream_t s);
 // Clears scal[0..count) (count <= 64) and stores the device clock's bits in scal[at].
 void launch_begin(double* scal, int count, int at, hipStream_t s);
+// Stores the device clock at *at (device).
+void launch_clock(unsigned long long* at, hipStream_t s);
 // Publishes *src (device) as a sink's launch would.
 void launch_publish(const double* src, const SumSink& sink, hipStream_t s);
 void launch_defect_norm(const double* u, const double* f, float* r32, int n, double h, const LevelBC& bc,
