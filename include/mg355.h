@@ -136,12 +136,13 @@ int mg_ctx_reserve(mg_ctx *ctx, const mg_params *p);
  *   MG_LAYOUT_BLOCKS: the block sweep (threads per workgroup, blocks staged per workgroup,
  *     one or two sweeps fused per launch; every such schedule gives bitwise the same result)
  *     and, on the finest block level, whether the streaming passes that cross block
- *     boundaries replace the per-block halo-tile sweeps (with V(2,2) from 128 cells per side:
- *     the two-sweep down and up passes against four halo-tile sweeps; otherwise, from 256
- *     cells per side, the one-sweep passes against one halo-tile sweep).
+ *     boundaries replace the per-block halo-tile sweeps (with one or two sweeps per leg, from 128
+ *     cells per side: the down and up passes against as many halo-tile sweeps; otherwise, from
+ *     256 cells per side, the one-sweep passes against one halo-tile sweep).
  *   MG_LAYOUT_DENSE (n >= 64): whether the restricted defect (and, on the FP64 finest level,
  *     the residual norm) is fused into the last smoothing pass or runs as its own streaming
- *     pass, and whether sweeps run one per pass or two per pass (temporally blocked).  The
+ *     pass, and whether sweeps run one per pass or two per pass (temporally blocked; where the
+ *     finest level's legs run as streaming passes, whether blocked sweeps replace them).  The
  *     alternatives differ only in floating-point contraction (same expressions).
  * Allocates and frees its own scratch (3.25 n^3 values); synchronises its own stream. */
 int mg_autotune(mg_ctx *ctx, const mg_params *p, int reps);

@@ -1734,22 +1734,23 @@ int autotune_blocks(mg_ctx* c, const mg_params* p, int Lb, int reps) {
           if (ms < best_ms) { best_ms = ms; best = t; }
         }
     c->blk_tune[(sizeof(T) == 8 ? 0 : 1000) + 100 * Lm + Lb] = best;
-    if (l == L && p->npre == 2 && p->npost == 2 && (1 << l) >= march_min_n<T>(c) && blk_march_fits(l)) {
-      // V(2,2) on the finest block level: both legs as the streaming passes across
-      // blocks against the four halo-tile sweeps alone (a lower bound on that schedule)
+    if (l == L && march_sweeps_ok(p->npre) && march_sweeps_ok(p->npost) && (1 << l) >= march_min_n<T>(c) &&
+        blk_march_fits(l)) {
+      // one or two sweeps per leg on the finest block level: both legs as the streaming passes across
+      // blocks against the halo-tile sweeps alone (a lower bound on that schedule)
       T* fc = buf[3];
       T* uc = buf[3] + cellsL / 8;
       LevelBC hom = bc;
       (void)hipEventRecord(e0, s);
       for (int r = 0; r < reps; ++r) {
-        march_down<T>(buf[0], buf[1], buf[2], fc, uc, 1 << l, 2, h, p->omega, bc, s, Lm);
-        (void)march_up<T>(buf[1], buf[0], buf[2], uc, hom, nullptr, 1 << l, 2, h, p->omega, bc, s, Lm);
+        march_down<T>(buf[0], buf[1], buf[2], fc, uc, 1 << l, p->npre, h, p->omega, bc, s, Lm);
+        march_up<T>(buf[1], buf[0], buf[2], uc, hom, nullptr, 1 << l, p->npost, h, p->omega, bc, s, Lm);
       }
       (void)hipEventRecord(e1, s);
       HIP_CHECK(c, hipEventSynchronize(e1));
       HIP_CHECK(c, hipGetLastError());
       const double t_m = elapsed(e0, e1) / reps;
-      c->blk_zmarch[sizeof(T) == 8 ? 0 : 1] = t_m < 4.0 * best_ms ? 1 : 0;
+      c->blk_zmarch[sizeof(T) == 8 ? 0 : 1] = t_m < (p->npre + p->npost) * best_ms ? 1 : 0;
     } else if (l == L && (1 << l) >= kFusedDefaultMinN) {
       // the finest block level: halo-tile sweeps against the streaming passes across blocks
       (void)hipEventRecord(e0, s);
@@ -1823,7 +1824,23 @@ int autotune_dense(mg_ctx* c, const mg_params* p, int reps) {
       });
       if (t_ns < t_nf) split |= 2;
     }
-    if (l == L) {
+    const int march = c->march[sizeof(T) == 8 ? 0 : 1];
+    if (l == L && march != 0 && march_sweeps_ok(p->npre) && march_sweeps_ok(p->npost) && n >= march_min_n<T>(c)) {
+      // the level's legs run as streaming passes, which the temporally blocked sweeps would replace:
+      // a cycle's legs one way and the other (cycles at 128^3 FP64 periodic: V(1,1) 80 and 97 us,
+      // V(2,2) 116 and 132)
+      const double t_legs = time_it([&] {
+        march_down<T>(buf[0], buf[1], buf[2], buf[3], buf[4], n, p->npre, h, p->omega, bc, s);
+        march_up<T>(buf[1], buf[0], buf[2], buf[4], bc, nullptr, n, p->npost, h, p->omega, bc, s);
+      });
+      const double t_tb = time_it([&] {
+        tb_sweeps<T>(buf[0], buf[1], buf[2], nullptr, bc, p->npre, n, h, p->omega, bc, s);
+        fused_defect_restrict<T>(buf[1], buf[2], buf[3], buf[4], n, h, bc, s);
+        fused_prolong_sweep<T>(buf[1], buf[0], buf[2], buf[4], bc, n, h, p->omega, bc, s);
+        if (p->npost > 1) tb_sweeps<T>(buf[0], buf[1], buf[2], nullptr, bc, p->npost - 1, n, h, p->omega, bc, s);
+      });
+      c->tblock[sizeof(T) == 8 ? 0 : 1] = t_tb < t_legs ? 1 : 0;
+    } else if (l == L) {
       // sweep fusion: two one-sweep passes against one temporally blocked two-sweep pass
       const double t_one = time_it([&] {
         fused_sweep<T>(buf[0], buf[1], buf[2], n, h, p->omega, bc, s);
