@@ -278,7 +278,7 @@ __global__ void __launch_bounds__(kB) k_smooth_set(Set<SmoothA> S, double omega,
 }
 
 // ---- out = a + s L u on the active cells (defect: a = f, s = -1; FAS source: a = restricted
-// defect, s = +1); covered cells get 0
+// defect, s = +1); covered cells get 0.  Three distinct arrays
 __device__ inline void lap_body(const double* __restrict__ u, const double* __restrict__ a, double* __restrict__ out,
                                 const Dims& d, const Hole& H, double ih2, double s, size_t t) {
   if (t >= cells(d)) return;
@@ -746,6 +746,23 @@ struct MidMem {
   }
 };
 
+// The FAS source f = dres + L u of a level; in LDS f holds dres before (each item reads its own cell of
+// f alone, but lap_body takes its arrays as distinct).
+template <bool LDS>
+__device__ __forceinline__ void source_body(const double* __restrict__ u, const Arr& a, const Dims& d, double ih2, size_t t) {
+  const Hole none{};
+  if constexpr (LDS) {
+    if (t >= cells(d)) return;
+    int x, y, z;
+    cell_of(t, d, x, y, z);
+    const size_t c = gx(d, x, y, z);
+    const double L = (nbsum(u, d, none, x, y, z) - 6.0 * u[c]) * ih2;
+    a.f[c] = a.f[c] + L;
+  } else {
+    lap_body(u, a.dres, a.f, d, none, ih2, 1.0, t);
+  }
+}
+
 template <bool LDS>
 __device__ __forceinline__ void root_tail_run(const MidMem<LDS>& M, const RootSet& S, int q0, int npre, int npost,
                                               double omega) {
@@ -772,7 +789,7 @@ __device__ __forceinline__ void root_tail_run(const MidMem<LDS>& M, const RootSe
       restrict_body(a.tmp, L.d, none, c.dres, nullptr, C.d, 0, 0, 0, C.d, t);
     });
     forall(ghost_faces(C.d), [&](size_t t) { fill_phys_body(c.pbar, C.d, C.phys, 0, t); });
-    forall(cells(C.d), [&](size_t t) { lap_body(c.pbar, c.dres, c.f, C.d, none, 1.0 / (C.h * C.h), 1.0, t); });
+    forall(cells(C.d), [&](size_t t) { source_body<LDS>(c.pbar, c, C.d, 1.0 / (C.h * C.h), t); });
     ++q;
   }
   // the single cell
@@ -908,7 +925,7 @@ __global__ void __launch_bounds__(kMidThreads) k_mid(OctSet O, RootSet R, MidPla
     const Arr p = M.oct(O, l), c = M.oct(O, l - 1);
     if (l < top || !src) {
       cons_all(oct_cons(P, p.pbar, C, c.pbar));
-      forall(cells(P.d), [&](size_t t) { lap_body(p.pbar, p.dres, p.f, P.d, none, 1.0 / (P.h * P.h), 1.0, t); });
+      forall(cells(P.d), [&](size_t t) { source_body<LDS>(p.pbar, p, P.d, 1.0 / (P.h * P.h), t); });
       forall(ghosted_d(P.d), [&](size_t t) { p.u[t] = p.pbar[t]; });
     } else if (!LDS) {
       forall(cells(P.d), [&](size_t t) { move_body(src, p.f, P.d, t); });
@@ -927,7 +944,7 @@ __global__ void __launch_bounds__(kMidThreads) k_mid(OctSet O, RootSet R, MidPla
     const RootLvl& L = R.l[0];
     const Arr a = M.oct(O, 0);
     forall(ghost_faces(L.d), [&](size_t t) { fill_phys_body(a.pbar, L.d, L.phys, 0, t); });
-    forall(cells(L.d), [&](size_t t) { lap_body(a.pbar, a.dres, a.f, L.d, none, 1.0 / (L.h * L.h), 1.0, t); });
+    forall(cells(L.d), [&](size_t t) { source_body<LDS>(a.pbar, a, L.d, 1.0 / (L.h * L.h), t); });
     forall(ghosted_d(L.d), [&](size_t t) { a.u[t] = a.pbar[t]; });
     root_tail_run<LDS>(M, R, 0, npre, npost, omega);
   }
