@@ -387,7 +387,7 @@ struct Solver {
                     aux_of());
       // algorithmic bytes: u and f read, u written, coarse source (and correction) written
       if (timed)
-        kernel_end(zin ? march_down1_name<T>(H.npre, true, bc) : march_name<T>(H.npre, false, false, bc),
+        kernel_end(zin ? march_down1_name<T>(H.npre, true, bc) : march_name<T>(H.npre, false, false, bc, n),
                    (zin ? 2 : 3) * cellsT + cellsT / (uc0 ? 4 : 8));
     } else {
       tile_down<T>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], nullptr, uc0, n, 0, H.npre, H.h[l], H.omega, bc, s);
@@ -402,7 +402,7 @@ struct Solver {
     if (timed) kernel_begin(true);
     if (big) march_down<T>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], H.u[l - 1], nl, H.npre, H.h[l], H.omega, bc, s, Lm, aux_of());
     else tile_down<T>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], nullptr, H.u[l - 1], nl, Lm, H.npre, H.h[l], H.omega, bc, s);
-    if (timed) kernel_end(big ? march_name<T>(H.npre, false, false, bc, true) : tile_name<T>(H.npre, false, bc, nl),
+    if (timed) kernel_end(big ? march_name<T>(H.npre, false, false, bc, nl, true) : tile_name<T>(H.npre, false, bc, nl),
                           3 * cellsT + cellsT / 4);
   }
 
@@ -624,7 +624,7 @@ struct Solver {
       if (timed) kernel_begin(true);
       march_up<T>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, norm ? &sink : nullptr, n, H.npost, h, H.omega, bc, s, 0, aux_of());
       // algorithmic bytes: u, f and the coarse correction read, u written
-      if (timed) kernel_end(march_name<T>(H.npost, true, norm, bc), 3 * cellsT + cellsT / 8);
+      if (timed) kernel_end(march_name<T>(H.npost, true, norm, bc, n), 3 * cellsT + cellsT / 8);
       return norm;
     }
     if (n < (sizeof(T) == 8 ? fused_min_n64 : fused_min_n32) && tile_on<T>(H, l)) {
@@ -828,7 +828,7 @@ struct Solver {
       if (timed) kernel_begin(true);
       march_up<double>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, norm ? &sink : nullptr, n, H.npost, H.h[l], H.omega, bc, s, 0,
                        aux_of());
-      if (timed) kernel_end(march_name<double>(H.npost, true, norm, bc), 3 * cellsT + cellsT / 8);
+      if (timed) kernel_end(march_name<double>(H.npost, true, norm, bc, n), 3 * cellsT + cellsT / 8);
       return norm;
     }
     if (done == 0 && n < fused_min_n64 && tile_on<double>(H, l)) {
@@ -998,7 +998,7 @@ struct Solver {
                            aux_of());
       else tile_up<T>(H.u2[l], H.u[l], H.f[l], H.u[l - 1], H.hom, norm ? &sink : nullptr, nl, Lm, H.npost, H.h[l], H.omega, bc, s);
       if (timed)
-        kernel_end(big ? march_name<T>(H.npost, true, norm, bc, true) : tile_name<T>(H.npost, true, bc, nl),
+        kernel_end(big ? march_name<T>(H.npost, true, norm, bc, nl, true) : tile_name<T>(H.npost, true, bc, nl),
                    3 * cellsT + cellsT / 8);
       return norm;
     }

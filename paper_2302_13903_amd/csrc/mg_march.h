@@ -15,6 +15,13 @@ namespace mg {
 // Smallest level the passes run on (a z chunk must hold many planes).
 constexpr int kMarchMinN = 128;
 
+// Dense levels whose passes issue a step's stores before its loads are taken up, not after: from
+// 256^3, where the tiles march faster than memory serves them.  Operator calls (with their copy of u),
+// periodic, two sweeps, down / up, late and early: FP64 256^3 155 / 155 and 149 / 148 us, 512^3
+// 1263 / 1215 and 1219 / 1185, 1024^3 11011 / 10483 and 10557 / 10020; FP32 256^3 78 / 75 and 76 / 73.
+// At 128^3 the calls are equal (FP64 42 / 38 us, FP32 31 / 28).
+inline bool march_early(int n) { return n >= 256; }
+
 // A second stream and two events for splitting a pass of a level with x or y walls into the
 // interior tiles and the wall tiles, run concurrently (owned by the caller; unused when null).
 struct MarchAux {
@@ -81,10 +88,11 @@ inline int march_walls(const LevelBC& bc) {
   return per ? 0 : xyper ? 1 : 2;
 }
 template <typename T>
-std::string march_name(int ns, bool up, bool norm, const LevelBC& bc, bool blk = false) {
+std::string march_name(int ns, bool up, bool norm, const LevelBC& bc, int n, bool blk = false) {
   auto b = [](bool v) { return std::string(v ? "true, " : "false, "); };
   return std::string("k_march<") + (sizeof(T) == 8 ? "double, " : "float, ") + std::to_string(kMarchWaves) + ", " + b(up) +
-         b(up && norm) + std::to_string(march_walls(bc)) + ", " + b(blk) + std::to_string(ns) + ">";
+         b(up && norm) + std::to_string(march_walls(bc)) + ", " + b(blk) + std::to_string(ns) +
+         (!blk && march_early(n) ? ", 1>" : ", 0>");
 }
 template <typename T>
 std::string march_down1_name(int ns, bool zero, const LevelBC& bc) {

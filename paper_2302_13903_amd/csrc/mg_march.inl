@@ -32,9 +32,10 @@
 //    the colour that no stage of this step changes on that plane, so all four stages' edge rows go
 //    out at the step's start, and the inner rows are done while they travel (the defect stage's
 //    red cells need one more);
-//  * no branch around a load or its take-up, and the step's stores after the take-up: loads and
-//    stores complete in one order, so a wait for loads behind stores, or at a join of paths, waits
-//    for the stores to reach memory.
+//  * no branch around a load or its take-up, and below 256^3 the step's stores after the take-up: loads
+//    and stores complete in one order, so a wait for loads behind stores, or at a join of paths, waits
+//    for the stores to reach memory.  (Where memory is the bound that wait costs nothing and the stores'
+//    earlier start gains: march_early.)
 //  * addresses are a uniform plane base and a 32-bit offset, coarse taps take their walls' signs
 //    when they are used, not as they are loaded.
 // Measured before these and now: 128^3 periodic legs 39 / 34 -> 32 / 32 us; V-cycles at 256^3
@@ -200,7 +201,8 @@ constexpr int kWaves = kMarchWaves;
 // phibar (mean of the 8 children of the pass's result) into A.pbar and starts the coarse level
 // from it (uc0 = phibar instead of 0).
 // VALUES: the face values are in A.bc and not in f (null: none on that face).
-template <typename T, int W, bool UP, bool NORM, int WALLS, bool BLK, bool FAS, bool ZIN, bool VALUES>
+// EARLY: a step's stores before its loads are taken up, else after.
+template <typename T, int W, bool UP, bool NORM, int WALLS, bool BLK, bool FAS, bool ZIN, bool VALUES, bool EARLY>
 __device__ __forceinline__ void march_body(const MarchArgs& A) {
   constexpr bool PER = WALLS == 0;                // every face periodic
   constexpr bool XYW = WALLS == 2;                // x or y walls may be in reach
@@ -770,49 +772,52 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
       if constexpr (DSTAGE)
         defect(ParL{}, FsL{}, u[slot(kStages + 1)], u[slot(kStages)], u[slot(kStages - 1)], P - kStages);
       else __syncthreads();   // (with a defect stage: its barrier) xe is free for the next step
+      // the last stage's plane is final, and on odd planes the one before's coarse cells: out
+      constexpr int sl = slot(kStages);
+      auto put = [&]() __attribute__((always_inline)) {
+        {
+          const int p = P - kStages;
+          if (p >= z0 && p < zend) {
+            const int pg = p & nm;
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+              if (out[r >> 1]) {
+                typedef T ntv2 __attribute__((ext_vector_type(2)));
+                const ntv2 v = {u[sl][r][0], u[sl][r][1]};
+                __builtin_nontemporal_store(v, reinterpret_cast<ntv2*>(const_cast<T*>(at(uout, r, pg))));
+              }
+          }
+        }
+        if constexpr (DEF && ((HZ + K + kStages + 1) & 1) != 0) {
+          const int p = P - kStages - 1;
+          if (p >= z0 && p < zend) {
+            T* __restrict__ fcp = reinterpret_cast<T*>(A.fc);
+            T* __restrict__ ucp = reinterpret_cast<T*>(A.uc0);
+#pragma unroll
+            for (int j = 0; j < R / 2; ++j)
+              if (out[j]) {
+                const size_t ci = cdx(xag >> 1, ygv[2 * j] >> 1, p >> 1);
+                fcp[ci] = stash[j];
+                if constexpr (FAS) reinterpret_cast<T*>(A.pbar)[ci] = stash_u[j];
+                if (FAS || ucp) ucp[ci] = FAS ? stash_u[j] : (T)0;
+              }
+          }
+        }
+      };
+      if constexpr (EARLY) put();
       prolong_apply(Pn, std::integral_constant<int, (HZ + K + 1) & 1>{});
       keep_in(Pn);
       // u(P+1) enters the ring in the slot of the oldest plane; f(P-1) moves to the LDS slot of the
       // last stage's plane (done with), f(P) into the registers
-      constexpr int so = slot(kStages + 1), sl = slot(kStages);
+      constexpr int so = slot(kStages + 1);
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         u[so][r][0] = pu[r][0]; u[so][r][1] = pu[r][1];
         fl[FsL::value][r][tid] = Pair<T>{fr[r][0], fr[r][1]};
         fr[r][0] = pf[r][0]; fr[r][1] = pf[r][1];
       }
-      // The last stage's plane is final, and on odd planes the one before's coarse cells: out, once the loads of plane P+1
-      // are in (loads and stores complete in one order, so a wait for the loads further on would
-      // wait for these stores)
       arrived(u[so], fr);
-      {
-        const int p = P - kStages;
-        if (p >= z0 && p < zend) {
-          const int pg = p & nm;
-#pragma unroll
-          for (int r = 0; r < R; ++r)
-            if (out[r >> 1]) {
-              typedef T ntv2 __attribute__((ext_vector_type(2)));
-              const ntv2 v = {u[sl][r][0], u[sl][r][1]};
-              __builtin_nontemporal_store(v, reinterpret_cast<ntv2*>(const_cast<T*>(at(uout, r, pg))));
-            }
-        }
-      }
-      if constexpr (DEF && ((HZ + K + kStages + 1) & 1) != 0) {
-        const int p = P - kStages - 1;
-        if (p >= z0 && p < zend) {
-          T* __restrict__ fcp = reinterpret_cast<T*>(A.fc);
-          T* __restrict__ ucp = reinterpret_cast<T*>(A.uc0);
-#pragma unroll
-          for (int j = 0; j < R / 2; ++j)
-            if (out[j]) {
-              const size_t ci = cdx(xag >> 1, ygv[2 * j] >> 1, p >> 1);
-              fcp[ci] = stash[j];
-              if constexpr (FAS) reinterpret_cast<T*>(A.pbar)[ci] = stash_u[j];
-              if (FAS || ucp) ucp[ci] = FAS ? stash_u[j] : (T)0;
-            }
-        }
-      }
+      if constexpr (!EARLY) put();
       take_values(P);   // (last: before the stores the FP64 up pass spills 100-160 bytes, 1.4 times its time)
     };
     for (int g = 0; g < nsteps; g += kRing) {
@@ -834,30 +839,40 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
   }
 }
 
-template <typename T, int W, bool UP, bool NORM, int WALLS, bool BLK, int NS>
+template <typename T, int W, bool UP, bool NORM, int WALLS, bool BLK, int NS, int EARLY>
 __global__ void __launch_bounds__(kLanes* W) k_march(MarchArgs A) {
-  march_body<T, W, UP, NORM, WALLS, BLK, false, false, false>(A);
+  march_body<T, W, UP, NORM, WALLS, BLK, false, false, false, EARLY != 0>(A);
 }
 
 // A leg with face values, f being the caller's (the operator entry points).
 template <typename T, int W, bool UP, int WALLS, int NS>
 __global__ void __launch_bounds__(kLanes* W) k_march_values(MarchArgs A) {
-  march_body<T, W, UP, false, WALLS, false, false, false, true>(A);
+  march_body<T, W, UP, false, WALLS, false, false, false, true, false>(A);
 }
 
 // The down pass of a Full Approximation Scheme cycle (dense FP64 levels).
 template <typename T, int W, int WALLS, int NS>
 __global__ void __launch_bounds__(kLanes* W) k_march_fas(MarchArgs A) {
-  march_body<T, W, false, false, WALLS, false, true, false, false>(A);
+  march_body<T, W, false, false, WALLS, false, true, false, false, false>(A);
 }
 
 // The down pass from u = 0, which is not read (the first leg of a mixed-precision correction).
 template <typename T, int W, int WALLS, int NS>
 __global__ void __launch_bounds__(kLanes* W) k_march_zero(MarchArgs A) {
-  march_body<T, W, false, false, WALLS, false, false, true, false>(A);
+  march_body<T, W, false, false, WALLS, false, false, true, false, false>(A);
 }
 
 constexpr int kCUs = 256;
+
+// Dynamic LDS, unused, that keeps a second FP32 workgroup off a CU (of up to 80 KiB, two fit) on the
+// levels with early stores: neighbouring tiles then march the same planes at the same time more often and meet in
+// L2.  Operator calls as above, FP32 two sweeps, with two on a CU and one: 512^3 761 / 698 and
+// 714 / 698 us, 1024^3 7383 / 6627 and 6073 / 5898, 256^3 79 / 73 and 78 / 73.  (With late stores 512^3
+// 754 / 711 and 790 / 711, so not where those are.)
+template <typename T>
+unsigned lds_beside(int n) {
+  return sizeof(T) == 4 && march_early(n) ? (kNS == 1 ? 61440u : 20480u) : 0u;
+}
 
 // Planes per workgroup: even (chunks then start on planes of the parity compiled in).  One workgroup per CU is resident (LDS), so
 // the grid runs in rounds of kCUs workgroups; the chunk minimises rounds x (planes marched,
@@ -939,8 +954,13 @@ void launch_march(MarchArgs A, hipStream_t s, const MarchAux* aux) {
     if (timed) (void)hipEventRecord(lt.e0, s);
     (void)hipEventRecord(aux->fork, s);
     (void)hipStreamWaitEvent(aux->s2, aux->fork, 0);
-    hipLaunchKernelGGL((k_march<T, W, UP, NORM, 2, BLK, kNS>), dim3(gr), dim3(kLanes * W), 0, aux->s2, Ar);
-    hipLaunchKernelGGL((k_march<T, W, UP, NORM, 1, BLK, kNS>), dim3(gi), dim3(kLanes * W), 0, s, Ai);
+    auto both = [&](auto early) {
+      constexpr int E = decltype(early)::value;
+      hipLaunchKernelGGL((k_march<T, W, UP, NORM, 2, BLK, kNS, E>), dim3(gr), dim3(kLanes * W), 0, aux->s2, Ar);
+      hipLaunchKernelGGL((k_march<T, W, UP, NORM, 1, BLK, kNS, E>), dim3(gi), dim3(kLanes * W), 0, s, Ai);
+    };
+    if (!BLK && march_early(A.n)) both(std::integral_constant<int, BLK ? 0 : 1>{});
+    else both(std::integral_constant<int, 0>{});
     (void)hipEventRecord(aux->join, aux->s2);
     (void)hipStreamWaitEvent(s, aux->join, 0);
     if (timed) (void)hipEventRecord(lt.e1, s);
@@ -951,9 +971,15 @@ void launch_march(MarchArgs A, hipStream_t s, const MarchAux* aux) {
   A.ntiles = A.tiles_x * A.tiles_y * chunks;
   const int grid = (A.ntiles + 7) / 8 * 8;
   A.sink.total = grid;
-  if (per) launch_maybe_timed(k_march<T, W, UP, NORM, 0, BLK, kNS>, dim3(grid), dim3(kLanes * W), 0, s, A);
-  else if (xyper) launch_maybe_timed(k_march<T, W, UP, NORM, 1, BLK, kNS>, dim3(grid), dim3(kLanes * W), 0, s, A);
-  else launch_maybe_timed(k_march<T, W, UP, NORM, 2, BLK, kNS>, dim3(grid), dim3(kLanes * W), 0, s, A);
+  auto go = [&](auto early) {
+    constexpr int E = decltype(early)::value;
+    auto run = [&](auto k) { launch_maybe_timed(k, dim3(grid), dim3(kLanes * W), E ? lds_beside<T>(A.n) : 0u, s, A); };
+    if (per) run(k_march<T, W, UP, NORM, 0, BLK, kNS, E>);
+    else if (xyper) run(k_march<T, W, UP, NORM, 1, BLK, kNS, E>);
+    else run(k_march<T, W, UP, NORM, 2, BLK, kNS, E>);
+  };
+  if (!BLK && march_early(A.n)) go(std::integral_constant<int, BLK ? 0 : 1>{});
+  else go(std::integral_constant<int, 0>{});
 }
 
 // The down passes of FAS and from zero, and the legs with face values: one launch over every tile,
