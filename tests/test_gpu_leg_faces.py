@@ -1,5 +1,5 @@
 """V-cycle legs at their faces: non-finite sources beside one wall, against the oracle; face values
-under a memory budget, and legs on a budget that holds no scratch."""
+under a memory budget, legs on a budget that holds no scratch, and the large levels' one-sweep up pass."""
 import numpy as np
 import pytest
 
@@ -136,3 +136,22 @@ def test_one_sweep_without_scratch(mg, kind, f32):
         assert np.abs(x - y).max() <= 2 * eps * scale
     with pytest.raises(mg.MgError, match="OOM"):
         down(u.clone(), f, torch.zeros_like(e), torch.zeros_like(e), h, OMEGA, 2, kinds, bext, ctx=tight)
+
+
+@pytest.mark.parametrize("kind", ["periodic", "layer"])
+def test_large_one_sweep_up_is_the_one_sweep_pass(mg, kind):
+    """FP32 at 512^3, one sweep, no x or y wall: the pass that runs with the streaming legs off, bitwise."""
+    n, kinds = 512, KINDS[kind]
+    print(f"up 512^3 one sweep {kind}", flush=True)
+    gen = torch.Generator(device="cuda:0").manual_seed(1)
+    u, f, e = (torch.randn((m,) * 3, generator=gen, dtype=torch.float32, device="cuda:0") for m in (n, n, n // 2))
+    out = []
+    for text in ("march fp32 2\n", "march fp32 0\n"):
+        ctx = mg.Context(0)
+        ctx.set_tuning(text)
+        a = u.clone()
+        mg.mg_op_up_f32(a, f, e, 1.0 / n, OMEGA, 1, kinds, None, homogeneous(kinds), ctx=ctx)
+        torch.cuda.synchronize()
+        out.append(a)
+        ctx.close()
+    assert torch.equal(*out)
