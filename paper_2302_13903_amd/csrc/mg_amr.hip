@@ -449,8 +449,6 @@ struct ProlongA {
   Dims df;
   int fo[3];
   Hole Hf;
-  int l[3];
-  Dims span;
 };
 // All eight children of one parent cell (modes 0 and 2, on levels of two or more cells per block,
 // where patches and holes hold whole octets): 27 parent values once instead of per child.  On
@@ -571,7 +569,7 @@ __global__ void __launch_bounds__(kB) k_sub_set(Set<SubA> S) {
 
 // kernel arguments are limited to 4 KiB
 static_assert(sizeof(Set<Cons>) <= 4096 && sizeof(Set<SmoothA>) <= 4096 && sizeof(Set<LapA>) <= 4096 &&
-                  sizeof(Set<RestrictA>) <= 4096 && sizeof(Set<ProlongA>) + 256 <= 4096 && sizeof(Set<SubA>) <= 4096 &&
+                  sizeof(Set<RestrictA>) <= 4096 && sizeof(Set<ProlongA>) + sizeof(Dims) + sizeof(Phys) + 64 <= 4096 && sizeof(Set<SubA>) <= 4096 &&
                   sizeof(Set<DownA>) <= 4096,
               "batched launch arguments");
 

@@ -1089,8 +1089,10 @@ template void march_down_ns<MG_MARCH_T, kNS>(const MG_MARCH_T*, MG_MARCH_T*, con
 template void march_up_ns<MG_MARCH_T, kNS>(const MG_MARCH_T*, MG_MARCH_T*, const MG_MARCH_T*, const MG_MARCH_T*,
                                            const LevelBC&, const SumSink*, int, double, double, const LevelBC&,
                                            hipStream_t, int, const MarchAux*);
+#ifdef MG_MARCH_FAS
 template void march_down_fas_ns<MG_MARCH_T, kNS>(const MG_MARCH_T*, MG_MARCH_T*, const MG_MARCH_T*, MG_MARCH_T*,
                                                  MG_MARCH_T*, MG_MARCH_T*, int, double, double, const LevelBC&,
                                                  hipStream_t);
+#endif
 
 }  // namespace mg
