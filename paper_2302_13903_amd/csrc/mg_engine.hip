@@ -133,7 +133,7 @@ struct mg_ctx {
   // 0 = one sweep per pass; -1 = the built-in default
   int tblock[2] = {-1, -1};
   // legs of one or two sweeps as streaming passes (down: sweeps + restricted defect; up:
-  // prolongation + two sweeps [+ norm]): 0 = off, 1 = on levels whose faces are all periodic,
+  // prolongation + the sweeps [+ norm]): 0 = off, 1 = on levels whose faces are all periodic,
   // 2 = on every level; -1 = the built-in default (2)
   int march[2] = {-1, -1};
   // legs of the levels 32^3 .. 128^3 (and the MeshBlock levels) below the streaming passes as one region-tile launch each: 1 = on (default), 0 = per-operator launches
@@ -518,7 +518,7 @@ struct Solver {
   }
 
   // Does level l run its legs as the streaming passes of one or two sweeps (down: the sweeps and
-  // the restricted defect in one pass; up: prolongation, two sweeps and the norm in one)?
+  // the restricted defect in one pass; up: prolongation, the sweeps and the norm in one)?
   template <typename T>
   bool march_on(const Hier<T>& H, int l, const LevelBC& bc) const {
     const int mode = c->march[sizeof(T) == 8 ? 0 : 1] < 0 ? 2 : c->march[sizeof(T) == 8 ? 0 : 1];
@@ -815,7 +815,7 @@ struct Solver {
     if (done == 0 && march_on<double>(H, l, bc)) {
       // legs as the streaming passes: down (sweeps, restricted defect, phibar, the
       // coarse level started from it), steps 5-7 on the coarse level, up (the prolonged
-      // correction psi - phibar, two sweeps, and the norm of the result when asked)
+      // correction psi - phibar, the sweeps, and the norm of the result when asked)
       if (timed) kernel_begin(true);
       march_down_fas<double>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], pbar[l - 1], H.u[l - 1], n, H.npre, H.h[l], H.omega, bc, s);
       // algorithmic bytes: u and f read, u written, three coarse arrays written
@@ -834,7 +834,7 @@ struct Solver {
     if (done == 0 && n < fused_min_n64 && tile_on<double>(H, l)) {
       // a small level: each leg in one region-tile launch -- down (sweeps,
       // restricted defect, phibar, the coarse level started from it), steps 5-7 on the coarse
-      // level, up (the prolonged correction psi - phibar, two sweeps, the norm when asked)
+      // level, up (the prolonged correction psi - phibar, the sweeps, the norm when asked)
       if (timed) kernel_begin(true);
       tile_down<double>(H.u[l], H.u2[l], H.f[l], H.f[l - 1], pbar[l - 1], H.u[l - 1], n, 0, H.npre, H.h[l], H.omega, bc, s);
       if (timed) kernel_end(tile_name<double>(H.npre, false, bc, n), 3 * cellsT + 3 * cellsT / 8);

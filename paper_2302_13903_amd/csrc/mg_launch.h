@@ -119,9 +119,6 @@ void launch_zero(void* p, size_t bytes, hipStream_t s);
 // out ((n+2)^3) = u with its ghost layer, edges and corners included, filled from bc
 void launch_fill(const double* u, double* out, int n, const LevelBC& bc, hipStream_t s);
 
-// The extended arrays of the levels bottom..L (ext[l]: six of (2^l + 2)^2 one after another) of
-// the faces with values (src[f]: n^2 finest values, or null); adds the count of each face's
-// non-finite values to nonfinite[face] (null: not wanted).
 // Face values into the sources: on every listed level, the cells beside a face with values b take
 // f - 2 b / h^2 summed over their faces, so that the level's operator is the homogeneous one
 // (ghost = +-u) from then on.
@@ -133,6 +130,9 @@ struct FoldLevel {
 };
 template <typename T>
 void launch_fold_faces(const FoldLevel* levels, int count, hipStream_t s);
+// The extended arrays of the levels bottom..L (ext[l]: six of (2^l + 2)^2 one after another) of
+// the faces with values (src[f]: n^2 finest values, or null); adds the count of each face's
+// non-finite values to nonfinite[face] (null: not wanted).
 void launch_faces(const double* const src[6], double* const* ext, int L, int bottom, double* nonfinite, hipStream_t s);
 
 // multipole (mg_multipole.hip)

@@ -39,8 +39,8 @@
 //  * addresses are a uniform plane base and a 32-bit offset, coarse taps take their walls' signs
 //    when they are used, not as they are loaded.
 // Measured before these and now: 128^3 periodic legs 39 / 34 -> 32 / 32 us; V-cycles at 256^3
-// 386 -> 333 us periodic, 451 -> 352 between z walls, 522 -> 413 fixed; at 512^3 2285 -> 2005 and
-// 2610 -> 2193 (periodic 2000 -> 1953).  Loading two planes ahead: FP32 equal, FP64 spills.
+// 386 -> 307 us periodic, 451 -> 336 between z walls, 522 -> 383 fixed; at 512^3 2000 -> 1791,
+// 2285 -> 1777 and 2610 -> 1931.  Loading two planes ahead: FP32 equal, FP64 spills.
 //
 // The defect stage needs the final state of both neighbouring planes.  Black cells of P-4 have
 // only red neighbours, final after red sweep 2; red cells of P-4 get their in-plane and lower
@@ -733,9 +733,9 @@ __device__ __forceinline__ void march_body(const MarchArgs& A) {
     }
     arrived(u[0], fr);
     take_values(zstart - 1);
-    // one pipeline step: the plane in ring slot K is P = zstart + t, t = g + K with g a
-    // multiple of 6, so P - j sits in slot (K - j) mod 6, has parity (HZ + K + j) mod 2 (z0 is even),
-    // and its f is in LDS slot (K - HZ - j) mod 3
+    // one pipeline step: the plane in ring slot K is P = zstart + t, t = g + K with g a multiple of
+    // kRing, so P - j sits in slot (K - j) mod kRing, has parity (HZ + K + j) mod 2 (z0 and kRing are
+    // even), and its f is in LDS slot (K - HZ - j) mod kFSlots (which divides kRing)
     auto step = [&](int g, auto kk) __attribute__((always_inline)) {
       constexpr int K = decltype(kk)::value;
       const int t = g + K;
@@ -874,9 +874,9 @@ unsigned lds_beside(int n) {
   return sizeof(T) == 4 && march_early(n) ? (kNS == 1 ? 61440u : 20480u) : 0u;
 }
 
-// Planes per workgroup: even (chunks then start on planes of the parity compiled in).  One workgroup per CU is resident (LDS), so
-// the grid runs in rounds of kCUs workgroups; the chunk minimises rounds x (planes marched,
-// 2 hz halo planes included).
+// Planes per workgroup: even (chunks then start on planes of the parity compiled in).  With one workgroup
+// per CU resident (FP64 by its LDS) the grid runs in rounds of kCUs workgroups; the chunk minimises
+// rounds x (planes marched, 2 hz halo planes included).
 int march_zchunk(int n, int tiles_xy, int hz) {
   int best = n;
   long best_cost = -1;
@@ -935,7 +935,8 @@ void launch_march(MarchArgs A, hipStream_t s, const MarchAux* aux) {
     // the z-walls-only form on this stream, the ring of wall tiles in the full form on the
     // second stream, concurrently (fork and join through events); the ring's partials follow
     // the interior's.  Where the interior tiles are the more: at 512^3 (64 against 36) a V-cycle
-    // takes 2193 us so and 2210 in one launch, at 256^3 (9 against 16) 415 and 413.  (FP32's full
+    // takes 1931 us so and 1947 in one launch, at 1024^3 14.93 and 14.91 ms, at 256^3 (9 against 16) 415
+    // and 413 us.  (FP32's full
     // form, well within its registers, is slower split: 0.52 -> 0.57 ms at 512^3.)
     MarchArgs Ai = A, Ar = A;
     Ai.set = 1;

@@ -1,5 +1,5 @@
-// mg_tile.inl -- V-cycle legs of the small levels (32^3 .. 128^3, and the MeshBlock levels
-// below 256^3) as one launch each.
+// mg_tile.inl -- V-cycle legs of the small levels (32^3 and 64^3, and 128^3 where the streaming passes
+// are off; dense or in the MeshBlock layout) as one launch each.
 //
 // On these levels a V-cycle leg is a handful of microseconds of work spread over many
 // dependent launches (per colour, per operator), so the launch latency dominates.  Here one
